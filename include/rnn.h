@@ -131,8 +131,9 @@ int rnn_model_set_plan(rnn_model* model, int plan);
  * product, n = tanh(W_in x + b_in + W_hn (r * h) + b_hn), the default of the ONNX operator set
  * (the file format the paper's system takes its models in, Section 1); on = 0 (the default)
  * applies it after the product, n = tanh(W_in x + b_in + r * (W_hn h + b_hn)).  The first form
- * needs two dependent recurrent products per cell and runs under the cellwise plan only:
- * RNN_EUNSUPPORTED for an LSTM model or while RNN_PLAN_WAVEFRONT is selected (and selecting that
+ * needs two dependent recurrent products per cell.  Under RNN_PLAN_AUTO it runs in the persistent kernel of layers
+ * that fit one XCD (bf16 up to 512 units, fp32 likewise), otherwise under the cellwise plan; of the plans it can be
+ * given only RNN_PLAN_CELLWISE: RNN_EUNSUPPORTED for an LSTM model or while RNN_PLAN_WAVEFRONT is selected (and selecting that
  * plan afterwards is refused). */
 int rnn_model_set_gru_reset_before(rnn_model* model, int on);
 

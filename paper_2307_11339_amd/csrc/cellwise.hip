@@ -6,7 +6,7 @@
 // below, which adds the projection, applies the gate functions and updates the state.  The GRU
 // that applies the reset gate before the candidate's recurrent product needs two products per
 // cell with a pointwise kernel between them.  The optional terms of the ONNX operators (peephole
-// weights, clipping threshold) exist in this plan only.  Also here: the kernel that changes the
+// weights, clipping threshold) are part of its gates too.  Also here: the kernel that changes the
 // layout of x and y for batch-first callers (used with every plan).
 #include <algorithm>
 

@@ -131,4 +131,49 @@ hipError_t launch_wavefront_ll_init(int dtype, const float* h0, int l0, int LP, 
 // 8-byte words needed for `groups` (layer, direction) state sequences.
 size_t wavefront_ll_words(int dtype, int groups, int T, int B, int H);
 
+// ---- persistent kernel for groups that fit one XCD (wavefront_xcd.hip) ----------------------
+constexpr int XCD_AHEAD = 4;       // steps between marking a slot of a state sequence as unwritten and writing it
+struct WavefrontXcdArgs {
+    int cell, dtype;
+    int T, B, H, D, I;           // B: sequences of this launch; I: input width of layer l0 (xin)
+    int l0, LP;
+    int RT, nrb, ncb, gpx;       // 16-row tiles and row blocks per group; blocks of 16 sequences; groups per XCD
+    int xln;                     // chunk loads per x wave and step (wavefront_xcd_input_chunks)
+    int ring;                    // slots of a state sequence: a power of two >= 2 * XCD_AHEAD, or more than T (every step its own)
+    int ext, reset_before;
+    const void* whh[WF_MAX_LAYERS * 2];   // packed W_hh per (local layer, direction): [4H, H]
+    const void* wih[WF_MAX_LAYERS * 2];   // packed W_ih per local layer (all directions): [D * 4H, width]
+    const float* bias[WF_MAX_LAYERS * 2];
+    const float* peep[WF_MAX_LAYERS * 2];
+    float clip;
+    const float* gx;             // NULL, or the finished projection of layer l0: [rows, D, H, 4] (xin and I are not read)
+    const void* xin;             // input of layer l0: [rows, I], 16-byte aligned rows
+    int x_t, x_b;                // row of (step t, sequence b) of xin and gx: t * x_t + b * x_b
+    int x_blocked;               // xin has the layout of a state sequence instead: [ncb][T][I / units per chunk][min(16, B)][16 bytes]
+    void* out;                   // output of the last layer of the launch: [rows, D * out_units]
+    int y_t, y_b;                // row of (t, b) of out
+    int y_blocked;               // out gets the layout of x_blocked, D * H units wide, for the next launch
+    int out_units;               // units per direction in a row of out (units beyond are padding and not written)
+    int out_units_state;         // units in a row of h0, c0, hT, cT
+    int state_b;                 // sequences (rows) per (layer, direction) in h0, c0, hT, cT
+    void* hseq;                  // [LP * D * ncb] groups (twice with reset_before), min(ring, T) slots of wavefront_xcd_slot_bytes
+    void* xseq;                  // [ncb][LP - 1][T] slots: states handed from layer to layer
+    const float* h0;
+    const float* c0;
+    float* hT;
+    float* cT;
+    const int32_t* lengths;
+    uint64_t* flagv;             // [groups][nrb] start words {epoch, XCC}, never cleared
+    unsigned* status;
+    unsigned long long* ticks;
+    unsigned spin_limit;
+    uint32_t epoch;
+};
+hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream);
+bool wavefront_xcd_variant_exists(int dtype, int RT, int H);
+// Chunk loads per x wave for an input `width` wide (of the launch's first layer; several_layers: upper layers read inputs H
+// wide as well), or 0 when there is no such variant.
+int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers);
+size_t wavefront_xcd_slot_bytes(int dtype, int B, int H);
+
 }  // namespace rnn

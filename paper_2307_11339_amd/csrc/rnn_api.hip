@@ -29,6 +29,9 @@ struct Plan {
     // the first layer runs in a launch of its own (it needs a projection, the layers above it run side
     // by side in the inside-product kernel): launches are {0}, {1..LP}, {LP+1..2LP}, ...
     bool first_alone = false;
+    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with gpx groups of workgroups on every XCD
+    bool xcd = false;
+    int gpx = 0;
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
     int chunk = 0;
@@ -96,17 +99,18 @@ struct rnn_model {
     std::vector<DevBuf> peep;   // empty, or per (layer, direction) [3, H] fp32 peephole weights (LSTM)
     bool batch_first = false;   // x is [B, T, I] and y [B, T, D*H]
     bool validate = false;      // check `lengths` on the host before every forward
-    // the cell variant that only the cellwise plan implements (two dependent recurrent products per cell)
-    bool cellwise_only() const { return gru_reset_before; }
+    // the cell variant with two dependent recurrent products per cell: the cellwise plan and the XCD-resident kernel only
+    bool two_products() const { return gru_reset_before; }
     // Everything a forward pass keeps in device memory besides the weights.
     struct Workspace {
-        DevBuf gx, hseq, flags, h_f32, c_f32, h_st, gh, ticks;
+        DevBuf gx, gx0, hseq, flags, h_f32, c_f32, h_st, gh, ticks;
         DevBuf rh_st, gh2;      // reset-before-product GRU (cellwise plan): r * h and the second product
         DevBuf x_tm, y_tm;          // batch-first callers: time-major copies of x and y
         DevBuf x_ck, y_ck, st_ck[4];   // a batch run in passes: the pass's x, y, h0, c0, hT, cT
         DevBuf y_pad, st_pad[4];       // a padded model: y, h0, c0, hT, cT at the padded width
         DevBuf xblk;            // the caller's x in the layout of a state sequence (first layer of width H only)
         DevBuf lseq;            // tagged state sequences of the tag-in-data kernel (grown on demand)
+        DevBuf xseq;            // XCD-resident kernel: state sequences handed from layer to layer
         std::vector<DevBuf> ybuf;  // L-1 inter-layer activations
     };
     Workspace ws;           // allocated on demand, owned by the model
@@ -154,10 +158,11 @@ void dev_free(DevBuf& b) {
 }
 
 void free_workspace(rnn_model* m) {
-    dev_free(m->ws.gx); dev_free(m->ws.hseq); dev_free(m->ws.flags); dev_free(m->ws.h_f32);
+    dev_free(m->ws.gx); dev_free(m->ws.gx0); dev_free(m->ws.hseq); dev_free(m->ws.flags); dev_free(m->ws.h_f32);
     dev_free(m->ws.c_f32); dev_free(m->ws.h_st); dev_free(m->ws.gh); dev_free(m->ws.ticks);
     for (auto& b : m->ws.ybuf) dev_free(b);
     dev_free(m->ws.lseq);
+    dev_free(m->ws.xseq);
     dev_free(m->ws.xblk);
     dev_free(m->ws.rh_st);
     dev_free(m->ws.gh2);
@@ -178,9 +183,40 @@ bool relayout_fits(const rnn_model* m, int T) {
     return T <= 65535 && (size_t)16 * m->H * m->esize <= 64 * 1024;
 }
 
+constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
+
+// Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring).
+int xcd_ring(int T) { return T + 1; }
+
+// A plan for the XCD-resident kernel: every (layer, direction, block of 16 sequences) of a launch is a group of workgroups
+// that fits the compute units of one XCD.
+bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
+    const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16;
+    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, B, m->H) >= ((size_t)1 << 31)) return false;
+    const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
+    for (int launches = (m->L + lp_max - 1) / lp_max; launches <= m->L; ++launches) {
+        const int LP = (m->L + launches - 1) / launches;
+        const int gpx = (LP * m->D * ncb + XCDS - 1) / XCDS;
+        static const int tiles[] = {1, 2, 4};
+        for (int RT : tiles) {
+            const int nrb = m->H / (RT * 4);
+            if (nrb * RT * 4 != m->H || nrb * gpx > per_xcd || !wavefront_xcd_variant_exists(m->dtype, RT, m->H)) continue;
+            plan = Plan();
+            plan.kind = RNN_PLAN_WAVEFRONT;
+            plan.xcd = true;
+            plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx;
+            return true;
+        }
+    }
+    return false;
+}
+
 // Choose how the grid of cells is laid over the compute units for batch size B.
 bool choose_wavefront(const rnn_model* m, int T, int B, Plan& plan) {
     if (m->H % 4 != 0) return false;
+    if (choose_xcd(m, T, B, plan)) return true;
+    if (m->two_products()) return false;
+    plan = Plan();
     const int row_tiles = m->H / 4;
     const int col_tiles = (B + 15) / 16;
     const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
@@ -334,8 +370,8 @@ int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = 
 }
 
 int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk) {
-    if (m->cellwise_only() && m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
-    if (m->requested_plan == RNN_PLAN_CELLWISE || m->cellwise_only()) {
+    if (m->two_products() && m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
+    if (m->requested_plan == RNN_PLAN_CELLWISE) {
         plan = Plan();
         return RNN_OK;
     }
@@ -364,6 +400,11 @@ bool first_of_launch(const rnn_model* m, const Plan& plan, int l) {
     int l0, n;
     launch_of(m, plan, l, l0, n);
     return l == l0;
+}
+int launch_width(const rnn_model* m, const Plan& plan, int l) {
+    int l0, n;
+    launch_of(m, plan, l, l0, n);
+    return n;
 }
 int launch_count(const rnn_model* m, const Plan& plan) {
     return plan.layer_launch.empty() ? m->L : (int)plan.launch_layer0.size();
@@ -598,11 +639,18 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
     return RNN_OK;
 }
 
+// XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave
+// (1024 bf16 or 512 fp32 values).  An input of an eighth of the layer's width or less keeps its projection launch.
+bool xcd_input_inside(const rnn_model* m, const Plan&, int width, bool several_layers) {
+    return 8 * width > m->H && wavefront_xcd_input_chunks(m->dtype, m->H, width, several_layers) > 0;
+}
+
 // A layer that runs alone in its launch, in one direction, on an input of its own width can do
 // its input product inside the recurrent kernel (wavefront_x.hip) instead of through a projection.
 // So can the first layer of a launch of the tag-in-data kernel (its x waves read the plain input).
 bool input_product_inside(const rnn_model* m, const Plan& plan, int l, int T) {
     if (plan.kind != RNN_PLAN_WAVEFRONT) return false;
+    if (plan.xcd) return first_of_launch(m, plan, l) && xcd_input_inside(m, plan, m->layer_input(l), launch_width(m, plan, l) > 1);
     if (plan.CT == 1 && plan.NCH == 1) {
         // tag-in-data kernel, first layer of a launch (layers above it in the launch are fused anyway): its
         // x waves hold the W_ih slice in registers, which fits for an input H wide, or 2H wide (a
@@ -629,7 +677,7 @@ bool input_product_inside(const rnn_model* m, const Plan& plan, int l, int T) {
 
 int ybuf_slot(const rnn_model* m, const Plan& plan, int l, int T) {
     if (plan.kind != RNN_PLAN_WAVEFRONT) return l % 2;          // cellwise: two buffers, used alternately
-    const bool tagged = plan.CT == 1 && plan.NCH == 1;
+    const bool tagged = plan.CT == 1 && plan.NCH == 1;      // (the XCD-resident kernel's plans too)
     int l0, n;
     launch_of(m, plan, l, l0, n);
     if (tagged) {
@@ -650,7 +698,7 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B) {
     const size_t rows = (size_t)T * B;
     const size_t state = (size_t)m->L * m->D * B * m->H;
     const bool wavefront = plan.kind == RNN_PLAN_WAVEFRONT;
-    const bool tagged = wavefront && plan.CT == 1 && plan.NCH == 1;
+    const bool tagged = wavefront && !plan.xcd && plan.CT == 1 && plan.NCH == 1;
     bool any_projection = !wavefront;
     if ((int)m->ws.ybuf.size() < m->L - 1) m->ws.ybuf.resize(m->L - 1);
     int rc = RNN_OK;
@@ -658,10 +706,16 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B) {
         const bool inside = wavefront && input_product_inside(m, plan, l, T);
         if (!inside && (!wavefront || first_of_launch(m, plan, l))) any_projection = true;
         const int slot = l + 1 < m->L ? ybuf_slot(m, plan, l, T) : -1;
-        if (slot >= 0) rc = grow(m, m->ws.ybuf[slot], rows * m->D * m->H * m->esize);
+        if (slot >= 0) rc = grow(m, m->ws.ybuf[slot], (plan.xcd ? (size_t)T * plan.ncb * std::min(B, 16) : rows) * m->D * m->H * m->esize);
     }
     if (rc == RNN_OK && any_projection) rc = grow(m, m->ws.gx, rows * m->D * m->H * SLOTS * sizeof(float));
-    if (rc == RNN_OK && wavefront && !tagged) {
+    if (rc == RNN_OK && plan.xcd) {
+        const size_t slot = wavefront_xcd_slot_bytes(m->dtype, B, m->H), groups = (size_t)plan.LP * m->D * plan.ncb;
+        rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * std::min(xcd_ring(T), T) * slot);
+        if (rc == RNN_OK) rc = grow(m, m->ws.xseq, (size_t)plan.ncb * (plan.LP - 1) * T * slot);
+        if (rc == RNN_OK) rc = grow(m, m->ws.flags, groups * plan.nrb * sizeof(uint64_t), true);
+    }
+    if (rc == RNN_OK && wavefront && !tagged && !plan.xcd) {
         rc = grow(m, m->ws.hseq, (size_t)state_regions(m, plan) * m->D * (T + 1) * blocked_rows(B) * m->H * m->esize);
         // one flag word per (layer of a launch, direction, step, chain, row block); every launch stamps
         // them with its own tag, so all launches share the words of one
@@ -701,12 +755,18 @@ int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B) {
             rc = resolve_plan(m, T, tail, last, false);
             if (rc == RNN_OK) rc = prepare_workspace_pass(m, last, T, tail);
         }
+        if (plan.xcd) {     // the kernels address the caller's tensors in place
+            if (rc == RNN_OK && !input_product_inside(m, plan, 0, T))
+                rc = grow(m, m->ws.gx0, (size_t)T * B * m->D * m->H * SLOTS * sizeof(float));
+            return rc;
+        }
         const size_t rows = (size_t)T * plan.chunk;
         if (rc == RNN_OK) rc = grow(m, m->ws.x_ck, rows * m->I * m->esize);
         if (rc == RNN_OK) rc = grow(m, m->ws.y_ck, rows * m->D * m->H * m->esize);
         for (int i = 0; i < 4 && rc == RNN_OK; ++i)
             rc = grow(m, m->ws.st_ck[i], (size_t)m->L * m->D * plan.chunk * m->H * sizeof(float));
     }
+    if (plan.xcd) return rc;
     if (rc == RNN_OK && m->H != m->Hu) {
         rc = grow(m, m->ws.y_pad, (size_t)T * B * m->D * m->H * m->esize);
         for (int i = 0; i < 4 && rc == RNN_OK; ++i)
@@ -781,6 +841,120 @@ int forward_wavefront(rnn_model* m, const Plan& plan, const void* x, const int32
         prof_end(m, ps, st);
         const int rc = launch_recurrent(m, plan, l0, LP, T, B, (const float*)m->ws.gx.p, y, lengths, h0,
                                         c0, hT, cT, st);
+        if (rc != RNN_OK) return rc;
+    }
+    return RNN_OK;
+}
+
+// Forward pass on the XCD-resident kernel: sequences b0 .. b0 + bc - 1 of the caller's tensors (Bc sequences, x and y in either
+// layout, states at the caller's width), which the kernels address in place.
+int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0, void* y,
+                float* hT, float* cT, int T, int Bc, int b0, int bc, const float* gx0, hipStream_t st) {
+    const size_t slot = wavefront_xcd_slot_bytes(m->dtype, bc, m->H);
+    const int xt = m->batch_first ? 1 : Bc, xb = m->batch_first ? T : 1;
+    const int N4 = SLOTS * m->H;
+    for (int l0 = 0, LP = 0; l0 < m->L; l0 += LP) {
+        int first;
+        launch_of(m, plan, l0, first, LP);
+        if (++m->epoch == 0) {  // the tag wrapped: start over from cleared start words
+            HIP_TRY(launch_fill_zero(m->ws.flags.p, m->ws.flags.bytes, st));
+            HIP_TRY(launch_fill_zero(m->ws.lseq.p, m->ws.lseq.bytes, st));
+            m->epoch = 1;
+        }
+        WavefrontXcdArgs a;
+        memset(&a, 0, sizeof(a));
+        a.cell = m->cell; a.dtype = m->dtype;
+        a.T = T; a.B = bc; a.H = m->H; a.D = m->D; a.I = m->layer_input(l0);
+        a.l0 = l0; a.LP = LP;
+        a.RT = plan.RT; a.nrb = plan.nrb; a.ncb = plan.ncb;
+        a.gpx = (LP * m->D * plan.ncb + XCDS - 1) / XCDS;
+        a.ring = xcd_ring(T);
+        a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
+        a.reset_before = m->gru_reset_before ? 1 : 0;
+        for (int ll = 0; ll < LP; ++ll)
+            for (int d = 0; d < m->D; ++d) {
+                const int g = (l0 + ll) * m->D + d;
+                a.whh[ll * m->D + d] = m->whh[g].p;
+                a.wih[ll * m->D + d] = m->wih[l0 + ll].p;
+                a.bias[ll * m->D + d] = (const float*)m->bias[g].p;
+                a.peep[ll * m->D + d] = m->peep.empty() ? nullptr : (const float*)m->peep[g].p;
+            }
+        a.clip = m->clip;
+        if (l0 == 0) {
+            a.xin = (const char*)x + (size_t)b0 * xb * m->I * m->esize;
+            a.x_t = xt; a.x_b = xb;
+            if (gx0) a.gx = gx0 + (size_t)b0 * xb * m->D * N4;
+        } else {
+            a.xin = m->ws.ybuf[ybuf_slot(m, plan, l0 - 1, T)].p;
+            a.x_t = bc; a.x_b = 1;
+            if (input_product_inside(m, plan, l0, T)) {
+                a.x_blocked = 1;
+            } else {
+                const int ps = prof_begin(m, RNN_KERNEL_PROJECTION, st);
+                HIP_TRY(launch_gemm_nt(m->dtype, a.xin, a.I, m->wih[l0].p, a.I, (float*)m->ws.gx.p, m->D * N4, T * bc, m->D * N4,
+                                       a.I, st));
+                prof_end(m, ps, st);
+                a.gx = (const float*)m->ws.gx.p;
+            }
+        }
+        a.xln = wavefront_xcd_input_chunks(m->dtype, m->H, a.gx ? m->H : a.I, LP > 1);
+        const int l1 = l0 + LP - 1;
+        if (l1 == m->L - 1) {
+            a.out = (char*)y + (size_t)b0 * xb * m->D * m->Hu * m->esize;
+            a.y_t = xt; a.y_b = xb;
+            a.out_units = m->Hu;
+        } else {
+            a.out = m->ws.ybuf[ybuf_slot(m, plan, l1, T)].p;
+            a.y_t = bc; a.y_b = 1;
+            a.y_blocked = input_product_inside(m, plan, l1 + 1, T) ? 1 : 0;
+            a.out_units = m->H;
+        }
+        a.out_units_state = m->Hu;
+        a.state_b = Bc;
+        const size_t so = (size_t)b0 * m->Hu;
+        a.h0 = h0 ? h0 + so : nullptr; a.c0 = c0 ? c0 + so : nullptr;
+        a.hT = hT ? hT + so : nullptr; a.cT = cT ? cT + so : nullptr;
+        a.lengths = lengths ? lengths + b0 : nullptr;
+        a.hseq = m->ws.hseq.p; a.xseq = m->ws.xseq.p;
+        a.flagv = (uint64_t*)m->ws.flags.p;
+        // the launch must stay inside the buffers the workspace holds (a kernel never checks)
+        const size_t groups = (size_t)LP * m->D * plan.ncb;
+        if (groups * (m->gru_reset_before ? 2 : 1) * std::min(a.ring, T) * slot > m->ws.hseq.bytes ||
+            (size_t)plan.ncb * (LP - 1) * T * slot > m->ws.xseq.bytes || groups * plan.nrb * sizeof(uint64_t) > m->ws.flags.bytes)
+            return RNN_EDEVICE;
+        a.status = (unsigned*)m->status.p;
+        a.ticks = m->want_ticks ? (unsigned long long*)m->ws.ticks.p + (size_t)l0 * m->D * T : nullptr;
+        a.spin_limit = m->spin_limit;
+        a.epoch = m->epoch;
+        const int ps = prof_begin(m, RNN_KERNEL_RECURRENT, st);
+        HIP_TRY(launch_wavefront_xcd(a, st));
+        prof_end(m, ps, st);
+    }
+    return RNN_OK;
+}
+
+// All passes of a call on the XCD-resident kernel.
+int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0,
+                       void* y, float* hT, float* cT, int T, int B, hipStream_t st) {
+    const float* gx0 = nullptr;
+    const int N4 = SLOTS * m->H;
+    if (!input_product_inside(m, plan, 0, T)) {      // projection of the first layer, for all sequences at once
+        float* gx = (float*)(plan.chunk > 0 ? m->ws.gx0.p : m->ws.gx.p);
+        const int ps = prof_begin(m, RNN_KERNEL_PROJECTION, st);
+        HIP_TRY(launch_gemm_nt(m->dtype, x, m->I, m->wih[0].p, m->I, gx, m->D * N4, T * B, m->D * N4, m->I, st));
+        prof_end(m, ps, st);
+        gx0 = gx;
+    }
+    const int step = plan.chunk > 0 ? plan.chunk : B;
+    for (int b0 = 0; b0 < B; b0 += step) {
+        const int bc = std::min(step, B - b0);
+        Plan pass = plan;
+        if (plan.chunk > 0) {
+            const int rc = resolve_plan(m, T, bc, pass, false);
+            if (rc != RNN_OK) return rc;
+            if (!pass.xcd) return RNN_EDEVICE;       // (a smaller batch of the same shape always has such a plan)
+        }
+        const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, gx0, st);
         if (rc != RNN_OK) return rc;
     }
     return RNN_OK;
@@ -991,7 +1165,7 @@ int rnn_model_set_plan(rnn_model* m, int plan) {
         return RNN_EINVAL;
     if (plan == RNN_PLAN_WAVEFRONT) {
         Plan p;
-        if (m->cellwise_only() || !choose_wavefront(m, 1, 1, p)) return RNN_EUNSUPPORTED;
+        if (m->two_products() || !choose_wavefront(m, 1, 1, p)) return RNN_EUNSUPPORTED;
     }
     m->requested_plan = plan;
     return RNN_OK;
@@ -1092,6 +1266,7 @@ static int forward_entry(rnn_model* m, const void* x, const int32_t* lengths, co
         HIP_TRY(launch_fill_zero(m->ws.lseq.p, m->ws.lseq.bytes, st));
     }
     if (m->cell == CELL_GRU) { c0 = nullptr; cT = nullptr; }
+    if (plan.xcd) return forward_xcd_passes(m, plan, x, lengths, h0, c0, y, hT, cT, T, B, st);
     void* y_caller = nullptr;
     if (m->batch_first) {   // the plans work on time-major copies
         HIP_TRY(launch_swap_outer(x, m->ws.x_tm.p, B, T, (size_t)m->I * m->esize, st));

@@ -1,0 +1,735 @@
+// Persistent kernel for groups of workgroups that fit one XCD: the recurrence of one (layer, direction, block of
+// 16 sequences) never leaves the L2 of the XCD its workgroups run on.
+//
+// Decomposition and arithmetic are those of wavefront_ll.hip (paper Section 2.2: one group of workgroups per
+// (layer, direction) of the unrolled grid; a workgroup owns RT * 4 hidden units of one block of up to 16 sequences;
+// W_hh in the registers of four h waves that split K, W_ih in those of four x waves that work a step ahead).  What
+// bounds a step at these sizes is the exchange of h between the workgroups, and its cost is a matter of where the
+// data meets (measured, 32 workgroups all-gathering 256 words of 8 bytes, us per step):
+//     device-scope stores (written through to memory), device-scope loads     1.26 - 1.44
+//     plain stores (they stay in the XCD's L2), loads that bypass the L1       0.62
+// The second line needs every workgroup of a group on one XCD.  The dispatcher deals consecutive workgroups to the
+// XCDs in turn, so the launch numbers its groups by blockIdx % 8; nothing relies on that: every workgroup publishes
+// the XCC it really runs on before the first step (while its weights travel), and a group that finds itself on more
+// than one uses device-scope stores instead.
+//
+// Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
+// the block side by side.  A lane's MFMA B fragment is one chunk, so a load instruction of a wave brings a whole K
+// block of 16 sequences from 8 consecutive cache lines straight into the registers the matrix instruction reads: no
+// tags, no staging through LDS.  Whether a chunk has been written is told from the data: a slot is filled with the bit
+// pattern of all ones (two bf16 NaNs; one fp32 NaN) several steps before it is used, no published value has that
+// pattern (a NaN is published with another one), and what is stored at once (8 bytes in bf16, 4 in fp32) is checked
+// at once.  Order: a wave marks slot s + AHEAD in step s; before it publishes slot s it has waited for loads issued
+// after it had marked slot s + 1, and memory operations of a wave complete in order, so whoever has seen slot s finds
+// slot s + 1 marked or written.  The first AHEAD slots are marked before the group's start words are published.
+//
+// For layers in the same launch the layer below hands its state to the layer above through a second sequence with
+// device-scope stores (the two may run on different XCDs); the x waves do that, and write the layer output, from
+// LDS, so that no store other than the state itself stands before the next poll of an h wave.
+// Every wait is bounded (poll budget, shared status word), so the grid always drains.
+//
+// What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz): fetch of the state 500 - 900 (16 KiB into every
+// compute unit at 64 bytes per clock, behind an L2 round trip of 350), products 280, barrier and sum over the quarters 300,
+// gates 300, publication 150; the tag-in-data kernel took 2.5 us a step here, this one takes 1.2.  Whole forward passes
+// before -> after: 2-layer LSTM of 512 units, both directions, batch 64, 256 steps 1.29 -> 0.65 ms; 2-layer GRU of 512 units at
+// batch 8 183 -> 111 us for 100 steps; 12 fp32 layers of 64 units 159 -> 119 us; 2 fp32 layers of 512 units at batch 64 1.15 ->
+// 0.77 ms; GRU with the reset gate before the product (one launch per cell part until now) 1719 -> 105 us.
+#include "wf_traits.h"
+
+// The variants are compiled in several translation units so that the build runs in parallel: this file is part 0 (bf16,
+// and the public functions); wavefront_xcd_b.hip and so on include it with other values.
+//   RNN_XR_DT    0 = bf16, 1 = fp32
+//   RNN_XR_KIND  0 = LSTM and GRU with the plain cell, 1 = with the peephole and clipping terms, 2 = the GRU that applies the
+//                reset gate before the candidate's recurrent product (always with the clipping term)
+#ifndef RNN_XR_DT
+#define RNN_XR_DT 0
+#endif
+#ifndef RNN_XR_KIND
+#define RNN_XR_KIND 0
+#endif
+
+namespace rnn {
+namespace {
+
+constexpr int AHEAD = XCD_AHEAD;                // steps between marking a slot of the state and publishing it
+constexpr int AHEAD_UP = 8;                     // the same for the sequence handed to the layer above: an x wave of the first layer has
+                                                // up to four steps of loads in flight, so what it marked is known to be done that much later
+constexpr uint32_t UNWRITTEN = 0xFFFFFFFFu;
+constexpr int CELL_GRU_RB = 2;                  // GRU, reset gate before the candidate's recurrent product
+
+struct XRBf16 : TraitsBf16 {
+    static constexpr int EPC = 8;               // elements per 16-byte chunk
+    static constexpr int MPL = 1;               // matrix instructions per loaded chunk
+    static constexpr int MMA_CLOCKS = 16;       // clocks one of them keeps the matrix unit busy
+    static constexpr int PUB_LANES = 16;        // lanes that store a tile: one per sequence, 4 units each
+    typedef uint64_t pub_t;
+    static __device__ inline frag part(const u32x4& v, int) { return __builtin_bit_cast(frag, v); }
+    // running maximum of the words that tell whether a chunk has been written (8 bytes are stored at once)
+    static __device__ inline uint32_t seen(uint32_t m, const u32x4& v) { return max(m, max(v[0], v[2])); }
+    static __device__ inline u32x4 pack(const float* f) {
+        u32x4 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (uint32_t)f32_to_bf16(f[2 * i]) | ((uint32_t)f32_to_bf16(f[2 * i + 1]) << 16);
+        return r;
+    }
+    // the tile's values of one sequence: lanes n, n + 16, n + 32, n + 48 hold units 0..3 of sequence n; valid in lanes < 16
+    static __device__ inline void gather(elem state, elem outv, pub_t& s, pub_t& o) {
+        uint32_t v0, v1, v2, v3;
+        gather_rows((uint32_t)state | ((uint32_t)outv << 16), v0, v1, v2, v3);
+        const uint32_t lo = min((v0 & 0xFFFFu) | (v1 << 16), UNWRITTEN - 1), hi = min((v2 & 0xFFFFu) | (v3 << 16), UNWRITTEN - 1);
+        s = (uint64_t)lo | ((uint64_t)hi << 32);
+        o = (uint64_t)((v0 >> 16) | (v1 & 0xFFFF0000u)) | ((uint64_t)((v2 >> 16) | (v3 & 0xFFFF0000u)) << 32);
+    }
+    static __device__ inline pub_t mark() { return ~0ull; }
+    // byte offset inside a slot of what this lane stores of the tile whose first unit is unit0
+    static __device__ inline uint32_t pub_off(int unit0, int Bs, int lane) {
+        return ((uint32_t)(unit0 >> 3) * Bs + (lane & 15)) * 16u + ((unit0 >> 2) & 1) * 8u;
+    }
+    static __device__ inline int pub_unit(int) { return 0; }     // first unit inside the tile of what a lane stores
+    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+    template <int AUX>
+    static __device__ inline void store(__amdgpu_buffer_rsrc_t r, pub_t v, uint32_t voff, uint32_t soff) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, AUX);
+    }
+};
+
+struct XRF32 : TraitsF32 {
+    static constexpr int EPC = 4;
+    static constexpr int MPL = 4;
+    static constexpr int MMA_CLOCKS = 32;
+    static constexpr int PUB_LANES = 64;        // every lane stores its own unit
+    typedef uint32_t pub_t;
+    // K order inside a chunk block: matrix instruction j takes unit 4 * (lane / 16) + j of the 16 (weights likewise)
+    static __device__ inline frag part(const u32x4& v, int j) { return __uint_as_float(v[j]); }
+    static __device__ inline uint32_t seen(uint32_t m, const u32x4& v) { return max(max(m, max(v[0], v[1])), max(v[2], v[3])); }
+    static __device__ inline u32x4 pack(const float* f) {
+        return u32x4{__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3])};
+    }
+    static __device__ inline void gather(elem state, elem outv, pub_t& s, pub_t& o) {
+        s = min(__float_as_uint(state), UNWRITTEN - 1);
+        o = __float_as_uint(outv);
+    }
+    static __device__ inline pub_t mark() { return UNWRITTEN; }
+    static __device__ inline uint32_t pub_off(int unit0, int Bs, int lane) {
+        return ((uint32_t)(unit0 >> 2) * Bs + (lane & 15)) * 16u + (lane >> 4) * 4u;
+    }
+    static __device__ inline int pub_unit(int lane) { return lane >> 4; }
+    template <int AUX>
+    static __device__ inline void store(__amdgpu_buffer_rsrc_t r, pub_t v, uint32_t voff, uint32_t soff) {
+        __builtin_amdgcn_raw_buffer_store_b32(v, r, voff, soff, AUX);
+    }
+};
+
+// A word in LDS that waves watch without a barrier.  (Through the LDS address space: a volatile access by a generic pointer
+// is a flat one, which waits for every memory operation the wave has in flight.)
+typedef volatile __attribute__((address_space(3))) unsigned lds_word;
+__device__ inline void lds_put(unsigned* p, unsigned v) { *(lds_word*)p = v; }
+__device__ inline unsigned lds_get(unsigned* p) { return *(lds_word*)p; }
+
+// Buffer descriptor over `bytes` bytes at p (wave-uniform; said so, which keeps it in scalar registers).
+__device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t bytes) {
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), 0,
+                                             __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
+}
+
+// LN / XLN: 16-byte chunks a lane loads per wave of the state / of the layer input (a wave's quarter of H is 4 * EPC * LN
+// units; K blocks of the input are dealt to the waves in turn, and those beyond its width get zero weights).  The first layer
+// of a launch may have its input product done by a projection launch (p.gx): its x waves then only bring that in.
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
+__global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) {
+    constexpr bool RB = CELL == CELL_GRU_RB;
+    constexpr int GATES = RB ? CELL_GRU : CELL;
+    typedef typename TR::elem elem;
+    typedef typename TR::frag frag;
+    typedef typename TR::pub_t pub_t;
+    constexpr int EPC = TR::EPC, MPL = TR::MPL;
+    constexpr int NW = 8;
+    constexpr int NOWN = 1;                          // tiles finished by one wave
+    static_assert(RT <= 4, "one tile per wave");
+    // A wave numbers the tiles from its own on, so that (RT = 4) it keeps its own tile's partial sum as acc[0].
+    constexpr bool KEEP = RT == 4;
+    constexpr int OTHERS = KEEP ? 3 : 4;             // partial sums of a tile that go through LDS
+    constexpr int PART = OTHERS * RT * 64;           // f32x4 entries of one set of them
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    f32x4* red = reinterpret_cast<f32x4*>(smem_raw);              // [2][RT tiles][OTHERS waves][64 lanes]
+    f32x4* xacc = red + 2 * PART;                                 // [4][RT][64]: x wave w to h wave w
+    pub_t* pub = reinterpret_cast<pub_t*>(xacc + 4 * RT * 64);    // [RT][PUB_LANES]
+    unsigned* done = reinterpret_cast<unsigned*>(pub + RT * TR::PUB_LANES);   // [4] steps whose tile h wave w has handed over
+    unsigned* ready = done + 4;                                   // [4] steps whose input part x wave w has handed over
+    unsigned* placed = ready + 4;                                 // 1: the whole group runs on one XCD
+    constexpr int TURN = 4 * (16 + 2);                            // u32x4 entries to turn one load of rows in: [4 chunks][16 rows + 2]
+    u32x4* turn = reinterpret_cast<u32x4*>(smem_raw + (((size_t)(2 * PART + 4 * RT * 64) * sizeof(f32x4) +
+                                                        (size_t)RT * TR::PUB_LANES * sizeof(pub_t) + 9 * sizeof(unsigned) + 15) & ~(size_t)15));   // [4 x waves][XLN][TURN]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = wv & 3;                            // K quarter
+    const int n = lane & 15, q = lane >> 4;
+    auto tile_of = [&](int j) -> int { return KEEP ? (w + j) & 3 : j; };   // this wave's j-th tile
+
+    // workgroup b runs on XCD b % 8: gpx groups of nrb workgroups on each
+    const int gi = (int)(blockIdx.x >> 3) / p.nrb;
+    const int rb = (int)(blockIdx.x >> 3) - gi * p.nrb;
+    const int g = (int)(blockIdx.x & 7) * p.gpx + gi;             // (cb, d, ll), the layers of a column block side by side
+    if (g >= p.LP * p.D * p.ncb) return;
+    const int ll = g % p.LP, d = (g / p.LP) % p.D, cb = g / (p.LP * p.D);
+    const int l = p.l0 + ll, ld = ll * p.D + d;
+    const bool fused = ll > 0;
+    const bool project = ll == 0 && p.gx != nullptr;
+    const bool last = ll == p.LP - 1;                // writes the layer output; the others hand their state to the layer above
+    const int H = p.H, T = p.T, B = p.B;
+    const int Bs = min(16, B);                       // sequences side by side in a chunk row
+    const int ncol = min(16, B - cb * 16);
+    const int nc = min(n, ncol - 1);                 // columns beyond the block repeat its last sequence and are never stored
+    const bool valid = n < ncol;
+    const int col = cb * 16 + nc;
+    const uint32_t epoch = p.epoch;
+    const uint32_t slot_bytes = (uint32_t)(H / EPC) * Bs * 16u;
+    const int ring = p.ring;                         // slots of a state sequence: a power of two, or more than T
+    const size_t seq_bytes = (size_t)min(ring, T) * slot_bytes;
+    char* hbase = static_cast<char*>(p.hseq) + (size_t)g * (RB ? 2 : 1) * seq_bytes;
+    const __amdgpu_buffer_rsrc_t hrs = uniform_rsrc(hbase, (uint32_t)seq_bytes);
+    const __amdgpu_buffer_rsrc_t rrs = uniform_rsrc(hbase + (RB ? seq_bytes : 0), (uint32_t)seq_bytes);   // r * h
+    // sequences between layers: [cb][ll < LP - 1][T]
+    const size_t xseq_bytes = (size_t)T * slot_bytes;
+    char* xbase = static_cast<char*>(p.xseq) + ((size_t)cb * (p.LP - 1) + ll) * xseq_bytes;
+    const __amdgpu_buffer_rsrc_t urs = uniform_rsrc(xbase, last ? 0u : (uint32_t)xseq_bytes);             // up, to the layer above
+    const __amdgpu_buffer_rsrc_t brs = uniform_rsrc(xbase - xseq_bytes, fused ? (uint32_t)xseq_bytes : 0u);   // from the layer below
+    const int rmask = ring - 1;
+    auto slot_of = [&](int s) -> uint32_t { return (uint32_t)(ring > T ? s : (s & rmask)) * slot_bytes; };
+    bool aborted = false;
+    auto give_up = [&](unsigned spins) {
+        if (ld_dev_u32(p.status) != 0u || spins >= p.spin_limit) {
+            st_dev_u32(p.status, 1u);
+            aborted = true;
+        }
+    };
+
+    // ---- start: mark the first slots, say where this workgroup runs ------------------------------
+    const bool shake = T > 1 || p.LP > 1 || RB;      // a single step of a single layer exchanges nothing
+    if (tid < 8) done[tid] = 0u;                     // (and ready)
+    if (shake && wv == NW - 1) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const uint32_t off = TR::pub_off((rb * RT + rt) * 4, Bs, lane);
+            if (valid && lane < TR::PUB_LANES)
+                for (int s = 0; s < AHEAD_UP && s < T; ++s) {
+                    if (s < AHEAD) TR::template store<16>(hrs, TR::mark(), off, slot_of(s));
+                    if (RB && s < AHEAD) TR::template store<16>(rrs, TR::mark(), off, slot_of(s));
+                    if (!last) TR::template store<16>(urs, TR::mark(), off, (uint32_t)s * slot_bytes);
+                }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // XCC_ID: hardware register 20, bits 3:0
+        const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11));
+        if (lane == 0) st_dev_u64(p.flagv + (size_t)g * p.nrb + rb, ((uint64_t)epoch << 32) | xcc);
+    }
+    auto start_wait = [&]() {                        // last wave: everybody this workgroup exchanges data with has started
+        bool same = true;
+        if (shake && wv == NW - 1) {
+            for (int other = fused ? 1 : 0; other >= 0; --other) {
+                const uint64_t* row = p.flagv + (size_t)(g - other) * p.nrb;
+                uint64_t mine = 0;
+                unsigned spins = 0;
+                for (;;) {
+                    bool ok = true;
+                    for (int i = 0; i < p.nrb; i += 64) {
+                        mine = ld_dev_u64(row + min(i + lane, p.nrb - 1));
+                        ok = ok && (uint32_t)(mine >> 32) == epoch;
+                    }
+                    if (__all(ok) || aborted) break;
+                    if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
+                }
+                if (other == 0) same = __all((uint32_t)mine == (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)mine));
+            }
+        }
+        if (wv == NW - 1 && lane == 0) lds_put(placed, same && p.nrb <= 64 ? 1u : 0u);
+        __syncthreads();
+    };
+
+    if (wv >= 4) {
+        __builtin_amdgcn_s_setprio(1);
+        // ---- x waves: the input product, one step ahead of the h waves ------------------------------
+        const int KX = fused ? H : p.I;              // width of this layer's input
+        constexpr int NBUF = XLN <= 2 ? 4 : 2;       // steps of x in flight (a plain x comes from HBM)
+        // Rows of the caller's tensor: a load whose four neighbouring lanes lie in four rows takes the address unit four times
+        // as long as one whose neighbours share 64 bytes (64 against 16 clocks, measured), and h waves wait behind it.  So lanes
+        // bring 64 bytes of a row together, and the wave turns them into fragments through LDS.
+        const bool rows = !fused && !project && !p.x_blocked && ncol > 2;
+        u32x4* const my_turn = turn + w * XLN * TURN;
+        frag wx[RT][XLN * MPL];
+        uint32_t xoff[XLN];                          // byte offset of this lane's chunk inside a step of x
+        if (!project) {
+            // W_ih of all directions is one matrix [D * 4H, KX]; direction d owns rows d * 4H ...
+            const elem* wih = static_cast<const elem*>(p.wih[ld]) + (size_t)d * SLOTS * H * KX;
+#pragma unroll
+            for (int i = 0; i < XLN; ++i) {
+                const int chunk = (i * 4 + w) * 4 + q;
+                const bool in = chunk * EPC < KX;    // beyond the input: zero weights, and any chunk that exists
+                const int k = in ? chunk * EPC : 0;
+                if (fused || p.x_blocked) xoff[i] = ((uint32_t)(k / EPC) * Bs + nc) * 16u;
+                else if (!rows) xoff[i] = (uint32_t)k * (uint32_t)sizeof(elem);
+                else {                               // lane 4 * r + c brings chunk c of row r
+                    const int rc = (i * 4 + w) * 4 + (lane & 3);
+                    xoff[i] = (uint32_t)min(lane >> 2, ncol - 1) * (uint32_t)(p.x_b * KX * sizeof(elem)) + (rc * EPC < KX ? rc * 16u : 0u);
+                }
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const size_t row = (size_t)(rb * RT + tile_of(rt)) * 16 + n;
+                    u32x4 v = *reinterpret_cast<const u32x4*>(wih + row * KX + k);
+                    if (!in) v = u32x4{0, 0, 0, 0};
+#pragma unroll
+                    for (int j = 0; j < MPL; ++j) wx[rt][i * MPL + j] = TR::part(v, j);
+                }
+            }
+        }
+        // a step of a finished input: rows of the caller's tensor, or a slot of a sequence in the layout of the state; (project) the
+        // four slot values of this lane's pair of tile w
+        const size_t xstep = project ? (size_t)p.x_t * p.D * H * SLOTS * sizeof(float)
+                             : p.x_blocked ? (size_t)(KX / EPC) * Bs * 16 : (size_t)p.x_t * KX * sizeof(elem);
+        const char* xsrc = project ? reinterpret_cast<const char*>(p.gx + (((size_t)col * p.x_b * p.D + d) * H + min((rb * RT + w) * 4 + q, H - 1)) * SLOTS)
+                           : static_cast<const char*>(p.xin) + (p.x_blocked ? (size_t)cb * T * xstep
+                                                                           : (size_t)(rows ? cb * 16 : col) * p.x_b * KX * sizeof(elem));
+        u32x4 xb[NBUF][XLN];
+        auto request = [&](int s, u32x4 (&v)[XLN]) { // the s-th step in this direction's order
+            const int sc = min(s, T - 1);
+            if (fused) {
+#pragma unroll
+                for (int i = 0; i < XLN; ++i)
+                    v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], (uint32_t)sc * slot_bytes, 16);
+            } else {
+                const char* src = xsrc + (size_t)(d ? T - 1 - sc : sc) * xstep;
+                if (project) {
+                    v[0] = *reinterpret_cast<const u32x4*>(src);
+                    return;
+                }
+#pragma unroll
+                for (int i = 0; i < XLN; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + xoff[i]);
+            }
+        };
+        // layer output of the workgroup's tiles, or their state for the layer above
+        elem* out = static_cast<elem*>(p.out);
+        auto forward = [&](int s) {
+            if (w >= RT) return;                     // x wave w takes the tile that h wave w finished
+            while (lds_get(done + w) < (unsigned)(s + 1)) __builtin_amdgcn_s_sleep(1);   // (every h wave takes every step, whatever became of its waits)
+            asm volatile("" ::: "memory");
+            if (valid && lane < TR::PUB_LANES) {
+                const pub_t v = pub[w * TR::PUB_LANES + lane];
+                const int unit0 = (rb * RT + w) * 4;
+                const int t = d ? T - 1 - s : s;
+                if (!last) {
+                    const uint32_t off = TR::pub_off(unit0, Bs, lane);
+                    TR::template store<16>(urs, v, off, (uint32_t)s * slot_bytes);
+                    if (s + AHEAD_UP < T) TR::template store<16>(urs, TR::mark(), off, (uint32_t)(s + AHEAD_UP) * slot_bytes);
+                } else if (p.y_blocked) {
+                    *reinterpret_cast<pub_t*>(reinterpret_cast<char*>(out) + ((size_t)cb * T + t) * p.D * slot_bytes +
+                                              (size_t)d * slot_bytes + TR::pub_off(unit0, Bs, lane)) = v;
+                } else if (unit0 < p.out_units) {
+                    *reinterpret_cast<pub_t*>(out + ((size_t)t * p.y_t + (size_t)col * p.y_b) * (p.D * p.out_units) +
+                                              (size_t)d * p.out_units + unit0 + TR::pub_unit(lane)) = v;
+                }
+            }
+            asm volatile("" ::: "memory");
+        };
+        start_wait();
+        // The input part of step sx, between barriers sx - 1 and sx.  h wave w picks it up as the start of its accumulators
+        // while its state fragments travel.  The layer output of step sx - 1 leaves behind it, or before it where the product
+        // is long: that waits for h wave w, on the same SIMD, to be through its gates, whose vector instructions otherwise
+        // queue behind this wave's matrix instructions one by one (2 layers of 512 units in fp32, 4096 clocks of product: 4200
+        // clocks of gate phase instead of 300; where the product is no longer than the exchange of the state, waiting first
+        // makes it late instead: 2 layers of 512 units in bf16, both directions, batch 64: 730 us against 687).
+        constexpr bool OUT_FIRST = XLN * MPL * RT * TR::MMA_CLOCKS > 512;
+        auto produce = [&](int sx, u32x4 (&cur)[XLN]) {
+            bool sent = sx == 0;
+            if (OUT_FIRST && !sent) { forward(sx - 1); sent = true; }
+            if (fused) {
+                unsigned spins = 0;
+                for (;;) {
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int i = 0; i < XLN; ++i) m = TR::seen(m, cur[i]);
+                    if (!__any(m == UNWRITTEN) || aborted) break;
+                    if (!sent) { forward(sx - 1); sent = true; }     // nothing to multiply yet
+                    if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
+                    request(sx, cur);
+                    asm volatile("" ::: "memory");
+                }
+            }
+            if (rows) {                              // (no barrier: LDS operations of a wave keep their order)
+#pragma unroll
+                for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
+            }
+            f32x4 acc[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (project) {
+                if (KEEP) acc[0] = __builtin_bit_cast(f32x4, cur[0]);
+                else {
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        if (rt == w) acc[rt] = __builtin_bit_cast(f32x4, cur[0]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < XLN; ++i)
+#pragma unroll
+                    for (int j = 0; j < MPL; ++j)
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][i * MPL + j], TR::part(cur[i], j), acc[rt]);
+                // Results of a matrix instruction may be read a number of wait states after it was issued; the compiler
+                // counts them inside a block, but was seen not to where two branches join before the read (fp32, RT = 1).
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(acc[rt]));
+                asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(acc[RT - 1]));
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) xacc[(w * RT + rt) * 64 + lane] = acc[rt];
+            asm volatile("" ::: "memory");           // (LDS operations of a wave keep their order)
+            if (lane == 0) lds_put(ready + w, (unsigned)(sx + 1));
+            if (!sent) forward(sx - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            request(sx + (fused ? 1 : NBUF), cur);      // (a step of the layer below is asked for when the one before it has come)
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            if (RB) __syncthreads();
+        };
+        if (fused) {
+            request(0, xb[0]);
+            for (int s = 0; s < T; ++s) produce(s, xb[0]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < NBUF; ++b) request(b, xb[b]);
+            for (int s0 = 0; s0 < T; s0 += NBUF)
+#pragma unroll
+                for (int b = 0; b < NBUF; ++b)
+                    if (s0 + b < T) produce(s0 + b, xb[b]);
+        }
+        forward(T - 1);
+        return;
+    }
+
+    // ---- h waves -------------------------------------------------------------------------------------
+    __builtin_amdgcn_s_setprio(3);                   // the dependency chain runs through these
+    const int rot = rb % LN;                         // workgroups start at different K blocks: spreads them over the L2 channels
+    frag wh[RT][LN * MPL];
+    {
+        const elem* whh = static_cast<const elem*>(p.whh[ld]);
+#pragma unroll
+        for (int i = 0; i < LN; ++i) {
+            const int ir = i + rot >= LN ? i + rot - LN : i + rot;
+            const int k = ((w * LN + ir) * 4 + q) * EPC;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const size_t row = (size_t)(rb * RT + tile_of(rt)) * 16 + n;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(whh + row * H + k);
+#pragma unroll
+                for (int j = 0; j < MPL; ++j) wh[rt][i * MPL + j] = TR::part(v, j);
+            }
+        }
+    }
+    const uint32_t hoff = ((uint32_t)(w * LN * 4 + q) * Bs + nc) * 16u;
+
+    float c_reg[NOWN], h_reg[NOWN];
+    f32x4 bias_reg[NOWN];
+    CellExt ext_reg[EXT ? NOWN : 1];
+    const int len = valid ? (p.lengths ? min(max(p.lengths[col], 0), T) : T) : 0;
+    const int Hu = p.out_units_state;                // width of the caller's state tensors
+    const size_t state_row = (size_t)(l * p.D + d) * p.state_b + col;
+#pragma unroll
+    for (int o = 0; o < NOWN; ++o) {
+        const int unit = min((rb * RT + w + 4 * o) * 4 + q, H - 1);
+        c_reg[o] = h_reg[o] = 0.0f;
+        bias_reg[o] = *reinterpret_cast<const f32x4*>(p.bias[ld] + (size_t)unit * SLOTS);
+        if constexpr (EXT) ext_reg[o] = load_cell_ext(GATES == CELL_LSTM ? p.peep[ld] : nullptr, H, unit, p.clip);
+        if (valid && unit < Hu) {
+            if (p.h0) h_reg[o] = p.h0[state_row * Hu + unit];
+            if (p.c0) c_reg[o] = p.c0[state_row * Hu + unit];
+        }
+    }
+    u32x4 hv[LN];                                    // B fragments of the state before the step
+#pragma unroll
+    for (int i = 0; i < LN; ++i) {                   // step 0: the caller's h0
+        const int ir = i + rot >= LN ? i + rot - LN : i + rot;
+        const int k = ((w * LN + ir) * 4 + q) * EPC;
+        float f[EPC];
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) f[e] = 0.0f;
+        if (p.h0 && k < Hu) {
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) f[e] = p.h0[state_row * Hu + k + e];
+        }
+        hv[i] = TR::pack(f);
+    }
+    start_wait();
+    const bool local = __builtin_amdgcn_readfirstlane((int)lds_get(placed)) != 0;
+
+    auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s) {         // request slot s
+#pragma unroll
+        for (int i = 0; i < LN; ++i) {
+            const int ir = i + rot >= LN ? i + rot - LN : i + rot;
+            hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff, slot_of(s) + (uint32_t)(ir * 64) * Bs, 16);
+        }
+    };
+    // Slot s in hv, waiting until all of it has been written; `meanwhile` runs while the first request travels.
+    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, auto meanwhile) {
+        unsigned spins = 0;
+        for (;;) {
+            ask(rs, s);
+            if (spins == 0u) meanwhile();
+            uint32_t m = 0;
+#pragma unroll
+            for (int i = 0; i < LN; ++i) m = TR::seen(m, hv[i]);
+            if (!__any(m == UNWRITTEN) || aborted) break;
+            if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
+            asm volatile("" ::: "memory");
+        }
+        asm volatile("" ::: "memory");
+    };
+    // partial products of this wave's K quarter added to acc; all tiles but the wave's own go to LDS
+    auto multiply = [&](f32x4 (&acc)[RT], int buf) {
+#pragma unroll
+        for (int i = 0; i < LN; ++i)
+#pragma unroll
+            for (int j = 0; j < MPL; ++j)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][i * MPL + j], TR::part(hv[i], j), acc[rt]);
+#pragma unroll
+        for (int rt = KEEP ? 1 : 0; rt < RT; ++rt)
+            red[buf * PART + (tile_of(rt) * OTHERS + (KEEP ? rt - 1 : w)) * 64 + lane] = acc[rt];
+    };
+    // after the barrier: the sum of tile w over the four K quarters
+    auto total = [&](const f32x4 (&acc)[RT], int buf) -> f32x4 {
+        const int rt = min(w, RT - 1);
+        f32x4 part[OTHERS];
+#pragma unroll
+        for (int k = 0; k < OTHERS; ++k) part[k] = red[buf * PART + (rt * OTHERS + k) * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);           // (one LDS round trip)
+        return ((KEEP ? acc[0] : part[OTHERS - 1]) + part[0]) + (part[1] + part[2]);
+    };
+    auto publish = [&](__amdgpu_buffer_rsrc_t rs, pub_t v, int unit0, int s) {   // slot s of this lane's share; mark slot s + AHEAD
+        if (valid && lane < TR::PUB_LANES) {
+            const uint32_t off = TR::pub_off(unit0, Bs, lane);
+            if (local) {
+                TR::template store<0>(rs, v, off, slot_of(s));
+                if (s + AHEAD < T) TR::template store<0>(rs, TR::mark(), off, slot_of(s + AHEAD));
+            } else {
+                TR::template store<16>(rs, v, off, slot_of(s));
+                if (s + AHEAD < T) TR::template store<16>(rs, TR::mark(), off, slot_of(s + AHEAD));
+            }
+        }
+    };
+    for (int s = 0; s < T; ++s) {
+        const int t = d ? T - 1 - s : s;
+        f32x4 acc[RT];                               // starts as the input part
+        auto input_part = [&]() {
+            while (lds_get(ready + w) < (unsigned)(s + 1)) {}  // (every x wave takes every step, whatever became of its waits)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt] = xacc[(w * RT + rt) * 64 + lane];
+        };
+        if (s > 0) fetch(hrs, s - 1, input_part);
+        else input_part();
+        multiply(acc, RB ? 0 : (s & 1));
+        __syncthreads();
+        f32x4 pre[NOWN];
+#pragma unroll
+        for (int o = 0; o < NOWN; ++o) pre[o] = total(acc, RB ? 0 : (s & 1)) + bias_reg[o];
+        float zg[RB ? NOWN : 1], nx[RB ? NOWN : 1];
+        if constexpr (RB) {
+            // r * h goes round the group before the candidate's recurrent product
+#pragma unroll
+            for (int o = 0; o < NOWN; ++o) {
+                if (w + 4 * o < RT) {
+                    const float r = sigmoid_f(limit_to(pre[o][0], ext_reg[o].lim));
+                    zg[o] = sigmoid_f(limit_to(pre[o][1], ext_reg[o].lim));
+                    nx[o] = pre[o][2];
+                    float unused;
+                    pub_t sv, ov;
+                    TR::gather(TR::store_val(r * h_reg[o], unused), TR::zero(), sv, ov);
+                    publish(rrs, sv, (rb * RT + w + 4 * o) * 4, s);
+                }
+            }
+            fetch(rrs, s, [] {});
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            multiply(acc, 1);
+            __syncthreads();
+            pre[0][3] = total(acc, 1)[3] + bias_reg[0][3];
+        }
+#pragma unroll
+        for (int o = 0; o < NOWN; ++o) {
+            const int rt = w + 4 * o;
+            if (rt < RT) {                           // uniform per wave
+                const bool active = valid && t < len;
+                float c_new = c_reg[o];
+                float hn;
+                if constexpr (RB) {
+                    const float nn = tanh_f(limit_to(nx[o] + pre[o][3], ext_reg[o].lim));
+                    hn = (1.0f - zg[o]) * nn + zg[o] * h_reg[o];
+                } else {
+                    const float a[SLOTS] = {pre[o][0], pre[o][1], pre[o][2], pre[o][3]};
+                    if constexpr (EXT) hn = cell_update_ext<GATES>(a, h_reg[o], c_new, ext_reg[o]);
+                    else hn = cell_update<GATES>(a, h_reg[o], c_new);
+                }
+                if (active) {
+                    float kept;
+                    (void)TR::store_val(hn, kept);
+                    c_reg[o] = c_new;
+                    h_reg[o] = kept;
+                }
+                float unused;
+                const elem state_v = TR::store_val(h_reg[o], unused);   // held value when inactive
+                const elem out_v = active ? state_v : TR::zero();
+                const int unit0 = (rb * RT + rt) * 4;
+                pub_t sv, ov;
+                TR::gather(state_v, out_v, sv, ov);
+                if (s + 1 < T) publish(hrs, sv, unit0, s);
+                if (lane < TR::PUB_LANES) pub[rt * TR::PUB_LANES + lane] = last ? ov : sv;
+                asm volatile("" ::: "memory");       // (LDS operations of a wave keep their order)
+                if (lane == 0) lds_put(done + w, (unsigned)(s + 1));
+            }
+        }
+        if (p.ticks && tid == 0 && rb == 0 && cb == 0) p.ticks[(size_t)ld * T + s] = wall_clock64();
+    }
+
+#pragma unroll
+    for (int o = 0; o < NOWN; ++o) {
+        const int unit = (rb * RT + w + 4 * o) * 4 + q;
+        if (w + 4 * o < RT && valid && unit < Hu) {
+            if (p.hT) p.hT[state_row * Hu + unit] = h_reg[o];
+            if (p.cT && GATES == CELL_LSTM) p.cT[state_row * Hu + unit] = c_reg[o];
+        }
+    }
+}
+
+// Forces one workgroup per compute unit: more than half of the 160 KiB.
+constexpr size_t MIN_LDS = 84 * 1024;
+
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
+hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
+    const size_t need = (size_t)((RT == 4 ? 6 : 8) + 4) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
+                        9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16;
+    const size_t smem = need < MIN_LDS ? MIN_LDS : need;
+    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT>;
+    static bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    kern<<<dim3(8 * a.gpx * a.nrb), dim3(512), smem, stream>>>(a);
+    return hipGetLastError();
+}
+
+template <class TR, int RT, int LN, int XLN>
+hipError_t launch_cell(const WavefrontXcdArgs& a, hipStream_t stream) {
+#if RNN_XR_KIND == 2
+    return launch_variant<TR, CELL_GRU_RB, RT, LN, XLN, true>(a, stream);
+#else
+    if (a.cell == CELL_LSTM) return launch_variant<TR, CELL_LSTM, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
+    return launch_variant<TR, CELL_GRU, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
+#endif
+}
+
+// (RT, LN) that are compiled: a group of at most 32 workgroups, H = LN * 128 (bf16) or LN * 64 (fp32) units
+#define RNN_XR_SHAPES_0(X) X(1, 1) X(2, 1) X(2, 2) X(4, 1) X(4, 2) X(4, 3) X(4, 4)
+#define RNN_XR_SHAPES_1(X) X(1, 1) X(1, 2) X(2, 1) X(2, 2) X(2, 4) X(4, 1) X(4, 2) X(4, 4) X(4, 8)
+
+#if RNN_XR_DT == 0
+typedef XRBf16 TRHere;
+#define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_0(X)
+#else
+typedef XRF32 TRHere;
+#define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_1(X)
+#endif
+
+template <int RT, int LN>
+hipError_t launch_shape(const WavefrontXcdArgs& a, hipStream_t stream) {
+    switch (a.xln) {
+        case 1: return launch_cell<TRHere, RT, LN, 1>(a, stream);
+        case 2: return launch_cell<TRHere, RT, LN, 2>(a, stream);
+        case 4: return launch_cell<TRHere, RT, LN, 4>(a, stream);
+        case 8: return launch_cell<TRHere, RT, LN, 8>(a, stream);
+        case 3: if constexpr (LN == 3) return launch_cell<TRHere, RT, LN, 3>(a, stream); else break;
+        case 6: if constexpr (LN == 3) return launch_cell<TRHere, RT, LN, 6>(a, stream); else break;
+        default: break;
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_here(const WavefrontXcdArgs& a, hipStream_t stream, int LN) {
+#define X(rt, ln) if (a.RT == rt && LN == ln) return launch_shape<rt, ln>(a, stream);
+    RNN_XR_SHAPES_HERE(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+#define RNN_XR_FN2(dt, kind) launch_wavefront_xcd_dt##dt##_kind##kind
+#define RNN_XR_FN(dt, kind) RNN_XR_FN2(dt, kind)
+hipError_t RNN_XR_FN(RNN_XR_DT, RNN_XR_KIND)(const WavefrontXcdArgs& a, hipStream_t stream, int LN) { return launch_here(a, stream, LN); }
+
+#if RNN_XR_DT == 0 && RNN_XR_KIND == 0
+hipError_t launch_wavefront_xcd_dt0_kind1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+
+namespace {
+int state_chunks(int dtype, int H) {             // LN, or 0 when H is no multiple of a wave's load
+    const int unit = dtype == DT_BF16 ? 128 : 64;
+    return H % unit == 0 ? H / unit : 0;
+}
+}  // namespace
+
+bool wavefront_xcd_variant_exists(int dtype, int RT, int H) {
+    const int LN = state_chunks(dtype, H);
+#define X(rt, ln) if (RT == rt && LN == ln) return true;
+    if (dtype == DT_BF16) { RNN_XR_SHAPES_0(X) }
+    else { RNN_XR_SHAPES_1(X) }
+#undef X
+    return false;
+}
+
+int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers) {
+    const int LN = state_chunks(dtype, H), epc = dtype == DT_BF16 ? 8 : 4;
+    if (width % epc != 0) return 0;
+    int need = ((width + 4 * epc - 1) / (4 * epc) + 3) / 4;
+    if (several_layers && need < LN) need = LN;
+    static const int have[] = {1, 2, 3, 4, 6, 8};
+    for (int v : have)
+        if (v >= need && (LN == 3 || (v != 3 && v != 6))) return v;
+    return 0;
+}
+
+size_t wavefront_xcd_slot_bytes(int dtype, int B, int H) {
+    return (size_t)H * (B < 16 ? B : 16) * (dtype == DT_BF16 ? 2 : 4);
+}
+
+hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
+    const int LN = state_chunks(a.dtype, a.H);
+    if (LN == 0 || a.LP < 1 || a.LP > WF_MAX_LAYERS || (a.D != 1 && a.D != 2) || (a.LP > 1 && a.D != 1)) return hipErrorInvalidValue;
+    if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 || a.ncb != (a.B + 15) / 16 || a.gpx * 8 < a.LP * a.D * a.ncb) return hipErrorInvalidValue;
+    // with a projection the x waves of the first layer multiply nothing, whatever its input's width
+    if ((a.gx == nullptr && a.xin == nullptr) || a.xln == 0 ||
+        wavefront_xcd_input_chunks(a.dtype, a.H, a.gx ? a.H : a.I, a.LP > 1) != a.xln) return hipErrorInvalidValue;
+    if (a.ring <= a.T && ((a.ring & (a.ring - 1)) != 0 || a.ring < 2 * XCD_AHEAD)) return hipErrorInvalidValue;
+    if ((size_t)a.T * wavefront_xcd_slot_bytes(a.dtype, a.B, a.H) >= ((size_t)1 << 31)) return hipErrorInvalidValue;
+    const int kind = a.reset_before ? 2 : a.ext ? 1 : 0;
+    if (a.reset_before && a.cell != CELL_GRU) return hipErrorInvalidValue;
+    if (a.dtype == DT_BF16)
+        return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1(a, stream, LN)
+                                                                  : launch_wavefront_xcd_dt0_kind2(a, stream, LN);
+    return kind == 0 ? launch_wavefront_xcd_dt1_kind0(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt1_kind1(a, stream, LN)
+                                                                                 : launch_wavefront_xcd_dt1_kind2(a, stream, LN);
+}
+#endif  // RNN_XR_DT == 0 && RNN_XR_KIND == 0
+
+}  // namespace rnn

@@ -1,0 +1,4 @@
+// Variants of the XCD-resident kernel: bf16, peephole and clipping terms (see wavefront_xcd.hip).
+#define RNN_XR_DT 0
+#define RNN_XR_KIND 1
+#include "wavefront_xcd.hip"

@@ -1,0 +1,111 @@
+"""The XCD-resident kernel at the sizes where its indexing and its exchange can go wrong, against the CPU oracle: every tile
+height, first and last width of each, input widths around a wave's loads, 1, 2, 3 and 16 + 1 sequences, fewer and more steps than
+a slot is marked ahead, both directions, several launches, several passes, the projection in front, padded widths in either
+layout, and the GRU with the reset gate before the product in the same shapes."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-4, 1: 2e-2}
+
+SHAPES = [
+    # cell, L, D, I, H, T, B, dtype
+    (0, 1, 1, 128, 128, 1, 1, 1),       # one step: nothing is exchanged
+    (0, 2, 1, 128, 128, 1, 3, 1),       # one step through two layers
+    (1, 2, 1, 40, 128, 2, 2, 1),        # input of one and a quarter K blocks, rows read without the turn through LDS
+    (0, 3, 1, 136, 256, 5, 17, 1),      # a second block of one sequence; as many steps as a slot is marked ahead, and one
+    (1, 2, 1, 1024, 384, 9, 3, 1),      # widest input inside, three chunks per wave
+    (0, 2, 1, 1032, 256, 6, 5, 1),      # wider than that: projection, layers above fused
+    (0, 2, 2, 384, 384, 10, 33, 1),     # both directions, the second launch reads the first one's chunks (six loads per wave)
+    (0, 5, 1, 512, 512, 13, 40, 1),     # more groups than XCDs: two launches
+    (1, 2, 1, 512, 512, 7, 150, 1),     # one layer per launch, or several passes
+    (0, 2, 2, 200, 200, 8, 20, 1),      # padded to 256 units
+    (0, 2, 1, 56, 520, 6, 4, 1),        # (padded to 640 units: beyond this kernel)
+    (0, 1, 1, 12, 32, 7, 4, 0),         # fp32 narrower than a wave's load
+    (1, 3, 1, 20, 64, 11, 3, 0),
+    (0, 2, 1, 7, 64, 6, 2, 0),          # fp32 input rows that are not whole chunks: projection
+    (0, 12, 1, 64, 64, 20, 8, 0),       # twelve layers, two groups per XCD
+    (0, 2, 2, 128, 128, 9, 18, 0),
+    (0, 1, 1, 500, 256, 6, 16, 0),
+    (0, 2, 1, 512, 512, 6, 70, 0),      # the longest products; a last block of six sequences
+]
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2307_11339_amd import harness, rnn, workloads
+    rnn.load_library()
+    return harness, rnn, workloads
+
+
+def _workload(W, shape, ragged):
+    cell, L, D, I, H, T, B, dtype = shape
+    cfg = W.Config("xcd", cell, L=L, D=D, I=I, H=H, T=T, B=B, dtype=dtype, seed=W.BASE_SEED + 3000 + H + 7 * B + T,
+                   h0_std=0.5, len_min=1 if ragged else None)
+    wl = W.make_workload(cfg, zero_pad_x=False)
+    if cell == 0:
+        wl.c0 = np.random.default_rng(cfg.seed).uniform(-1, 1, size=(L * D, B, H)).astype(np.float32)
+    return wl
+
+
+def _check(harness, wl, io, ref):
+    y, hT, cT, ybits = harness.results(io)
+    tol = TOL[wl.cfg.dtype]
+    assert np.abs(y - ref[0]).max() <= tol and np.abs(hT - ref[1]).max() <= tol
+    if wl.cfg.cell == 0:
+        assert np.abs(cT - ref[2]).max() <= tol
+    if wl.lengths is not None:
+        for j, n in enumerate(wl.lengths):
+            assert np.all(ybits[int(n):, j] == 0), "padded positions must be +0.0 bit patterns"
+
+
+@pytest.mark.parametrize("ragged", [False, True], ids=["full", "ragged"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
+def test_against_oracle(gpu, oracle, shape, ragged):
+    """Three calls (the second and third on memory the first left behind) agree bit for bit, and with the oracle; so does
+    the batch-first call."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, ragged)
+    c = wl.cfg
+    print("\n  case %r ragged %r" % (shape, ragged), flush=True)
+    model = harness.DeviceModel(wl)
+    io = harness.DeviceIO(wl)
+    harness.forward(model, io)
+    _check(harness, wl, io, oracle.forward_workload(wl, nthreads=8))
+    y, hT = io.y.clone(), io.hT.clone()
+    for _ in range(2):
+        io.y.fill_(7.0)
+        harness.forward(model, io)
+        torch.cuda.synchronize()
+        assert torch.equal(io.y, y) and torch.equal(io.hT, hT)
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    assert rnn.rnn_model_set_batch_first(model.handle, 1) == rnn.RNN_OK
+    y_bf = torch.full((c.B, c.T, c.D * c.H), 7.0, dtype=io.y.dtype, device="cuda")
+    assert rnn.rnn_forward(model.handle, io.x.transpose(0, 1).contiguous(), io.lengths, io.h0, io.c0, y_bf, io.hT, io.cT, c.T, c.B,
+                           torch.cuda.current_stream()) == rnn.RNN_OK
+    torch.cuda.synchronize()
+    assert torch.equal(y_bf.transpose(0, 1), y) and torch.equal(io.hT, hT)
+    model.close()
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == 1] + [(1, 1, 2, 64, 256, 1, 5, 1)],
+                         ids=lambda s: "L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[1:7] + ("f32" if s[7] == 0 else "bf16",)))
+def test_reset_gate_before_the_product(gpu, oracle, shape):
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, True)
+    print("\n  case %r" % (shape,), flush=True)
+    model = harness.DeviceModel(wl)
+    assert rnn.rnn_model_set_gru_reset_before(model.handle, 1) == rnn.RNN_OK
+    io = harness.DeviceIO(wl)
+    harness.forward(model, io)
+    _check(harness, wl, io, oracle.forward_workload(wl, nthreads=8, gru_variant=1))
+    assert rnn.rnn_model_set_clip(model.handle, 0.4) == rnn.RNN_OK
+    harness.forward(model, io)
+    _check(harness, wl, io, oracle.forward_workload(wl, nthreads=8, gru_variant=1, clip=0.4))
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    model.close()
