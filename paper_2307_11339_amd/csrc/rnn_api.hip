@@ -846,12 +846,12 @@ int forward_wavefront(rnn_model* m, const Plan& plan, const void* x, const int32
     return RNN_OK;
 }
 
-// Forward pass on the XCD-resident kernel: sequences b0 .. b0 + bc - 1 of the caller's tensors (Bc sequences, x and y in either
-// layout, states at the caller's width), which the kernels address in place.
+// Forward pass on the XCD-resident kernel: sequences b0 .. b0 + bc - 1 of tensors that hold Bc sequences (x and y in either
+// layout, y and states `units` wide), which the kernels address in place.
 int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0, void* y,
-                float* hT, float* cT, int T, int Bc, int b0, int bc, const float* gx0, hipStream_t st) {
+                float* hT, float* cT, int T, int Bc, int b0, int bc, int units, bool batch_first, const float* gx0, hipStream_t st) {
     const size_t slot = wavefront_xcd_slot_bytes(m->dtype, bc, m->H);
-    const int xt = m->batch_first ? 1 : Bc, xb = m->batch_first ? T : 1;
+    const int xt = batch_first ? 1 : Bc, xb = batch_first ? T : 1;
     const int N4 = SLOTS * m->H;
     for (int l0 = 0, LP = 0; l0 < m->L; l0 += LP) {
         int first;
@@ -900,18 +900,18 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.xln = wavefront_xcd_input_chunks(m->dtype, m->H, a.gx ? m->H : a.I, LP > 1);
         const int l1 = l0 + LP - 1;
         if (l1 == m->L - 1) {
-            a.out = (char*)y + (size_t)b0 * xb * m->D * m->Hu * m->esize;
+            a.out = (char*)y + (size_t)b0 * xb * m->D * units * m->esize;
             a.y_t = xt; a.y_b = xb;
-            a.out_units = m->Hu;
+            a.out_units = units;
         } else {
             a.out = m->ws.ybuf[ybuf_slot(m, plan, l1, T)].p;
             a.y_t = bc; a.y_b = 1;
             a.y_blocked = input_product_inside(m, plan, l1 + 1, T) ? 1 : 0;
             a.out_units = m->H;
         }
-        a.out_units_state = m->Hu;
+        a.out_units_state = units;
         a.state_b = Bc;
-        const size_t so = (size_t)b0 * m->Hu;
+        const size_t so = (size_t)b0 * units;
         a.h0 = h0 ? h0 + so : nullptr; a.c0 = c0 ? c0 + so : nullptr;
         a.hT = hT ? hT + so : nullptr; a.cT = cT ? cT + so : nullptr;
         a.lengths = lengths ? lengths + b0 : nullptr;
@@ -933,9 +933,10 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
     return RNN_OK;
 }
 
-// All passes of a call on the XCD-resident kernel.
+// All passes of a call on the XCD-resident kernel: on the caller's tensors (units = Hu, the caller's layout), or on the time-major
+// copies at the padded width of a pass whose batch as a whole runs on another kernel.
 int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0,
-                       void* y, float* hT, float* cT, int T, int B, hipStream_t st) {
+                       void* y, float* hT, float* cT, int T, int B, int units, bool batch_first, hipStream_t st) {
     const float* gx0 = nullptr;
     const int N4 = SLOTS * m->H;
     if (!input_product_inside(m, plan, 0, T)) {      // projection of the first layer, for all sequences at once
@@ -954,7 +955,7 @@ int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int3
             if (rc != RNN_OK) return rc;
             if (!pass.xcd) return RNN_EDEVICE;       // (a smaller batch of the same shape always has such a plan)
         }
-        const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, gx0, st);
+        const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, units, batch_first, gx0, st);
         if (rc != RNN_OK) return rc;
     }
     return RNN_OK;
@@ -962,6 +963,7 @@ int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int3
 
 int forward_one_pass(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0,
                      const float* c0, void* y, float* hT, float* cT, int T, int B, hipStream_t st) {
+    if (plan.xcd) return forward_xcd_passes(m, plan, x, lengths, h0, c0, y, hT, cT, T, B, m->H, false, st);
     return (plan.kind == RNN_PLAN_WAVEFRONT) ? forward_wavefront(m, plan, x, lengths, h0, c0, y, hT, cT, T, B, st)
                                              : forward_cellwise(m, x, lengths, h0, c0, y, hT, cT, T, B, st);
 }
@@ -1266,7 +1268,7 @@ static int forward_entry(rnn_model* m, const void* x, const int32_t* lengths, co
         HIP_TRY(launch_fill_zero(m->ws.lseq.p, m->ws.lseq.bytes, st));
     }
     if (m->cell == CELL_GRU) { c0 = nullptr; cT = nullptr; }
-    if (plan.xcd) return forward_xcd_passes(m, plan, x, lengths, h0, c0, y, hT, cT, T, B, st);
+    if (plan.xcd) return forward_xcd_passes(m, plan, x, lengths, h0, c0, y, hT, cT, T, B, m->Hu, m->batch_first, st);
     void* y_caller = nullptr;
     if (m->batch_first) {   // the plans work on time-major copies
         HIP_TRY(launch_swap_outer(x, m->ws.x_tm.p, B, T, (size_t)m->I * m->esize, st));
