@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librnn_mi355x.so")
-SOURCES = ["wavefront_xcd_d.hip", "wavefront_xcd_e.hip", "wavefront_xcd.hip", "wavefront_xcd_b.hip", "wavefront_xcd_f.hip", "wavefront_xcd_c.hip",
+SOURCES = ["wavefront_xcd_g.hip", "wavefront_xcd_h.hip", "wavefront_xcd_d.hip", "wavefront_xcd_e.hip", "wavefront_xcd.hip", "wavefront_xcd_b.hip", "wavefront_xcd_f.hip", "wavefront_xcd_c.hip",
            "wavefront_ll.hip", "wavefront_ll_b.hip", "wavefront_ll_c.hip", "wavefront_ll_d.hip", "wavefront_ll_e.hip",
            "wavefront_ll_f.hip", "wavefront_x.hip", "wavefront_x_b.hip", "wavefront.hip", "wavefront_b.hip",
            "rnn_api.hip", "gemm.hip", "cellwise.hip", "schedule.hip", "probe.hip", "rnn_stack.hip"]   # the slowest first

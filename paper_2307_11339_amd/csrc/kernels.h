@@ -131,13 +131,15 @@ hipError_t launch_wavefront_ll_init(int dtype, const float* h0, int l0, int LP, 
 // 8-byte words needed for `groups` (layer, direction) state sequences.
 size_t wavefront_ll_words(int dtype, int groups, int T, int B, int H);
 
-// ---- persistent kernel for groups that fit one XCD (wavefront_xcd.hip) ----------------------
+// ---- persistent kernel for groups that fit one XCD, or two of them (wavefront_xcd.hip) --------
 constexpr int XCD_AHEAD = 4;       // steps between marking a slot of a state sequence as unwritten and writing it
 struct WavefrontXcdArgs {
     int cell, dtype;
     int T, B, H, D, I;           // B: sequences of this launch; I: input width of layer l0 (xin)
     int l0, LP;
-    int RT, nrb, ncb, gpx;       // 16-row tiles and row blocks per group; blocks of 16 sequences; groups per XCD
+    int RT, nrb, ncb, gpx;       // 16-row tiles and row blocks per group; blocks of 16 sequences; groups per XCD (per `span` XCDs)
+    int stride;                  // sequences side by side in a chunk row of a state sequence: min(16, B) to 16
+    int span;                    // XCDs a group is spread over: 1, or 2 (groups of more than 32 workgroups)
     int xln;                     // chunk loads per x wave and step (wavefront_xcd_input_chunks)
     int ring;                    // slots of a state sequence: a power of two >= 2 * XCD_AHEAD, or more than T (every step its own)
     int ext, reset_before;
@@ -149,7 +151,7 @@ struct WavefrontXcdArgs {
     const float* gx;             // NULL, or the finished projection of layer l0: [rows, D, H, 4] (xin and I are not read)
     const void* xin;             // input of layer l0: [rows, I], 16-byte aligned rows
     int x_t, x_b;                // row of (step t, sequence b) of xin and gx: t * x_t + b * x_b
-    int x_blocked;               // xin has the layout of a state sequence instead: [ncb][T][I / units per chunk][min(16, B)][16 bytes]
+    int x_blocked;               // xin has the layout of a state sequence instead: [ncb][T][I / units per chunk][stride][16 bytes]
     void* out;                   // output of the last layer of the launch: [rows, D * out_units]
     int y_t, y_b;                // row of (t, b) of out
     int y_blocked;               // out gets the layout of x_blocked, D * H units wide, for the next launch
@@ -171,9 +173,10 @@ struct WavefrontXcdArgs {
 };
 hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream);
 bool wavefront_xcd_variant_exists(int dtype, int RT, int H);
+bool wavefront_xcd_wide_exists(int dtype, int RT, int H, bool reset_before);   // groups on two XCDs
 // Chunk loads per x wave for an input `width` wide (of the launch's first layer; several_layers: upper layers read inputs H
 // wide as well), or 0 when there is no such variant.
 int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers);
-size_t wavefront_xcd_slot_bytes(int dtype, int B, int H);
+size_t wavefront_xcd_slot_bytes(int dtype, int stride, int H);
 
 }  // namespace rnn

@@ -194,6 +194,10 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
     const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16;
     if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, B, m->H) >= ((size_t)1 << 31)) return false;
     const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
+    // One sequence in fp32, more than 256 units: a wave's share of the state is one load of tagged words but eight loads of
+    // chunks that hold one sequence each, and the tag-in-data kernel is faster (2 layers of 512 units, 64 steps: 322 us against
+    // 362; two sequences: 372 against 359).
+    if (m->dtype == DT_F32 && B == 1 && m->H > 256 && !m->two_products()) return false;
     for (int launches = (m->L + lp_max - 1) / lp_max; launches <= m->L; ++launches) {
         const int LP = (m->L + launches - 1) / launches;
         const int gpx = (LP * m->D * ncb + XCDS - 1) / XCDS;

@@ -12,9 +12,12 @@
 // XCDs in turn, so the launch numbers its groups by blockIdx % 8; nothing relies on that: every workgroup publishes
 // the XCC it really runs on before the first step (while its weights travel), and a group that finds itself on more
 // than one uses device-scope stores instead.
+// A bf16 layer of 640 to 1024 units needs more workgroups than an XCD has compute units: its group is laid over two, always with
+// device-scope stores.  What that still gains over tagged words (half the bytes, MFMA fragments straight from the load) stands at
+// the rule that chooses it; 16 sequences through one layer of 1024 units take 2.6 us a step instead of 4.
 //
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
-// the block side by side.  A lane's MFMA B fragment is one chunk, so a load instruction of a wave brings a whole K
+// the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B fragment is one chunk, so a load instruction of a wave brings a whole K
 // block of 16 sequences from 8 consecutive cache lines straight into the registers the matrix instruction reads: no
 // tags, no staging through LDS.  Whether a chunk has been written is told from the data: a slot is filled with the bit
 // pattern of all ones (two bf16 NaNs; one fp32 NaN) several steps before it is used, no published value has that
@@ -169,10 +172,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     const int n = lane & 15, q = lane >> 4;
     auto tile_of = [&](int j) -> int { return KEEP ? (w + j) & 3 : j; };   // this wave's j-th tile
 
-    // workgroup b runs on XCD b % 8: gpx groups of nrb workgroups on each
-    const int gi = (int)(blockIdx.x >> 3) / p.nrb;
-    const int rb = (int)(blockIdx.x >> 3) - gi * p.nrb;
-    const int g = (int)(blockIdx.x & 7) * p.gpx + gi;             // (cb, d, ll), the layers of a column block side by side
+    // workgroup b runs on XCD b % 8: gpx groups of nrb workgroups on each, or on each pair of neighbouring XCDs (half a group on
+    // either; consecutive row blocks, which write neighbouring chunks, stay together)
+    const int two = p.span == 2 ? 1 : 0;
+    const int here = p.nrb >> two;                                // workgroups of a group on one XCD
+    const int gi = (int)(blockIdx.x >> 3) / here;
+    const int rb = (int)(blockIdx.x >> 3) - gi * here + (two ? (int)(blockIdx.x & 1) * here : 0);
+    const int g = ((int)(blockIdx.x & 7) >> two) * p.gpx + gi;    // (cb, d, ll), the layers of a column block side by side
     if (g >= p.LP * p.D * p.ncb) return;
     const int ll = g % p.LP, d = (g / p.LP) % p.D, cb = g / (p.LP * p.D);
     const int l = p.l0 + ll, ld = ll * p.D + d;
@@ -180,7 +186,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     const bool project = ll == 0 && p.gx != nullptr;
     const bool last = ll == p.LP - 1;                // writes the layer output; the others hand their state to the layer above
     const int H = p.H, T = p.T, B = p.B;
-    const int Bs = min(16, B);                       // sequences side by side in a chunk row
+    const int Bs = p.stride;                         // sequences side by side in a chunk row
     const int ncol = min(16, B - cb * 16);
     const int nc = min(n, ncol - 1);                 // columns beyond the block repeat its last sequence and are never stored
     const bool valid = n < ncol;
@@ -622,7 +628,7 @@ hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
         if (e != hipSuccess) return e;
         configured = true;
     }
-    kern<<<dim3(8 * a.gpx * a.nrb), dim3(512), smem, stream>>>(a);
+    kern<<<dim3(8 * a.gpx * (a.nrb / a.span)), dim3(512), smem, stream>>>(a);
     return hipGetLastError();
 }
 
@@ -640,9 +646,20 @@ hipError_t launch_cell(const WavefrontXcdArgs& a, hipStream_t stream) {
 #define RNN_XR_SHAPES_0(X) X(1, 1) X(2, 1) X(2, 2) X(4, 1) X(4, 2) X(4, 3) X(4, 4)
 #define RNN_XR_SHAPES_1(X) X(1, 1) X(1, 2) X(2, 1) X(2, 2) X(2, 4) X(4, 1) X(4, 2) X(4, 4) X(4, 8)
 
+// ... and, in bf16, of 40, 48 or 64 workgroups on two XCDs (1024 units are as many as the registers hold: 32 K blocks of four
+// tiles are 128 registers of weights in a wave).  Translation units of their own (RNN_XR_WIDE).
+#define RNN_XR_SHAPES_WIDE(X) X(4, 5) X(4, 6) X(4, 8)
+#ifndef RNN_XR_WIDE
+#define RNN_XR_WIDE 0
+#endif
+
 #if RNN_XR_DT == 0
 typedef XRBf16 TRHere;
+#if RNN_XR_WIDE
+#define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_WIDE(X)
+#else
 #define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_0(X)
+#endif
 #else
 typedef XRF32 TRHere;
 #define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_1(X)
@@ -656,7 +673,7 @@ hipError_t launch_shape(const WavefrontXcdArgs& a, hipStream_t stream) {
         case 4: return launch_cell<TRHere, RT, LN, 4>(a, stream);
         case 8: return launch_cell<TRHere, RT, LN, 8>(a, stream);
         case 3: if constexpr (LN == 3) return launch_cell<TRHere, RT, LN, 3>(a, stream); else break;
-        case 6: if constexpr (LN == 3) return launch_cell<TRHere, RT, LN, 6>(a, stream); else break;
+        case 6: if constexpr (LN == 3 || LN == 5 || LN == 6) return launch_cell<TRHere, RT, LN, 6>(a, stream); else break;
         default: break;
     }
     return hipErrorInvalidValue;
@@ -671,16 +688,18 @@ hipError_t launch_here(const WavefrontXcdArgs& a, hipStream_t stream, int LN) {
 
 }  // namespace
 
-#define RNN_XR_FN2(dt, kind) launch_wavefront_xcd_dt##dt##_kind##kind
-#define RNN_XR_FN(dt, kind) RNN_XR_FN2(dt, kind)
-hipError_t RNN_XR_FN(RNN_XR_DT, RNN_XR_KIND)(const WavefrontXcdArgs& a, hipStream_t stream, int LN) { return launch_here(a, stream, LN); }
+#define RNN_XR_FN2(dt, kind, wide) launch_wavefront_xcd_dt##dt##_kind##kind##_wide##wide
+#define RNN_XR_FN(dt, kind, wide) RNN_XR_FN2(dt, kind, wide)
+hipError_t RNN_XR_FN(RNN_XR_DT, RNN_XR_KIND, RNN_XR_WIDE)(const WavefrontXcdArgs& a, hipStream_t stream, int LN) { return launch_here(a, stream, LN); }
 
-#if RNN_XR_DT == 0 && RNN_XR_KIND == 0
-hipError_t launch_wavefront_xcd_dt0_kind1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+#if RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE
+hipError_t launch_wavefront_xcd_dt0_kind1_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind2_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind0_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind1_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind2_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind0_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind1_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
 
 namespace {
 int state_chunks(int dtype, int H) {             // LN, or 0 when H is no multiple of a wave's load
@@ -698,6 +717,15 @@ bool wavefront_xcd_variant_exists(int dtype, int RT, int H) {
     return false;
 }
 
+bool wavefront_xcd_wide_exists(int dtype, int RT, int H, bool reset_before) {
+    const int LN = state_chunks(dtype, H);
+    if (dtype != DT_BF16 || reset_before) return false;
+#define X(rt, ln) if (RT == rt && LN == ln) return true;
+    RNN_XR_SHAPES_WIDE(X)
+#undef X
+    return false;
+}
+
 int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers) {
     const int LN = state_chunks(dtype, H), epc = dtype == DT_BF16 ? 8 : 4;
     if (width % epc != 0) return 0;
@@ -705,31 +733,38 @@ int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers)
     if (several_layers && need < LN) need = LN;
     static const int have[] = {1, 2, 3, 4, 6, 8};
     for (int v : have)
-        if (v >= need && (LN == 3 || (v != 3 && v != 6))) return v;
+        if (v >= need && (LN == 3 || v != 3) && (LN == 3 || LN == 5 || LN == 6 || v != 6)) return v;
     return 0;
 }
 
-size_t wavefront_xcd_slot_bytes(int dtype, int B, int H) {
-    return (size_t)H * (B < 16 ? B : 16) * (dtype == DT_BF16 ? 2 : 4);
+size_t wavefront_xcd_slot_bytes(int dtype, int stride, int H) {
+    return (size_t)H * stride * (dtype == DT_BF16 ? 2 : 4);
 }
 
 hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     const int LN = state_chunks(a.dtype, a.H);
     if (LN == 0 || a.LP < 1 || a.LP > WF_MAX_LAYERS || (a.D != 1 && a.D != 2) || (a.LP > 1 && a.D != 1)) return hipErrorInvalidValue;
-    if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 || a.ncb != (a.B + 15) / 16 || a.gpx * 8 < a.LP * a.D * a.ncb) return hipErrorInvalidValue;
+    if ((a.span != 1 && a.span != 2) || a.nrb % a.span != 0) return hipErrorInvalidValue;
+    if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 * a.span || a.ncb != (a.B + 15) / 16 || a.gpx * (8 / a.span) < a.LP * a.D * a.ncb)
+        return hipErrorInvalidValue;
     // with a projection the x waves of the first layer multiply nothing, whatever its input's width
     if ((a.gx == nullptr && a.xin == nullptr) || a.xln == 0 ||
         wavefront_xcd_input_chunks(a.dtype, a.H, a.gx ? a.H : a.I, a.LP > 1) != a.xln) return hipErrorInvalidValue;
     if (a.ring <= a.T && ((a.ring & (a.ring - 1)) != 0 || a.ring < 2 * XCD_AHEAD)) return hipErrorInvalidValue;
-    if ((size_t)a.T * wavefront_xcd_slot_bytes(a.dtype, a.B, a.H) >= ((size_t)1 << 31)) return hipErrorInvalidValue;
+    if (a.stride < (a.B < 16 ? a.B : 16) || a.stride > 16) return hipErrorInvalidValue;
+    if ((size_t)a.T * wavefront_xcd_slot_bytes(a.dtype, a.stride, a.H) >= ((size_t)1 << 31)) return hipErrorInvalidValue;
     const int kind = a.reset_before ? 2 : a.ext ? 1 : 0;
     if (a.reset_before && a.cell != CELL_GRU) return hipErrorInvalidValue;
+    if (a.span == 2) {
+        if (!wavefront_xcd_wide_exists(a.dtype, a.RT, a.H, a.reset_before != 0)) return hipErrorInvalidValue;
+        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide1(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide1(a, stream, LN);
+    }
     if (a.dtype == DT_BF16)
-        return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1(a, stream, LN)
-                                                                  : launch_wavefront_xcd_dt0_kind2(a, stream, LN);
-    return kind == 0 ? launch_wavefront_xcd_dt1_kind0(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt1_kind1(a, stream, LN)
-                                                                                 : launch_wavefront_xcd_dt1_kind2(a, stream, LN);
+        return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1_wide0(a, stream, LN)
+                                                                  : launch_wavefront_xcd_dt0_kind2_wide0(a, stream, LN);
+    return kind == 0 ? launch_wavefront_xcd_dt1_kind0_wide0(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt1_kind1_wide0(a, stream, LN)
+                                                                                       : launch_wavefront_xcd_dt1_kind2_wide0(a, stream, LN);
 }
-#endif  // RNN_XR_DT == 0 && RNN_XR_KIND == 0
+#endif  // RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE
 
 }  // namespace rnn

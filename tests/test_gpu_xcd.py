@@ -28,6 +28,8 @@ SHAPES = [
     (0, 12, 1, 64, 64, 20, 8, 0),       # twelve layers, two groups per XCD
     (0, 2, 2, 128, 128, 9, 18, 0),
     (0, 1, 1, 500, 256, 6, 16, 0),
+    (0, 2, 1, 512, 512, 6, 1, 0),       # (tagged words)
+    (0, 2, 1, 512, 512, 6, 2, 0),
     (0, 2, 1, 512, 512, 6, 70, 0),      # the longest products; a last block of six sequences
     (0, 1, 1, 512, 512, 4, 520, 1),     # passes of another kernel, the last eight sequences on this one
     (0, 1, 1, 64, 504, 3, 520, 1),      # the same through copies at the padded width
