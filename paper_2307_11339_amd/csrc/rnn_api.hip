@@ -29,9 +29,10 @@ struct Plan {
     // the first layer runs in a launch of its own (it needs a projection, the layers above it run side
     // by side in the inside-product kernel): launches are {0}, {1..LP}, {LP+1..2LP}, ...
     bool first_alone = false;
-    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with gpx groups of workgroups on every XCD
+    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with gpx groups of workgroups on every XCD, or on every
+    // pair of XCDs (span = 2)
     bool xcd = false;
-    int gpx = 0;
+    int gpx = 0, span = 1, stride = 0;
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
     int chunk = 0;
@@ -188,11 +189,22 @@ constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 // Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring).
 int xcd_ring(int T) { return T + 1; }
 
+// Sequences side by side in a chunk row of its state sequences (WavefrontXcdArgs::stride): 4, 8 or 16, so that a workgroup's
+// chunks start a half or a whole cache line of their own.  With B side by side, workgroups that share a line hold up each other's
+// stores (64 steps, us: 4 bf16 layers of 512 units at batch 1 100 -> 86, at batch 6 91 -> 87; 2 GRU layers of 256 at batch 1
+// 71 -> 64; 12 fp32 layers of 64 at batch 1 99 -> 94; groups on two XCDs, 4 layers of 768 at batch 6 161 -> 151).  A workspace in
+// the static array keeps B side by side: rounded up, a call that fits it could stop fitting.
+int xcd_stride(const rnn_model* m, int B) {
+    const int rows = B < 16 ? B : 16;
+    if (m->arena.on) return rows;
+    return rows <= 4 ? 4 : rows <= 8 ? 8 : 16;
+}
+
 // A plan for the XCD-resident kernel: every (layer, direction, block of 16 sequences) of a launch is a group of workgroups
 // that fits the compute units of one XCD.
 bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
-    const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16;
-    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, B, m->H) >= ((size_t)1 << 31)) return false;
+    const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16, stride = xcd_stride(m, B);
+    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
     const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
     // One sequence in fp32, more than 256 units: a wave's share of the state is one load of tagged words but eight loads of
     // chunks that hold one sequence each, and the tag-in-data kernel is faster (2 layers of 512 units, 64 steps: 322 us against
@@ -208,11 +220,33 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
             plan = Plan();
             plan.kind = RNN_PLAN_WAVEFRONT;
             plan.xcd = true;
-            plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx;
+            plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
             return true;
         }
     }
     return false;
+}
+
+// The same with every group on two XCDs, for `LP` layers in a launch: bf16 layers of 640 to 1024 units.  The state then goes
+// through memory (device-scope stores) as in the tag-in-data kernel, whose launches it takes over, but at half the bytes, without
+// tags to strip and without staging.  The line lies where that kernel needs more than four loads a wave for the state of a step,
+// B * H > 4096; below, its one to four probe-paced loads win.  64 steps, us, tag-in-data -> this:
+//     4 x 1024 units   batch 1 133 -> 170, 6 196 -> 191, 8 219 -> 192, 12 256 -> 200, 16 313 -> 204
+//     2 x 1024 units   batch 4 146 -> 149, 6 184 -> 174, 16 256 -> 186, 32 281 -> 188
+//     4 x 768 units    batch 4 134 -> 145, 6 170 -> 151, 8 177 -> 152, 16 270 -> 171
+//     2 x 640 units    batch 4 127 -> 133, 6 132 -> 131, 8 165 -> 130, 16 210 -> 146
+bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
+    const int RT = 4, ncb = (B + 15) / 16, nrb = m->H / (RT * 4), stride = xcd_stride(m, B);
+    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
+    if ((size_t)B * m->H <= 4096) return false;
+    const int gpx = (LP * m->D * ncb + XCDS / 2 - 1) / (XCDS / 2);
+    if (!wavefront_xcd_wide_exists(m->dtype, RT, m->H, m->gru_reset_before) || gpx * nrb > 2 * (m->num_cus / XCDS)) return false;
+    plan = Plan();
+    plan.kind = RNN_PLAN_WAVEFRONT;
+    plan.xcd = true;
+    plan.span = 2;
+    plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
+    return true;
 }
 
 // Choose how the grid of cells is laid over the compute units for batch size B.
@@ -275,7 +309,10 @@ bool choose_wavefront(const rnn_model* m, int T, int B, Plan& plan) {
                 best_first_alone = side_by_side && m->I != m->H;
             }
         }
-        if (tag_large >= 0) best = tag_small >= 0 ? tag_small : tag_large;
+        if (tag_large >= 0) {
+            if (choose_xcd_wide(m, T, B, LP, plan)) return true;
+            best = tag_small >= 0 ? tag_small : tag_large;
+        }
         if (best >= 0) {
             plan.kind = RNN_PLAN_WAVEFRONT;
             plan.LP = LP;
@@ -710,11 +747,11 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B) {
         const bool inside = wavefront && input_product_inside(m, plan, l, T);
         if (!inside && (!wavefront || first_of_launch(m, plan, l))) any_projection = true;
         const int slot = l + 1 < m->L ? ybuf_slot(m, plan, l, T) : -1;
-        if (slot >= 0) rc = grow(m, m->ws.ybuf[slot], (plan.xcd ? (size_t)T * plan.ncb * std::min(B, 16) : rows) * m->D * m->H * m->esize);
+        if (slot >= 0) rc = grow(m, m->ws.ybuf[slot], (plan.xcd ? (size_t)T * plan.ncb * plan.stride : rows) * m->D * m->H * m->esize);
     }
     if (rc == RNN_OK && any_projection) rc = grow(m, m->ws.gx, rows * m->D * m->H * SLOTS * sizeof(float));
     if (rc == RNN_OK && plan.xcd) {
-        const size_t slot = wavefront_xcd_slot_bytes(m->dtype, B, m->H), groups = (size_t)plan.LP * m->D * plan.ncb;
+        const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H), groups = (size_t)plan.LP * m->D * plan.ncb;
         rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * std::min(xcd_ring(T), T) * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.xseq, (size_t)plan.ncb * (plan.LP - 1) * T * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.flags, groups * plan.nrb * sizeof(uint64_t), true);
@@ -854,7 +891,7 @@ int forward_wavefront(rnn_model* m, const Plan& plan, const void* x, const int32
 // layout, y and states `units` wide), which the kernels address in place.
 int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0, void* y,
                 float* hT, float* cT, int T, int Bc, int b0, int bc, int units, bool batch_first, const float* gx0, hipStream_t st) {
-    const size_t slot = wavefront_xcd_slot_bytes(m->dtype, bc, m->H);
+    const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H);
     const int xt = batch_first ? 1 : Bc, xb = batch_first ? T : 1;
     const int N4 = SLOTS * m->H;
     for (int l0 = 0, LP = 0; l0 < m->L; l0 += LP) {
@@ -871,7 +908,8 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.T = T; a.B = bc; a.H = m->H; a.D = m->D; a.I = m->layer_input(l0);
         a.l0 = l0; a.LP = LP;
         a.RT = plan.RT; a.nrb = plan.nrb; a.ncb = plan.ncb;
-        a.gpx = (LP * m->D * plan.ncb + XCDS - 1) / XCDS;
+        a.span = plan.span; a.stride = plan.stride;
+        a.gpx = (LP * m->D * plan.ncb + XCDS / plan.span - 1) / (XCDS / plan.span);
         a.ring = xcd_ring(T);
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;

@@ -33,6 +33,13 @@ SHAPES = [
     (0, 2, 1, 512, 512, 6, 70, 0),      # the longest products; a last block of six sequences
     (0, 1, 1, 512, 512, 4, 520, 1),     # passes of another kernel, the last eight sequences on this one
     (0, 1, 1, 64, 504, 3, 520, 1),      # the same through copies at the padded width
+    (0, 4, 1, 1024, 1024, 1, 5, 1),     # groups on two XCDs: one step, the whole chip
+    (0, 4, 1, 1024, 1024, 11, 12, 1),   # chunk rows wider than the batch
+    (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
+    (1, 1, 1, 1032, 1024, 6, 40, 1),    # projection in front, three blocks of sequences
+    (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD
+    (1, 2, 2, 768, 768, 7, 20, 1),      # both directions, the second launch behind a projection
+    (0, 1, 1, 896, 896, 6, 5, 1),       # padded to 1024
 ]
 
 
