@@ -98,6 +98,7 @@ struct rnn_model {
     bool gru_reset_before = false;
     float clip = 0.0f;          // clipping threshold of the gate arguments, 0 = none
     std::vector<DevBuf> peep;   // empty, or per (layer, direction) [3, H] fp32 peephole weights (LSTM)
+    bool avoid_xcd = false;     // for one call: no plan of the XCD-resident kernel (rnn_forward_static)
     bool batch_first = false;   // x is [B, T, I] and y [B, T, D*H]
     bool validate = false;      // check `lengths` on the host before every forward
     // the cell variant with two dependent recurrent products per cell: the cellwise plan and the XCD-resident kernel only
@@ -203,6 +204,7 @@ int xcd_stride(const rnn_model* m, int B) {
 // A plan for the XCD-resident kernel: every (layer, direction, block of 16 sequences) of a launch is a group of workgroups
 // that fits the compute units of one XCD.
 bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
+    if (m->avoid_xcd) return false;
     const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16, stride = xcd_stride(m, B);
     if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
     const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
@@ -238,7 +240,7 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
 bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     const int RT = 4, ncb = (B + 15) / 16, nrb = m->H / (RT * 4), stride = xcd_stride(m, B);
     if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
-    if ((size_t)B * m->H <= 4096) return false;
+    if (m->avoid_xcd || (size_t)B * m->H <= 4096) return false;
     const int gpx = (LP * m->D * ncb + XCDS / 2 - 1) / (XCDS / 2);
     if (!wavefront_xcd_wide_exists(m->dtype, RT, m->H, m->gru_reset_before) || gpx * nrb > 2 * (m->num_cus / XCDS)) return false;
     plan = Plan();
@@ -1384,7 +1386,20 @@ int rnn_forward_static(rnn_model* m, const void* x, const int32_t* lengths, cons
     m->arena.used = 0;
     m->arena.stream = (hipStream_t)stream;
     m->arena.on = true;
-    const int rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
+    int rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
+    if (rc == RNN_ESCRATCH) {
+        // The XCD-resident kernel holds blocks of 16 sequences whole (17 sequences take as much as 32): where that does not fit,
+        // the plan that would be taken without it may.  Nothing but fills of fresh memory has been launched yet.
+        for (auto& b : m->ws.ybuf) b = DevBuf();
+        std::vector<DevBuf> keep;
+        keep.swap(m->ws.ybuf);
+        m->ws = rnn_model::Workspace();
+        m->ws.ybuf.swap(keep);
+        m->arena.used = 0;
+        m->avoid_xcd = true;
+        rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
+        m->avoid_xcd = false;
+    }
     m->arena.on = false;
     std::swap(m->ws, m->ws_static);
     return rc;

@@ -120,3 +120,19 @@ def test_reset_gate_before_the_product(gpu, oracle, shape):
     _check(harness, wl, io, oracle.forward_workload(wl, nthreads=8, gru_variant=1, clip=0.4))
     assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
     model.close()
+
+
+def test_static_array_that_only_tagged_words_fit(gpu):
+    """17 sequences: two blocks of 16 here (75 MiB for 800 steps), 17 rows of tagged words (54 MiB) in the static array of 64 MiB."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, (0, 2, 1, 512, 512, 800, 17, 1), False)
+    model, io, io2 = harness.DeviceModel(wl), harness.DeviceIO(wl), harness.DeviceIO(wl)
+    harness.forward(model, io)
+    assert rnn.rnn_forward_static(model.handle, io2.x, io2.lengths, io2.h0, io2.c0, io2.y, io2.hT, io2.cT, 800, 17,
+                                  torch.cuda.current_stream()) == rnn.RNN_OK
+    torch.cuda.synchronize()
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    assert (io.y.float() - io2.y.float()).abs().max().item() <= TOL[1]
+    assert (io.hT - io2.hT).abs().max().item() <= TOL[1]
+    model.close()
