@@ -432,6 +432,19 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
     return RNN_OK;
 }
 
+// Plan of the last, shorter pass of a batch that runs in passes.  Passes of the XCD-resident kernel address the caller's tensors
+// in place, the last one too: where fewer sequences alone would run on another kernel (one fp32 sequence of more than 256 units,
+// a bf16 block of few sequences over two XCDs), it keeps the plan of the full passes, laid out for its own sequences.
+int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last) {
+    const int rc = resolve_plan(m, T, B, last, false);
+    if (rc != RNN_OK || !plan.xcd || last.xcd) return rc;
+    last = plan;
+    last.chunk = 0;
+    last.ncb = (B + 15) / 16;
+    last.stride = xcd_stride(m, B);
+    return RNN_OK;
+}
+
 // First layer and number of layers of the launch that holds layer l (from the scheduler's table).
 void launch_of(const rnn_model* m, const Plan& plan, int l, int& l0, int& n) {
     if (plan.layer_launch.empty()) { l0 = l; n = 1; return; }
@@ -795,7 +808,7 @@ int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B) {
         const int tail = B % plan.chunk;
         if (rc == RNN_OK && tail != 0) {
             Plan last;
-            rc = resolve_plan(m, T, tail, last, false);
+            rc = resolve_last_pass(m, plan, T, tail, last);
             if (rc == RNN_OK) rc = prepare_workspace_pass(m, last, T, tail);
         }
         if (plan.xcd) {     // the kernels address the caller's tensors in place
@@ -994,10 +1007,10 @@ int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int3
     for (int b0 = 0; b0 < B; b0 += step) {
         const int bc = std::min(step, B - b0);
         Plan pass = plan;
-        if (plan.chunk > 0) {
-            const int rc = resolve_plan(m, T, bc, pass, false);
+        pass.chunk = 0;
+        if (bc != step) {
+            const int rc = resolve_last_pass(m, plan, T, bc, pass);
             if (rc != RNN_OK) return rc;
-            if (!pass.xcd) return RNN_EDEVICE;       // (a smaller batch of the same shape always has such a plan)
         }
         const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, units, batch_first, gx0, st);
         if (rc != RNN_OK) return rc;
@@ -1024,7 +1037,7 @@ int forward_in_passes(rnn_model* m, const Plan& plan, const void* x, const int32
         Plan pass = plan;
         pass.chunk = 0;
         if (bc != plan.chunk) {
-            const int rc = resolve_plan(m, T, bc, pass, false);
+            const int rc = resolve_last_pass(m, plan, T, bc, pass);
             if (rc != RNN_OK) return rc;
         }
         HIP_TRY(launch_copy_2d((const char*)x + b0 * xrow, B * xrow, m->ws.x_ck.p, bc * xrow, T, bc * xrow, st));

@@ -33,6 +33,8 @@ SHAPES = [
     (0, 2, 1, 512, 512, 6, 70, 0),      # the longest products; a last block of six sequences
     (0, 1, 1, 512, 512, 4, 520, 1),     # passes of another kernel, the last eight sequences on this one
     (0, 1, 1, 64, 504, 3, 520, 1),      # the same through copies at the padded width
+    (0, 1, 1, 512, 512, 4, 129, 0),     # passes of 128 sequences; the last one, alone, would run on tagged words
+    (0, 2, 2, 300, 300, 4, 65, 0),      # the same padded, both directions, two launches
     (0, 4, 1, 1024, 1024, 1, 5, 1),     # groups on two XCDs: one step, the whole chip
     (0, 4, 1, 1024, 1024, 11, 12, 1),   # chunk rows wider than the batch
     (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
