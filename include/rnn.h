@@ -188,7 +188,8 @@ int rnn_model_reserve(rnn_model* model, int T, int B);
  *   y        [T, B, D*H]    dtype     output of the last layer; positions t >= lengths[b] receive
  *                                      +0.0 (all-zero bits)
  *   hT, cT   [L*D, B, H]    fp32      state after the last valid step of each sequence in each
- *                                      direction; either may be NULL; cT unused for GRU
+ *                                      direction; either may be NULL; cT unused for GRU.  hT = h0 and
+ *                                      cT = c0 are allowed (a stream's state updated in place)
  *   T, B                               steps and sequences in this call (>= 1)
  *   stream                             hipStream_t passed as void* (NULL = the default stream)
  * The call enqueues work on `stream` and returns without waiting; outputs are valid once the

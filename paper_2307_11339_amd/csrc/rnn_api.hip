@@ -902,6 +902,10 @@ int forward_wavefront(rnn_model* m, const Plan& plan, const void* x, const int32
     return RNN_OK;
 }
 
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    return a && b && (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 // Forward pass on the XCD-resident kernel: sequences b0 .. b0 + bc - 1 of tensors that hold Bc sequences (x and y in either
 // layout, y and states `units` wide), which the kernels address in place.
 int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0, void* y,
@@ -909,6 +913,10 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
     const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H);
     const int xt = batch_first ? 1 : Bc, xb = batch_first ? T : 1;
     const int N4 = SLOTS * m->H;
+    // the state of a streaming step updated in place (hT = h0): with more steps the exchange has every h0 read before hT is written
+    const size_t state_bytes = (size_t)m->L * m->D * Bc * units * sizeof(float);
+    const bool in_place = overlap(h0, state_bytes, y, (size_t)T * Bc * m->D * units * m->esize) ||
+                          (T == 1 && (overlap(h0, state_bytes, hT, state_bytes) || overlap(h0, state_bytes, cT, state_bytes)));
     for (int l0 = 0, LP = 0; l0 < m->L; l0 += LP) {
         int first;
         launch_of(m, plan, l0, first, LP);
@@ -928,6 +936,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.ring = xcd_ring(T);
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
+        a.in_place = in_place ? 1 : 0;
         for (int ll = 0; ll < LP; ++ll)
             for (int d = 0; d < m->D; ++d) {
                 const int g = (l0 + ll) * m->D + d;

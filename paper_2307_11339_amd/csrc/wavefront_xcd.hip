@@ -214,7 +214,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     };
 
     // ---- start: mark the first slots, say where this workgroup runs ------------------------------
-    const bool shake = T > 1 || p.LP > 1 || RB;      // a single step of a single layer exchanges nothing
+    const bool shake = T > 1 || p.LP > 1 || RB || p.in_place;   // else: a single step of a single layer exchanges nothing
     if (tid < 8) done[tid] = 0u;                     // (and ready)
     if (shake && wv == NW - 1) {
 #pragma unroll
@@ -228,11 +228,21 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 }
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    auto start_word = [&]() {                        // last wave
         // XCC_ID: hardware register 20, bits 3:0
         const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11));
         if (lane == 0) st_dev_u64(p.flagv + (size_t)g * p.nrb + rb, ((uint64_t)epoch << 32) | xcc);
-    }
+    };
+    if (shake && wv == NW - 1 && !p.in_place) start_word();
     auto start_wait = [&]() {                        // last wave: everybody this workgroup exchanges data with has started
+        // Every workgroup reads the h0 of all units.  Where an output takes its place, a start word says as well that this has
+        // been read (otherwise the exchange orders it: whoever writes hT has seen the states of step 0).
+        if (p.in_place) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (wv == NW - 1) start_word();
+        }
         bool same = true;
         if (shake && wv == NW - 1) {
             for (int other = fused ? 1 : 0; other >= 0; --other) {

@@ -138,3 +138,38 @@ def test_static_array_that_only_tagged_words_fit(gpu):
     assert (io.y.float() - io2.y.float()).abs().max().item() <= TOL[1]
     assert (io.hT - io2.hT).abs().max().item() <= TOL[1]
     model.close()
+
+
+@pytest.mark.parametrize("shape", [(0, 1, 1, 128, 128, 1, 1, 1), (0, 4, 1, 512, 512, 1, 16, 1), (1, 2, 1, 64, 200, 1, 17, 1),
+                                   (0, 2, 1, 256, 256, 1, 40, 0), (0, 2, 2, 384, 384, 1, 5, 1), (0, 2, 1, 1024, 1024, 1, 8, 1),
+                                   (0, 4, 1, 1024, 1024, 1, 1, 1), (1, 1, 1, 512, 512, 1, 300, 1)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
+def test_state_of_a_stream_in_place(gpu, shape):
+    """One frame per call, the state updated in place (hT = h0, cT = c0): every workgroup of a layer reads the h0 of all units, and
+    none may write its hT before all have.  Bit for bit the stream with the two states in buffers of their own."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, False)
+    c = wl.cfg
+    print("\n  case %r" % (shape,), flush=True)
+    model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
+    x = torch.randn((20,) + tuple(io.x.shape), device="cuda", generator=torch.Generator("cuda").manual_seed(c.seed % 1000)).to(io.x.dtype)
+    c0 = io.c0 if io.c0 is not None else torch.zeros_like(io.h0)
+    stream = torch.cuda.current_stream()
+
+    def run(in_place):
+        h, cc, ys = io.h0.clone(), c0.clone(), []
+        for k in range(x.shape[0]):
+            hn, cn = (h, cc) if in_place else (torch.full_like(h, 7.0), torch.full_like(cc, 7.0))
+            assert rnn.rnn_forward(model.handle, x[k], None, h, cc, io.y, hn, cn, 1, c.B, stream) == rnn.RNN_OK
+            ys.append(io.y.clone())
+            h, cc = hn, (cn if c.cell == 0 else cc)
+        torch.cuda.synchronize()
+        assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+        return torch.stack(ys), h, cc
+
+    want = run(False)
+    for _ in range(3):
+        for a, b in zip(run(True), want):
+            assert torch.equal(a, b)
+    model.close()
