@@ -276,7 +276,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         const bool rows = !fused && !project && !p.x_blocked && ncol > 2;
         u32x4* const my_turn = turn + w * XLN * TURN;
         frag wx[RT][XLN * MPL];
-        uint32_t xoff[XLN];                          // byte offset of this lane's chunk inside a step of x
+        uint32_t xoff[XLN];                          // byte offset of this lane's chunk inside a step of x, or inside its row (rows of a
+                                                     // batch-first x can lie 4 GiB apart: the row is in the 64-bit address)
         if (!project) {
             // W_ih of all directions is one matrix [D * 4H, KX]; direction d owns rows d * 4H ...
             const elem* wih = static_cast<const elem*>(p.wih[ld]) + (size_t)d * SLOTS * H * KX;
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 else if (!rows) xoff[i] = (uint32_t)k * (uint32_t)sizeof(elem);
                 else {                               // lane 4 * r + c brings chunk c of row r
                     const int rc = (i * 4 + w) * 4 + (lane & 3);
-                    xoff[i] = (uint32_t)min(lane >> 2, ncol - 1) * (uint32_t)(p.x_b * KX * sizeof(elem)) + (rc * EPC < KX ? rc * 16u : 0u);
+                    xoff[i] = rc * EPC < KX ? rc * 16u : 0u;
                 }
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
@@ -307,7 +308,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                              : p.x_blocked ? (size_t)(KX / EPC) * Bs * 16 : (size_t)p.x_t * KX * sizeof(elem);
         const char* xsrc = project ? reinterpret_cast<const char*>(p.gx + (((size_t)col * p.x_b * p.D + d) * H + min((rb * RT + w) * 4 + q, H - 1)) * SLOTS)
                            : static_cast<const char*>(p.xin) + (p.x_blocked ? (size_t)cb * T * xstep
-                                                                           : (size_t)(rows ? cb * 16 : col) * p.x_b * KX * sizeof(elem));
+                                                                           : (size_t)(rows ? cb * 16 + min(lane >> 2, ncol - 1) : col) * p.x_b * KX * sizeof(elem));
         u32x4 xb[NBUF][XLN];
         auto request = [&](int s, u32x4 (&v)[XLN]) { // the s-th step in this direction's order
             const int sc = min(s, T - 1);

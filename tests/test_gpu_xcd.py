@@ -173,3 +173,24 @@ def test_state_of_a_stream_in_place(gpu, shape):
         for a, b in zip(run(True), want):
             assert torch.equal(a, b)
     model.close()
+
+
+def test_rows_of_x_more_than_4_gib_apart(gpu):
+    """A batch-first x of 16 sequences of 140000 steps of 1024 features: sequences 14 and 15 begin beyond 2^32 bytes.  Bit for bit
+    the time-major call, whose rows of a step lie side by side."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, (0, 1, 1, 1024, 128, 2, 16, 1), False)
+    model, T, B = harness.DeviceModel(wl), 140000, 16
+    x = torch.randn((T, B, 1024), dtype=torch.bfloat16, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    y = [torch.full((T, B, 128), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    stream = torch.cuda.current_stream()
+    assert rnn.rnn_forward(model.handle, x, None, None, None, y[0], None, None, T, B, stream) == rnn.RNN_OK
+    assert rnn.rnn_model_set_batch_first(model.handle, 1) == rnn.RNN_OK
+    x_bf, y_bf = x.transpose(0, 1).contiguous(), y[1].view(B, T, 128)
+    assert rnn.rnn_forward(model.handle, x_bf, None, None, None, y_bf, None, None, T, B, stream) == rnn.RNN_OK
+    torch.cuda.synchronize()
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    for b in range(B):
+        assert torch.equal(y_bf[b], y[0][:, b]), b
+    model.close()
