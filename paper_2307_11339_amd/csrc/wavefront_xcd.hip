@@ -374,6 +374,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     asm volatile("" ::: "memory");
                 }
             }
+            if (!project && XLN * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+#pragma unroll
+                for (int i = 0; i < XLN; ++i) {
+                    const int chunk = (i * 4 + w) * 4;
+                    if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
+                }
+            }
             if (rows) {                              // (no barrier: LDS operations of a wave keep their order)
 #pragma unroll
                 for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];

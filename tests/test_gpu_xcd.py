@@ -194,3 +194,26 @@ def test_rows_of_x_more_than_4_gib_apart(gpu):
     for b in range(B):
         assert torch.equal(y_bf[b], y[0][:, b]), b
     model.close()
+
+
+@pytest.mark.parametrize("shape", [(0, 1, 1, 80, 256, 5, 4, 1), (0, 2, 1, 40, 128, 4, 2, 1), (0, 1, 2, 136, 384, 4, 17, 1),
+                                   (0, 1, 1, 20, 64, 5, 3, 0), (0, 1, 1, 80, 768, 4, 16, 1), (0, 2, 1, 1024, 128, 4, 5, 1)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
+def test_an_infinite_feature_saturates_the_gates(gpu, oracle, shape):
+    """One infinite feature among the first of a row: every weight of it is finite and not zero, so the gates saturate and all
+    results are finite.  Lanes whose chunk lies beyond the input must not make it zero times infinity."""
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, False)
+    c = wl.cfg
+    for w in wl.weights:
+        w[w == 0.0] = 0.125
+    wl.x[0, 0, 1] = np.inf
+    wl.x[c.T - 1, c.B - 1, 0] = -np.inf
+    print("\n  case %r" % (shape,), flush=True)
+    ref = oracle.forward_workload(wl, nthreads=8)
+    assert np.isfinite(ref[0]).all() and np.isfinite(ref[2]).all()
+    model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
+    harness.forward(model, io)
+    _check(harness, wl, io, ref)
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    model.close()
