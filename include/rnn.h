@@ -211,7 +211,7 @@ int rnn_forward(rnn_model* model, const void* x, const int32_t* lengths, const f
 
 /*
  * rnn_forward for callers that cannot allocate device memory: code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and same results as rnn_forward, but
+ * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and same results as rnn_forward (see below), but
  * the call allocates and frees nothing, whatever shape it is given: its workspace (tagged state words, step
  * flags, inter-layer activations, projection and layout copies: everything rnn_forward keeps in the model's
  * own workspace) is laid out, per call, in one static device array of RNN_STATIC_SCRATCH_MIB mebibytes that
@@ -219,6 +219,10 @@ int rnn_forward(rnn_model* model, const void* x, const int32_t* lengths, const f
  *   - A shape whose plan needs more than that returns RNN_ESCRATCH with nothing enqueued (for example C3 of the
  *     named workloads needs about 3 MiB, a 2-layer bidirectional model of 512 units on 64 sequences of 256 steps
  *     about 140 MiB); RNN_EDEVICE if the array's address could not be obtained when the model was created.
+ *   - Where the launches of rnn_forward do not fit but those of the plans without the kernel of layers that fit one XCD do,
+ *     that kernel runs in a more compact form, with the same bits as results.  One call leaves it, with results that differ in
+ *     the rounding of the stored type: a GRU with the reset gate before the product, behind a projection, whose sequences in
+ *     blocks of 16 exceed the array where the cellwise plan fits it (within a tenth of the limit).
  *   - All models of a device share the array, which keeps what the last call left: the call clears, on
  *     `stream`, the parts that must start at zero (step flags, tagged words).  Two calls that overlap in time
  *     on one GPU (different streams or different models) race on it and give undefined results; calls on one

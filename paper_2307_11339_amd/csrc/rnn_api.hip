@@ -98,7 +98,10 @@ struct rnn_model {
     bool gru_reset_before = false;
     float clip = 0.0f;          // clipping threshold of the gate arguments, 0 = none
     std::vector<DevBuf> peep;   // empty, or per (layer, direction) [3, H] fp32 peephole weights (LSTM)
-    bool avoid_xcd = false;     // for one call: no plan of the XCD-resident kernel (rnn_forward_static)
+    // rnn_forward_static, where the workspace of rnn_forward's launches does not fit: most layers in a launch of the XCD-resident
+    // kernel, which then keeps few slots of a state sequence and projects the sequences of a pass by themselves (the same sums in
+    // the same order).  0: as rnn_forward; -1: no plan of that kernel.
+    int compact = 0;
     bool batch_first = false;   // x is [B, T, I] and y [B, T, D*H]
     bool validate = false;      // check `lengths` on the host before every forward
     // the cell variant with two dependent recurrent products per cell: the cellwise plan and the XCD-resident kernel only
@@ -118,7 +121,7 @@ struct rnn_model {
     Workspace ws;           // allocated on demand, owned by the model
     Workspace ws_static;    // rnn_forward_static: the same buffers as pieces of the device's static array, per call
     // rnn_forward_static: the device's static array and how much of it this call has handed out
-    struct Arena { char* base = nullptr; size_t used = 0; bool on = false; hipStream_t stream = nullptr; } arena;
+    struct Arena { char* base = nullptr; size_t used = 0; bool on = false; } arena;
     char* scratch = nullptr;   // this device's copy of the static array (NULL: the lookup failed)
     uint32_t epoch = 0;     // tag of the most recent tag-in-data launch
     size_t workspace_bytes = 0;
@@ -187,26 +190,31 @@ bool relayout_fits(const rnn_model* m, int T) {
 
 constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 
-// Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring).
-int xcd_ring(int T) { return T + 1; }
+// Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring): one for every step, or (compact) few that are
+// used in turn.
+int xcd_ring(const rnn_model* m, int T) { return m->compact > 0 && T >= 2 * XCD_AHEAD ? 2 * XCD_AHEAD : T + 1; }
 
 // Sequences side by side in a chunk row of its state sequences (WavefrontXcdArgs::stride): 4, 8 or 16, so that a workgroup's
 // chunks start a half or a whole cache line of their own.  With B side by side, workgroups that share a line hold up each other's
 // stores (64 steps, us: 4 bf16 layers of 512 units at batch 1 100 -> 86, at batch 6 91 -> 87; 2 GRU layers of 256 at batch 1
 // 71 -> 64; 12 fp32 layers of 64 at batch 1 99 -> 94; groups on two XCDs, 4 layers of 768 at batch 6 161 -> 151).  A workspace in
 // the static array keeps B side by side: rounded up, a call that fits it could stop fitting.
-int xcd_stride(const rnn_model* m, int B) {
-    const int rows = B < 16 ? B : 16;
-    if (m->arena.on) return rows;
-    return rows <= 4 ? 4 : rows <= 8 ? 8 : 16;
+int xcd_stride_apart(int B) { return B <= 4 ? 4 : B <= 8 ? 8 : 16; }
+int xcd_stride(const rnn_model* m, int B) { return m->arena.on ? std::min(B, 16) : xcd_stride_apart(B); }
+
+// A state sequence of T steps can be addressed (the same answer for both strides: rnn_forward_static takes rnn_forward's plans).
+bool xcd_addressable(const rnn_model* m, int T, int B) {
+    return T == 1 || (size_t)T * wavefront_xcd_slot_bytes(m->dtype, xcd_stride_apart(B), m->H) < ((size_t)1 << 31);
 }
+
+int xcd_layers(const rnn_model* m, int LP) { return m->compact > 0 ? std::min(LP, m->compact) : LP; }
 
 // A plan for the XCD-resident kernel: every (layer, direction, block of 16 sequences) of a launch is a group of workgroups
 // that fits the compute units of one XCD.
 bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
-    if (m->avoid_xcd) return false;
+    if (m->compact < 0) return false;
     const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16, stride = xcd_stride(m, B);
-    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
+    if (!xcd_addressable(m, T, B)) return false;
     const int lp_max = (m->D == 1) ? (m->L < WF_MAX_LAYERS ? m->L : WF_MAX_LAYERS) : 1;
     // One sequence in fp32, more than 256 units: a wave's share of the state is one load of tagged words but eight loads of
     // chunks that hold one sequence each, and the tag-in-data kernel is faster (2 layers of 512 units, 64 steps: 322 us against
@@ -222,7 +230,7 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
             plan = Plan();
             plan.kind = RNN_PLAN_WAVEFRONT;
             plan.xcd = true;
-            plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
+            plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
             return true;
         }
     }
@@ -239,15 +247,15 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
 //     2 x 640 units    batch 4 127 -> 133, 6 132 -> 131, 8 165 -> 130, 16 210 -> 146
 bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     const int RT = 4, ncb = (B + 15) / 16, nrb = m->H / (RT * 4), stride = xcd_stride(m, B);
-    if (T > 1 && (size_t)T * wavefront_xcd_slot_bytes(m->dtype, stride, m->H) >= ((size_t)1 << 31)) return false;
-    if (m->avoid_xcd || (size_t)B * m->H <= 4096) return false;
+    if (!xcd_addressable(m, T, B)) return false;
+    if (m->compact < 0 || (size_t)B * m->H <= 4096) return false;
     const int gpx = (LP * m->D * ncb + XCDS / 2 - 1) / (XCDS / 2);
     if (!wavefront_xcd_wide_exists(m->dtype, RT, m->H, m->gru_reset_before) || gpx * nrb > 2 * (m->num_cus / XCDS)) return false;
     plan = Plan();
     plan.kind = RNN_PLAN_WAVEFRONT;
     plan.xcd = true;
     plan.span = 2;
-    plan.LP = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
+    plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
     return true;
 }
 
@@ -591,14 +599,13 @@ int forward_cellwise(rnn_model* m, const void* x, const int32_t* lengths, const 
 int grow(rnn_model* m, DevBuf& b, size_t bytes, bool zeroed = false) {
     if (b.bytes >= bytes) return RNN_OK;
     if (m->arena.on) {
-        // rnn_forward_static: the buffer is the next piece of the device's static array (256-byte aligned);
-        // the array keeps what the last call left, so what must start at zero is cleared on the stream
+        // rnn_forward_static: the buffer is the next piece of the device's static array (256-byte aligned); the array
+        // keeps what the last call left, and what must start at zero is cleared once the whole workspace is known to fit
         const size_t at = (m->arena.used + 255) & ~(size_t)255;
         if (bytes > STATIC_SCRATCH_BYTES || at > STATIC_SCRATCH_BYTES - bytes) return RNN_ESCRATCH;
         b.p = m->arena.base + at;
         b.bytes = bytes;
         m->arena.used = at + bytes;
-        if (zeroed) HIP_TRY(launch_fill_zero(b.p, (bytes + 3) & ~(size_t)3, m->arena.stream));
         return RNN_OK;
     }
     if (m->capturing) return RNN_EUNSUPPORTED;   // no allocation and no waiting inside a stream capture
@@ -750,7 +757,8 @@ int ybuf_slot(const rnn_model* m, const Plan& plan, int l, int T) {
 // Size the workspace for one forward pass of T steps and B sequences under `plan`: only what that
 // plan touches is allocated (the paper's memory model, Section 3, Equation 4, charges a model with
 // its weights, outputs and temporaries; this is the temporaries part).
-int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B) {
+// first_projected: the input product of the first layer is done outside (ws.gx0)
+int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B, bool first_projected = false) {
     const size_t rows = (size_t)T * B;
     const size_t state = (size_t)m->L * m->D * B * m->H;
     const bool wavefront = plan.kind == RNN_PLAN_WAVEFRONT;
@@ -760,14 +768,14 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B) {
     int rc = RNN_OK;
     for (int l = 0; l < m->L && rc == RNN_OK; ++l) {
         const bool inside = wavefront && input_product_inside(m, plan, l, T);
-        if (!inside && (!wavefront || first_of_launch(m, plan, l))) any_projection = true;
+        if (!inside && (!wavefront || first_of_launch(m, plan, l)) && !(l == 0 && first_projected)) any_projection = true;
         const int slot = l + 1 < m->L ? ybuf_slot(m, plan, l, T) : -1;
         if (slot >= 0) rc = grow(m, m->ws.ybuf[slot], (plan.xcd ? (size_t)T * plan.ncb * plan.stride : rows) * m->D * m->H * m->esize);
     }
     if (rc == RNN_OK && any_projection) rc = grow(m, m->ws.gx, rows * m->D * m->H * SLOTS * sizeof(float));
     if (rc == RNN_OK && plan.xcd) {
         const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H), groups = (size_t)plan.LP * m->D * plan.ncb;
-        rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * std::min(xcd_ring(T), T) * slot);
+        rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * std::min(xcd_ring(m, T), T) * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.xseq, (size_t)plan.ncb * (plan.LP - 1) * T * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.flags, groups * plan.nrb * sizeof(uint64_t), true);
     }
@@ -804,16 +812,18 @@ int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B) {
     } else {
         Plan one = plan;
         one.chunk = 0;
-        rc = prepare_workspace_pass(m, one, T, plan.chunk);
+        const bool project = plan.xcd && !input_product_inside(m, plan, 0, T);
+        const bool at_once = project && m->compact == 0;    // one projection for all passes
+        rc = prepare_workspace_pass(m, one, T, plan.chunk, at_once);
         const int tail = B % plan.chunk;
         if (rc == RNN_OK && tail != 0) {
             Plan last;
             rc = resolve_last_pass(m, plan, T, tail, last);
-            if (rc == RNN_OK) rc = prepare_workspace_pass(m, last, T, tail);
+            if (rc == RNN_OK) rc = prepare_workspace_pass(m, last, T, tail, at_once);
         }
         if (plan.xcd) {     // the kernels address the caller's tensors in place
-            if (rc == RNN_OK && !input_product_inside(m, plan, 0, T))
-                rc = grow(m, m->ws.gx0, (size_t)T * B * m->D * m->H * SLOTS * sizeof(float));
+            if (rc == RNN_OK && at_once) rc = grow(m, m->ws.gx0, (size_t)T * B * m->D * m->H * SLOTS * sizeof(float));
+            if (rc == RNN_OK && project && !at_once && !m->batch_first) rc = grow(m, m->ws.x_ck, (size_t)T * plan.chunk * m->I * m->esize);
             return rc;
         }
         const size_t rows = (size_t)T * plan.chunk;
@@ -907,9 +917,10 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
 }
 
 // Forward pass on the XCD-resident kernel: sequences b0 .. b0 + bc - 1 of tensors that hold Bc sequences (x and y in either
-// layout, y and states `units` wide), which the kernels address in place.
+// layout, y and states `units` wide), which the kernels address in place.  gx0: NULL, or the projection of the first layer, sequence
+// b0 first, with the row of (step t, sequence b) at t * gx_t + b * gx_b.
 int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0, void* y,
-                float* hT, float* cT, int T, int Bc, int b0, int bc, int units, bool batch_first, const float* gx0, hipStream_t st) {
+                float* hT, float* cT, int T, int Bc, int b0, int bc, int units, bool batch_first, const float* gx0, int gx_t, int gx_b, hipStream_t st) {
     const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H);
     const int xt = batch_first ? 1 : Bc, xb = batch_first ? T : 1;
     const int N4 = SLOTS * m->H;
@@ -933,7 +944,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.RT = plan.RT; a.nrb = plan.nrb; a.ncb = plan.ncb;
         a.span = plan.span; a.stride = plan.stride;
         a.gpx = (LP * m->D * plan.ncb + XCDS / plan.span - 1) / (XCDS / plan.span);
-        a.ring = xcd_ring(T);
+        a.ring = xcd_ring(m, T);
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
         a.in_place = in_place ? 1 : 0;
@@ -948,8 +959,8 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.clip = m->clip;
         if (l0 == 0) {
             a.xin = (const char*)x + (size_t)b0 * xb * m->I * m->esize;
-            a.x_t = xt; a.x_b = xb;
-            if (gx0) a.gx = gx0 + (size_t)b0 * xb * m->D * N4;
+            a.x_t = gx0 ? gx_t : xt; a.x_b = gx0 ? gx_b : xb;
+            a.gx = gx0;
         } else {
             a.xin = m->ws.ybuf[ybuf_slot(m, plan, l0 - 1, T)].p;
             a.x_t = bc; a.x_b = 1;
@@ -1003,16 +1014,23 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
 // copies at the padded width of a pass whose batch as a whole runs on another kernel.
 int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int32_t* lengths, const float* h0, const float* c0,
                        void* y, float* hT, float* cT, int T, int B, int units, bool batch_first, hipStream_t st) {
-    const float* gx0 = nullptr;
     const int N4 = SLOTS * m->H;
-    if (!input_product_inside(m, plan, 0, T)) {      // projection of the first layer, for all sequences at once
-        float* gx = (float*)(plan.chunk > 0 ? m->ws.gx0.p : m->ws.gx.p);
+    const bool project = !input_product_inside(m, plan, 0, T);
+    const bool at_once = project && (plan.chunk == 0 || m->compact == 0);   // for all passes
+    float* const gx = (float*)(at_once && plan.chunk > 0 ? m->ws.gx0.p : m->ws.gx.p);
+    auto projection = [&](const void* in, int rows) -> int {
         const int ps = prof_begin(m, RNN_KERNEL_PROJECTION, st);
-        HIP_TRY(launch_gemm_nt(m->dtype, x, m->I, m->wih[0].p, m->I, gx, m->D * N4, T * B, m->D * N4, m->I, st));
+        HIP_TRY(launch_gemm_nt(m->dtype, in, m->I, m->wih[0].p, m->I, gx, m->D * N4, rows, m->D * N4, m->I, st));
         prof_end(m, ps, st);
-        gx0 = gx;
+        return RNN_OK;
+    };
+    if (at_once) {
+        const int rc = projection(x, T * B);
+        if (rc != RNN_OK) return rc;
     }
     const int step = plan.chunk > 0 ? plan.chunk : B;
+    const int xb = batch_first ? T : 1;
+    const size_t xrow = (size_t)m->I * m->esize;
     for (int b0 = 0; b0 < B; b0 += step) {
         const int bc = std::min(step, B - b0);
         Plan pass = plan;
@@ -1021,7 +1039,20 @@ int forward_xcd_passes(rnn_model* m, const Plan& plan, const void* x, const int3
             const int rc = resolve_last_pass(m, plan, T, bc, pass);
             if (rc != RNN_OK) return rc;
         }
-        const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, units, batch_first, gx0, st);
+        const float* gx0 = at_once ? gx + (size_t)b0 * xb * m->D * N4 : nullptr;
+        int gx_t = batch_first ? 1 : B;
+        if (project && !at_once) {       // this pass's rows of x: side by side if batch-first, else through a copy
+            const void* in = (const char*)x + (size_t)b0 * xb * xrow;
+            if (!batch_first) {
+                HIP_TRY(launch_copy_2d(in, B * xrow, m->ws.x_ck.p, bc * xrow, T, bc * xrow, st));
+                in = m->ws.x_ck.p;
+                gx_t = bc;
+            }
+            const int rc = projection(in, T * bc);
+            if (rc != RNN_OK) return rc;
+            gx0 = gx;
+        }
+        const int rc = forward_xcd(m, pass, x, lengths, h0, c0, y, hT, cT, T, B, b0, bc, units, batch_first, gx0, gx_t, xb, st);
         if (rc != RNN_OK) return rc;
     }
     return RNN_OK;
@@ -1305,6 +1336,36 @@ int rnn_model_reserve(rnn_model* m, int T, int B) {
     return prepare_workspace(m, plan, T, B);
 }
 
+// The workspace as a set of empty buffers that grow() fills with pieces of the static array.
+static void clear_arena(rnn_model* m) {
+    for (auto& b : m->ws.ybuf) b = DevBuf();
+    std::vector<DevBuf> keep;
+    keep.swap(m->ws.ybuf);              // no reallocation: the vector keeps its L-1 entries
+    m->ws = rnn_model::Workspace();
+    m->ws.ybuf.swap(keep);
+    m->arena.used = 0;
+}
+
+// rnn_forward_static: the workspace out of the static array, before anything is enqueued.  With blocks of 16 sequences and a slot for
+// every step the XCD-resident kernel can need more than the plan without it (2 layers of 512 bf16 units, 800 steps of 17 sequences:
+// 75 MiB against 54).  What that plan fits runs all the same, and on rnn_forward's kernel: slots in turn, one projection a pass, and
+// layer after layer where the sequences that layers of a launch hand to each other are too long.  One case is left to the plan without
+// it: a reset-before GRU that is projected, whose blocks take up to a tenth more than the cellwise plan (4 layers of 512 bf16 units on
+// 1712 features, 286 steps of 22 sequences: 67.5 MiB against 62.2).
+static int fit_arena(rnn_model* m, int T, int B, Plan& plan) {
+    auto fits = [&](int compact) -> int {
+        m->compact = compact;
+        clear_arena(m);
+        const int rc = resolve_plan(m, T, B, plan);
+        return rc == RNN_OK ? prepare_workspace(m, plan, T, B) : rc;
+    };
+    int rc = fits(0);
+    if (rc != RNN_ESCRATCH || (rc = fits(-1)) != RNN_OK) return rc;
+    for (int most = WF_MAX_LAYERS; most >= 1; most /= 2)
+        if ((rc = fits(most)) != RNN_ESCRATCH) return rc;
+    return fits(-1);
+}
+
 // rnn_forward and rnn_forward_static: the second with the workspace carved from the device's static array.
 static int forward_entry(rnn_model* m, const void* x, const int32_t* lengths, const float* h0,
                          const float* c0, void* y, float* hT, float* cT, int T, int B, void* stream) {
@@ -1324,9 +1385,10 @@ static int forward_entry(rnn_model* m, const void* x, const int32_t* lengths, co
     Plan plan;
     int rc = resolve_plan(m, T, B, plan);
     if (rc != RNN_OK) return rc;
-    rc = prepare_workspace(m, plan, T, B);   // no-op when rnn_model_reserve has seen this shape and plan
+    rc = m->arena.on ? fit_arena(m, T, B, plan) : prepare_workspace(m, plan, T, B);   // no-op when rnn_model_reserve has seen this shape and plan
     if (rc != RNN_OK) return rc;
-    if (m->capturing) {
+    if (m->capturing || m->arena.on) {
+        // (rnn_forward_static: the pieces of the static array hold whatever the last call left there.)
         // The launches recorded now carry the tags chosen now, and every replay runs them again with
         // the same tags: what the previous replay (or any other forward) left in the flag words and
         // the tagged state words must not be taken for this run's, so a replay starts by clearing them.
@@ -1397,32 +1459,12 @@ int rnn_forward_static(rnn_model* m, const void* x, const int32_t* lengths, cons
     // For the length of this call the model's workspace is a set of empty buffers that grow() fills with
     // pieces of the static array; the model's own workspace is put back untouched afterwards.
     std::swap(m->ws, m->ws_static);
-    for (auto& b : m->ws.ybuf) b = DevBuf();
-    {
-        std::vector<DevBuf> keep;
-        keep.swap(m->ws.ybuf);              // no reallocation: the vector keeps its L-1 entries
-        m->ws = rnn_model::Workspace();
-        m->ws.ybuf.swap(keep);
-    }
+    clear_arena(m);
     m->arena.base = m->scratch;
-    m->arena.used = 0;
-    m->arena.stream = (hipStream_t)stream;
     m->arena.on = true;
-    int rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
-    if (rc == RNN_ESCRATCH) {
-        // The XCD-resident kernel holds blocks of 16 sequences whole (17 sequences take as much as 32): where that does not fit,
-        // the plan that would be taken without it may.  Nothing but fills of fresh memory has been launched yet.
-        for (auto& b : m->ws.ybuf) b = DevBuf();
-        std::vector<DevBuf> keep;
-        keep.swap(m->ws.ybuf);
-        m->ws = rnn_model::Workspace();
-        m->ws.ybuf.swap(keep);
-        m->arena.used = 0;
-        m->avoid_xcd = true;
-        rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
-        m->avoid_xcd = false;
-    }
+    const int rc = forward_entry(m, x, lengths, h0, c0, y, hT, cT, T, B, stream);
     m->arena.on = false;
+    m->compact = 0;
     std::swap(m->ws, m->ws_static);
     return rc;
 }

@@ -124,19 +124,44 @@ def test_reset_gate_before_the_product(gpu, oracle, shape):
     model.close()
 
 
-def test_static_array_that_only_tagged_words_fit(gpu):
-    """17 sequences: two blocks of 16 here (75 MiB for 800 steps), 17 rows of tagged words (54 MiB) in the static array of 64 MiB."""
+@pytest.mark.parametrize("shape", [
+    (0, 2, 1, 512, 512, 800, 17, 1, 0, 0),      # slots in turn: two blocks of 16 take 75 MiB, tagged words 54
+    (0, 2, 1, 1024, 1024, 400, 17, 1, 0, 0),    # the same on two XCDs
+    (1, 4, 2, 384, 384, 461, 17, 1, 1, 0),      # both directions, batch-first
+    (1, 6, 1, 8, 360, 323, 12, 1, 0, 1),        # r * h in turn as well
+    (1, 16, 1, 48, 148, 358, 22, 0, 1, 1),      # ... and four layers to a launch instead of eight
+    (0, 4, 2, 12, 512, 20, 374, 0, 0, 0),       # passes that project their own sequences
+    (0, 4, 2, 12, 512, 14, 374, 0, 1, 0),
+    (1, 4, 1, 1712, 512, 286, 22, 1, 0, 1),     # left to the cellwise plan
+], ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s_bf%d_rb%d" % (s[:7] + ("f32" if s[7] == 0 else "bf16",) + s[8:]))
+def test_static_array_that_only_tagged_words_fit(gpu, shape):
+    """Calls whose workspace with a slot for every step exceeds the static array of 64 MiB, and that fit without this kernel: the
+    bits of rnn_forward all the same (of the cellwise plan where only that one fits)."""
     import torch
     harness, rnn, W = gpu
-    wl = _workload(W, (0, 2, 1, 512, 512, 800, 17, 1), False)
+    wl = _workload(W, shape[:8], True)
+    c = wl.cfg
+    print("\n  case %r" % (shape,), flush=True)
     model, io, io2 = harness.DeviceModel(wl), harness.DeviceIO(wl), harness.DeviceIO(wl)
-    harness.forward(model, io)
-    assert rnn.rnn_forward_static(model.handle, io2.x, io2.lengths, io2.h0, io2.c0, io2.y, io2.hT, io2.cT, 800, 17,
-                                  torch.cuda.current_stream()) == rnn.RNN_OK
-    torch.cuda.synchronize()
-    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
-    assert (io.y.float() - io2.y.float()).abs().max().item() <= TOL[1]
-    assert (io.hT - io2.hT).abs().max().item() <= TOL[1]
+    if shape[9]:
+        assert rnn.rnn_model_set_gru_reset_before(model.handle, 1) == rnn.RNN_OK
+    if shape[3] == 1712:
+        assert rnn.rnn_model_set_plan(model.handle, rnn.RNN_PLAN_CELLWISE) == rnn.RNN_OK
+    assert rnn.rnn_model_set_batch_first(model.handle, shape[8]) == rnn.RNN_OK
+    stream = torch.cuda.current_stream()
+    if shape[8]:
+        for t in (io, io2):
+            t.x, t.y = t.x.transpose(0, 1).contiguous(), t.y.view(c.B, c.T, c.D * c.H)
+    assert rnn.rnn_forward(model.handle, io.x, io.lengths, io.h0, io.c0, io.y, io.hT, io.cT, c.T, c.B, stream) == rnn.RNN_OK
+    assert rnn.rnn_model_set_plan(model.handle, rnn.RNN_PLAN_AUTO) == rnn.RNN_OK
+    for _ in range(2):
+        assert rnn.rnn_forward_static(model.handle, io2.x, io2.lengths, io2.h0, io2.c0, io2.y, io2.hT, io2.cT, c.T, c.B,
+                                      stream) == rnn.RNN_OK
+        torch.cuda.synchronize()
+        assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+        assert torch.equal(io.y, io2.y) and torch.equal(io.hT, io2.hT)
+        assert c.cell == 1 or torch.equal(io.cT, io2.cT)
+        io2.y.fill_(7.0)
     model.close()
 
 
