@@ -69,12 +69,14 @@ SMALL = [
     ("lstm_f32_padded_h20", 0, 2, 1, 12, 20, 8, 3, 0, True, True),             # fp32 20 -> 32
     ("lstm_bf16_padded_h896_inside", 0, 2, 1, 896, 896, 5, 130, 1, True, True),  # 896 -> 1024 at a large batch
     ("lstm_bf16_t1", 0, 2, 1, 64, 128, 1, 2, 1, False, True),
-    # small batches, several layers in one launch of the tag-in-data kernel (fused layers have their own waves
-    # for the input product): taller tiles, a quarter too large to be requested a step early, fp32
-    ("lstm_bf16_8layer_h256", 0, 8, 1, 48, 256, 12, 3, 1, True, True),     # 8 layers x 16 workgroups, 16-row tiles x 4
-    ("gru_bf16_2layer_h1024_b12", 1, 2, 1, 40, 1024, 6, 12, 1, True, True),  # x fetched after the barriers (12 x 128 words per wave)
-    ("lstm_bf16_4layer_sq_h1024_b1", 0, 4, 1, 1024, 1024, 7, 1, 1, False, True),   # one load instruction per wave: the lean fetch loop
-    ("gru_bf16_3layer_h1024_b6", 1, 3, 1, 1024, 1024, 5, 6, 1, True, True),   # 6 x 128 words per wave: probe word, then the generic fetch of six instructions
+    # small batches, several layers in one launch (fused layers have their own waves for the input product).  bf16 layers of up to 512
+    # units and fp32 layers of 64 to 512 run on the XCD-resident kernel, bf16 ones of 640 to 1024 on its groups over two XCDs where
+    # B * H > 4096; below, and for one fp32 sequence of 512 units and layers beyond 1024 units, the tag-in-data kernel
+    ("lstm_bf16_8layer_h256", 0, 8, 1, 48, 256, 12, 3, 1, True, True),     # XCD-resident
+    ("gru_bf16_2layer_h1024_b12", 1, 2, 1, 40, 1024, 6, 12, 1, True, True),  # two XCDs, behind a projection
+    ("lstm_bf16_4layer_sq_h1024_b1", 0, 4, 1, 1024, 1024, 7, 1, 1, False, True),   # tag-in-data, one load instruction per wave: the lean fetch loop
+    ("lstm_f32_8layer_sq_h512_b1", 0, 8, 1, 512, 512, 6, 1, 0, True, True),   # tag-in-data, all eight layers in a launch
+    ("gru_bf16_3layer_h1024_b6", 1, 3, 1, 1024, 1024, 5, 6, 1, True, True),   # two XCDs, 4 + 2 columns of a chunk row
     ("lstm_bf16_2layer_h1024_b3", 0, 2, 1, 1024, 1024, 5, 3, 1, True, True),  # 3 x 128 words per wave: three instructions, fetched outright
     ("lstm_f32_6layer_h128", 0, 6, 1, 24, 128, 9, 5, 0, True, True),
     ("gru_bf16_4layer_h512_t1", 1, 4, 1, 32, 512, 1, 2, 1, False, True),   # a single step
@@ -87,7 +89,7 @@ SMALL = [
     ("lstm_f32_half_h64", 0, 1, 1, 32, 64, 7, 33, 0, True, True),
     ("lstm_bf16_bidir_sq_h256", 0, 2, 2, 256, 256, 9, 20, 1, True, True),
     ("gru_bf16_bidir_half_h128", 1, 2, 2, 64, 128, 8, 5, 1, True, False),
-    # fp32 layers of 256 and 512 units (tag-in-data kernel: 16 and 32 K blocks of 4 per wave)
+    # fp32 layers of 256 and 512 units
     ("lstm_f32_2layer_sq_h256", 0, 2, 1, 256, 256, 7, 5, 0, True, True),
     ("gru_f32_3layer_h512", 1, 3, 1, 100, 512, 5, 3, 0, True, True),
     ("lstm_f32_half_h256", 0, 2, 1, 128, 256, 6, 1, 0, False, True),
@@ -196,7 +198,8 @@ def test_small_shapes(gpu, oracle, spec, plan):
 
 
 # models whose upper layers wait a long time at the start of a launch (the layers below have to get there first)
-@pytest.mark.parametrize("name", ["lstm_bf16_8layer_h256", "lstm_bf16_20layer_h256",  # tag-in-data kernel (8 and 16 layers in a launch)
+@pytest.mark.parametrize("name", ["lstm_bf16_8layer_h256", "lstm_bf16_20layer_h256",  # XCD-resident kernel (8 and 10 layers in a launch)
+                                  "lstm_f32_8layer_sq_h512_b1",                        # tag-in-data kernel
                                   "lstm_bf16_sidebyside_l4",                           # inside-product kernel
                                   "lstm_f32_fusedflag_l6_h32"])                        # flag-vector kernel
 def test_abandoned_wait_is_reported_and_the_model_recovers(gpu, oracle, name):
@@ -526,7 +529,8 @@ def test_length_validation(gpu):
     model.close()
 
 
-@pytest.mark.parametrize("name", ["lstm_bf16_8layer_h256", "lstm_bf16_inside_sq", "lstm_bf16_b299"])
+@pytest.mark.parametrize("name", ["lstm_bf16_8layer_h256", "lstm_bf16_inside_sq", "lstm_bf16_b299", "lstm_bf16_4layer_sq_h1024_b1",
+                                  "lstm_bf16_2layer_sq_h2048"])       # the last two: tag-in-data kernel, one and two launches
 def test_launch_tag_wraps(gpu, name):
     """The 32-bit launch tag wraps after 2^32 launches: the launch that wraps clears the flag words and the
     tagged words and starts again from tag 1.  Forced here by setting the tag just below the wrap: the
@@ -583,7 +587,7 @@ def test_onnx_gate_order(gpu, oracle, cell):
 
 
 OPT_SPECS = [
-    (("lstm_opts_bf16", 0, 2, 2, 40, 128, 9, 21, 1, True, True), 0.5, True),           # tag-in-data kernel, both directions
+    (("lstm_opts_bf16", 0, 2, 2, 40, 128, 9, 21, 1, True, True), 0.5, True),           # XCD-resident kernel, both directions
     (("lstm_opts_f32", 0, 3, 1, 20, 64, 12, 5, 0, True, True), 0.4, True),
     (("lstm_peep_only", 0, 2, 1, 64, 128, 8, 6, 1, True, True), 0.0, True),
     (("lstm_clip_only", 0, 2, 1, 64, 128, 8, 6, 1, True, True), 0.3, False),
@@ -703,7 +707,7 @@ def test_batch_first_layout(gpu, oracle, name, plan):
                                   ("gru_rb_f32", 1, 2, 1, 24, 64, 7, 5, 0, True, True)], ids=lambda s: s[0])
 def test_gru_reset_before_product(gpu, oracle, spec):
     """The GRU that applies the reset gate before the candidate's recurrent product (the oracle's
-    variant 1, pinned by its own closed-form tests) runs under the cellwise plan."""
+    variant 1, pinned by its own closed-form tests); of the plans it can be given only the cellwise one."""
     harness, rnn, W = gpu
     wl = _small_workload(W, spec)
     model = harness.DeviceModel(wl)
@@ -732,8 +736,10 @@ def test_gru_reset_before_product(gpu, oracle, spec):
     lstm.close()
 
 
-@pytest.mark.parametrize("name,plan", [("lstm_bf16_8layer_h256", "auto"),      # tag-in-data kernel
-                                       ("gru_bf16_bidir", "auto"),               # tag-in-data kernel, two launches
+@pytest.mark.parametrize("name,plan", [("lstm_bf16_8layer_h256", "auto"),      # XCD-resident kernel
+                                       ("gru_bf16_bidir", "auto"),               # XCD-resident kernel, two launches
+                                       ("lstm_bf16_4layer_sq_h1024_b1", "auto"), # tag-in-data kernel
+                                       ("lstm_bf16_2layer_sq_h2048", "auto"),    # tag-in-data kernel, two launches
                                        ("lstm_bf16_inside_sq", "auto"),          # inside-product kernel, one launch per layer
                                        ("lstm_bf16_sidebyside_l4", "auto"),      # inside-product kernel, layers side by side
                                        ("lstm_f32_fusedflag_l6_h32", "auto"),    # flag-vector kernel
@@ -835,13 +841,13 @@ def test_workspace_follows_the_plan(gpu):
     harness.forward(model, io)
     torch.cuda.synchronize()
     y_first = io.y.clone()
-    # the same model on 3 sequences runs both layers in one launch of the tag-in-data kernel
+    # the same model on 3 sequences runs both layers in one launch of the XCD-resident kernel
     small = wl.take_batch(np.arange(3))
     io_small = harness.DeviceIO(small)
     harness.forward(model, io_small)
     torch.cuda.synchronize()
     assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
-    assert rnn.rnn_model_device_bytes(model.handle) > bytes_large          # grew: projection, tagged sequences
+    assert rnn.rnn_model_device_bytes(model.handle) > bytes_large          # grew: projection, chunk sequences
     # the same sequences under another plan (another kernel, another summation order): equal within the bf16 tolerance
     assert float((io_small.y.float() - y_first[:, :3].float()).abs().max()) <= 2e-2
     harness.forward(model, io)
@@ -850,7 +856,7 @@ def test_workspace_follows_the_plan(gpu):
     model.close()
 
 
-@pytest.mark.parametrize("kind", ["inside_product", "tagged", "cellwise"])
+@pytest.mark.parametrize("kind", ["inside_product", "one_xcd", "tagged", "cellwise"])
 def test_workspace_keeps_only_live_layers(gpu, oracle, kind):
     """A deeper model needs no more workspace than a shallow one: the state sequences of two launches and two
     inter-layer output buffers are used alternately (only the layer being written and the one being read are
@@ -858,11 +864,13 @@ def test_workspace_keeps_only_live_layers(gpu, oracle, kind):
     (re-used regions hold another layer's data when a launch starts)."""
     import torch
     harness, rnn, W = gpu
-    shape = {"inside_product": dict(I=512, H=512, T=9, B=300), "tagged": dict(I=256, H=256, T=12, B=3),
+    shape = {"inside_product": dict(I=512, H=512, T=9, B=300), "one_xcd": dict(I=256, H=256, T=12, B=3),
+             "tagged": dict(I=1024, H=1024, T=12, B=1),
              "cellwise": dict(I=64, H=128, T=6, B=5)}[kind]
     plan = rnn.RNN_PLAN_CELLWISE if kind == "cellwise" else rnn.RNN_PLAN_WAVEFRONT
-    deep_layers = 40 if kind == "tagged" else 7        # tagged: 16 layers per launch, so 3 launches
-    shallow_layers = 32 if kind == "tagged" else 2     # two launches already use both halves
+    # one_xcd and tagged: at most 16 and 4 layers per launch, so 3 launches; two already use both halves
+    deep_layers = {"one_xcd": 40, "tagged": 12}.get(kind, 7)
+    shallow_layers = {"one_xcd": 32, "tagged": 8}.get(kind, 2)
     work = {}
     for L in (shallow_layers, deep_layers):
         cfg = W.Config("ws_%s_%d" % (kind, L), W.LSTM, L=L, D=1, dtype=W.BF16, seed=W.BASE_SEED + 60 + L, len_min=2, **shape)
@@ -954,7 +962,7 @@ def test_input_product_placement(gpu):
     assert rnn.rnn_model_set_plan(model.handle, rnn.RNN_PLAN_CELLWISE) == rnn.RNN_OK
     assert [rnn.rnn_model_input_product_placement(model.handle, c.T, c.B, l)[1] for l in range(c.L)] == [1, 1]
     model.close()
-    # small batch, square first layer: the tag-in-data kernel's first layer reads the plain input
+    # small batch, square first layer: the XCD-resident kernel's first layer reads the plain input
     wl = _small_workload(W, by_name["lstm_bf16_3layer_sq_h256"])
     model = harness.DeviceModel(wl, plan=rnn.RNN_PLAN_WAVEFRONT)
     c = wl.cfg

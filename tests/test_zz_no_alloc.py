@@ -54,7 +54,8 @@ def _forward_both(harness, rnn, model, wl):
 
 SHAPES = [
     # name, cell, L, D, I, H, T, B, dtype, ragged: first the larger call, then a smaller one on the same array
-    [("lstm_bf16_tagged", 0, 4, 1, 256, 256, 40, 6, 1, True), ("lstm_bf16_tagged_small", 0, 4, 1, 256, 256, 9, 2, 1, True)],
+    [("lstm_bf16_one_xcd", 0, 4, 1, 256, 256, 40, 6, 1, True), ("lstm_bf16_one_xcd_small", 0, 4, 1, 256, 256, 9, 2, 1, True)],
+    [("lstm_bf16_tagged", 0, 4, 1, 1024, 1024, 40, 4, 1, True), ("lstm_bf16_tagged_small", 0, 4, 1, 1024, 1024, 9, 1, 1, True)],
     [("gru_bf16_bidir", 1, 2, 2, 128, 128, 25, 20, 1, True), ("gru_bf16_bidir_small", 1, 2, 2, 128, 128, 7, 3, 1, False)],
     [("lstm_f32_grid", 0, 12, 1, 64, 64, 48, 8, 0, False), ("lstm_f32_grid_small", 0, 12, 1, 64, 64, 16, 1, 0, False)],
     [("lstm_bf16_large_batch", 0, 2, 1, 256, 256, 12, 300, 1, True), ("lstm_bf16_large_batch_small", 0, 2, 1, 256, 256, 5, 130, 1, True)],
