@@ -295,6 +295,11 @@ int rnn_model_set_spin_limit(rnn_model* model, unsigned polls);
  * flag and tagged-word buffers of the model's own workspace, so no earlier launch's tags can be met again. */
 int rnn_model_set_launch_tag(rnn_model* model, uint32_t tag);
 
+/* Test aid.  The kernel of layers that fit one XCD exchanges a layer's state through that XCD's L2 once the workgroups have
+ * found themselves on one, and through memory otherwise.  on = 1: through memory always, which gives the same results, slower;
+ * a test reaches that way of exchange so, as the dispatcher places the workgroups as the launch asks.  0 = the default. */
+int rnn_model_set_device_scope(rnn_model* model, int on);
+
 /* Where the input product W_ih x_t of `layer` is computed for a forward pass of T steps and B
  * sequences under the current plan: *separate_launch = 1 when it is a projection launch of its own
  * (RNN_KERNEL_PROJECTION: the product over all steps, hoisted out of the cell), 0 when it runs

@@ -103,6 +103,7 @@ struct rnn_model {
     // the same order).  0: as rnn_forward; -1: no plan of that kernel.
     int compact = 0;
     bool batch_first = false;   // x is [B, T, I] and y [B, T, D*H]
+    bool device_scope = false;  // the XCD-resident kernel exchanges through memory wherever it runs
     bool validate = false;      // check `lengths` on the host before every forward
     // the cell variant with two dependent recurrent products per cell: the cellwise plan and the XCD-resident kernel only
     bool two_products() const { return gru_reset_before; }
@@ -948,6 +949,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
         a.in_place = in_place ? 1 : 0;
+        a.device_scope = m->device_scope ? 1 : 0;
         for (int ll = 0; ll < LP; ++ll)
             for (int d = 0; d < m->D; ++d) {
                 const int g = (l0 + ll) * m->D + d;
@@ -1319,6 +1321,12 @@ int rnn_model_set_peepholes(rnn_model* m, const float* const* peepholes, int on_
 int rnn_model_set_batch_first(rnn_model* m, int on) {
     if (!m || (on != 0 && on != 1)) return RNN_EINVAL;
     m->batch_first = on != 0;
+    return RNN_OK;
+}
+
+int rnn_model_set_device_scope(rnn_model* m, int on) {
+    if (!m || (on != 0 && on != 1)) return RNN_EINVAL;
+    m->device_scope = on != 0;
     return RNN_OK;
 }
 

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 if (other == 0) same = __all((uint32_t)mine == (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)mine));
             }
         }
-        if (wv == NW - 1 && lane == 0) lds_put(placed, same && p.nrb <= 64 ? 1u : 0u);
+        if (wv == NW - 1 && lane == 0) lds_put(placed, same && p.nrb <= 64 && !p.device_scope ? 1u : 0u);
         __syncthreads();
     };
 

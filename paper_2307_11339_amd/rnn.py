@@ -31,7 +31,7 @@ EXPORTS = ("rnn_model_create", "rnn_model_destroy", "rnn_model_set_plan", "rnn_m
            "rnn_model_read_step_ticks", "rnn_model_input_product_placement", "rnn_model_create_ordered",
            "rnn_model_set_gru_reset_before", "rnn_plan_query", "rnn_model_set_spin_limit",
            "rnn_model_set_clip", "rnn_model_set_peepholes", "rnn_model_set_batch_first", "rnn_forward_static",
-           "rnn_model_set_validation", "rnn_model_set_launch_tag", "rnn_probe_matrix_rate", "rnn_plan_launches", "rnn_probe_exchange_step",
+           "rnn_model_set_validation", "rnn_model_set_launch_tag", "rnn_model_set_device_scope", "rnn_probe_matrix_rate", "rnn_plan_launches", "rnn_probe_exchange_step",
            "rnn_stack_create", "rnn_stack_destroy", "rnn_stack_runs", "rnn_stack_run", "rnn_stack_device_bytes",
            "rnn_stack_forward")
 
@@ -99,6 +99,8 @@ def load_library() -> ctypes.CDLL:
     lib.rnn_probe_matrix_rate.argtypes = [ci, ci] + [ctypes.POINTER(ctypes.c_double)] * 3 + [vp]
     lib.rnn_model_set_launch_tag.restype = ci
     lib.rnn_model_set_launch_tag.argtypes = [vp, ctypes.c_uint32]
+    lib.rnn_model_set_device_scope.restype = ci
+    lib.rnn_model_set_device_scope.argtypes = [vp, ci]
     lib.rnn_model_set_batch_first.restype = ci
     lib.rnn_model_set_batch_first.argtypes = [vp, ci]
     lib.rnn_model_set_spin_limit.restype = ci
@@ -208,6 +210,10 @@ def rnn_model_set_validation(model: int, on: int) -> int:
 
 def rnn_model_set_launch_tag(model: int, tag: int) -> int:
     return load_library().rnn_model_set_launch_tag(model, tag)
+
+
+def rnn_model_set_device_scope(model: int, on: int) -> int:
+    return load_library().rnn_model_set_device_scope(model, on)
 
 
 def rnn_stack_create(cell: int, input_size: int, hidden_sizes: Sequence[int], num_directions: int, dtype: int,

@@ -35,6 +35,9 @@ SHAPES = [
     (0, 1, 1, 64, 504, 3, 520, 1),      # the same through copies at the padded width
     (0, 1, 1, 512, 512, 4, 129, 0),     # passes of 128 sequences; the last one, alone, would run on tagged words
     (0, 2, 2, 300, 300, 4, 65, 0),      # the same padded, both directions, two launches
+    (0, 1, 1, 20, 512, 4, 150, 0),      # passes of 128 and 22 behind one projection (input narrower than an eighth of the layer)
+    (0, 2, 2, 520, 512, 3, 70, 0),      # ... (wider than the x waves hold), both directions; the second layer projects by itself
+    (1, 1, 1, 40, 512, 4, 150, 1),      # one pass of another kernel; with the reset gate before the product, as above
     (0, 4, 1, 1024, 1024, 1, 5, 1),     # groups on two XCDs: one step, the whole chip
     (0, 4, 1, 1024, 1024, 11, 12, 1),   # chunk rows wider than the batch
     (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
@@ -241,4 +244,33 @@ def test_an_infinite_feature_saturates_the_gates(gpu, oracle, shape):
     harness.forward(model, io)
     _check(harness, wl, io, ref)
     assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    model.close()
+
+
+@pytest.mark.parametrize("shape", [(0, 2, 1, 128, 128, 9, 3, 1), (1, 3, 1, 256, 256, 12, 17, 1), (0, 2, 1, 512, 512, 14, 16, 1),
+                                   (0, 2, 2, 384, 384, 10, 33, 1), (0, 12, 1, 64, 64, 20, 8, 0), (1, 1, 1, 256, 256, 9, 5, 0),
+                                   (0, 2, 1, 512, 512, 8, 20, 0)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
+@pytest.mark.parametrize("reset_before", [0, 1])
+def test_a_group_that_is_not_on_one_xcd(gpu, shape, reset_before):
+    """The exchange through memory, which a group uses that the dispatcher has laid over several XCDs: the same bits."""
+    import torch
+    harness, rnn, W = gpu
+    if reset_before and shape[0] == 0:
+        shape = (1,) + shape[1:]
+    wl = _workload(W, shape, True)
+    print("\n  case %r reset before %d" % (shape, reset_before), flush=True)
+    model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
+    assert rnn.rnn_model_set_gru_reset_before(model.handle, reset_before) == rnn.RNN_OK
+    harness.forward(model, io)
+    torch.cuda.synchronize()
+    want = (io.y.clone(), io.hT.clone(), io.cT.clone())
+    assert rnn.rnn_model_set_device_scope(model.handle, 2) == rnn.RNN_EINVAL
+    assert rnn.rnn_model_set_device_scope(model.handle, 1) == rnn.RNN_OK
+    for _ in range(3):
+        io.y.fill_(7.0)
+        harness.forward(model, io)
+        torch.cuda.synchronize()
+        assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+        assert torch.equal(io.y, want[0]) and torch.equal(io.hT, want[1]) and (shape[0] == 1 or torch.equal(io.cT, want[2]))
     model.close()
