@@ -37,6 +37,9 @@ def _hipcc() -> str:
 NO_SPILL = {"wavefront_x.hip": ("wavefront_x_kernel", "ELi2ELb"),     # file: (kernel name, piece of the name that says two chains)
             "wavefront_x_b.hip": ("wavefront_x_kernel", "ELi2ELb"),
             "gemm.hip": ("gemm_bf16_nt_wide_kernel", "")}               # 256 accumulation + 244 vector registers of 512
+# The variants of the XCD-resident kernel hold up to 128 registers of weights a wave (250 of 256 in use): a spill there goes
+# through memory in every step (2 bf16 layers of 512 units, both directions: 659 -> 5197 us).
+NO_SPILL.update({"wavefront_xcd%s.hip" % part: ("wavefront_xcd_kernel", "") for part in ("", "_b", "_c", "_d", "_e", "_f", "_g", "_h")})
 
 
 def _check_no_spill(src: str, remarks: str) -> None:

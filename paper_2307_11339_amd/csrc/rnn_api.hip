@@ -29,10 +29,9 @@ struct Plan {
     // the first layer runs in a launch of its own (it needs a projection, the layers above it run side
     // by side in the inside-product kernel): launches are {0}, {1..LP}, {LP+1..2LP}, ...
     bool first_alone = false;
-    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with gpx groups of workgroups on every XCD, or on every
-    // pair of XCDs (span = 2)
+    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with its groups of workgroups on an XCD each, or on a pair (span = 2)
     bool xcd = false;
-    int gpx = 0, span = 1, stride = 0;
+    int span = 1, stride = 0;
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
     int chunk = 0;
@@ -231,7 +230,7 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
             plan = Plan();
             plan.kind = RNN_PLAN_WAVEFRONT;
             plan.xcd = true;
-            plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
+            plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
             return true;
         }
     }
@@ -256,7 +255,7 @@ bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     plan.kind = RNN_PLAN_WAVEFRONT;
     plan.xcd = true;
     plan.span = 2;
-    plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.gpx = gpx; plan.stride = stride;
+    plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
     return true;
 }
 
@@ -705,7 +704,7 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
 
 // XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave
 // (1024 bf16 or 512 fp32 values).  An input of an eighth of the layer's width or less keeps its projection launch.
-bool xcd_input_inside(const rnn_model* m, const Plan&, int width, bool several_layers) {
+bool xcd_input_inside(const rnn_model* m, int width, bool several_layers) {
     return 8 * width > m->H && wavefront_xcd_input_chunks(m->dtype, m->H, width, several_layers) > 0;
 }
 
@@ -714,7 +713,7 @@ bool xcd_input_inside(const rnn_model* m, const Plan&, int width, bool several_l
 // So can the first layer of a launch of the tag-in-data kernel (its x waves read the plain input).
 bool input_product_inside(const rnn_model* m, const Plan& plan, int l, int T) {
     if (plan.kind != RNN_PLAN_WAVEFRONT) return false;
-    if (plan.xcd) return first_of_launch(m, plan, l) && xcd_input_inside(m, plan, m->layer_input(l), launch_width(m, plan, l) > 1);
+    if (plan.xcd) return first_of_launch(m, plan, l) && xcd_input_inside(m, m->layer_input(l), launch_width(m, plan, l) > 1);
     if (plan.CT == 1 && plan.NCH == 1) {
         // tag-in-data kernel, first layer of a launch (layers above it in the launch are fused anyway): its
         // x waves hold the W_ih slice in registers, which fits for an input H wide, or 2H wide (a
