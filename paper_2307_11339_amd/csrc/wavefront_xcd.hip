@@ -5,9 +5,9 @@
 // (layer, direction) of the unrolled grid; a workgroup owns RT * 4 hidden units of one block of up to 16 sequences;
 // W_hh in the registers of four h waves that split K, W_ih in those of four x waves that work a step ahead).  What
 // bounds a step at these sizes is the exchange of h between the workgroups, and its cost is a matter of where the
-// data meets (measured, 32 workgroups all-gathering 256 words of 8 bytes, us per step):
-//     device-scope stores (written through to memory), device-scope loads     1.26 - 1.44
-//     plain stores (they stay in the XCD's L2), loads that bypass the L1       0.62
+// data meets (this kernel, us per step, one bf16 layer of 128 / 256 / 512 units, 16 sequences; rnn_model_set_device_scope):
+//     device-scope stores (written through to memory), device-scope loads     1.05 / 1.41 / 2.24
+//     plain stores (they stay in the XCD's L2), loads that bypass the L1       0.76 / 0.94 / 1.09
 // The second line needs every workgroup of a group on one XCD.  The dispatcher deals consecutive workgroups to the
 // XCDs in turn, so the launch numbers its groups by blockIdx % 8; nothing relies on that: every workgroup publishes
 // the XCC it really runs on before the first step (while its weights travel), and a group that finds itself on more
@@ -128,6 +128,7 @@ struct XRF32 : TraitsF32 {
 typedef volatile __attribute__((address_space(3))) unsigned lds_word;
 __device__ inline void lds_put(unsigned* p, unsigned v) { *(lds_word*)p = v; }
 __device__ inline unsigned lds_get(unsigned* p) { return *(lds_word*)p; }
+typedef volatile __attribute__((address_space(3))) u32x4 lds_chunk;
 
 // Buffer descriptor over `bytes` bytes at p (wave-uniform; said so, which keeps it in scalar registers).
 __device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t bytes) {
@@ -551,12 +552,34 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     };
     for (int s = 0; s < T; ++s) {
         const int t = d ? T - 1 - s : s;
-        f32x4 acc[RT];                               // starts as the input part
-        auto input_part = [&]() {
-            while (lds_get(ready + w) < (unsigned)(s + 1)) {}  // (every x wave takes every step, whatever became of its waits)
-            asm volatile("" ::: "memory");
+        // The recurrent product starts from the input part.  Not so in fp32, where one chain of sums as long as both products loses
+        // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7; in bf16 the rounding of the stored
+        // state hides it): there the wave that finishes a tile sums the tile's input part, and the bias, for itself meanwhile.
+        constexpr bool APART = MPL > 1;
+        f32x4 acc[RT], from_x;
+        if constexpr (APART) from_x = bias_reg[0];
+        auto input_part = [&]() {                    // (every x wave takes every step, whatever became of its waits)
+            if constexpr (APART) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt] = xacc[(w * RT + rt) * 64 + lane];
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (w < RT) {
+                    // the words first, the sums behind them in one LDS round trip (operations of a wave keep their order)
+                    u32x4 at;
+                    f32x4 part[4];
+                    do {
+                        at = *(lds_chunk*)ready;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            part[k] = __builtin_bit_cast(f32x4, (u32x4)*(lds_chunk*)&xacc[(k * RT + (KEEP ? (w - k) & 3 : w)) * 64 + lane]);
+                    } while (min(min(at[0], at[1]), min(at[2], at[3])) < (unsigned)(s + 1));
+                    from_x += (part[0] + part[1]) + (part[2] + part[3]);
+                }
+            } else {
+                while (lds_get(ready + w) < (unsigned)(s + 1)) {}
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = xacc[(w * RT + rt) * 64 + lane];
+            }
         };
         if (s > 0) fetch(hrs, s - 1, input_part);
         else input_part();
@@ -564,7 +587,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         __syncthreads();
         f32x4 pre[NOWN];
 #pragma unroll
-        for (int o = 0; o < NOWN; ++o) pre[o] = total(acc, RB ? 0 : (s & 1)) + bias_reg[o];
+        for (int o = 0; o < NOWN; ++o) {
+            pre[o] = total(acc, RB ? 0 : (s & 1));
+            if constexpr (APART) pre[o] += from_x;
+            else pre[o] += bias_reg[o];
+        }
         float zg[RB ? NOWN : 1], nx[RB ? NOWN : 1];
         if constexpr (RB) {
             // r * h goes round the group before the candidate's recurrent product
