@@ -210,7 +210,9 @@ bool xcd_addressable(const rnn_model* m, int T, int B) {
 int xcd_layers(const rnn_model* m, int LP) { return m->compact > 0 ? std::min(LP, m->compact) : LP; }
 
 // A plan for the XCD-resident kernel: every (layer, direction, block of 16 sequences) of a launch is a group of workgroups
-// that fits the compute units of one XCD.
+// that fits the compute units of one XCD.  A test of fit: wherever it fits it is faster, also at the edge, where layers that could run
+// side by side on the other kernels get a launch each (64 steps, us, those -> this: 4 bf16 layers of 512 units at batch 128
+// 355 -> 313, 6 of 256 at batch 256 713 -> 365, 2 of 128 at batch 512 307 -> 108; 6 fp32 layers of 128 units at batch 128 335 -> 307).
 bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
     if (m->compact < 0) return false;
     const int per_xcd = m->num_cus / XCDS, ncb = (B + 15) / 16, stride = xcd_stride(m, B);

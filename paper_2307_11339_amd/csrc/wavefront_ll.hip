@@ -21,6 +21,10 @@
 // sequence is still running the state is the layer's output, and where it is padded the cell
 // above is inactive as well and ignores its input.
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
+//
+// Layers that fit one XCD, or two, run in wavefront_xcd.hip instead where that is faster (choose_xcd, choose_xcd_wide).  On 256
+// compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, wider ones, fp32 layers of 32 units, one
+// sequence of 512 fp32 units and a few batches of 384 units; its other variants serve devices with fewer compute units to an XCD.
 #include "wf_traits.h"
 
 // The variants of this kernel are compiled in three translation units so that the build runs in

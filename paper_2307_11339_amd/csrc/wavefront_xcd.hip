@@ -35,8 +35,8 @@
 // compute unit at 64 bytes per clock, behind an L2 round trip of 350), products 280, barrier and sum over the quarters 300,
 // gates 300, publication 150; the tag-in-data kernel took 2.5 us a step here, this one takes 1.2.  Whole forward passes
 // before -> after: 2-layer LSTM of 512 units, both directions, batch 64, 256 steps 1.29 -> 0.65 ms; 2-layer GRU of 512 units at
-// batch 8 183 -> 111 us for 100 steps; 12 fp32 layers of 64 units 159 -> 119 us; 2 fp32 layers of 512 units at batch 64 1.15 ->
-// 0.77 ms; GRU with the reset gate before the product (one launch per cell part until now) 1719 -> 105 us.
+// batch 8 183 -> 111 us for 100 steps; 12 fp32 layers of 64 units 159 -> 118 us; 2 fp32 layers of 512 units at batch 64 1.15 ->
+// 0.73 ms; GRU with the reset gate before the product (one launch per cell part until now) 1719 -> 105 us.
 #include "wf_traits.h"
 
 // The variants are compiled in several translation units so that the build runs in parallel: this file is part 0 (bf16,
