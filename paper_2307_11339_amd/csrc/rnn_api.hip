@@ -950,6 +950,9 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
         a.in_place = in_place ? 1 : 0;
+        // Input products a step ahead make a step 3 to 5 % shorter and every layer above the first a step later (us, 0 -> 1: 2 fp32
+        // layers of 512 units, 128 steps 664 -> 635; 2 GRU layers of 512, 100 steps 115 -> 111; 12 fp32 layers of 64, 96 steps 105 -> 112).
+        a.lead = 25 * (LP - 1) <= T ? 1 : 0;
         a.device_scope = m->device_scope ? 1 : 0;
         for (int ll = 0; ll < LP; ++ll)
             for (int d = 0; d < m->D; ++d) {
@@ -977,7 +980,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
                 a.gx = (const float*)m->ws.gx.p;
             }
         }
-        a.xln = wavefront_xcd_input_chunks(m->dtype, m->H, a.gx ? m->H : a.I, LP > 1);
+        a.xln = wavefront_xcd_input_chunks(m->dtype, m->H, a.gx ? 8 : a.I, LP > 1);
         const int l1 = l0 + LP - 1;
         if (l1 == m->L - 1) {
             a.out = (char*)y + (size_t)b0 * xb * m->D * units * m->esize;

@@ -31,13 +31,16 @@
 // LDS, so that no store other than the state itself stands before the next poll of an h wave.
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
-// What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz): fetch of the state 500 - 900 (16 KiB into every
-// compute unit at 64 bytes per clock, behind an L2 round trip of 350), products 280, barrier and sum over the quarters 300,
-// gates 300, publication 150; the tag-in-data kernel took 2.5 us a step here, this one takes 1.2.  Whole forward passes
-// before -> after: 2-layer LSTM of 512 units, both directions, batch 64, 256 steps 1.29 -> 0.65 ms; 2-layer GRU of 512 units at
-// batch 8 183 -> 111 us for 100 steps; 12 fp32 layers of 64 units 159 -> 118 us; 2 fp32 layers of 512 units at batch 64 1.15 ->
-// 0.73 ms; GRU with the reset gate before the product (one launch per cell part until now) 1719 -> 105 us.
+// What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz, each with the stamp that took it): fetch of the state 820
+// (16 KiB into every compute unit, its 32 load instructions with those of the x waves behind an L2 round trip of 400; one of four
+// as much state takes 440), products 350, barrier 200, sum over the quarters 240, gates 370, publication 150; the tag-in-data
+// kernel took 2.5 us a step here, this one takes 1.15.  Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
+// batch 64, 256 steps 1.29 -> 0.62 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64
+// units 159 -> 103 us; 2 fp32 layers of 512 units at batch 64 1.15 -> 0.63 ms; GRU with the reset gate before the product (one
+// launch per cell part without it) 1719 -> 98 us.
 #include "wf_traits.h"
+
+#include <type_traits>
 
 // The variants are compiled in several translation units so that the build runs in parallel: this file is part 0 (bf16,
 // and the public functions); wavefront_xcd_b.hip and so on include it with other values.
@@ -160,13 +163,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     constexpr int PART = OTHERS * RT * 64;           // f32x4 entries of one set of them
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     f32x4* red = reinterpret_cast<f32x4*>(smem_raw);              // [2][RT tiles][OTHERS waves][64 lanes]
-    f32x4* xacc = red + 2 * PART;                                 // [4][RT][64]: x wave w to h wave w
-    pub_t* pub = reinterpret_cast<pub_t*>(xacc + 4 * RT * 64);    // [RT][PUB_LANES]
+    constexpr int XPART = 4 * RT * 64;
+    f32x4* xacc = red + 2 * PART;                                 // [2][4][RT][64]: x wave w to h wave w
+    pub_t* pub = reinterpret_cast<pub_t*>(xacc + 2 * XPART);      // [RT][PUB_LANES]
     unsigned* done = reinterpret_cast<unsigned*>(pub + RT * TR::PUB_LANES);   // [4] steps whose tile h wave w has handed over
     unsigned* ready = done + 4;                                   // [4] steps whose input part x wave w has handed over
     unsigned* placed = ready + 4;                                 // 1: the whole group runs on one XCD
     constexpr int TURN = 4 * (16 + 2);                            // u32x4 entries to turn one load of rows in: [4 chunks][16 rows + 2]
-    u32x4* turn = reinterpret_cast<u32x4*>(smem_raw + (((size_t)(2 * PART + 4 * RT * 64) * sizeof(f32x4) +
+    u32x4* turn = reinterpret_cast<u32x4*>(smem_raw + (((size_t)(2 * PART + 2 * XPART) * sizeof(f32x4) +
                                                         (size_t)RT * TR::PUB_LANES * sizeof(pub_t) + 9 * sizeof(unsigned) + 15) & ~(size_t)15));   // [4 x waves][XLN][TURN]
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -272,7 +276,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         __builtin_amdgcn_s_setprio(1);
         // ---- x waves: the input product, one step ahead of the h waves ------------------------------
         const int KX = fused ? H : p.I;              // width of this layer's input
-        constexpr int NBUF = XLN <= 2 ? 4 : 2;       // steps of x in flight (a plain x comes from HBM)
+        constexpr int NBUF = 2;                      // steps of x in flight (a plain x comes from HBM)
         // Rows of the caller's tensor: a load whose four neighbouring lanes lie in four rows takes the address unit four times
         // as long as one whose neighbours share 64 bytes (64 against 16 clocks, measured), and h waves wait behind it.  So lanes
         // bring 64 bytes of a row together, and the wave turns them into fragments through LDS.
@@ -281,7 +285,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         frag wx[RT][XLN * MPL];
         uint32_t xoff[XLN];                          // byte offset of this lane's chunk inside a step of x, or inside its row (rows of a
                                                      // batch-first x can lie 4 GiB apart: the row is in the 64-bit address)
-        if (!project) {
+        if (project) {
+#pragma unroll
+            for (int i = 0; i < XLN; ++i) xoff[i] = 0u;
+        } else {
             // W_ih of all directions is one matrix [D * 4H, KX]; direction d owns rows d * 4H ...
             const elem* wih = static_cast<const elem*>(p.wih[ld]) + (size_t)d * SLOTS * H * KX;
 #pragma unroll
@@ -313,28 +320,29 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                            : static_cast<const char*>(p.xin) + (p.x_blocked ? (size_t)cb * T * xstep
                                                                            : (size_t)(rows ? cb * 16 + min(lane >> 2, ncol - 1) : col) * p.x_b * KX * sizeof(elem));
         u32x4 xb[NBUF][XLN];
-        auto request = [&](int s, u32x4 (&v)[XLN]) { // the s-th step in this direction's order
+        // The s-th step in this direction's order.  No branch stands between the loads and their use: where two ways of loading
+        // meet, the compiler copies what they loaded, and waits for it there and then (an x from HBM then stops the x wave for its
+        // whole latency in every step: 657 us instead of 615 for 2 layers of 512 units, both directions, batch 64, 256 steps).
+        auto request_below = [&](int s, u32x4 (&v)[XLN]) {
+            const uint32_t at = (uint32_t)min(s, T - 1) * slot_bytes;
+#pragma unroll
+            for (int i = 0; i < XLN; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
+        };
+        auto request = [&](int s, u32x4 (&v)[XLN]) {
             const int sc = min(s, T - 1);
-            if (fused) {
+            const char* src = xsrc + (size_t)(d ? T - 1 - sc : sc) * xstep;
 #pragma unroll
-                for (int i = 0; i < XLN; ++i)
-                    v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], (uint32_t)sc * slot_bytes, 16);
-            } else {
-                const char* src = xsrc + (size_t)(d ? T - 1 - sc : sc) * xstep;
-                if (project) {
-                    v[0] = *reinterpret_cast<const u32x4*>(src);
-                    return;
-                }
-#pragma unroll
-                for (int i = 0; i < XLN; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + xoff[i]);
-            }
+            for (int i = 0; i < XLN; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + xoff[i]);
         };
         // layer output of the workgroup's tiles, or their state for the layer above
         elem* out = static_cast<elem*>(p.out);
-        auto forward = [&](int s) {
-            if (w >= RT) return;                     // x wave w takes the tile that h wave w finished
+        auto gates_done = [&](int s) {
             while (lds_get(done + w) < (unsigned)(s + 1)) __builtin_amdgcn_s_sleep(1);   // (every h wave takes every step, whatever became of its waits)
             asm volatile("" ::: "memory");
+        };
+        auto forward = [&](int s) {
+            if (w >= RT) return;                     // x wave w takes the tile that h wave w finished
+            gates_done(s);
             if (valid && lane < TR::PUB_LANES) {
                 const pub_t v = pub[w * TR::PUB_LANES + lane];
                 const int unit0 = (rb * RT + w) * 4;
@@ -354,26 +362,31 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             asm volatile("" ::: "memory");
         };
         start_wait();
-        // The input part of step sx, between barriers sx - 1 and sx.  h wave w picks it up as the start of its accumulators
-        // while its state fragments travel.  The layer output of step sx - 1 leaves behind it, or before it where the product
-        // is long: that waits for h wave w, on the same SIMD, to be through its gates, whose vector instructions otherwise
-        // queue behind this wave's matrix instructions one by one (2 layers of 512 units in fp32, 4096 clocks of product: 4200
-        // clocks of gate phase instead of 300; where the product is no longer than the exchange of the state, waiting first
-        // makes it late instead: 2 layers of 512 units in bf16, both directions, batch 64: 730 us against 687).
+        // Between barriers s - 1 and s an x wave asks for the input of a later step (at once: the h waves are in their gates then,
+        // and the address unit, which the state of the next step waits for, is free) and produces the input part of step
+        // sx = s + lead.
+        // With lead = 1 the part is there a step before h wave w picks it up, as the start of its accumulators, while its state
+        // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
+        // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: 1078 clocks of
+        // gates instead of 860).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
+        // (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that is long.
+        const int lead = fused ? p.lead : 1;
         constexpr bool OUT_FIRST = XLN * MPL * RT * TR::MMA_CLOCKS > 512;
-        auto produce = [&](int sx, u32x4 (&cur)[XLN]) {
-            bool sent = sx == 0;
-            if (OUT_FIRST && !sent) { forward(sx - 1); sent = true; }
-            if (fused) {
+        auto produce = [&](auto from_below, int sx, u32x4 (&cur)[XLN]) {
+            constexpr bool BELOW = decltype(from_below)::value;
+            const int s = sx - lead;                 // between barriers s - 1 and s
+            bool sent = s <= 0 || s >= T;
+            if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
+            if constexpr (BELOW) {
                 unsigned spins = 0;
                 for (;;) {
                     uint32_t m = 0;
 #pragma unroll
                     for (int i = 0; i < XLN; ++i) m = TR::seen(m, cur[i]);
                     if (!__any(m == UNWRITTEN) || aborted) break;
-                    if (!sent) { forward(sx - 1); sent = true; }     // nothing to multiply yet
+                    if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
                     if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
-                    request(sx, cur);
+                    request_below(sx, cur);
                     asm volatile("" ::: "memory");
                 }
             }
@@ -384,17 +397,18 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
                 }
             }
-            if (rows) {                              // (no barrier: LDS operations of a wave keep their order)
+            if (!BELOW && rows) {                    // (no barrier: LDS operations of a wave keep their order)
 #pragma unroll
                 for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
             }
+            if (lead && w < RT && !sent) gates_done(s - 1);
             f32x4 acc[RT];
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (project) {
+            if (!BELOW && project) {
                 if (KEEP) acc[0] = __builtin_bit_cast(f32x4, cur[0]);
                 else {
 #pragma unroll
@@ -414,27 +428,36 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(acc[rt]));
                 asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(acc[RT - 1]));
             }
+            if (sx < T) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) xacc[(w * RT + rt) * 64 + lane] = acc[rt];
-            asm volatile("" ::: "memory");           // (LDS operations of a wave keep their order)
-            if (lane == 0) lds_put(ready + w, (unsigned)(sx + 1));
-            if (!sent) forward(sx - 1);
+                for (int rt = 0; rt < RT; ++rt) xacc[(sx & 1) * XPART + (w * RT + rt) * 64 + lane] = acc[rt];
+                asm volatile("" ::: "memory");       // (LDS operations of a wave keep their order)
+                if (lane == 0) lds_put(ready + w, (unsigned)(sx + 1));
+            }
+            if (!sent) forward(s - 1);
+            if (s >= 0 && s < T) {
+                __syncthreads();
+                if (RB) __syncthreads();
+            }
             __builtin_amdgcn_sched_barrier(0);
-            request(sx + (fused ? 1 : NBUF), cur);      // (a step of the layer below is asked for when the one before it has come)
+            if constexpr (BELOW) request_below(sx + 1, cur);
+            else request(sx + NBUF, cur);
             __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-            if (RB) __syncthreads();
         };
         if (fused) {
-            request(0, xb[0]);
-            for (int s = 0; s < T; ++s) produce(s, xb[0]);
+            request_below(0, xb[0]);
+            for (int sx = 0; sx < T + lead; ++sx) produce(std::true_type(), sx, xb[0]);
         } else {
 #pragma unroll
-            for (int b = 0; b < NBUF; ++b) request(b, xb[b]);
-            for (int s0 = 0; s0 < T; s0 += NBUF)
+            for (int b = 0; b < NBUF; ++b) {
+                request(b, xb[b]);
+                __builtin_amdgcn_sched_barrier(0);   // (in this order: the loop's waits count on it)
+            }
+            // (A whole number of rounds, beyond the last step where need be: a way round a step, or out of the loop between steps,
+            // would make the compiler wait for the newest loads at the head of the loop.)
+            for (int s0 = 0; s0 < T + lead; s0 += NBUF)
 #pragma unroll
-                for (int b = 0; b < NBUF; ++b)
-                    if (s0 + b < T) produce(s0 + b, xb[b]);
+                for (int b = 0; b < NBUF; ++b) produce(std::false_type(), s0 + b, xb[b]);
         }
         forward(T - 1);
         return;
@@ -570,7 +593,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                         at = *(lds_chunk*)ready;
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            part[k] = __builtin_bit_cast(f32x4, (u32x4)*(lds_chunk*)&xacc[(k * RT + (KEEP ? (w - k) & 3 : w)) * 64 + lane]);
+                            part[k] = __builtin_bit_cast(f32x4, (u32x4)*(lds_chunk*)&xacc[(s & 1) * XPART + (k * RT + (KEEP ? (w - k) & 3 : w)) * 64 + lane]);
                     } while (min(min(at[0], at[1]), min(at[2], at[3])) < (unsigned)(s + 1));
                     from_x += (part[0] + part[1]) + (part[2] + part[3]);
                 }
@@ -578,9 +601,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 while (lds_get(ready + w) < (unsigned)(s + 1)) {}
                 asm volatile("" ::: "memory");
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) acc[rt] = xacc[(w * RT + rt) * 64 + lane];
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = xacc[(s & 1) * XPART + (w * RT + rt) * 64 + lane];
             }
         };
+        if (w >= RT && s > 0)                        // (no use in asking before the workgroup's own tiles are out)
+            while (lds_get(done + (w & (RT - 1))) < (unsigned)s) __builtin_amdgcn_s_sleep(1);
         if (s > 0) fetch(hrs, s - 1, input_part);
         else input_part();
         multiply(acc, RB ? 0 : (s & 1));
@@ -665,7 +690,7 @@ constexpr size_t MIN_LDS = 84 * 1024;
 
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
-    const size_t need = (size_t)((RT == 4 ? 6 : 8) + 4) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
+    const size_t need = (size_t)((RT == 4 ? 6 : 8) + 8) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
                         9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16;
     const size_t smem = need < MIN_LDS ? MIN_LDS : need;
     auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT>;
@@ -794,9 +819,9 @@ hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     if ((a.span != 1 && a.span != 2) || a.nrb % a.span != 0) return hipErrorInvalidValue;
     if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 * a.span || a.ncb != (a.B + 15) / 16 || a.gpx * (8 / a.span) < a.LP * a.D * a.ncb)
         return hipErrorInvalidValue;
-    // with a projection the x waves of the first layer multiply nothing, whatever its input's width
+    // with a projection the x waves of the first layer multiply nothing and load the four values of their pair (one chunk)
     if ((a.gx == nullptr && a.xin == nullptr) || a.xln == 0 ||
-        wavefront_xcd_input_chunks(a.dtype, a.H, a.gx ? a.H : a.I, a.LP > 1) != a.xln) return hipErrorInvalidValue;
+        wavefront_xcd_input_chunks(a.dtype, a.H, a.gx ? 8 : a.I, a.LP > 1) != a.xln) return hipErrorInvalidValue;
     if (a.ring <= a.T && ((a.ring & (a.ring - 1)) != 0 || a.ring < 2 * XCD_AHEAD)) return hipErrorInvalidValue;
     if (a.stride < (a.B < 16 ? a.B : 16) || a.stride > 16) return hipErrorInvalidValue;
     if ((size_t)a.T * wavefront_xcd_slot_bytes(a.dtype, a.stride, a.H) >= ((size_t)1 << 31)) return hipErrorInvalidValue;

@@ -40,6 +40,9 @@ SHAPES = [
     (1, 1, 1, 40, 512, 4, 150, 1),      # one pass of another kernel; with the reset gate before the product, as above
     (0, 4, 1, 1024, 1024, 1, 5, 1),     # groups on two XCDs: one step, the whole chip
     (0, 4, 1, 1024, 1024, 11, 12, 1),   # chunk rows wider than the batch
+    (0, 2, 1, 128, 128, 24, 3, 1),      # too few steps for the upper layer to run its input product a step ahead
+    (1, 2, 1, 512, 512, 25, 9, 1),      # just enough, an odd number
+    (0, 3, 1, 64, 64, 50, 5, 0),
     (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
     (1, 1, 1, 1032, 1024, 6, 40, 1),    # projection in front, three blocks of sequences
     (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD
