@@ -368,10 +368,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // With lead = 1 the part is there a step before h wave w picks it up, as the start of its accumulators, while its state
         // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
         // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: 1078 clocks of
-        // gates instead of 860).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
+        // gates instead of 860).  A product of a few instructions, in a launch of one layer, does not wait (128 units, 48 steps, 16
+        // groups or more: 51 us with the wait, 45 without; with layers above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
         // (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that is long.
         const int lead = fused ? p.lead : 1;
-        constexpr bool OUT_FIRST = XLN * MPL * RT * TR::MMA_CLOCKS > 512;
+        constexpr int PRODUCT = XLN * MPL * RT * TR::MMA_CLOCKS;
+        constexpr bool OUT_FIRST = PRODUCT > 512;
+        const bool wait_gates = lead && w < RT && (PRODUCT > 128 || p.LP > 1);
         auto produce = [&](auto from_below, int sx, u32x4 (&cur)[XLN]) {
             constexpr bool BELOW = decltype(from_below)::value;
             const int s = sx - lead;                 // between barriers s - 1 and s
@@ -404,7 +407,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
                 for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
             }
-            if (lead && w < RT && !sent) gates_done(s - 1);
+            if (wait_gates && !sent) gates_done(s - 1);
             f32x4 acc[RT];
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
