@@ -32,6 +32,7 @@ struct Plan {
     // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with its groups of workgroups on an XCD each, or on a pair (span = 2)
     bool xcd = false;
     int span = 1, stride = 0;
+    int LP_asked = 1;               // LP before a compact workspace lowered it (rnn_forward_static decides as rnn_forward does)
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
     int chunk = 0;
@@ -232,7 +233,7 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
             plan = Plan();
             plan.kind = RNN_PLAN_WAVEFRONT;
             plan.xcd = true;
-            plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
+            plan.LP = xcd_layers(m, LP); plan.LP_asked = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
             return true;
         }
     }
@@ -257,7 +258,7 @@ bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     plan.kind = RNN_PLAN_WAVEFRONT;
     plan.xcd = true;
     plan.span = 2;
-    plan.LP = xcd_layers(m, LP); plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
+    plan.LP = xcd_layers(m, LP); plan.LP_asked = LP; plan.RT = RT; plan.nrb = nrb; plan.ncb = ncb; plan.stride = stride;
     return true;
 }
 
@@ -327,7 +328,7 @@ bool choose_wavefront(const rnn_model* m, int T, int B, Plan& plan) {
         }
         if (best >= 0) {
             plan.kind = RNN_PLAN_WAVEFRONT;
-            plan.LP = LP;
+            plan.LP = plan.LP_asked = LP;
             plan.RT = cand[best][0];
             plan.CT = cand[best][1];
             plan.NCH = cand[best][2];
@@ -422,20 +423,64 @@ int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = 
     return derive_launches(m, plan, T);
 }
 
+// What one pass of `plan` over B sequences takes, in us: launches of T steps each.  Fitted to launches of 48 steps, 40 to 1100
+// sequences through 2 layers of 128 to 512 bf16 units, one and both directions (within a sixth where it decides); steps of
+//     the XCD-resident kernel          0.8 (128 units, 64 to 128 sequences) to 1.3 (512 units, 128), 1.0 with 8 of 128 sequences
+//     the tag-in-data kernel           2.7 (384 units, both directions, 72 sequences)
+//     large tiles, 64 columns          4.0 (256 units, 136 sequences) to 5.4 (512, 400); two layers in a launch 5.2 to 6.7
+//     large tiles, two chains          4.5 (512 units, 512 sequences) with the input product inside, else no faster than the former
+double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
+    const int launches = (m->L + plan.LP_asked - 1) / plan.LP_asked;
+    double step;
+    if (plan.xcd) {
+        const double fill = m->D == 1 ? std::min(1.0, plan.LP_asked * plan.ncb / (double)XCDS) : 1.0;
+        step = (0.8 + m->H / 1000.0) * (0.6 + 0.4 * fill);
+    } else if (plan.CT == 1 && plan.NCH == 1) {
+        step = 2.7;
+    } else {
+        const bool inside = m->D == 1 && m->I == m->H && plan.NCH == 2;
+        step = (3.3 + 0.0013 * m->H + 7e-6 * m->H * m->D * plan.LP_asked * B) * (plan.LP_asked > 1 ? 1.2 : 1.0) * (inside ? 0.75 : 1.0);
+    }
+    return launches * (6.0 + T * step);
+}
+
+int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last);
+
+// ... and what all passes of a call take.
+double call_us(const rnn_model* m, const Plan& plan, int T, int B) {
+    if (plan.chunk == 0) return pass_us(m, plan, T, B);
+    double us = B / plan.chunk * pass_us(m, plan, T, plan.chunk);
+    Plan last;
+    if (B % plan.chunk != 0 && resolve_last_pass(m, plan, T, B % plan.chunk, last) == RNN_OK) us += pass_us(m, last, T, B % plan.chunk);
+    return us;
+}
+
+// The largest multiple of 16 below B that `choose` has a plan for (every workgroup's tiles full).
+template <class F>
+bool choose_passes(const rnn_model* m, int T, int B, Plan& plan, F choose) {
+    for (int bc = ((B - 1) / 16) * 16; bc >= 16; bc -= 16)
+        if (choose(m, T, bc, plan)) {
+            plan.chunk = bc;
+            return true;
+        }
+    return false;
+}
+
 int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk) {
     if (m->two_products() && m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
     if (m->requested_plan == RNN_PLAN_CELLWISE) {
         plan = Plan();
         return RNN_OK;
     }
-    if (choose_wavefront(m, T, B, plan)) return RNN_OK;
-    if (may_chunk) {
-        // the largest multiple of 16 sequences below B that has a plan (every workgroup's tiles full)
-        for (int bc = ((B - 1) / 16) * 16; bc >= 16; bc -= 16)
-            if (choose_wavefront(m, T, bc, plan)) {
-                plan.chunk = bc;
-                return RNN_OK;
-            }
+    if (choose_wavefront(m, T, B, plan) || (may_chunk && choose_passes(m, T, B, plan, choose_wavefront))) {
+        // A batch that the XCD-resident kernel does not hold at once: in passes it is up to twice as fast as the other kernels
+        // (48 steps, 2 layers, us, those -> passes: both directions, 512 units, 72 sequences 465 -> 263, 512 sequences 1404 -> 998;
+        // 256 units, 136 sequences 385 -> 202; one direction, 512 units, 136 sequences 320 -> 189), but not where many passes stand
+        // against a well filled launch (512 units, 512 sequences 431 -> 481; both directions, 384 units, 260 sequences 518 -> 570).
+        Plan passes;
+        if (!plan.xcd && may_chunk && m->H <= 512 && choose_passes(m, T, B, passes, choose_xcd) &&
+            1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B)) plan = passes;
+        return RNN_OK;
     }
     if (m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
     plan = Plan();
@@ -705,9 +750,11 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
 }
 
 // XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave
-// (1024 bf16 or 512 fp32 values).  An input of an eighth of the layer's width or less keeps its projection launch.
+// (1024 bf16 or 512 fp32 values).  With several layers in the launch an input of an eighth of their width or less keeps its projection
+// launch; a launch of one layer takes it inside as well (48 steps, us, projected -> inside: 8 values into 128 units, 1 and 64
+// sequences 42 -> 38 and 54 -> 39; 64 into 512 units 61 -> 57 and 71 -> 62; fp32, 8 into 256 units 80 -> 68 and 93 -> 70).
 bool xcd_input_inside(const rnn_model* m, int width, bool several_layers) {
-    return 8 * width > m->H && wavefront_xcd_input_chunks(m->dtype, m->H, width, several_layers) > 0;
+    return (!several_layers || 8 * width > m->H) && wavefront_xcd_input_chunks(m->dtype, m->H, width, several_layers) > 0;
 }
 
 // A layer that runs alone in its launch, in one direction, on an input of its own width can do

@@ -43,6 +43,9 @@ SHAPES = [
     (0, 2, 1, 128, 128, 24, 3, 1),      # too few steps for the upper layer to run its input product a step ahead
     (1, 2, 1, 512, 512, 25, 9, 1),      # just enough, an odd number
     (0, 3, 1, 64, 64, 50, 5, 0),
+    (0, 2, 2, 512, 512, 6, 72, 1),      # passes of 64 and 8 sequences where a launch of larger tiles holds all 72
+    (1, 3, 2, 40, 200, 5, 140, 1),      # the same padded, 128 and 12, a narrow input inside
+    (0, 4, 1, 520, 256, 6, 300, 1),     # 256 and 44, the last pass with all layers in a launch
     (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
     (1, 1, 1, 1032, 1024, 6, 40, 1),    # projection in front, three blocks of sequences
     (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD

@@ -51,6 +51,19 @@ def test_medium_batch_layers_side_by_side():
     assert rc == rnn.RNN_OK and plan["layers_per_launch"] == 4 and plan["launches"] == 1 and sep == [1, 0, 0, 0]
 
 
+@pytest.mark.parametrize("D,I,H,T,B,passes", [
+    (2, 512, 512, 48, 72, True), (2, 512, 512, 48, 512, False), (2, 256, 256, 48, 136, True), (2, 384, 384, 48, 260, False),
+    (1, 512, 512, 48, 136, True), (1, 512, 512, 48, 512, False), (1, 64, 512, 48, 700, True), (2, 512, 512, 1, 72, False)])
+def test_passes_of_small_tiles_against_a_launch_of_large_ones(D, I, H, T, B, passes):
+    """Batches beyond one launch of 16-sequence tiles: passes of them, or one launch of larger tiles where that is faster."""
+    c = W.Config("p", W.LSTM, L=2, D=D, I=I, H=H, T=T, B=B, dtype=W.BF16, seed=1)
+    rc, plan, sep = _query(c)
+    assert rc == rnn.RNN_OK and plan["kind"] == rnn.RNN_PLAN_WAVEFRONT
+    assert ((plan["row_tiles"], plan["col_tiles"], plan["chains"]) == (4, 1, 1)) == passes
+    if passes:
+        assert 16 * plan["col_blocks"] < B and plan["launches"] > 2 and sep == [0, 0]
+
+
 def test_cellwise_requested_or_forced():
     c = W.CONFIGS["C2"]
     rc, plan, sep = _query(c, plan=rnn.RNN_PLAN_CELLWISE)
