@@ -139,7 +139,7 @@ struct WavefrontXcdArgs {
     int l0, LP;
     int RT, nrb, ncb, gpx;       // 16-row tiles and row blocks per group; blocks of 16 sequences; groups per XCD (per `span` XCDs)
     int stride;                  // sequences side by side in a chunk row of a state sequence: min(16, B) to 16
-    int span;                    // XCDs a group is spread over: 1, or 2 (groups of more than 32 workgroups)
+    int span;                    // XCDs a group is spread over: 1, or 2 or 8 (groups of more than 32 workgroups, of more than 64)
     int xln;                     // chunk loads per x wave and step (wavefront_xcd_input_chunks)
     int ring;                    // slots of a state sequence: a power of two >= 2 * XCD_AHEAD, or more than T (every step its own)
     int ext, reset_before;
@@ -177,6 +177,7 @@ struct WavefrontXcdArgs {
 hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream);
 bool wavefront_xcd_variant_exists(int dtype, int RT, int H);
 bool wavefront_xcd_wide_exists(int dtype, int RT, int H, bool reset_before);   // groups on two XCDs
+bool wavefront_xcd_chip_exists(int dtype, int RT, int H, bool reset_before);   // groups on all eight
 // Chunk loads per x wave for an input `width` wide (of the launch's first layer; several_layers: upper layers read inputs H
 // wide as well), or 0 when there is no such variant.
 int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers);

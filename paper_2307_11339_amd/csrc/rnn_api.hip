@@ -262,10 +262,27 @@ bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     return true;
 }
 
+// The same with a group on all eight XCDs: bf16 layers of 1280, 1536 and 2048 units, 8 units a workgroup, one block of 16 sequences
+// and one layer in a launch.  A test of fit: faster than tagged words at every batch (2 layers, 48 steps, us, tagged words -> this):
+//     1280 units   batch 1 273 -> 221, 4 336 -> 223, 8 420 -> 220, 16 541 -> 224, 32 (two passes) 1091 -> 447
+//     1536 units   batch 1 283 -> 240, 4 452 -> 243, 8 523 -> 234, 16 656 -> 243
+//     2048 units   batch 1 346 -> 263, 4 1067 -> 269, 8 1187 -> 282, 16 1466 -> 302, 64 (four passes) 5890 -> 1172
+bool choose_xcd_chip(const rnn_model* m, int T, int B, Plan& plan) {
+    const int RT = 2, nrb = m->H / (RT * 4);
+    if (m->compact < 0 || m->D != 1 || B > 16 || !xcd_addressable(m, T, B)) return false;
+    if (!wavefront_xcd_chip_exists(m->dtype, RT, m->H, m->gru_reset_before) || nrb > XCDS * (m->num_cus / XCDS)) return false;
+    plan = Plan();
+    plan.kind = RNN_PLAN_WAVEFRONT;
+    plan.xcd = true;
+    plan.span = XCDS;
+    plan.LP = plan.LP_asked = 1; plan.RT = RT; plan.nrb = nrb; plan.ncb = 1; plan.stride = xcd_stride(m, B);
+    return true;
+}
+
 // Choose how the grid of cells is laid over the compute units for batch size B.
 bool choose_wavefront(const rnn_model* m, int T, int B, Plan& plan) {
     if (m->H % 4 != 0) return false;
-    if (choose_xcd(m, T, B, plan)) return true;
+    if (choose_xcd(m, T, B, plan) || choose_xcd_chip(m, T, B, plan)) return true;
     if (m->two_products()) return false;
     plan = Plan();
     const int row_tiles = m->H / 4;

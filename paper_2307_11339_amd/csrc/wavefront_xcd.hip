@@ -15,6 +15,10 @@
 // A bf16 layer of 640 to 1024 units needs more workgroups than an XCD has compute units: its group is laid over two, always with
 // device-scope stores.  What that still gains over tagged words (half the bytes, MFMA fragments straight from the load) stands at
 // the rule that chooses it; 16 sequences through one layer of 1024 units take 2.6 us a step instead of 4.
+// Layers of 1280 to 2048 units are laid over all eight, 8 units a workgroup (160 to 256 of them, one layer in a launch): every
+// workgroup brings in the whole state, 16 sequences x 3 KiB at 1536 units, 9.4 MiB a step over the chip at about 6 TB/s from the
+// infinity cache, and a step takes 2.4 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
+// halves, one after the other: its fragments do not all fit the registers beside the weights (2.9 us).
 //
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
 // the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B fragment is one chunk, so a load instruction of a wave brings a whole K
@@ -179,13 +183,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     const int n = lane & 15, q = lane >> 4;
     auto tile_of = [&](int j) -> int { return KEEP ? (w + j) & 3 : j; };   // this wave's j-th tile
 
-    // workgroup b runs on XCD b % 8: gpx groups of nrb workgroups on each, or on each pair of neighbouring XCDs (half a group on
-    // either; consecutive row blocks, which write neighbouring chunks, stay together)
-    const int two = p.span == 2 ? 1 : 0;
-    const int here = p.nrb >> two;                                // workgroups of a group on one XCD
+    // workgroup b runs on XCD b % 8: gpx groups of nrb workgroups on each, or on each pair of neighbouring XCDs, or on all eight (as
+    // much of a group on each; consecutive row blocks, which write neighbouring chunks, stay together)
+    const int spread = p.span == 8 ? 3 : p.span == 2 ? 1 : 0;
+    const int here = p.nrb >> spread;                             // workgroups of a group on one XCD
     const int gi = (int)(blockIdx.x >> 3) / here;
-    const int rb = (int)(blockIdx.x >> 3) - gi * here + (two ? (int)(blockIdx.x & 1) * here : 0);
-    const int g = ((int)(blockIdx.x & 7) >> two) * p.gpx + gi;    // (cb, d, ll), the layers of a column block side by side
+    const int rb = (int)(blockIdx.x >> 3) - gi * here + (int)(blockIdx.x & (p.span - 1)) * here;
+    const int g = ((int)(blockIdx.x & 7) >> spread) * p.gpx + gi; // (cb, d, ll), the layers of a column block side by side
     if (g >= p.LP * p.D * p.ncb) return;
     const int ll = g % p.LP, d = (g / p.LP) % p.D, cb = g / (p.LP * p.D);
     const int l = p.l0 + ll, ld = ll * p.D + d;
@@ -276,7 +280,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         __builtin_amdgcn_s_setprio(1);
         // ---- x waves: the input product, one step ahead of the h waves ------------------------------
         const int KX = fused ? H : p.I;              // width of this layer's input
-        constexpr int NBUF = 2;                      // steps of x in flight (a plain x comes from HBM)
+        constexpr int NBUF = XLN <= 8 ? 2 : 1;       // steps of x in flight (a plain x comes from HBM; the widest steps are long)
         // Rows of the caller's tensor: a load whose four neighbouring lanes lie in four rows takes the address unit four times
         // as long as one whose neighbours share 64 bytes (64 against 16 clocks, measured), and h waves wait behind it.  So lanes
         // bring 64 bytes of a row together, and the wave turns them into fragments through LDS.
@@ -380,61 +384,61 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             const int s = sx - lead;                 // between barriers s - 1 and s
             bool sent = s <= 0 || s >= T;
             if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
-            if constexpr (BELOW) {
-                unsigned spins = 0;
-                for (;;) {
-                    uint32_t m = 0;
-#pragma unroll
-                    for (int i = 0; i < XLN; ++i) m = TR::seen(m, cur[i]);
-                    if (!__any(m == UNWRITTEN) || aborted) break;
-                    if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
-                    if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
-                    request_below(sx, cur);
-                    asm volatile("" ::: "memory");
-                }
-            }
-            if (!project && XLN * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
-#pragma unroll
-                for (int i = 0; i < XLN; ++i) {
-                    const int chunk = (i * 4 + w) * 4;
-                    if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
-                }
-            }
-            if (!BELOW && rows) {                    // (no barrier: LDS operations of a wave keep their order)
-#pragma unroll
-                for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
-            }
-            if (wait_gates && !sent) gates_done(s - 1);
-            f32x4 acc[RT];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (!BELOW && project) {
-                if (KEEP) acc[0] = __builtin_bit_cast(f32x4, cur[0]);
-                else {
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-                        if (rt == w) acc[rt] = __builtin_bit_cast(f32x4, cur[0]);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < XLN; ++i)
-#pragma unroll
-                    for (int j = 0; j < MPL; ++j)
-#pragma unroll
-                        for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][i * MPL + j], TR::part(cur[i], j), acc[rt]);
-                // Results of a matrix instruction may be read a number of wait states after it was issued; the compiler
-                // counts them inside a block, but was seen not to where two branches join before the read (fp32, RT = 1).
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(acc[rt]));
-                asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(acc[RT - 1]));
-            }
             if (sx < T) {
+                if constexpr (BELOW) {
+                    unsigned spins = 0;
+                    for (;;) {
+                        uint32_t m = 0;
+#pragma unroll
+                        for (int i = 0; i < XLN; ++i) m = TR::seen(m, cur[i]);
+                        if (!__any(m == UNWRITTEN) || aborted) break;
+                        if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
+                        if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
+                        request_below(sx, cur);
+                        asm volatile("" ::: "memory");
+                    }
+                }
+                if (!project && XLN * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+#pragma unroll
+                    for (int i = 0; i < XLN; ++i) {
+                        const int chunk = (i * 4 + w) * 4;
+                        if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
+                    }
+                }
+                if (!BELOW && rows) {                    // (no barrier: LDS operations of a wave keep their order)
+#pragma unroll
+                    for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
+                }
+                if (wait_gates && !sent) gates_done(s - 1);
+                f32x4 acc[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (!BELOW && project) {
+                    if (KEEP) acc[0] = __builtin_bit_cast(f32x4, cur[0]);
+                    else {
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+                            if (rt == w) acc[rt] = __builtin_bit_cast(f32x4, cur[0]);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < XLN; ++i)
+#pragma unroll
+                        for (int j = 0; j < MPL; ++j)
+#pragma unroll
+                            for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][i * MPL + j], TR::part(cur[i], j), acc[rt]);
+                    // Results of a matrix instruction may be read a number of wait states after it was issued; the compiler
+                    // counts them inside a block, but was seen not to where two branches join before the read (fp32, RT = 1).
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) asm volatile("" : "+v"(acc[rt]));
+                    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(acc[RT - 1]));
+                }
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) xacc[(sx & 1) * XPART + (w * RT + rt) * 64 + lane] = acc[rt];
-                asm volatile("" ::: "memory");       // (LDS operations of a wave keep their order)
+                asm volatile("" ::: "memory");           // (LDS operations of a wave keep their order)
                 if (lane == 0) lds_put(ready + w, (unsigned)(sx + 1));
             }
             if (!sent) forward(s - 1);
@@ -504,7 +508,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (p.c0) c_reg[o] = p.c0[state_row * Hu + unit];
         }
     }
-    u32x4 hv[LN];                                    // B fragments of the state before the step
+    constexpr int HL = LN > 12 ? LN / 2 : LN;        // B fragments of the state before the step, HL at a time (16 do not fit the
+    u32x4 hv[HL];                                    // registers beside 32 K blocks of weights)
+    u32x4* const h0_rest = turn + 4 * XLN * TURN + (w * 64 + lane) * (LN - HL);   // the other half of h0, read with the first: an
+                                                                                  // output may take its place
 #pragma unroll
     for (int i = 0; i < LN; ++i) {                   // step 0: the caller's h0
         const int ir = i + rot >= LN ? i + rot - LN : i + rot;
@@ -516,41 +523,46 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
             for (int e = 0; e < EPC; ++e) f[e] = p.h0[state_row * Hu + k + e];
         }
-        hv[i] = TR::pack(f);
+        if (i < HL) hv[i < HL ? i : 0] = TR::pack(f);
+        else h0_rest[i - HL] = TR::pack(f);
     }
     start_wait();
     const bool local = __builtin_amdgcn_readfirstlane((int)lds_get(placed)) != 0;
 
-    auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s) {         // request slot s
+    auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s, int first) {   // request HL chunks of slot s
 #pragma unroll
-        for (int i = 0; i < LN; ++i) {
-            const int ir = i + rot >= LN ? i + rot - LN : i + rot;
+        for (int i = 0; i < HL; ++i) {
+            const int ir = first + i + rot >= LN ? first + i + rot - LN : first + i + rot;
             hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff, slot_of(s) + (uint32_t)(ir * 64) * Bs, 16);
         }
     };
-    // Slot s in hv, waiting until all of it has been written; `meanwhile` runs while the first request travels.
-    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, auto meanwhile) {
+    // The chunks of slot s from `first` on in hv, waiting until all of them have been written; `meanwhile` runs while the first
+    // request travels.
+    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, int first, auto meanwhile) {
         unsigned spins = 0;
         for (;;) {
-            ask(rs, s);
+            ask(rs, s, first);
             if (spins == 0u) meanwhile();
             uint32_t m = 0;
 #pragma unroll
-            for (int i = 0; i < LN; ++i) m = TR::seen(m, hv[i]);
+            for (int i = 0; i < HL; ++i) m = TR::seen(m, hv[i]);
             if (!__any(m == UNWRITTEN) || aborted) break;
             if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
             asm volatile("" ::: "memory");
         }
         asm volatile("" ::: "memory");
     };
-    // partial products of this wave's K quarter added to acc; all tiles but the wave's own go to LDS
-    auto multiply = [&](f32x4 (&acc)[RT], int buf) {
+    // partial products of this wave's K quarter (of the chunks from `first` on) added to acc
+    auto multiply = [&](f32x4 (&acc)[RT], auto first) {
 #pragma unroll
-        for (int i = 0; i < LN; ++i)
+        for (int i = 0; i < HL; ++i)
 #pragma unroll
             for (int j = 0; j < MPL; ++j)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][i * MPL + j], TR::part(hv[i], j), acc[rt]);
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][(first + i) * MPL + j], TR::part(hv[i], j), acc[rt]);
+    };
+    // all tiles but the wave's own go to LDS
+    auto hand_over = [&](const f32x4 (&acc)[RT], int buf) {
 #pragma unroll
         for (int rt = KEEP ? 1 : 0; rt < RT; ++rt)
             red[buf * PART + (tile_of(rt) * OTHERS + (KEEP ? rt - 1 : w)) * 64 + lane] = acc[rt];
@@ -609,9 +621,20 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         };
         if (w >= RT && s > 0)                        // (no use in asking before the workgroup's own tiles are out)
             while (lds_get(done + (w & (RT - 1))) < (unsigned)s) __builtin_amdgcn_s_sleep(1);
-        if (s > 0) fetch(hrs, s - 1, input_part);
+        constexpr std::integral_constant<int, 0> FRONT{};
+        if (s > 0) fetch(hrs, s - 1, FRONT, input_part);
         else input_part();
-        multiply(acc, RB ? 0 : (s & 1));
+        multiply(acc, FRONT);
+        if constexpr (HL < LN) {
+            constexpr std::integral_constant<int, HL> REST{};
+            if (s > 0) fetch(hrs, s - 1, REST, [] {});
+            else {
+#pragma unroll
+                for (int i = 0; i < HL; ++i) hv[i] = h0_rest[i];
+            }
+            multiply(acc, REST);
+        }
+        hand_over(acc, RB ? 0 : (s & 1));
         __syncthreads();
         f32x4 pre[NOWN];
 #pragma unroll
@@ -635,10 +658,12 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     publish(rrs, sv, (rb * RT + w + 4 * o) * 4, s);
                 }
             }
-            fetch(rrs, s, [] {});
+            static_assert(HL == LN, "the reset gate first: no variant of more than 512 units");
+            fetch(rrs, s, FRONT, [] {});
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            multiply(acc, 1);
+            multiply(acc, FRONT);
+            hand_over(acc, 1);
             __syncthreads();
             pre[0][3] = total(acc, 1)[3] + bias_reg[0][3];
         }
@@ -694,7 +719,7 @@ constexpr size_t MIN_LDS = 84 * 1024;
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     const size_t need = (size_t)((RT == 4 ? 6 : 8) + 8) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
-                        9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16;
+                        9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16 + (LN > 12 ? (size_t)4 * 64 * (LN / 2) * 16 : 0);
     const size_t smem = need < MIN_LDS ? MIN_LDS : need;
     auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT>;
     static bool configured = false;
@@ -722,15 +747,19 @@ hipError_t launch_cell(const WavefrontXcdArgs& a, hipStream_t stream) {
 #define RNN_XR_SHAPES_1(X) X(1, 1) X(1, 2) X(2, 1) X(2, 2) X(2, 4) X(4, 1) X(4, 2) X(4, 4) X(4, 8)
 
 // ... and, in bf16, of 40, 48 or 64 workgroups on two XCDs (1024 units are as many as the registers hold: 32 K blocks of four
-// tiles are 128 registers of weights in a wave).  Translation units of their own (RNN_XR_WIDE).
+// tiles are 128 registers of weights in a wave).  Translation units of their own (RNN_XR_WIDE = 1).  Layers of 1280, 1536 and 2048
+// units in groups of 160, 192 and 256 workgroups of 8 units on all XCDs (RNN_XR_WIDE = 2).
 #define RNN_XR_SHAPES_WIDE(X) X(4, 5) X(4, 6) X(4, 8)
+#define RNN_XR_SHAPES_CHIP(X) X(2, 10) X(2, 12) X(2, 16)
 #ifndef RNN_XR_WIDE
 #define RNN_XR_WIDE 0
 #endif
 
 #if RNN_XR_DT == 0
 typedef XRBf16 TRHere;
-#if RNN_XR_WIDE
+#if RNN_XR_WIDE == 2
+#define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_CHIP(X)
+#elif RNN_XR_WIDE
 #define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_WIDE(X)
 #else
 #define RNN_XR_SHAPES_HERE(X) RNN_XR_SHAPES_0(X)
@@ -742,6 +771,12 @@ typedef XRF32 TRHere;
 
 template <int RT, int LN>
 hipError_t launch_shape(const WavefrontXcdArgs& a, hipStream_t stream) {
+    if constexpr (LN > 8) {
+        if (a.xln == 2) return launch_cell<TRHere, RT, LN, 2>(a, stream);
+        if (a.xln == 8) return launch_cell<TRHere, RT, LN, 8>(a, stream);
+        if (a.xln == LN) return launch_cell<TRHere, RT, LN, LN>(a, stream);
+        return hipErrorInvalidValue;
+    } else
     switch (a.xln) {
         case 1: return launch_cell<TRHere, RT, LN, 1>(a, stream);
         case 2: return launch_cell<TRHere, RT, LN, 2>(a, stream);
@@ -775,6 +810,8 @@ hipError_t launch_wavefront_xcd_dt1_kind1_wide0(const WavefrontXcdArgs& a, hipSt
 hipError_t launch_wavefront_xcd_dt1_kind2_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
 hipError_t launch_wavefront_xcd_dt0_kind0_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
 hipError_t launch_wavefront_xcd_dt0_kind1_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind0_wide2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind1_wide2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
 
 namespace {
 int state_chunks(int dtype, int H) {             // LN, or 0 when H is no multiple of a wave's load
@@ -801,10 +838,20 @@ bool wavefront_xcd_wide_exists(int dtype, int RT, int H, bool reset_before) {
     return false;
 }
 
+bool wavefront_xcd_chip_exists(int dtype, int RT, int H, bool reset_before) {
+    const int LN = state_chunks(dtype, H);
+    if (dtype != DT_BF16 || reset_before) return false;
+#define X(rt, ln) if (RT == rt && LN == ln) return true;
+    RNN_XR_SHAPES_CHIP(X)
+#undef X
+    return false;
+}
+
 int wavefront_xcd_input_chunks(int dtype, int H, int width, bool several_layers) {
     const int LN = state_chunks(dtype, H), epc = dtype == DT_BF16 ? 8 : 4;
     if (width % epc != 0) return 0;
     int need = ((width + 4 * epc - 1) / (4 * epc) + 3) / 4;
+    if (LN > 8) return several_layers || need > LN ? 0 : need <= 2 ? 2 : need <= 8 ? 8 : LN;
     if (several_layers && need < LN) need = LN;
     static const int have[] = {1, 2, 3, 4, 6, 8};
     for (int v : have)
@@ -819,7 +866,7 @@ size_t wavefront_xcd_slot_bytes(int dtype, int stride, int H) {
 hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     const int LN = state_chunks(a.dtype, a.H);
     if (LN == 0 || a.LP < 1 || a.LP > WF_MAX_LAYERS || (a.D != 1 && a.D != 2) || (a.LP > 1 && a.D != 1)) return hipErrorInvalidValue;
-    if ((a.span != 1 && a.span != 2) || a.nrb % a.span != 0) return hipErrorInvalidValue;
+    if ((a.span != 1 && a.span != 2 && a.span != 8) || a.nrb % a.span != 0) return hipErrorInvalidValue;
     if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 * a.span || a.ncb != (a.B + 15) / 16 || a.gpx * (8 / a.span) < a.LP * a.D * a.ncb)
         return hipErrorInvalidValue;
     // with a projection the x waves of the first layer multiply nothing and load the four values of their pair (one chunk)
@@ -833,6 +880,10 @@ hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     if (a.span == 2) {
         if (!wavefront_xcd_wide_exists(a.dtype, a.RT, a.H, a.reset_before != 0)) return hipErrorInvalidValue;
         return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide1(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide1(a, stream, LN);
+    }
+    if (a.span == 8) {
+        if (!wavefront_xcd_chip_exists(a.dtype, a.RT, a.H, a.reset_before != 0)) return hipErrorInvalidValue;
+        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide2(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide2(a, stream, LN);
     }
     if (a.dtype == DT_BF16)
         return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1_wide0(a, stream, LN)

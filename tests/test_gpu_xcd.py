@@ -51,6 +51,12 @@ SHAPES = [
     (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD
     (1, 2, 2, 768, 768, 7, 20, 1),      # both directions, the second launch behind a projection
     (0, 1, 1, 896, 896, 6, 5, 1),       # padded to 1024
+    (0, 2, 1, 1280, 1280, 6, 9, 1),     # groups on all XCDs: 160 workgroups, the second layer reads the first one's chunks
+    (1, 2, 1, 40, 1536, 7, 16, 1),      # 192, a narrow input
+    (0, 1, 1, 1032, 1400, 5, 3, 1),     # padded, an input of nine loads a wave
+    (0, 2, 1, 2048, 2048, 6, 16, 1),    # every compute unit, the state in two halves
+    (1, 1, 1, 64, 2048, 1, 2, 1),       # one step of it
+    (0, 1, 1, 2056, 1800, 9, 20, 1),    # two passes behind a projection
 ]
 
 
