@@ -327,10 +327,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // The s-th step in this direction's order.  No branch stands between the loads and their use: where two ways of loading
         // meet, the compiler copies what they loaded, and waits for it there and then (an x from HBM then stops the x wave for its
         // whole latency in every step: 657 us instead of 615 for 2 layers of 512 units, both directions, batch 64, 256 steps).
+        constexpr int XBELOW = XLN < LN ? XLN : LN;  // (layers above the first: as many loads as their H takes)
         auto request_below = [&](int s, u32x4 (&v)[XLN]) {
             const uint32_t at = (uint32_t)min(s, T - 1) * slot_bytes;
 #pragma unroll
-            for (int i = 0; i < XLN; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
+            for (int i = 0; i < XBELOW; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
         };
         auto request = [&](int s, u32x4 (&v)[XLN]) {
             const int sc = min(s, T - 1);
@@ -372,15 +373,21 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // With lead = 1 the part is there a step before h wave w picks it up, as the start of its accumulators, while its state
         // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
         // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: 1078 clocks of
-        // gates instead of 860).  A product of a few instructions, in a launch of one layer, does not wait (128 units, 48 steps, 16
+        // gates instead of 860).  A product of a few instructions, or of an input wider than the state, which would come too late,
+        // does not wait in a launch of one layer (128 units, 48 steps, 16
         // groups or more: 51 us with the wait, 45 without; with layers above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
         // (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that is long.
-        const int lead = fused ? p.lead : 1;
+        // With the reset gate first, r * h goes round the group behind the barrier: a first layer whose input is wider than its
+        // state asks before the barrier and multiplies in the step itself (1 layer of 512 units on 848 values, 33 sequences, 20
+        // steps: 54.7 us, 58.4 the other way).
+        constexpr bool LATE = RB && XLN > LN;
+        const int lead = fused ? p.lead : LATE ? 0 : 1;
         constexpr int PRODUCT = XLN * MPL * RT * TR::MMA_CLOCKS;
         constexpr bool OUT_FIRST = PRODUCT > 512;
-        const bool wait_gates = lead && w < RT && (PRODUCT > 128 || p.LP > 1);
+        const bool wait_gates = lead && w < RT && ((PRODUCT > 128 && XLN <= LN) || p.LP > 1);
         auto produce = [&](auto from_below, int sx, u32x4 (&cur)[XLN]) {
             constexpr bool BELOW = decltype(from_below)::value;
+            constexpr int XL = BELOW ? XBELOW : XLN;
             const int s = sx - lead;                 // between barriers s - 1 and s
             bool sent = s <= 0 || s >= T;
             if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
@@ -390,7 +397,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     for (;;) {
                         uint32_t m = 0;
 #pragma unroll
-                        for (int i = 0; i < XLN; ++i) m = TR::seen(m, cur[i]);
+                        for (int i = 0; i < XL; ++i) m = TR::seen(m, cur[i]);
                         if (!__any(m == UNWRITTEN) || aborted) break;
                         if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
                         if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
@@ -398,19 +405,19 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                         asm volatile("" ::: "memory");
                     }
                 }
-                if (!project && XLN * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+                if (!project && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
 #pragma unroll
-                    for (int i = 0; i < XLN; ++i) {
+                    for (int i = 0; i < XL; ++i) {
                         const int chunk = (i * 4 + w) * 4;
                         if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
                     }
                 }
                 if (!BELOW && rows) {                    // (no barrier: LDS operations of a wave keep their order)
 #pragma unroll
-                    for (int i = 0; i < XLN; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
+                    for (int i = 0; i < XL; ++i) my_turn[i * TURN + (lane & 3) * 18 + (lane >> 2)] = cur[i];
                     asm volatile("" ::: "memory");
 #pragma unroll
-                    for (int i = 0; i < XLN; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
+                    for (int i = 0; i < XL; ++i) cur[i] = my_turn[i * TURN + q * 18 + n];
                 }
                 if (wait_gates && !sent) gates_done(s - 1);
                 f32x4 acc[RT];
@@ -425,7 +432,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     }
                 } else {
 #pragma unroll
-                    for (int i = 0; i < XLN; ++i)
+                    for (int i = 0; i < XL; ++i)
 #pragma unroll
                         for (int j = 0; j < MPL; ++j)
 #pragma unroll
@@ -442,7 +449,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 if (lane == 0) lds_put(ready + w, (unsigned)(sx + 1));
             }
             if (!sent) forward(s - 1);
-            if (s >= 0 && s < T) {
+            if (!(LATE && !BELOW) && s >= 0 && s < T) {
                 __syncthreads();
                 if (RB) __syncthreads();
             }
@@ -450,6 +457,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if constexpr (BELOW) request_below(sx + 1, cur);
             else request(sx + NBUF, cur);
             __builtin_amdgcn_sched_barrier(0);
+            if (LATE && !BELOW && s >= 0 && s < T) {
+                __syncthreads();
+                __syncthreads();
+            }
         };
         if (fused) {
             request_below(0, xb[0]);
