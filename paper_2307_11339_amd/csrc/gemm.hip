@@ -278,45 +278,106 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_wide_kernel(const bf16_t*
         }
 }
 
-// fp32: 64x64 tile, 256 threads, each thread a 4x4 micro-tile; K slabs of 16 through LDS.
-__global__ __launch_bounds__(256) void gemm_f32_nt_kernel(const float* __restrict__ A, int lda,
-                                                          const float* __restrict__ W, int ldw,
-                                                          float* __restrict__ C, int ldc, int M,
-                                                          int N, int K, int tiles_n) {
-    constexpr int T = 64, KS = 16;
-    __shared__ float sA[KS][T + 1];
-    __shared__ float sW[KS][T + 1];
-    const int tid = threadIdx.x;
-    const int tile_n = blockIdx.x % tiles_n, tile_m = blockIdx.x / tiles_n;
-    const int m0 = tile_m * T, n0 = tile_n * T;
-    const int tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += KS) {
-        for (int i = tid; i < T * KS; i += 256) {
-            const int r = i / KS, k = i % KS;
-            sA[k][r] = (m0 + r < M && k0 + k < K) ? A[(size_t)(m0 + r) * lda + k0 + k] : 0.0f;
-            sW[k][r] = (n0 + r < N && k0 + k < K) ? W[(size_t)(n0 + r) * ldw + k0 + k] : 0.0f;
-        }
-        __syncthreads();
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+// fp32: a workgroup owns TM x TN tiles of 16 x 16, its four waves split K (blocks of 16, in turn) and add up through LDS.  What
+// bounds the small calls (the projection in front of a launch, a product of the cellwise plan) is a wave's chain of loads and
+// products, so K is split and the tile is small (TM = TN = 2: 32 x 32) until there are two workgroups of the larger tile (64 x 64, half
+// the operand traffic) per compute unit.  Fragments come straight from the rows: matrix instruction j of a K block takes k = 4 *
+// (lane / 16) + j, so 16 bytes a lane are the operands of four, and the next block's travel behind them.  Every element is
+// summed in the same order whatever the tile.  Measured (M x N x K, with 64 x 64 tiles of vector instructions -> this):
+//     104 x 512 x 720 102 -> 9.7 us    444 x 256 x 744 107 -> 10.0    1952 x 4096 x 1024 374 -> 190
+// VEC: 16-byte aligned rows of a multiple of 4 values; otherwise the values are loaded one by one.
+template <int TM, int TN, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_nt_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
+                                                          float* __restrict__ C, int ldc, int M, int N, int K, int tiles_n) {
+    __shared__ f32x4 part[4][TM * TN][64];
+    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // consecutive tiles on one XCD (workgroup b runs on XCD b % 8): they share rows of A
+    int b = blockIdx.x;
+    if ((gridDim.x & 7) == 0) b = (b & 7) * (gridDim.x >> 3) + (b >> 3);
+    const int m0 = b / tiles_n * (TM * 16), n0 = b % tiles_n * (TN * 16);
+    const float* ap[TM];
+    const float* wp[TN];
 #pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            float a[4], w[4];
+    for (int i = 0; i < TM; ++i) ap[i] = A + (size_t)min(m0 + i * 16 + n, M - 1) * lda;   // rows beyond are not stored
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; w[i] = sW[k][tx * 4 + i]; }
+    for (int i = 0; i < TN; ++i) wp[i] = W + (size_t)min(n0 + i * 16 + n, N - 1) * ldw;
+    const int blocks = (K + 15) / 16;
+    auto load = [&](int block, f32x4 (&a)[TM], f32x4 (&v)[TN]) {      // beyond K: zeros
+        const int k = block * 16 + 4 * q;
+        auto chunk = [&](const float* row) -> f32x4 {
+            f32x4 r;
+            if constexpr (VEC) {
+                r = *reinterpret_cast<const f32x4*>(row + (k < K ? k : 0));
+                if (k >= K) r = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int j = 0; j < 4; ++j) {
+                    const float x = row[k + j < K ? k + j : 0];
+                    r[j] = k + j < K ? x : 0.0f;
+                }
+            }
+            return r;
+        };
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-        }
-        __syncthreads();
+        for (int i = 0; i < TM; ++i) a[i] = chunk(ap[i]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) v[i] = chunk(wp[i]);
+    };
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int t = 0; t < TN; ++t) acc[i][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 a[2][TM], v[2][TN];
+    load(w, a[0], v[0]);
+    auto step = [&](int block, int cur) {
+        load(block + 4, a[cur ^ 1], v[cur ^ 1]);     // (the last one loads zeros)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[cur][t][j], a[cur][i][j], acc[i][t], 0, 0, 0);
+    };
+    for (int block = w; block < blocks; block += 8) {
+        step(block, 0);
+        step(block + 4, 1);                          // (zeros where there is none)
     }
+    // acc[i][t][r]: row m0 + 16 i + n of C, column n0 + 16 t + 4 q + r
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < M && n < N) C[(size_t)m * ldc + n] = acc[i][j];
+        for (int t = 0; t < TN; ++t) part[w][i * TN + t][lane] = acc[i][t];
+    __syncthreads();
+    const bool whole = (ldc & 3) == 0 && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
+#pragma unroll
+    for (int o = 0; o < TM * TN / 4; ++o) {
+        const int t = o * 4 + w;
+        const f32x4 sum = (part[0][t][lane] + part[1][t][lane]) + (part[2][t][lane] + part[3][t][lane]);
+        const int m = m0 + t / TN * 16 + n, c = n0 + t % TN * 16 + 4 * q;
+        if (m < M) {
+            float* dst = C + (size_t)m * ldc + c;
+            if (whole) {
+                if (c < N) *reinterpret_cast<f32x4*>(dst) = sum;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (c + r < N) dst[r] = sum[r];
+            }
         }
+    }
+}
+
+template <int TM, int TN>
+void launch_gemm_f32(const float* A, int lda, const float* W, int ldw, float* C, int ldc, int M, int N, int K, hipStream_t stream) {
+    const int tm = (M + TM * 16 - 1) / (TM * 16), tn = (N + TN * 16 - 1) / (TN * 16);
+    const bool vec = ((K | lda | ldw) & 3) == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W)) & 15) == 0;
+    auto kern = vec ? gemm_f32_nt_kernel<TM, TN, true> : gemm_f32_nt_kernel<TM, TN, false>;
+    kern<<<dim3(tm * tn), dim3(256), 0, stream>>>(A, lda, W, ldw, C, ldc, M, N, K, tn);
 }
 
 }  // namespace
@@ -355,9 +416,9 @@ hipError_t launch_gemm_nt(int dtype, const void* A, int lda, const void* W, int 
                 (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C, ldc, M, N, K, tn);
         }
     } else {
-        const int tm = (M + 63) / 64, tn = (N + 63) / 64;
-        gemm_f32_nt_kernel<<<dim3(tm * tn), dim3(256), 0, stream>>>(
-            (const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, tn);
+        const size_t large = (size_t)((M + 63) / 64) * ((N + 63) / 64);
+        if (large >= 512) launch_gemm_f32<4, 4>((const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, stream);
+        else launch_gemm_f32<2, 2>((const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, stream);
     }
     return hipGetLastError();
 }

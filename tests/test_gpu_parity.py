@@ -297,6 +297,34 @@ def test_input_projection(gpu, oracle):
         model.close()
 
 
+@pytest.mark.parametrize("rows,I,H,D,shift", [(1, 4, 32, 1, 0), (33, 7, 32, 1, 0), (70, 20, 64, 2, 0), (100, 720, 128, 1, 0), (31, 129, 64, 1, 0),
+                                              (200, 64, 128, 1, 1), (4100, 68, 512, 1, 0), (2049, 513, 512, 2, 0)])
+def test_fp32_input_projection(gpu, rows, I, H, D, shift):
+    """The fp32 projection at the edges of its tiles and K blocks, with rows that are no whole chunks, an x off by one value (loads
+    of one value each), and both tiles; against 64 bits, no further off than K roundings of the sum of the absolute products."""
+    import torch
+    harness, rnn, W = gpu
+    cfg = W.Config("proj32", 0, L=1, D=D, I=I, H=H, T=rows, B=1, dtype=0, seed=W.BASE_SEED + 58 + I)
+    wl = W.make_workload(cfg)
+    model = harness.DeviceModel(wl)
+    x = wl.x.reshape(rows, I).astype(np.float32)
+    buf = torch.zeros(rows * I + 4, device="cuda")
+    xd = buf[shift:shift + rows * I]
+    xd.copy_(torch.from_numpy(x.reshape(-1)))
+    gx = torch.full((rows, D, H, 4), 9.0, device="cuda")
+    print("\n  case %r" % ((rows, I, H, D, shift),), flush=True)
+    assert rnn.rnn_input_projection(model.handle, 0, xd, gx, rows, torch.cuda.current_stream()) == 0
+    torch.cuda.synchronize()
+    got = gx.cpu().numpy().astype(np.float64)
+    for d in range(D):
+        w = np.asarray(wl.weight(0, d, 0), dtype=np.float64).reshape(4, H, I)
+        for g in range(4):
+            exact = x.astype(np.float64) @ w[g].T
+            bound = (I + 8) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(w[g]).T) + 1e-30
+            assert np.all(np.abs(got[:, d, :, g] - exact) <= bound)
+    model.close()
+
+
 def test_input_projection_at_full_size(gpu, oracle):
     """The projection of one layer of the headline workload over all its time steps (131072 x 1024 times
     1024 x 4096): the shape the large-tile kernel with the XCD-blocked tile order is made for.  The oracle computes
