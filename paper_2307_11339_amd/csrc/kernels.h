@@ -125,9 +125,6 @@ hipError_t launch_to_blocked(int dtype, const void* src, void* dst, int T, int B
 // ---- persistent wavefront kernel, tag-in-data variant for CT == 1 (wavefront_ll.hip) --------
 hipError_t launch_wavefront_ll(const WavefrontArgs& a, hipStream_t stream);
 bool wavefront_ll_variant_exists(int dtype, int RT, int H);
-// Write slot 0 of the tagged state sequences (h0, tagged with `epoch`).
-hipError_t launch_wavefront_ll_init(int dtype, const float* h0, int l0, int LP, int D, int T, int B,
-                                    int H, uint64_t* lseq, uint32_t epoch, hipStream_t stream);
 // 8-byte words needed for `groups` (layer, direction) state sequences.
 size_t wavefront_ll_words(int dtype, int groups, int T, int B, int H);
 

@@ -709,13 +709,9 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
         HIP_TRY(launch_fill_zero(m->ws.flags.p, m->ws.flags.bytes, st));
         m->epoch = 1;
     }
-    if (tagged) {
-        HIP_TRY(launch_wavefront_ll_init(m->dtype, h0, l0, LP, m->D, T, B, m->H,
-                                         (uint64_t*)m->ws.lseq.p, m->epoch, st));
-    } else {
+    if (!tagged)
         HIP_TRY(launch_wavefront_init(m->dtype, h0, l0, LP, m->D, T, B, (int)blocked_rows(B), m->H,
                                       state_region(m, plan, l0, T, B), st));
-    }
     WavefrontArgs a;
     memset(&a, 0, sizeof(a));
     a.cell = m->cell; a.dtype = m->dtype;

@@ -22,9 +22,10 @@
 // above is inactive as well and ignores its input.
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
-// Layers that fit one XCD, or two, run in wavefront_xcd.hip instead where that is faster (choose_xcd, choose_xcd_wide).  On 256
-// compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, wider ones, fp32 layers of 32 units, one
-// sequence of 512 fp32 units and a few batches of 384 units; its other variants serve devices with fewer compute units to an XCD.
+// wavefront_xcd.hip takes the layers that fit one XCD, two, or all, where that is faster (choose_xcd, choose_xcd_wide,
+// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, fp32 layers of
+// 32 units, one sequence of 512 fp32 units and workspaces in the static array that hold no chunks; its other variants serve devices
+// with fewer compute units to an XCD.
 #include "wf_traits.h"
 
 // The variants of this kernel are compiled in three translation units so that the build runs in
@@ -381,6 +382,21 @@ __global__ __launch_bounds__((XWO & 7) ? 512 : 256) void wavefront_ll_kernel(Wav
     const uint32_t slot_bytes = (uint32_t)B * row_bytes;
     bool aborted = false;
 
+    // Slot 0: this workgroup's share of h0, rounded to the storage type; the others find it while their weights travel.  (A launch of
+    // its own for it costs a one-step call of 4 layers of 1024 units 2 us of 21.)
+    {
+        constexpr int UPW = KW / TR::WORDS_PER_KW;   // units in a word
+        constexpr int NW = RT * 4 / UPW;             // this workgroup's words of a sequence
+        for (int i = tid; i < ncol * NW; i += (int)blockDim.x) {
+            const int ci = i / NW, wd = rb * NW + (i - ci * NW);
+            const float* src = p.h0 ? p.h0 + ((size_t)(l * p.D + d) * B + cb * 16 + ci) * H + (size_t)wd * UPW : nullptr;
+            uint32_t payload;
+            if constexpr (UPW == 2) payload = src ? (uint32_t)f32_to_bf16(src[0]) | ((uint32_t)f32_to_bf16(src[1]) << 16) : 0u;
+            else payload = __float_as_uint(src ? src[0] : 0.0f);
+            st_dev_u64(lseq + (size_t)(cb * 16 + ci) * row_words + wd, ((uint64_t)epoch << 32) | payload);
+        }
+    }
+
     if (xwave) {
         // ---- input product of the next step (fused layers); the x waves of the first layer of the
         // launch only keep the barriers company ----
@@ -610,28 +626,6 @@ __global__ __launch_bounds__((XWO & 7) ? 512 : 256) void wavefront_ll_kernel(Wav
     }
 }
 
-// slot 0 of every state sequence of the launch = h0 (rounded to the storage type), tagged
-template <int DT>
-__global__ void wavefront_ll_init_kernel(const float* h0, int l0, int LP, int D, int T, int B, int H,
-                                         uint64_t* lseq, uint32_t epoch) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // one tagged word each
-    const int row_words = (DT == DT_BF16) ? H / 2 : H;
-    const size_t per = (size_t)B * row_words;
-    const size_t n = (size_t)LP * D * per;
-    if (i >= n) return;
-    const size_t g = i / per, rem = i - g * per;
-    const size_t b = rem / row_words, wd = rem - b * row_words;
-    const float* src = h0 ? h0 + (((size_t)l0 * D + g) * B + b) * H : nullptr;
-    uint32_t payload;
-    if (DT == DT_BF16) {
-        const float a = src ? src[2 * wd] : 0.0f, c = src ? src[2 * wd + 1] : 0.0f;
-        payload = (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(c) << 16);
-    } else {
-        payload = __float_as_uint(src ? src[wd] : 0.0f);
-    }
-    lseq[g * (size_t)(T + 1) * per + rem] = ((uint64_t)epoch << 32) | payload;
-}
-
 template <class TR, int CELL, int RT, int KB, int XWO>
 hipError_t launch_ll_variant(const WavefrontArgs& a, hipStream_t stream) {
     constexpr int XW = XWO & 7;
@@ -794,17 +788,6 @@ hipError_t launch_wavefront_ll(const WavefrontArgs& a, hipStream_t stream) {
     RNN_LL_VARIANTS_2(X)
 #undef X
     return hipErrorInvalidValue;
-}
-
-hipError_t launch_wavefront_ll_init(int dtype, const float* h0, int l0, int LP, int D, int T, int B,
-                                    int H, uint64_t* lseq, uint32_t epoch, hipStream_t stream) {
-    const size_t n = (size_t)LP * D * B * (dtype == DT_BF16 ? H / 2 : H);
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    if (dtype == DT_BF16)
-        wavefront_ll_init_kernel<DT_BF16><<<blocks, 256, 0, stream>>>(h0, l0, LP, D, T, B, H, lseq, epoch);
-    else
-        wavefront_ll_init_kernel<DT_F32><<<blocks, 256, 0, stream>>>(h0, l0, LP, D, T, B, H, lseq, epoch);
-    return hipGetLastError();
 }
 
 size_t wavefront_ll_words(int dtype, int groups, int T, int B, int H) {
