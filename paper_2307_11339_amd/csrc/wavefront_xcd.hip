@@ -378,9 +378,12 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // groups or more: 51 us with the wait, 45 without; with layers above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
         // (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that is long.
         // With the reset gate first, r * h goes round the group behind the barrier: a first layer whose input is wider than its
-        // state asks before the barrier and multiplies in the step itself (1 layer of 512 units on 848 values, 33 sequences, 20
-        // steps: 54.7 us, 58.4 the other way).
-        constexpr bool LATE = RB && XLN > LN;
+        // state, by more than four chunks a wave, asks before the barrier and multiplies in the step itself (1 layer of 512 units
+        // on 848 values, 33 sequences, 20 steps: 54.7 us, 58.4 the other way).  Up to four chunks the product is short and better
+        // done ahead (48 steps, late -> ahead: 2 layers of 64 to 256 units on 136 to 504 values, one sequence, 10 to 15 % shorter,
+        // 16 sequences 0 to 12 %; 1 layer 1 to 4 %, but 2 % longer at 256 units, 40 sequences; fp32, on 136 and 224 values, 2 layers,
+        // one sequence 8 to 15 % shorter, 16 sequences 3 to 5 % longer).
+        constexpr bool LATE = RB && XLN > LN && XLN > 4;
         const int lead = fused ? p.lead : LATE ? 0 : 1;
         constexpr int PRODUCT = XLN * MPL * RT * TR::MMA_CLOCKS;
         constexpr bool OUT_FIRST = PRODUCT > 512;

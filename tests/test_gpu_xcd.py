@@ -37,6 +37,10 @@ SHAPES = [
     (0, 2, 2, 300, 300, 4, 65, 0),      # the same padded, both directions, two launches
     (0, 1, 1, 20, 512, 4, 150, 0),      # passes of 128 and 22 behind one projection (input narrower than an eighth of the layer)
     (0, 2, 2, 520, 512, 3, 70, 0),      # ... (wider than the x waves hold), both directions; the second layer projects by itself
+    (1, 2, 1, 504, 64, 7, 5, 1),        # inputs of four chunks a wave (with the reset gate before the product a step ahead still)
+    (1, 2, 1, 520, 128, 8, 18, 1),      # ... of more (then in the step itself)
+    (1, 2, 1, 248, 64, 7, 9, 0),        # the same line in fp32
+    (1, 1, 1, 260, 128, 5, 40, 0),
     (1, 1, 1, 40, 512, 4, 150, 1),      # one pass of another kernel; with the reset gate before the product, as above
     (0, 4, 1, 1024, 1024, 1, 5, 1),     # groups on two XCDs: one step, the whole chip
     (0, 4, 1, 1024, 1024, 11, 12, 1),   # chunk rows wider than the batch
