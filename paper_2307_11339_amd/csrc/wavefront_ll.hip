@@ -23,9 +23,9 @@
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
 // wavefront_xcd.hip takes the layers that fit one XCD, two, or all, where that is faster (choose_xcd, choose_xcd_wide,
-// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, wider ones in both
-// directions, fp32 layers of 32 units, one sequence of 512 fp32 units and workspaces in the static array that hold no chunks; its other variants serve devices
-// with fewer compute units to an XCD.
+// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, wider ones in
+// both directions, fp32 layers of 32 units, one sequence of 512 fp32 units and workspaces in the static array that hold no chunks;
+// its other variants serve devices with fewer compute units to an XCD.
 #include "wf_traits.h"
 
 // The variants of this kernel are compiled in three translation units so that the build runs in

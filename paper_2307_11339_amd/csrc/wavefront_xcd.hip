@@ -17,7 +17,7 @@
 // the rule that chooses it; 16 sequences through one layer of 1024 units take 2.6 us a step instead of 4.
 // Layers of 1280 to 2048 units are laid over all eight, 8 units a workgroup (160 to 256 of them, one layer in a launch): every
 // workgroup brings in the whole state, 16 sequences x 3 KiB at 1536 units, 9.4 MiB a step over the chip at about 6 TB/s from the
-// infinity cache, and a step takes 2.4 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
+// infinity cache, and a step takes 2.2 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
 // halves, one after the other: its fragments do not all fit the registers beside the weights (2.9 us).
 //
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
@@ -374,9 +374,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
         // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: 1078 clocks of
         // gates instead of 860).  A product of a few instructions, or of an input wider than the state, which would come too late,
-        // does not wait in a launch of one layer (128 units, 48 steps, 16
-        // groups or more: 51 us with the wait, 45 without; with layers above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few steps take lead = 0 there
-        // (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that is long.
+        // does not wait in a launch of one layer (128 units, 48 steps, 16 groups or more: 51 us with the wait, 45 without; with layers
+        // above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few
+        // steps take lead = 0 there (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that
+        // is long.
         // With the reset gate first, r * h goes round the group behind the barrier: a first layer whose input is wider than its
         // state, by more than four chunks a wave, asks before the barrier and multiplies in the step itself (1 layer of 512 units
         // on 848 values, 33 sequences, 20 steps: 54.7 us, 58.4 the other way).  Up to four chunks the product is short and better
