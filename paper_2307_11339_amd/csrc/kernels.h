@@ -141,7 +141,7 @@ struct WavefrontXcdArgs {
     int ring;                    // slots of a state sequence: a power of two >= 2 * XCD_AHEAD, or more than T (every step its own)
     int ext, reset_before;
     int device_scope;            // 1: exchange through memory wherever the workgroups run
-    int lead0, lead;                    // steps a layer above the first of the launch computes its input product ahead of the one it is in, 0 or 1
+    int lead;                    // steps a layer above the first of the launch computes its input product ahead of the one it is in, 0 or 1
     int in_place;                // an output may overwrite h0 before the exchange has ordered its reads
     const void* whh[WF_MAX_LAYERS * 2];   // packed W_hh per (local layer, direction): [4H, H]
     const void* wih[WF_MAX_LAYERS * 2];   // packed W_ih per local layer (all directions): [D * 4H, width]
