@@ -606,9 +606,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     for (int s = 0; s < T; ++s) {
         const int t = d ? T - 1 - s : s;
         // The recurrent product starts from the input part.  Not so in fp32, where one chain of sums as long as both products loses
-        // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7; in bf16 the rounding of the stored
-        // state hides it): there the wave that finishes a tile sums the tile's input part, and the bias, for itself meanwhile.
-        constexpr bool APART = MPL > 1;
+        // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7), nor in layers of more than 1024 units,
+        // whose chains are the longest (cT after one step, 1536 units on 1536 values 1.92e-7 against 1.35e-7, 2048 on 2048 2.17e-7
+        // against 1.45e-7; tagged words 1.37e-7 and 1.46e-7, and no time lost: 64 steps of 2 such layers 0 to 2 % shorter): there the
+        // wave that finishes a tile sums the tile's input part, and the bias, for itself meanwhile.
+        constexpr bool APART = MPL > 1 || LN > 8;
         f32x4 acc[RT], from_x;
         if constexpr (APART) from_x = bias_reg[0];
         auto input_part = [&]() {                    // (every x wave takes every step, whatever became of its waits)
