@@ -10,7 +10,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librnn_mi355x.so")
-SOURCES = ["wavefront_xcd_i.hip", "wavefront_xcd_j.hip", "wavefront_xcd_g.hip", "wavefront_xcd_h.hip", "wavefront_xcd_d.hip", "wavefront_xcd_e.hip", "wavefront_xcd.hip", "wavefront_xcd_b.hip", "wavefront_xcd_f.hip", "wavefront_xcd_c.hip",
+SOURCES = ["wavefront_xcd_i.hip", "wavefront_xcd_j.hip", "wavefront_xcd_g.hip", "wavefront_xcd_h.hip", "wavefront_xcd_d.hip", "wavefront_xcd_e.hip", "wavefront_xcd.hip", "wavefront_xcd_b.hip",
+           "wavefront_xcd_k.hip", "wavefront_xcd_l.hip", "wavefront_xcd_f.hip", "wavefront_xcd_c.hip",
            "wavefront_ll.hip", "wavefront_ll_b.hip", "wavefront_ll_c.hip", "wavefront_ll_d.hip", "wavefront_ll_e.hip",
            "wavefront_ll_f.hip", "wavefront_x.hip", "wavefront_x_b.hip", "wavefront.hip", "wavefront_b.hip",
            "rnn_api.hip", "gemm.hip", "cellwise.hip", "schedule.hip", "probe.hip", "rnn_stack.hip"]   # the slowest first
@@ -39,7 +40,7 @@ NO_SPILL = {"wavefront_x.hip": ("wavefront_x_kernel", "ELi2ELb"),     # file: (k
             "gemm.hip": ("gemm_bf16_nt_wide_kernel", "")}               # 256 accumulation + 244 vector registers of 512
 # The variants of the XCD-resident kernel hold up to 128 registers of weights a wave (250 of 256 in use): a spill there goes
 # through memory in every step (2 bf16 layers of 512 units, both directions: 659 -> 5197 us).
-NO_SPILL.update({"wavefront_xcd%s.hip" % part: ("wavefront_xcd_kernel", "") for part in ("", "_b", "_c", "_d", "_e", "_f", "_g", "_h", "_i", "_j")})
+NO_SPILL.update({"wavefront_xcd%s.hip" % part: ("wavefront_xcd_kernel", "") for part in ("", "_b", "_c", "_d", "_e", "_f", "_g", "_h", "_i", "_j", "_k", "_l")})
 
 
 def _check_no_spill(src: str, remarks: str) -> None:

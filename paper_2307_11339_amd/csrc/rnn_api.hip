@@ -32,6 +32,7 @@ struct Plan {
     // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with its groups of workgroups on an XCD each, or on a pair (span = 2)
     bool xcd = false;
     int span = 1, stride = 0;
+    bool apart = false;             // its variant that sums the two products apart, as the kernels do that its passes take a batch over from
     int LP_asked = 1;               // LP before a compact workspace lowered it (rnn_forward_static decides as rnn_forward does)
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
@@ -496,7 +497,10 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
         // against a well filled launch (512 units, 512 sequences 431 -> 481; both directions, 384 units, 260 sequences 518 -> 570).
         Plan passes;
         if (!plan.xcd && may_chunk && m->H <= 512 && choose_passes(m, T, B, passes, choose_xcd) &&
-            1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B)) plan = passes;
+            1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B)) {
+            plan = passes;
+            plan.apart = true;
+        }
         return RNN_OK;
     }
     if (m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
@@ -509,6 +513,7 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
 // a bf16 block of few sequences over two XCDs), it keeps the plan of the full passes, laid out for its own sequences.
 int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last) {
     const int rc = resolve_plan(m, T, B, last, false);
+    last.apart = plan.apart;
     if (rc != RNN_OK || !plan.xcd || last.xcd) return rc;
     last = plan;
     last.chunk = 0;
@@ -1009,6 +1014,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.ring = xcd_ring(m, T);
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
+        a.apart = plan.apart ? 1 : 0;
         a.in_place = in_place ? 1 : 0;
         // Input products a step ahead make a step 3 to 5 % shorter and every layer above the first a step later (us, 0 -> 1: 2 fp32
         // layers of 512 units, 128 steps 664 -> 635; 2 GRU layers of 512, 100 steps 115 -> 111; 12 fp32 layers of 64, 96 steps 105 -> 112).

@@ -51,11 +51,15 @@
 //   RNN_XR_DT    0 = bf16, 1 = fp32
 //   RNN_XR_KIND  0 = LSTM and GRU with the plain cell, 1 = with the peephole and clipping terms, 2 = the GRU that applies the
 //                reset gate before the candidate's recurrent product (always with the clipping term)
+//   RNN_XR_APART (bf16, groups on an XCD each) 1 = the sums of the two products apart (see there)
 #ifndef RNN_XR_DT
 #define RNN_XR_DT 0
 #endif
 #ifndef RNN_XR_KIND
 #define RNN_XR_KIND 0
+#endif
+#ifndef RNN_XR_APART
+#define RNN_XR_APART 0
 #endif
 
 namespace rnn {
@@ -148,7 +152,7 @@ __device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t by
 // LN / XLN: 16-byte chunks a lane loads per wave of the state / of the layer input (a wave's quarter of H is 4 * EPC * LN
 // units; K blocks of the input are dealt to the waves in turn, and those beyond its width get zero weights).  The first layer
 // of a launch may have its input product done by a projection launch (p.gx): its x waves then only bring that in.
-template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT, bool APART>
 __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) {
     constexpr bool RB = CELL == CELL_GRU_RB;
     constexpr int GATES = RB ? CELL_GRU : CELL;
@@ -608,9 +612,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // The recurrent product starts from the input part.  Not so in fp32, where one chain of sums as long as both products loses
         // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7), nor in layers of more than 1024 units,
         // whose chains are the longest (cT after one step, 1536 units on 1536 values 1.92e-7 against 1.35e-7, 2048 on 2048 2.17e-7
-        // against 1.45e-7; tagged words 1.37e-7 and 1.46e-7, and no time lost: 64 steps of 2 such layers 0 to 2 % shorter): there the
-        // wave that finishes a tile sums the tile's input part, and the bias, for itself meanwhile.
-        constexpr bool APART = MPL > 1 || LN > 8;
+        // against 1.45e-7; tagged words 1.37e-7 and 1.46e-7, and no time lost: 64 steps of 2 such layers 0 to 2 % shorter), nor in
+        // passes that take a batch over from launches of larger tiles, which sum apart as well (p.apart; both directions of 512 units,
+        // 72 sequences: larger tiles 1.29e-7, one chain 1.35e-7, apart 1.13e-7; 256 units, 136 sequences 1.14e-7, 1.18e-7, 1.08e-7.
+        // Everywhere up to 512 units it would make calls 0 to 4 % longer): there (APART) the wave that finishes a tile sums the tile's
+        // input part, and the bias, for itself meanwhile.
         f32x4 acc[RT], from_x;
         if constexpr (APART) from_x = bias_reg[0];
         auto input_part = [&]() {                    // (every x wave takes every step, whatever became of its waits)
@@ -733,12 +739,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 // Forces one workgroup per compute unit: more than half of the 160 KiB.
 constexpr size_t MIN_LDS = 84 * 1024;
 
+constexpr bool apart(int MPL, int LN) { return MPL > 1 || LN > 8 || RNN_XR_APART; }
+
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     const size_t need = (size_t)((RT == 4 ? 6 : 8) + 8) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
                         9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16 + (LN > 12 ? (size_t)4 * 64 * (LN / 2) * 16 : 0);
     const size_t smem = need < MIN_LDS ? MIN_LDS : need;
-    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT>;
+    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT, apart(TR::MPL, LN)>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -815,20 +823,22 @@ hipError_t launch_here(const WavefrontXcdArgs& a, hipStream_t stream, int LN) {
 
 }  // namespace
 
-#define RNN_XR_FN2(dt, kind, wide) launch_wavefront_xcd_dt##dt##_kind##kind##_wide##wide
-#define RNN_XR_FN(dt, kind, wide) RNN_XR_FN2(dt, kind, wide)
-hipError_t RNN_XR_FN(RNN_XR_DT, RNN_XR_KIND, RNN_XR_WIDE)(const WavefrontXcdArgs& a, hipStream_t stream, int LN) { return launch_here(a, stream, LN); }
+#define RNN_XR_FN2(dt, kind, wide, apart) launch_wavefront_xcd_dt##dt##_kind##kind##_wide##wide##_apart##apart
+#define RNN_XR_FN(dt, kind, wide, apart) RNN_XR_FN2(dt, kind, wide, apart)
+hipError_t RNN_XR_FN(RNN_XR_DT, RNN_XR_KIND, RNN_XR_WIDE, RNN_XR_APART)(const WavefrontXcdArgs& a, hipStream_t stream, int LN) { return launch_here(a, stream, LN); }
 
-#if RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE
-hipError_t launch_wavefront_xcd_dt0_kind1_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind2_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind0_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind1_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt1_kind2_wide0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind0_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind1_wide1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind0_wide2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
-hipError_t launch_wavefront_xcd_dt0_kind1_wide2(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+#if RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE && !RNN_XR_APART
+hipError_t launch_wavefront_xcd_dt0_kind1_wide0_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind2_wide0_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind0_wide0_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind1_wide0_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt1_kind2_wide0_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind0_wide1_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind1_wide1_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind0_wide2_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind1_wide2_apart0(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind0_wide0_apart1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
+hipError_t launch_wavefront_xcd_dt0_kind1_wide0_apart1(const WavefrontXcdArgs& a, hipStream_t stream, int LN);
 
 namespace {
 int state_chunks(int dtype, int H) {             // LN, or 0 when H is no multiple of a wave's load
@@ -896,18 +906,20 @@ hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     if (a.reset_before && a.cell != CELL_GRU) return hipErrorInvalidValue;
     if (a.span == 2) {
         if (!wavefront_xcd_wide_exists(a.dtype, a.RT, a.H, a.reset_before != 0)) return hipErrorInvalidValue;
-        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide1(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide1(a, stream, LN);
+        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide1_apart0(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide1_apart0(a, stream, LN);
     }
     if (a.span == 8) {
         if (!wavefront_xcd_chip_exists(a.dtype, a.RT, a.H, a.reset_before != 0)) return hipErrorInvalidValue;
-        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide2(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide2(a, stream, LN);
+        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide2_apart0(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide2_apart0(a, stream, LN);
     }
+    if (a.dtype == DT_BF16 && a.apart && kind < 2)
+        return kind == 0 ? launch_wavefront_xcd_dt0_kind0_wide0_apart1(a, stream, LN) : launch_wavefront_xcd_dt0_kind1_wide0_apart1(a, stream, LN);
     if (a.dtype == DT_BF16)
-        return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1_wide0(a, stream, LN)
-                                                                  : launch_wavefront_xcd_dt0_kind2_wide0(a, stream, LN);
-    return kind == 0 ? launch_wavefront_xcd_dt1_kind0_wide0(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt1_kind1_wide0(a, stream, LN)
-                                                                                       : launch_wavefront_xcd_dt1_kind2_wide0(a, stream, LN);
+        return kind == 0 ? launch_here(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt0_kind1_wide0_apart0(a, stream, LN)
+                                                                  : launch_wavefront_xcd_dt0_kind2_wide0_apart0(a, stream, LN);
+    return kind == 0 ? launch_wavefront_xcd_dt1_kind0_wide0_apart0(a, stream, LN) : kind == 1 ? launch_wavefront_xcd_dt1_kind1_wide0_apart0(a, stream, LN)
+                                                                                       : launch_wavefront_xcd_dt1_kind2_wide0_apart0(a, stream, LN);
 }
-#endif  // RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE
+#endif  // RNN_XR_DT == 0 && RNN_XR_KIND == 0 && !RNN_XR_WIDE && !RNN_XR_APART
 
 }  // namespace rnn
