@@ -279,16 +279,19 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_nt_wide_kernel(const bf16_t*
 }
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;   // (a load of 16 bytes needs no more than whole words)
 
 // fp32: a workgroup owns TM x TN tiles of 16 x 16, its four waves split K (blocks of 16, in turn) and add up through LDS.  What
 // bounds the small calls (the projection in front of a launch, a product of the cellwise plan) is a wave's chain of loads and
 // products, so K is split and the tile is small (TM = TN = 2: 32 x 32) until there are two workgroups of the larger tile (64 x 64, half
 // the operand traffic) per compute unit.  Fragments come straight from the rows: matrix instruction j of a K block takes k = 4 *
-// (lane / 16) + j, so 16 bytes a lane are the operands of four, and the next block's travel behind them.  Every element is
-// summed in the same order whatever the tile.  Measured (M x N x K, with 64 x 64 tiles of vector instructions -> this):
-//     104 x 512 x 720 102 -> 9.7 us    444 x 256 x 744 107 -> 10.0    1952 x 4096 x 1024 374 -> 190
-// VEC: 16-byte aligned rows of a multiple of 4 values; otherwise the values are loaded one by one.
-template <int TM, int TN, bool VEC>
+// (lane / 16) + j, so 16 bytes a lane are the operands of four, and the next block's travel behind them.  A load of 16 bytes needs no
+// more than whole words, so rows may lie anywhere; values behind the last whole block are loaded one by one, by the wave whose
+// turn it is, ahead of everything else.  Every element is summed in the same order whatever the tile.  Measured (M x N x K, us,
+// with 64 x 64 tiles of vector instructions, with rows off 16 bytes and their remainder loaded one value at a time -> this):
+//     104 x 512 x 723       103, 17.8 -> 6.6      32000 x 512 x 67       69, 101 -> 50     32000 x 2048 x 1023    2557, 2614 -> 1330
+//     1952 x 2048 x 1024    209, 90.5 -> 87       100000 x 512 x 64, x off by a word    162, 523 -> 112 (on 16 bytes 154, 187 -> 112)
+template <int TM, int TN>
 __global__ __launch_bounds__(256) void gemm_f32_nt_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
                                                           float* __restrict__ C, int ldc, int M, int N, int K, int tiles_n) {
     __shared__ f32x4 part[4][TM * TN][64];
@@ -304,48 +307,64 @@ __global__ __launch_bounds__(256) void gemm_f32_nt_kernel(const float* __restric
     for (int i = 0; i < TM; ++i) ap[i] = A + (size_t)min(m0 + i * 16 + n, M - 1) * lda;   // rows beyond are not stored
 #pragma unroll
     for (int i = 0; i < TN; ++i) wp[i] = W + (size_t)min(n0 + i * 16 + n, N - 1) * ldw;
-    const int blocks = (K + 15) / 16;
-    auto load = [&](int block, f32x4 (&a)[TM], f32x4 (&v)[TN]) {      // beyond K: zeros
-        const int k = block * 16 + 4 * q;
-        auto chunk = [&](const float* row) -> f32x4 {
-            f32x4 r;
-            if constexpr (VEC) {
-                r = *reinterpret_cast<const f32x4*>(row + (k < K ? k : 0));
-                if (k >= K) r = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float x = row[k + j < K ? k + j : 0];
-                    r[j] = k + j < K ? x : 0.0f;
-                }
-            }
-            return r;
-        };
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[i] = chunk(ap[i]);
-#pragma unroll
-        for (int i = 0; i < TN; ++i) v[i] = chunk(wp[i]);
-    };
+    const int full = K / 16, mine = (full - w + 3) / 4;               // whole blocks, and this wave's
+    const bool tail = full * 16 < K && w == (full & 3);
     f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int t = 0; t < TN; ++t) acc[i][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 a[2][TM], v[2][TN];
-    load(w, a[0], v[0]);
-    auto step = [&](int block, int cur) {
-        load(block + 4, a[cur ^ 1], v[cur ^ 1]);     // (the last one loads zeros)
+    f32x4 ta[TM], tv[TN];
+    if (tail) {
+        auto chunk = [&](const float* row) -> f32x4 {
+            f32x4 r;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = row[min(full * 16 + 4 * q + j, K - 1)];
+            return r;
+        };
+#pragma unroll
+        for (int i = 0; i < TM; ++i) ta[i] = chunk(ap[i]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) tv[i] = chunk(wp[i]);
+    }
+    auto load = [&](int block, f32x4 (&a)[TM], f32x4 (&v)[TN]) {
+        const int k = min(block, full - 1) * 16 + 4 * q;              // (behind the last one nobody multiplies)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4_any*>(ap[i] + k);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) v[i] = *reinterpret_cast<const f32x4_any*>(wp[i] + k);
+    };
+    auto multiply = [&](const f32x4 (&a)[TM], const f32x4 (&v)[TN]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int t = 0; t < TN; ++t)
-                    acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[cur][t][j], a[cur][i][j], acc[i][t], 0, 0, 0);
+                for (int t = 0; t < TN; ++t) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[t][j], a[i][j], acc[i][t], 0, 0, 0);
     };
-    for (int block = w; block < blocks; block += 8) {
-        step(block, 0);
-        step(block + 4, 1);                          // (zeros where there is none)
+    if (mine > 0) {
+        f32x4 a[2][TM], v[2][TN];
+        load(w, a[0], v[0]);
+        int block = w;
+        for (int pair = mine >> 1; pair > 0; --pair, block += 8) {
+            load(block + 4, a[1], v[1]);
+            multiply(a[0], v[0]);
+            load(block + 8, a[0], v[0]);
+            multiply(a[1], v[1]);
+        }
+        if (mine & 1) multiply(a[0], v[0]);
+    }
+    if (tail) {
+        auto end = [&](f32x4& r) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (full * 16 + 4 * q + j >= K) r[j] = 0.0f;
+        };
+#pragma unroll
+        for (int i = 0; i < TM; ++i) end(ta[i]);
+#pragma unroll
+        for (int i = 0; i < TN; ++i) end(tv[i]);
+        multiply(ta, tv);
     }
     // acc[i][t][r]: row m0 + 16 i + n of C, column n0 + 16 t + 4 q + r
 #pragma unroll
@@ -375,9 +394,7 @@ __global__ __launch_bounds__(256) void gemm_f32_nt_kernel(const float* __restric
 template <int TM, int TN>
 void launch_gemm_f32(const float* A, int lda, const float* W, int ldw, float* C, int ldc, int M, int N, int K, hipStream_t stream) {
     const int tm = (M + TM * 16 - 1) / (TM * 16), tn = (N + TN * 16 - 1) / (TN * 16);
-    const bool vec = ((K | lda | ldw) & 3) == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W)) & 15) == 0;
-    auto kern = vec ? gemm_f32_nt_kernel<TM, TN, true> : gemm_f32_nt_kernel<TM, TN, false>;
-    kern<<<dim3(tm * tn), dim3(256), 0, stream>>>(A, lda, W, ldw, C, ldc, M, N, K, tn);
+    gemm_f32_nt_kernel<TM, TN><<<dim3(tm * tn), dim3(256), 0, stream>>>(A, lda, W, ldw, C, ldc, M, N, K, tn);
 }
 
 }  // namespace
@@ -416,8 +433,10 @@ hipError_t launch_gemm_nt(int dtype, const void* A, int lda, const void* W, int 
                 (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C, ldc, M, N, K, tn);
         }
     } else {
+        // (short rows are bound by what they store, and the small tile hides that better: 32000 x 512, 64 x 64 -> 32 x 32 tiles, 16 values
+        // 29.4 -> 24.6 us, 48 values 36.1 -> 33.3, 80 values 55.8 -> 44.5, 96 values 57.1 -> 61.0)
         const size_t large = (size_t)((M + 63) / 64) * ((N + 63) / 64);
-        if (large >= 512) launch_gemm_f32<4, 4>((const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, stream);
+        if (large >= 512 && K > 80) launch_gemm_f32<4, 4>((const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, stream);
         else launch_gemm_f32<2, 2>((const float*)A, lda, (const float*)W, ldw, C, ldc, M, N, K, stream);
     }
     return hipGetLastError();

@@ -298,10 +298,11 @@ def test_input_projection(gpu, oracle):
 
 
 @pytest.mark.parametrize("rows,I,H,D,shift", [(1, 4, 32, 1, 0), (33, 7, 32, 1, 0), (70, 20, 64, 2, 0), (100, 720, 128, 1, 0), (31, 129, 64, 1, 0),
-                                              (200, 64, 128, 1, 1), (4100, 68, 512, 1, 0), (2049, 513, 512, 2, 0)])
+                                              (200, 64, 128, 1, 1), (4100, 68, 512, 1, 0), (2049, 513, 512, 2, 0), (5, 1, 32, 1, 3), (40, 3, 32, 1, 1),
+                                              (65, 17, 64, 1, 2), (33, 48, 32, 1, 3), (2049, 83, 512, 2, 1), (2049, 96, 512, 2, 2)])
 def test_fp32_input_projection(gpu, rows, I, H, D, shift):
-    """The fp32 projection at the edges of its tiles and K blocks, with rows that are no whole chunks, an x off by one value (loads
-    of one value each), and both tiles; against 64 bits, no further off than K roundings of the sum of the absolute products."""
+    """The fp32 projection at the edges of its tiles and K blocks, with rows that are no whole chunks, an x off by one to three values,
+    and both tiles; against 64 bits, no further off than K roundings of the sum of the absolute products."""
     import torch
     harness, rnn, W = gpu
     cfg = W.Config("proj32", 0, L=1, D=D, I=I, H=H, T=rows, B=1, dtype=0, seed=W.BASE_SEED + 58 + I)
