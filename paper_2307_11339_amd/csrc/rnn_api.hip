@@ -1429,7 +1429,8 @@ static void clear_arena(rnn_model* m) {
 // 75 MiB against 54).  What that plan fits runs all the same, and on rnn_forward's kernel: slots in turn, one projection a pass, and
 // layer after layer where the sequences that layers of a launch hand to each other are too long.  One case is left to the plan without
 // it: a reset-before GRU that is projected, whose blocks take up to a tenth more than the cellwise plan (4 layers of 512 bf16 units on
-// 1712 features, 286 steps of 22 sequences: 67.5 MiB against 62.2).
+// 1712 features, 286 steps of 22 sequences: 67.5 MiB against 62.2).  Layers of 1280 to 2048 units have no other persistent plan: what
+// fits on that kernel runs.
 static int fit_arena(rnn_model* m, int T, int B, Plan& plan) {
     auto fits = [&](int compact) -> int {
         m->compact = compact;
@@ -1438,10 +1439,11 @@ static int fit_arena(rnn_model* m, int T, int B, Plan& plan) {
         return rc == RNN_OK ? prepare_workspace(m, plan, T, B) : rc;
     };
     int rc = fits(0);
-    if (rc != RNN_ESCRATCH || (rc = fits(-1)) != RNN_OK) return rc;
+    const bool chip = plan.span == XCDS;
+    if (rc != RNN_ESCRATCH || (!chip && (rc = fits(-1)) != RNN_OK)) return rc;
     for (int most = WF_MAX_LAYERS; most >= 1; most /= 2)
         if ((rc = fits(most)) != RNN_ESCRATCH) return rc;
-    return fits(-1);
+    return chip ? rc : fits(-1);
 }
 
 // rnn_forward and rnn_forward_static: the second with the workspace carved from the device's static array.

@@ -23,9 +23,10 @@
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
 // wavefront_xcd.hip takes the layers that fit one XCD, two, or all, where that is faster (choose_xcd, choose_xcd_wide,
-// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, wider ones in
-// both directions, fp32 layers of 32 units, one sequence of 512 fp32 units and workspaces in the static array that hold no chunks;
-// its other variants serve devices with fewer compute units to an XCD.
+// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, fp32 layers of
+// 32 units, one sequence of 512 fp32 units, and calls of a few steps on batches of 384 units that passes of that kernel do not pay for;
+// its other variants serve devices with fewer compute units to an XCD.  Layers of more than 1024 units have none: where the 160 to 256
+// workgroups of such a layer fit the chip, wavefront_xcd.hip takes it, and both directions of one do not fit.
 #include "wf_traits.h"
 
 // The variants of this kernel are compiled in three translation units so that the build runs in
@@ -717,9 +718,7 @@ hipError_t launch_ll_cell_fused(const WavefrontArgs& a, hipStream_t stream) {
 #define RNN_LL_VARIANTS_2(X)                                                     \
     X(LLBf16, 1, 3) X(LLBf16, 2, 3) X(LLBf16, 4, 3)                               \
     X(LLBf16, 1, 5) X(LLBf16, 2, 5) X(LLBf16, 4, 5)                               \
-    X(LLBf16, 1, 6) X(LLBf16, 2, 6) X(LLBf16, 4, 6)                               \
-    X(LLBf16, 1, 10) X(LLBf16, 2, 10) X(LLBf16, 1, 12) X(LLBf16, 2, 12)           \
-    X(LLBf16, 1, 16) X(LLBf16, 2, 16)
+    X(LLBf16, 1, 6) X(LLBf16, 2, 6) X(LLBf16, 4, 6)
 #define RNN_LL_VARIANTS(X) RNN_LL_VARIANTS_0(X) RNN_LL_VARIANTS_1(X) RNN_LL_VARIANTS_2(X)
 #if RNN_LL_PART == 0
 #define RNN_LL_VARIANTS_HERE(X) RNN_LL_VARIANTS_0(X)

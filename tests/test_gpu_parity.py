@@ -71,7 +71,7 @@ SMALL = [
     ("lstm_bf16_t1", 0, 2, 1, 64, 128, 1, 2, 1, False, True),
     # small batches, several layers in one launch (fused layers have their own waves for the input product).  bf16 layers of up to 512
     # units and fp32 layers of 64 to 512 run on the XCD-resident kernel, bf16 ones of 640 to 1024 on its groups over two XCDs where
-    # B * H > 4096; below, and for one fp32 sequence of 512 units and layers beyond 1024 units, the tag-in-data kernel
+    # B * H > 4096 and layers beyond 1024 units over all eight; below, and for one fp32 sequence of 512 units, the tag-in-data kernel
     ("lstm_bf16_8layer_h256", 0, 8, 1, 48, 256, 12, 3, 1, True, True),     # XCD-resident
     ("gru_bf16_2layer_h1024_b12", 1, 2, 1, 40, 1024, 6, 12, 1, True, True),  # two XCDs, behind a projection
     ("lstm_bf16_4layer_sq_h1024_b1", 0, 4, 1, 1024, 1024, 7, 1, 1, False, True),   # tag-in-data, one load instruction per wave: the lean fetch loop
@@ -559,7 +559,7 @@ def test_length_validation(gpu):
 
 
 @pytest.mark.parametrize("name", ["lstm_bf16_8layer_h256", "lstm_bf16_inside_sq", "lstm_bf16_b299", "lstm_bf16_4layer_sq_h1024_b1",
-                                  "lstm_bf16_2layer_sq_h2048"])       # the last two: tag-in-data kernel, one and two launches
+                                  "lstm_bf16_bidir_sq_h768", "lstm_bf16_2layer_sq_h2048"])   # tag-in-data kernel, one and two launches; all XCDs
 def test_launch_tag_wraps(gpu, name):
     """The 32-bit launch tag wraps after 2^32 launches: the launch that wraps clears the flag words and the
     tagged words and starts again from tag 1.  Forced here by setting the tag just below the wrap: the
@@ -768,7 +768,8 @@ def test_gru_reset_before_product(gpu, oracle, spec):
 @pytest.mark.parametrize("name,plan", [("lstm_bf16_8layer_h256", "auto"),      # XCD-resident kernel
                                        ("gru_bf16_bidir", "auto"),               # XCD-resident kernel, two launches
                                        ("lstm_bf16_4layer_sq_h1024_b1", "auto"), # tag-in-data kernel
-                                       ("lstm_bf16_2layer_sq_h2048", "auto"),    # tag-in-data kernel, two launches
+                                       ("lstm_bf16_bidir_sq_h768", "auto"),      # tag-in-data kernel, two launches
+                                       ("lstm_bf16_2layer_sq_h2048", "auto"),    # XCD-resident kernel over all XCDs, two launches
                                        ("lstm_bf16_inside_sq", "auto"),          # inside-product kernel, one launch per layer
                                        ("lstm_bf16_sidebyside_l4", "auto"),      # inside-product kernel, layers side by side
                                        ("lstm_f32_fusedflag_l6_h32", "auto"),    # flag-vector kernel

@@ -152,6 +152,7 @@ def test_reset_gate_before_the_product(gpu, oracle, shape):
     (0, 4, 2, 12, 512, 20, 374, 0, 0, 0),       # passes that project their own sequences
     (0, 4, 2, 12, 512, 14, 374, 0, 1, 0),
     (1, 4, 1, 1712, 512, 286, 22, 1, 0, 1),     # left to the cellwise plan
+    (0, 1, 1, 1608, 1536, 110, 24, 1, 0, 0),    # on all eight XCDs, passes that project their own sequences
 ], ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s_bf%d_rb%d" % (s[:7] + ("f32" if s[7] == 0 else "bf16",) + s[8:]))
 def test_static_array_that_only_tagged_words_fit(gpu, shape):
     """Calls whose workspace with a slot for every step exceeds the static array of 64 MiB, and that fit without this kernel: the

@@ -112,7 +112,7 @@ def test_widths_covered_by_the_persistent_kernels():
         return plan["kind"]
     for H in (128, 256, 384, 512, 640, 768, 1024):          # small and large batches
         assert kind(H, 1) == rnn.RNN_PLAN_WAVEFRONT and kind(H, 300) == rnn.RNN_PLAN_WAVEFRONT, H
-    for H in (1280, 1536, 2048):                            # tag-in-data kernel only: large batches in many passes
+    for H in (1280, 1536, 2048):                            # XCD-resident kernel over all XCDs: large batches in many passes
         assert kind(H, 1) == rnn.RNN_PLAN_WAVEFRONT and kind(H, 8) == rnn.RNN_PLAN_WAVEFRONT, H
         assert kind(H, 300) == rnn.RNN_PLAN_WAVEFRONT, H
     for H in (64, 192, 896, 1152, 1800):                    # padded up to 128, 256, 1024, 1280, 2048 units
@@ -142,10 +142,10 @@ def test_batches_beyond_one_launch_run_in_passes():
     assert (plan["row_blocks"], plan["col_blocks"], plan["launches"]) == (192, 2, 1)
     rc, plan, _ = _query(wide.scaled(B=200))
     assert (plan["row_blocks"], plan["col_blocks"], plan["launches"]) == (192, 2, 4)     # 64 + 64 + 64 + 8 sequences
-    # with 16 sequences or fewer the tag-in-data kernel, one block
+    # with 16 sequences or fewer the XCD-resident kernel over all XCDs, one block (no other kernel has such a tile at this width)
     rc, plan, _ = _query(wide.scaled(B=9))
     assert (plan["row_tiles"], plan["col_tiles"], plan["chains"], plan["row_blocks"], plan["launches"]) == (2, 1, 1, 192, 1)
-    # 2048 units: no large-batch tile fits the registers; 256 workgroups of the tag-in-data kernel hold 16 sequences
+    # 2048 units: no large-batch tile fits the registers; 256 workgroups of the XCD-resident kernel hold 16 sequences
     rc, plan, _ = _query(wide.scaled(H=2048, I=2048))
     assert (plan["row_tiles"], plan["col_tiles"], plan["chains"]) == (2, 1, 1)
     assert (plan["row_blocks"], plan["col_blocks"], plan["launches"]) == (256, 1, 3)
