@@ -171,8 +171,8 @@ int rnn_model_set_validation(rnn_model* model, int on);
 /* Size the workspace now for forwards of T steps and B sequences under the current plan, so that
  * later rnn_forward calls of that shape allocate nothing.  Only what the plan chosen for (T, B)
  * touches is allocated (the paper's memory model, Section 3, Equation 4, counts exactly such
- * temporaries); a call of another shape may be given another plan and then grows the workspace
- * itself.  Buffers never shrink.  May synchronise the device. */
+ * temporaries), and where fewer steps of as many sequences are given another plan, that one's; a call of
+ * another shape may be given another plan and then grows the workspace itself.  Buffers never shrink.  May synchronise the device. */
 int rnn_model_reserve(rnn_model* model, int T, int B);
 
 /*

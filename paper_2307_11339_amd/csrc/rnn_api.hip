@@ -1409,9 +1409,15 @@ int rnn_model_set_validation(rnn_model* m, int on) {
 int rnn_model_reserve(rnn_model* m, int T, int B) {
     if (!m || T < 1 || B < 1) return RNN_EINVAL;
     Plan plan;
-    const int rc = resolve_plan(m, T, B, plan);
+    int rc = resolve_plan(m, T, B, plan);
+    if (rc == RNN_OK) rc = prepare_workspace(m, plan, T, B);
     if (rc != RNN_OK) return rc;
-    return prepare_workspace(m, plan, T, B);
+    // Shorter calls of these sequences allocate nothing either.  The one choice that depends on the steps, passes or a launch of
+    // larger tiles (call_us: both sides are linear in the steps), is made as for T steps or as for one.
+    Plan shorter;
+    rc = resolve_plan(m, 1, B, shorter);
+    if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
+    return prepare_workspace(m, shorter, T, B);
 }
 
 // The workspace as a set of empty buffers that grow() fills with pieces of the static array.

@@ -349,3 +349,44 @@ def test_bf16_sums_of_the_two_products_are_kept_apart(gpu, shape, bound):
     assert rel <= bound
     assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
     model.close()
+
+
+@pytest.mark.parametrize("shape", [(0, 2, 2, 512, 512, 48, 72, 1), (1, 1, 1, 64, 256, 64, 300, 1)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d" % s[:7])
+def test_reserved_steps_cover_fewer(gpu, shape):
+    """Passes at the reserved number of steps, a launch of larger tiles at one: after rnn_model_reserve neither call allocates, so
+    both can be recorded into a graph (which refuses to grow the workspace)."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, False)
+    c = wl.cfg
+    plans = [rnn.rnn_plan_query(c.cell, c.L, c.I, c.H, c.D, c.dtype, rnn.RNN_PLAN_AUTO, T, c.B, 256, 160 * 1024)[1] for T in (c.T, 1)]
+    assert (plans[0]["col_tiles"], plans[0]["chains"]) == (1, 1) and plans[0]["col_blocks"] * 16 < c.B <= 16 * plans[1]["col_blocks"] * plans[1]["col_tiles"]
+    print("\n  case %r" % (shape,), flush=True)
+    warm, model, io = harness.DeviceModel(wl), harness.DeviceModel(wl), harness.DeviceIO(wl)
+    for T in (1, c.T):                           # one-time set-up of the kernels
+        assert rnn.rnn_forward(warm.handle, io.x, None, None, None, io.y, None, None, T, c.B, torch.cuda.current_stream()) == rnn.RNN_OK
+    torch.cuda.synchronize()
+    warm.close()
+    assert rnn.rnn_model_reserve(model.handle, c.T, c.B) == rnn.RNN_OK
+    held = rnn.rnn_model_device_bytes(model.handle)
+    side = torch.cuda.Stream()
+    for T in (1, c.T):
+        def call(h, cc):
+            return rnn.rnn_forward(model.handle, io.x, None, io.h0, io.c0, io.y, h, cc, T, c.B, torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            assert call(io.hT, io.cT) == rnn.RNN_OK
+        want, wantc = torch.full_like(io.hT, 7.0), torch.full_like(io.cT, 7.0)
+        assert call(want, wantc) == rnn.RNN_OK
+        torch.cuda.synchronize()
+        y = io.y[:T].clone()
+        for _ in range(2):
+            io.y.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(io.y[:T], y) and torch.equal(io.hT, want) and (c.cell == 1 or torch.equal(io.cT, wantc))
+        del graph
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    assert rnn.rnn_model_device_bytes(model.handle) == held
+    model.close()
