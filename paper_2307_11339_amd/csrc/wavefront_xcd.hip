@@ -69,6 +69,7 @@ constexpr int AHEAD = XCD_AHEAD;                // steps between marking a slot 
 constexpr int AHEAD_UP = 8;                     // the same for the sequence handed to the layer above: an x wave of the first layer has
                                                 // up to four steps of loads in flight, so what it marked is known to be done that much later
 constexpr uint32_t UNWRITTEN = 0xFFFFFFFFu;
+enum { X_PLAIN, X_BELOW, X_PROJECTED };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
 constexpr int CELL_GRU_RB = 2;                  // GRU, reset gate before the candidate's recurrent product
 
 struct XRBf16 : TraitsBf16 {
@@ -337,11 +338,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
             for (int i = 0; i < XBELOW; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
         };
-        auto request = [&](int s, u32x4 (&v)[XLN]) {
+        auto request = [&](auto from, int s, u32x4 (&v)[XLN]) {
             const int sc = min(s, T - 1);
             const char* src = xsrc + (size_t)(d ? T - 1 - sc : sc) * xstep;
+            if constexpr (decltype(from)::value == X_PROJECTED) v[0] = *reinterpret_cast<const u32x4*>(src);
+            else {
 #pragma unroll
-            for (int i = 0; i < XLN; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + xoff[i]);
+                for (int i = 0; i < XLN; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + xoff[i]);
+            }
         };
         // layer output of the workgroup's tiles, or their state for the layer above
         elem* out = static_cast<elem*>(p.out);
@@ -393,9 +397,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         constexpr int PRODUCT = XLN * MPL * RT * TR::MMA_CLOCKS;
         constexpr bool OUT_FIRST = PRODUCT > 512;
         const bool wait_gates = lead && w < RT && ((PRODUCT > 128 && XLN <= LN) || p.LP > 1);
-        auto produce = [&](auto from_below, int sx, u32x4 (&cur)[XLN]) {
-            constexpr bool BELOW = decltype(from_below)::value;
-            constexpr int XL = BELOW ? XBELOW : XLN;
+        auto produce = [&](auto from, int sx, u32x4 (&cur)[XLN]) {
+            constexpr int FROM = decltype(from)::value;
+            constexpr bool BELOW = FROM == X_BELOW, PROJECTED = FROM == X_PROJECTED;
+            constexpr int XL = PROJECTED ? 1 : BELOW ? XBELOW : XLN;
             const int s = sx - lead;                 // between barriers s - 1 and s
             bool sent = s <= 0 || s >= T;
             if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
@@ -463,27 +468,44 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (BELOW) request_below(sx + 1, cur);
-            else request(sx + NBUF, cur);
+            else request(from, sx + NBUF, cur);
             __builtin_amdgcn_sched_barrier(0);
             if (LATE && !BELOW && s >= 0 && s < T) {
                 __syncthreads();
                 __syncthreads();
             }
         };
+        // A projection is one load a step: in a loop of its own in the variants of three chunk loads and of more than four (64 steps,
+        // us, as many loads of the same chunk as the layers above take -> one: 4 layers of 768 units, batch 8 and 16 169 -> 142 and
+        // 198 -> 154, of 1024 190 -> 163 and 215 -> 204, of 640 158 -> 133 and 184 -> 149; 2 of 384, batch 1, 8 and 16 75 -> 77.5,
+        // 82.8 -> 80 and 90 -> 79; but with four loads, 4 layers of 512 units at batch 1 and 8, 82 -> 83 and 90 -> 92; fp32 the same).
+        // Launches of one layer take one or two loads for it as it is.
+        constexpr bool OWN_LOOP = MPL == 1 && LN <= 8 && XLN >= LN && (XLN == 3 || XLN > 4);
         if (fused) {
             request_below(0, xb[0]);
-            for (int sx = 0; sx < T + lead; ++sx) produce(std::true_type(), sx, xb[0]);
-        } else {
+            for (int sx = 0; sx < T + lead; ++sx) produce(std::integral_constant<int, X_BELOW>(), sx, xb[0]);
+        } else if (OWN_LOOP && project) {
+            constexpr std::integral_constant<int, OWN_LOOP ? X_PROJECTED : X_PLAIN> FROM{};
 #pragma unroll
             for (int b = 0; b < NBUF; ++b) {
-                request(b, xb[b]);
+                request(FROM, b, xb[b]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            for (int s0 = 0; s0 < T + lead; s0 += NBUF)
+#pragma unroll
+                for (int b = 0; b < NBUF; ++b) produce(FROM, s0 + b, xb[b]);
+        } else {
+            constexpr std::integral_constant<int, X_PLAIN> FROM{};
+#pragma unroll
+            for (int b = 0; b < NBUF; ++b) {
+                request(FROM, b, xb[b]);
                 __builtin_amdgcn_sched_barrier(0);   // (in this order: the loop's waits count on it)
             }
             // (A whole number of rounds, beyond the last step where need be: a way round a step, or out of the loop between steps,
             // would make the compiler wait for the newest loads at the head of the loop.)
             for (int s0 = 0; s0 < T + lead; s0 += NBUF)
 #pragma unroll
-                for (int b = 0; b < NBUF; ++b) produce(std::false_type(), s0 + b, xb[b]);
+                for (int b = 0; b < NBUF; ++b) produce(FROM, s0 + b, xb[b]);
         }
         forward(T - 1);
         return;
@@ -896,7 +918,7 @@ hipError_t launch_wavefront_xcd(const WavefrontXcdArgs& a, hipStream_t stream) {
     if ((a.span != 1 && a.span != 2 && a.span != 8) || a.nrb % a.span != 0) return hipErrorInvalidValue;
     if (a.nrb * a.RT * 4 != a.H || a.nrb > 32 * a.span || a.ncb != (a.B + 15) / 16 || a.gpx * (8 / a.span) < a.LP * a.D * a.ncb)
         return hipErrorInvalidValue;
-    // with a projection the x waves of the first layer multiply nothing and load the four values of their pair (one chunk)
+    // with a projection the x waves of the first layer multiply nothing: they bring in the four values of their pair (one chunk)
     if ((a.gx == nullptr && a.xin == nullptr) || a.xln == 0 ||
         wavefront_xcd_input_chunks(a.dtype, a.H, a.gx ? 8 : a.I, a.LP > 1) != a.xln) return hipErrorInvalidValue;
     if (a.ring <= a.T && ((a.ring & (a.ring - 1)) != 0 || a.ring < 2 * XCD_AHEAD)) return hipErrorInvalidValue;
