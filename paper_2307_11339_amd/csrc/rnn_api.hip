@@ -1019,6 +1019,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         // Input products a step ahead make a step 3 to 5 % shorter and every layer above the first a step later (us, 0 -> 1: 2 fp32
         // layers of 512 units, 128 steps 664 -> 635; 2 GRU layers of 512, 100 steps 115 -> 111; 12 fp32 layers of 64, 96 steps 105 -> 112).
         a.lead = 25 * (LP - 1) <= T ? 1 : 0;
+        a.lead_first = LP == 1 || T == 1 || a.lead;   // (one step has no second product to wait for)
         a.device_scope = m->device_scope ? 1 : 0;
         for (int ll = 0; ll < LP; ++ll)
             for (int d = 0; d < m->D; ++d) {
