@@ -625,6 +625,11 @@ OPT_SPECS = [
     (("lstm_opts_padded_h72", 0, 2, 2, 24, 72, 6, 5, 1, True, True), 0.6, True),      # 72 -> 128 units: padded peephole weights
     (("lstm_opts_4layer_sq_h1024_b1", 0, 4, 1, 1024, 1024, 7, 1, 1, False, True), 0.15, True),   # the batch-1 latency shape
     (("lstm_opts_two_xcds", 0, 2, 1, 768, 768, 7, 18, 1, True, True), 0.3, True),     # a layer's workgroups on two XCDs
+    (("lstm_opts_all_xcds_h1280", 0, 2, 1, 40, 1280, 6, 5, 1, True, True), 0.3, True),   # ... on all eight
+    (("lstm_opts_all_xcds_padded_h1400", 0, 1, 1, 1032, 1400, 5, 16, 1, True, True), 0.3, True),
+    (("lstm_opts_all_xcds_h2048", 0, 1, 1, 2048, 2048, 4, 3, 1, True, True), 0.15, True),
+    (("gru_clip_all_xcds_h1536", 1, 2, 1, 1536, 1536, 5, 9, 1, True, True), 0.25, False),
+    (("gru_clip_all_xcds_h2048", 1, 1, 1, 64, 2048, 4, 16, 1, True, True), 0.25, False),
     (("lstm_opts_inside_sq", 0, 2, 1, 512, 512, 11, 300, 1, True, True), 0.5, True),  # inside-product kernel, two chains
     (("lstm_opts_b300", 0, 1, 1, 64, 512, 6, 300, 1, True, True), 0.5, True),         # flag-vector kernel
     (("gru_clip_b256_bidir", 1, 1, 2, 64, 128, 5, 256, 1, True, True), 0.4, False),   # flag-vector kernel, both directions

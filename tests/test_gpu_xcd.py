@@ -61,6 +61,11 @@ SHAPES = [
     (0, 2, 1, 2048, 2048, 6, 16, 1),    # every compute unit, the state in two halves
     (1, 1, 1, 64, 2048, 1, 2, 1),       # one step of it
     (0, 1, 1, 2056, 1800, 9, 20, 1),    # two passes behind a projection
+    (0, 1, 1, 1536, 1536, 33, 6, 1),    # many more steps than a slot is marked ahead
+    (1, 1, 1, 64, 2048, 26, 3, 1),
+    (0, 2, 1, 1032, 768, 9, 8, 1),      # several layers behind a projection, six chunk loads a wave: a loop of one load
+    (1, 3, 1, 40, 384, 7, 17, 1),       # ... three
+    (0, 2, 1, 80, 1024, 6, 16, 1),      # ... eight
 ]
 
 
@@ -187,7 +192,8 @@ def test_static_array_that_only_tagged_words_fit(gpu, shape):
 
 @pytest.mark.parametrize("shape", [(0, 1, 1, 128, 128, 1, 1, 1), (0, 4, 1, 512, 512, 1, 16, 1), (1, 2, 1, 64, 200, 1, 17, 1),
                                    (0, 2, 1, 256, 256, 1, 40, 0), (0, 2, 2, 384, 384, 1, 5, 1), (0, 2, 1, 1024, 1024, 1, 8, 1),
-                                   (0, 4, 1, 1024, 1024, 1, 1, 1), (1, 1, 1, 512, 512, 1, 300, 1)],
+                                   (0, 4, 1, 1024, 1024, 1, 1, 1), (1, 1, 1, 512, 512, 1, 300, 1), (0, 1, 1, 40, 1280, 1, 3, 1),
+                                   (1, 2, 1, 1536, 1536, 1, 16, 1), (0, 2, 1, 2048, 2048, 1, 9, 1)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
 def test_state_of_a_stream_in_place(gpu, shape):
     """One frame per call, the state updated in place (hT = h0, cT = c0): every workgroup of a layer reads the h0 of all units, and
@@ -242,7 +248,8 @@ def test_rows_of_x_more_than_4_gib_apart(gpu):
 
 
 @pytest.mark.parametrize("shape", [(0, 1, 1, 80, 256, 5, 4, 1), (0, 2, 1, 40, 128, 4, 2, 1), (0, 1, 2, 136, 384, 4, 17, 1),
-                                   (0, 1, 1, 20, 64, 5, 3, 0), (0, 1, 1, 80, 768, 4, 16, 1), (0, 2, 1, 1024, 128, 4, 5, 1)],
+                                   (0, 1, 1, 20, 64, 5, 3, 0), (0, 1, 1, 80, 768, 4, 16, 1), (0, 2, 1, 1024, 128, 4, 5, 1),
+                                   (0, 1, 1, 80, 1536, 4, 16, 1), (0, 1, 1, 1032, 1536, 4, 5, 1)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
 def test_an_infinite_feature_saturates_the_gates(gpu, oracle, shape):
     """One infinite feature among the first of a row: every weight of it is finite and not zero, so the gates saturate and all
