@@ -142,7 +142,7 @@ struct WavefrontXcdArgs {
     int ext, reset_before;
     int device_scope;            // 1: exchange through memory wherever the workgroups run
     int lead;                    // steps a layer above the first of the launch computes its input product ahead of the one it is in, 0 or 1
-    int lead_first;              // the same for the first layer of a launch of several
+    int lead_first;              // the same for the first layer, in the variants that have the choice (fp32, 256 units and more)
     int apart;                   // bf16, groups on an XCD each: the sums of the input and the recurrent product in chains of their own
     int in_place;                // an output may overwrite h0 before the exchange has ordered its reads
     const void* whh[WF_MAX_LAYERS * 2];   // packed W_hh per (local layer, direction): [4H, H]

@@ -32,7 +32,7 @@ struct Plan {
     // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with its groups of workgroups on an XCD each, or on a pair (span = 2)
     bool xcd = false;
     int span = 1, stride = 0;
-    bool apart = false;             // its variant that sums the two products apart, as the kernels do that its passes take a batch over from
+    bool apart = false;             // its variant that sums the two products apart, for passes that take a batch over from kernels that do
     int LP_asked = 1;               // LP before a compact workspace lowered it (rnn_forward_static decides as rnn_forward does)
     // > 0: the batch is larger than one pass of this plan can hold; it runs in passes of `chunk` sequences
     // (sequences are independent) through copies in the workspace, the last pass with a plan of its own
@@ -433,6 +433,7 @@ int derive_launches(const rnn_model* m, Plan& plan, int T) {
 }
 
 int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk);
+bool input_product_inside(const rnn_model* m, const Plan& plan, int l, int T);
 
 // may_chunk: a batch that no persistent launch can hold may be split into passes
 int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = true) {
@@ -463,6 +464,14 @@ double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
 }
 
 int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last);
+
+// Every layer runs in the inside-product kernel, where one chain of sums holds the input product and the recurrent product.
+bool inside_everywhere(const rnn_model* m, Plan plan, int T) {
+    if ((plan.CT == 1 && plan.NCH == 1) || derive_launches(m, plan, T) != RNN_OK) return false;
+    for (int l = 0; l < m->L; ++l)
+        if (!input_product_inside(m, plan, l, T)) return false;
+    return true;
+}
 
 // ... and what all passes of a call take.
 double call_us(const rnn_model* m, const Plan& plan, int T, int B) {
@@ -498,8 +507,8 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
         Plan passes;
         if (!plan.xcd && may_chunk && m->H <= 512 && choose_passes(m, T, B, passes, choose_xcd) &&
             1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B)) {
+            passes.apart = !inside_everywhere(m, plan, T);
             plan = passes;
-            plan.apart = true;
         }
         return RNN_OK;
     }

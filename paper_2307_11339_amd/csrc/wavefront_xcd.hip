@@ -393,13 +393,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // 16 sequences 0 to 12 %; 1 layer 1 to 4 %, but 2 % longer at 256 units, 40 sequences; fp32, on 136 and 224 values, 2 layers,
         // one sequence 8 to 15 % shorter, 16 sequences 3 to 5 % longer).
         constexpr bool LATE = RB && XLN > LN && XLN > 4;
-        // In a launch of several layers on few steps the first layer does without as well (p.lead_first): its first barrier would
-        // wait for two products, and every layer above with it (2 fp32 layers of 512 units, 16 sequences, us with the lead -> without
-        // it: 3 steps 39.0 -> 34.3, 8 steps 64.3 -> 59.6, 16 steps 104 -> 99.5, 32 steps 169 -> 180; bf16 1 to 4 % shorter up to 16
-        // steps).  Variants of more than 512 bf16 units gain 2 % and pay for the choice in the code around it (2 GRU layers of 768
-        // units, 64 steps, 131 -> 143): they always lead.
-        constexpr bool SEVERAL = (MPL > 1 || LN <= 4) && XLN >= LN;
-        const int lead = fused ? p.lead : LATE ? 0 : SEVERAL ? p.lead_first : 1;
+        // In a launch of several fp32 layers of 256 units or more, on few steps, the first layer does without as well (p.lead_first): its
+        // first barrier would wait for two long products, and every layer above with it (2 layers of 512 units, 16 sequences, us with
+        // the lead -> without it: 3 steps 39.0 -> 34.3, 8 steps 64.3 -> 59.6, 16 steps 104 -> 99.5, 32 steps 169 -> 180; of 296 units, 3
+        // steps 36.9 -> 32.0).  Short products lose by it from the first steps on (16 steps, 2 layers of 128 fp32 units 20.6 -> 22.4, of
+        // 256 bf16 units 19.3 -> 21.2), and inputs wider than the state come too late (6 layers of 384 bf16 units on 1024 values, 100
+        // steps, 137 -> 166).
+        constexpr bool CHOICE = MPL > 1 && LN >= 4 && XLN == LN;
+        const int lead = fused ? p.lead : LATE ? 0 : CHOICE ? p.lead_first : 1;
         constexpr int PRODUCT = XLN * MPL * RT * TR::MMA_CLOCKS;
         constexpr bool OUT_FIRST = PRODUCT > 512;
         const bool wait_gates = lead && w < RT && ((PRODUCT > 128 && XLN <= LN) || p.LP > 1);
