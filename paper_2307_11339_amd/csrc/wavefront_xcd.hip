@@ -150,6 +150,21 @@ __device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t by
                                              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 
+// cell_update with what the compiler makes of it in the tag-in-data kernel spelled out: which of the two products of the new state is
+// rounded by itself.  (With peepholes it makes the same of both kernels.)
+template <int CELL, bool EXT>
+__device__ inline float cell_update_tagged(const float a[SLOTS], float h_prev, float& c, const CellExt& ext) {
+    if constexpr (CELL == CELL_LSTM) {
+        if constexpr (EXT) return cell_update_ext<CELL>(a, h_prev, c, ext);
+        c = __builtin_fmaf(sigmoid_f(a[1]), c, __fmul_rn(sigmoid_f(a[0]), tanh_f(a[2])));
+        return sigmoid_f(a[3]) * tanh_f(c);
+    } else {
+        auto limit = [&](float v) { return EXT ? limit_to(v, ext.lim) : v; };
+        const float r = sigmoid_f(limit(a[0])), z = sigmoid_f(limit(a[1])), n = tanh_f(limit(__builtin_fmaf(r, a[3], a[2])));
+        return __builtin_fmaf(z, h_prev, __fmul_rn(1.0f - z, n));
+    }
+}
+
 // LN / XLN: 16-byte chunks a lane loads per wave of the state / of the layer input (a wave's quarter of H is 4 * EPC * LN
 // units; K blocks of the input are dealt to the waves in turn, and those beyond its width get zero weights).  The first layer
 // of a launch may have its input product done by a projection launch (p.gx): its x waves then only bring that in.
@@ -166,6 +181,16 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                                                      // the compiler contracts and orders the gate phase otherwise, and 2 GRU
                                                      // layers of 256 units, reset gate first, take 110 us for 64 steps instead of 104)
     static_assert(RT <= 4, "one tile per wave");
+    // Layers of 1280 and 1536 units sum in the order of the tag-in-data kernel, which ran them before: the same results, to the bit, on
+    // inputs H or H / 2 wide and behind a projection (48 steps, us, in an order of their own, each workgroup from another K block on -> in
+    // that order: 2 layers of 1280, batch 8 214 -> 206, 1 on 1032 values, batch 16 117 -> 106; 2 of 1536, batch 16 255 -> 240).  At 2048
+    // units that order does not fit the registers.
+    constexpr bool TAGGED_ORDER = LN > 8 && LN <= 12;
+    // ... the i-th block of four chunks of wave w: of an input KX wide a quarter of the blocks, not every fourth; none from there on
+    auto quarter_block = [](int i, int w, int KX) -> int {
+        const int mine = XLN == LN ? LN : (KX + 16 * EPC - 1) / (16 * EPC);
+        return i < mine ? w * mine + i : 4 * mine;
+    };
     // A wave numbers the tiles from its own on, so that (RT = 4) it keeps its own tile's partial sum as acc[0].
     constexpr bool KEEP = RT == 4;
     constexpr int OTHERS = KEEP ? 3 : 4;             // partial sums of a tile that go through LDS
@@ -302,13 +327,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             const elem* wih = static_cast<const elem*>(p.wih[ld]) + (size_t)d * SLOTS * H * KX;
 #pragma unroll
             for (int i = 0; i < XLN; ++i) {
-                const int chunk = (i * 4 + w) * 4 + q;
+                const int chunk = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4 + q;
                 const bool in = chunk * EPC < KX;    // beyond the input: zero weights, and any chunk that exists
                 const int k = in ? chunk * EPC : 0;
                 if (fused || p.x_blocked) xoff[i] = ((uint32_t)(k / EPC) * Bs + nc) * 16u;
                 else if (!rows) xoff[i] = (uint32_t)k * (uint32_t)sizeof(elem);
                 else {                               // lane 4 * r + c brings chunk c of row r
-                    const int rc = (i * 4 + w) * 4 + (lane & 3);
+                    const int rc = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4 + (lane & 3);
                     xoff[i] = rc * EPC < KX ? rc * 16u : 0u;
                 }
 #pragma unroll
@@ -428,7 +453,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 if (!project && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
 #pragma unroll
                     for (int i = 0; i < XL; ++i) {
-                        const int chunk = (i * 4 + w) * 4;
+                        const int chunk = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4;
                         if ((chunk + 4) * EPC > KX && (chunk + (rows ? lane & 3 : q)) * EPC >= KX) cur[i] = u32x4{0, 0, 0, 0};
                     }
                 }
@@ -520,7 +545,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 
     // ---- h waves -------------------------------------------------------------------------------------
     __builtin_amdgcn_s_setprio(3);                   // the dependency chain runs through these
-    const int rot = rb % LN;                         // workgroups start at different K blocks: spreads them over the L2 channels
+    const int rot = TAGGED_ORDER ? 0 : rb % LN;      // workgroups start at different K blocks: spreads them over the L2 channels
     frag wh[RT][LN * MPL];
     {
         const elem* whh = static_cast<const elem*>(p.whh[ld]);
@@ -622,6 +647,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
         for (int k = 0; k < OTHERS; ++k) part[k] = red[buf * PART + (rt * OTHERS + k) * 64 + lane];
         __builtin_amdgcn_sched_barrier(0);           // (one LDS round trip)
+        if constexpr (TAGGED_ORDER) return (part[0] + part[1]) + (part[2] + part[OTHERS - 1]);
         return ((KEEP ? acc[0] : part[OTHERS - 1]) + part[0]) + (part[1] + part[2]);
     };
     auto publish = [&](__amdgpu_buffer_rsrc_t rs, pub_t v, int unit0, int s) {   // slot s of this lane's share; mark slot s + AHEAD
@@ -647,7 +673,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // Everywhere up to 512 units it would make calls 0 to 4 % longer): there (APART) the wave that finishes a tile sums the tile's
         // input part, and the bias, for itself meanwhile.
         f32x4 acc[RT], from_x;
-        if constexpr (APART) from_x = bias_reg[0];
+        if constexpr (APART) from_x = TAGGED_ORDER ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : bias_reg[0];
         auto input_part = [&]() {                    // (every x wave takes every step, whatever became of its waits)
             if constexpr (APART) {
 #pragma unroll
@@ -693,7 +719,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         for (int o = 0; o < NOWN; ++o) {
             pre[o] = total(acc, RB ? 0 : (s & 1));
             if constexpr (APART) pre[o] += from_x;
-            else pre[o] += bias_reg[o];
+            if constexpr (!APART || TAGGED_ORDER) pre[o] += bias_reg[o];
         }
         float zg[RB ? NOWN : 1], nx[RB ? NOWN : 1];
         if constexpr (RB) {
@@ -731,7 +757,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     hn = (1.0f - zg[o]) * nn + zg[o] * h_reg[o];
                 } else {
                     const float a[SLOTS] = {pre[o][0], pre[o][1], pre[o][2], pre[o][3]};
-                    if constexpr (EXT) hn = cell_update_ext<GATES>(a, h_reg[o], c_new, ext_reg[o]);
+                    if constexpr (TAGGED_ORDER) hn = cell_update_tagged<GATES, EXT>(a, h_reg[o], c_new, ext_reg[0]);
+                    else if constexpr (EXT) hn = cell_update_ext<GATES>(a, h_reg[o], c_new, ext_reg[o]);
                     else hn = cell_update<GATES>(a, h_reg[o], c_new);
                 }
                 if (active) {

@@ -397,3 +397,21 @@ def test_reserved_steps_cover_fewer(gpu, shape):
     assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
     assert rnn.rnn_model_device_bytes(model.handle) == held
     model.close()
+
+
+@pytest.mark.parametrize("shape,digest", [((0, 2, 1, 1536, 1536, 24, 8, 1), "4ab4e57c91be3f6a"), ((1, 1, 1, 640, 1280, 20, 16, 1), "7776007b4d984933"),
+                                          ((0, 1, 1, 1544, 1536, 12, 3, 1), "05ed68978cff64da")],
+                         ids=["lstm_1536", "gru_1280_on_640", "lstm_1536_projected"])
+def test_bits_of_the_tag_in_data_kernel(gpu, shape, digest):
+    """Layers of 1280 and 1536 units sum in the order of the tag-in-data kernel, which ran them first: its bits of y and hT."""
+    import hashlib
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, True)
+    model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
+    harness.forward(model, io)
+    torch.cuda.synchronize()
+    got = hashlib.sha256(io.y.view(torch.int16).cpu().numpy().tobytes() + io.hT.cpu().numpy().tobytes()).hexdigest()[:16]
+    print("\n  case %r: %s" % (shape, got), flush=True)
+    assert got == digest
+    model.close()
