@@ -29,7 +29,7 @@ struct Plan {
     // the first layer runs in a launch of its own (it needs a projection, the layers above it run side
     // by side in the inside-product kernel): launches are {0}, {1..LP}, {LP+1..2LP}, ...
     bool first_alone = false;
-    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), with its groups of workgroups on an XCD each, or on a pair (span = 2)
+    // the XCD-resident kernel (wavefront_xcd.hip; CT = NCH = 1), its groups of workgroups on `span` XCDs each: 1, 2 or 8
     bool xcd = false;
     int span = 1, stride = 0;
     bool apart = false;             // its variant that sums the two products apart, for passes that take a batch over from kernels that do
@@ -443,7 +443,9 @@ int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = 
 }
 
 // What one pass of `plan` over B sequences takes, in us: launches of T steps each.  Fitted to launches of 48 steps, 40 to 1100
-// sequences through 2 layers of 128 to 512 bf16 units, one and both directions (within a sixth where it decides); steps of
+// sequences through 2 layers of 128 to 512 bf16 units, one and both directions (within a sixth where it decides), and checked where it
+// is used beyond that: of 150 shapes around the line, 1 to 8 layers, both cells, 1 to 400 steps, the 44 that it gives to passes (all in
+// bf16) take 0.34 to 0.79 of the time of the other plan.  Steps of
 //     the XCD-resident kernel          0.8 (128 units, 64 to 128 sequences) to 1.3 (512 units, 128), 1.0 with 8 of 128 sequences
 //     the tag-in-data kernel           2.7 (384 units, both directions, 72 sequences)
 //     large tiles, 64 columns          4.0 (256 units, 136 sequences) to 5.4 (512, 400); two layers in a launch 5.2 to 6.7
@@ -464,6 +466,8 @@ double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
 }
 
 int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last);
+
+constexpr int PASSES_MAX_H = 512;   // layers whose passes are compared with launches of larger tiles (choose_xcd has no wider ones)
 
 // Every layer runs in the inside-product kernel, where one chain of sums holds the input product and the recurrent product.
 bool inside_everywhere(const rnn_model* m, Plan plan, int T) {
@@ -505,7 +509,7 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
         // 256 units, 136 sequences 385 -> 202; one direction, 512 units, 136 sequences 320 -> 189), but not where many passes stand
         // against a well filled launch (512 units, 512 sequences 431 -> 481; both directions, 384 units, 260 sequences 518 -> 570).
         Plan passes;
-        if (!plan.xcd && may_chunk && m->H <= 512 && choose_passes(m, T, B, passes, choose_xcd) &&
+        if (!plan.xcd && may_chunk && m->H <= PASSES_MAX_H && choose_passes(m, T, B, passes, choose_xcd) &&
             1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B)) {
             passes.apart = !inside_everywhere(m, plan, T);
             plan = passes;
@@ -776,8 +780,8 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
     return RNN_OK;
 }
 
-// XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave
-// (1024 bf16 or 512 fp32 values).  With several layers in the launch an input of an eighth of their width or less keeps its projection
+// XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave (1024 bf16
+// or 512 fp32 values), in layers of more than 1024 units for inputs as wide as the layer (up to 16).  With several layers in the launch an input of an eighth of their width or less keeps its projection
 // launch; a launch of one layer takes it inside as well (48 steps, us, projected -> inside: 8 values into 128 units, 1 and 64
 // sequences 42 -> 38 and 54 -> 39; 64 into 512 units 61 -> 57 and 71 -> 62; fp32, 8 into 256 units 80 -> 68 and 93 -> 70).
 bool xcd_input_inside(const rnn_model* m, int width, bool several_layers) {
@@ -1424,6 +1428,7 @@ int rnn_model_reserve(rnn_model* m, int T, int B) {
     if (rc != RNN_OK) return rc;
     // Shorter calls of these sequences allocate nothing either.  The one choice that depends on the steps, passes or a launch of
     // larger tiles (call_us: both sides are linear in the steps), is made as for T steps or as for one.
+    if (m->H > PASSES_MAX_H || m->requested_plan == RNN_PLAN_CELLWISE) return RNN_OK;
     Plan shorter;
     rc = resolve_plan(m, 1, B, shorter);
     if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
