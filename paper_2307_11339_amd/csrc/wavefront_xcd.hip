@@ -16,14 +16,14 @@
 // device-scope stores.  What that still gains over tagged words (half the bytes, MFMA fragments straight from the load) stands at
 // the rule that chooses it; 16 sequences through one layer of 1024 units take 2.6 us a step instead of 4.
 // Layers of 1280 to 2048 units are laid over all eight, 8 units a workgroup (160 to 256 of them, one layer in a launch): every
-// workgroup brings in the whole state, 16 sequences x 3 KiB at 1536 units, 9.4 MiB a step over the chip at about 6 TB/s from the
-// infinity cache, and a step takes 2.2 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
+// workgroup brings in the whole state, 16 sequences x 3 KiB at 1536 units, 9.4 MiB a step over the chip, 93 % of the requests found in
+// the L2s, and a step takes 2.2 to 2.4 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
 // halves, one after the other: its fragments do not all fit the registers beside the weights (2.9 us).
 //
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
-// the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B fragment is one chunk, so a load instruction of a wave brings a whole K
-// block of 16 sequences from 8 consecutive cache lines straight into the registers the matrix instruction reads: no
-// tags, no staging through LDS.  Whether a chunk has been written is told from the data: a slot is filled with the bit
+// the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B
+// fragment is one chunk, so a load instruction of a wave brings a whole K block of 16 sequences from 8 consecutive cache lines straight
+// into the registers the matrix instruction reads: no tags, no staging through LDS.  Whether a chunk has been written is told from the data: a slot is filled with the bit
 // pattern of all ones (two bf16 NaNs; one fp32 NaN) several steps before it is used, no published value has that
 // pattern (a NaN is published with another one), and what is stored at once (8 bytes in bf16, 4 in fp32) is checked
 // at once.  Order: a wave marks slot s + AHEAD in step s; before it publishes slot s it has waited for loads issued
@@ -37,8 +37,8 @@
 //
 // What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz, each with the stamp that took it): fetch of the state 820
 // (16 KiB into every compute unit, its 32 load instructions with those of the x waves behind an L2 round trip of 400; one of four
-// as much state takes 440), products 350, barrier 200, sum over the quarters 240, gates 370, publication 150; the tag-in-data
-// kernel took 2.5 us a step here, this one takes 1.15.  Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
+// as much state takes 440), products 350, barrier 200, sum over the quarters 240, gates 370, publication 150: 0.89 of the 1.15 us that a
+// step takes (what lies between the stamps was not taken apart); the tag-in-data kernel took 2.5 us here.  Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
 // batch 64, 256 steps 1.29 -> 0.62 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64
 // units 159 -> 103 us; 2 fp32 layers of 512 units at batch 64 1.15 -> 0.63 ms; GRU with the reset gate before the product (one
 // launch per cell part without it) 1719 -> 98 us.
@@ -66,8 +66,9 @@ namespace rnn {
 namespace {
 
 constexpr int AHEAD = XCD_AHEAD;                // steps between marking a slot of the state and publishing it
-constexpr int AHEAD_UP = 8;                     // the same for the sequence handed to the layer above: an x wave of the first layer has
-                                                // up to four steps of loads in flight, so what it marked is known to be done that much later
+constexpr int AHEAD_UP = 8;                     // the same for the sequence handed to the layer above: an x wave of the first layer has up
+                                                // to three steps of loads in flight (two buffers and the lead), so that what it marked in a
+                                                // step is known to be done that much later: before the slot in front of it is published
 constexpr uint32_t UNWRITTEN = 0xFFFFFFFFu;
 enum { X_PLAIN, X_BELOW, X_PROJECTED };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
 constexpr int CELL_GRU_RB = 2;                  // GRU, reset gate before the candidate's recurrent product
@@ -405,8 +406,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // sx = s + lead.
         // With lead = 1 the part is there a step before h wave w picks it up, as the start of its accumulators, while its state
         // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
-        // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: 1078 clocks of
-        // gates instead of 860).  A product of a few instructions, or of an input wider than the state, which would come too late,
+        // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: a gate phase, sum
+        // and publication with it, of 1078 clocks instead of 860).  A product of a few instructions, or of an input wider than the state, which would come too late,
         // does not wait in a launch of one layer (128 units, 48 steps, 16 groups or more: 51 us with the wait, 45 without; with layers
         // above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few
         // steps take lead = 0 there (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that
