@@ -192,9 +192,22 @@ bool relayout_fits(const rnn_model* m, int T) {
 
 constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 
-// Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring): one for every step, or (compact) few that are
-// used in turn.
-int xcd_ring(const rnn_model* m, int T) { return m->compact > 0 && T >= 2 * XCD_AHEAD ? 2 * XCD_AHEAD : T + 1; }
+// Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring): few that are used in turn, or one for every step.
+// In turn where a group exchanges its state through one L2: the lines are there already, while with a slot for every step a fetch
+// waits for lines that are new to the L2 (880 clocks of the 2600 of a step at 512 units, whatever the number of loads; 620 in
+// turn.  us, a slot a step -> 64 / 16 / 8 slots: 3 layers of 320 units, both directions, 57 sequences, 301 steps 907 -> 804 / 788 / 786;
+// 2 of 512, both directions, batch 64, 256 steps 547 -> 528 / 517 / 518; 2 GRU layers of 256, reset gate first, 64 steps 99.9 -> 99.7 /
+// 92.6 / 99.2).  fp32 launches of one layer gain as well (2 of 256 units, both directions, batch 64, 128 steps 510 -> 472), those of
+// several lose a little (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48, 268 -> 270) and keep a slot a step.  Groups on several XCDs exchange through memory, where a line that other XCDs have
+// read before costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.
+constexpr int XCD_RING = 16;
+int xcd_ring(const rnn_model* m, const Plan& plan, int T) {
+    const bool in_turn = plan.span == 1 && (m->dtype == DT_BF16 || plan.LP == 1);
+    const int few = m->compact > 0 ? 2 * XCD_AHEAD : in_turn ? XCD_RING : T + 1;
+    return T >= few ? few : T + 1;
+}
+// Slots that the workspace holds.  The static array holds one for every step unless compact: what fits it stays what it was.
+int xcd_slots(const rnn_model* m, const Plan& plan, int T) { return m->arena.on && m->compact <= 0 ? T : std::min(xcd_ring(m, plan, T), T); }
 
 // Sequences side by side in a chunk row of its state sequences (WavefrontXcdArgs::stride): 4, 8 or 16, so that a workgroup's
 // chunks start a half or a whole cache line of their own.  With B side by side, workgroups that share a line hold up each other's
@@ -855,7 +868,7 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B, bool fi
     if (rc == RNN_OK && any_projection) rc = grow(m, m->ws.gx, rows * m->D * m->H * SLOTS * sizeof(float));
     if (rc == RNN_OK && plan.xcd) {
         const size_t slot = wavefront_xcd_slot_bytes(m->dtype, plan.stride, m->H), groups = (size_t)plan.LP * m->D * plan.ncb;
-        rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * std::min(xcd_ring(m, T), T) * slot);
+        rc = grow(m, m->ws.hseq, groups * (m->gru_reset_before ? 2 : 1) * xcd_slots(m, plan, T) * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.xseq, (size_t)plan.ncb * (plan.LP - 1) * T * slot);
         if (rc == RNN_OK) rc = grow(m, m->ws.flags, groups * plan.nrb * sizeof(uint64_t), true);
     }
@@ -1024,7 +1037,7 @@ int forward_xcd(rnn_model* m, const Plan& plan, const void* x, const int32_t* le
         a.RT = plan.RT; a.nrb = plan.nrb; a.ncb = plan.ncb;
         a.span = plan.span; a.stride = plan.stride;
         a.gpx = (LP * m->D * plan.ncb + XCDS / plan.span - 1) / (XCDS / plan.span);
-        a.ring = xcd_ring(m, T);
+        a.ring = xcd_ring(m, plan, T);
         a.ext = (m->clip > 0.0f || !m->peep.empty()) ? 1 : 0;
         a.reset_before = m->gru_reset_before ? 1 : 0;
         a.apart = plan.apart ? 1 : 0;

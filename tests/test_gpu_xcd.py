@@ -66,6 +66,10 @@ SHAPES = [
     (0, 2, 1, 1032, 768, 9, 8, 1),      # several layers behind a projection, six chunk loads a wave: a loop of one load
     (1, 3, 1, 40, 384, 7, 17, 1),       # ... three
     (0, 2, 1, 80, 1024, 6, 16, 1),      # ... eight
+    (0, 1, 2, 64, 256, 15, 18, 1),      # one step fewer than the slots of a sequence that are used in turn,
+    (1, 2, 1, 128, 128, 16, 9, 1),      # as many,
+    (0, 1, 1, 128, 512, 17, 20, 1),     # one more,
+    (1, 1, 2, 64, 128, 33, 17, 0),      # twice as many and one
 ]
 
 
