@@ -61,6 +61,10 @@
 #ifndef RNN_XR_APART
 #define RNN_XR_APART 0
 #endif
+//   RNN_XR_WIDE  1 = groups on two XCDs, 2 = on all of them
+#ifndef RNN_XR_WIDE
+#define RNN_XR_WIDE 0
+#endif
 
 namespace rnn {
 namespace {
@@ -610,9 +614,22 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff, slot_of(s) + (uint32_t)(ir * 64) * Bs, 16);
         }
     };
+    // Groups on several XCDs: a wave waits before its first request of a step.  A request that finds a chunk unwritten costs a whole
+    // round trip through memory, and its answers delay the stores everybody waits for, so it is better sent late than too early; how late depends on
+    // the shape, the step and the wave (those without a tile of their own ask first and were sent back in four steps of five), so every wave finds out for
+    // itself: longer after a step that sent it back, a little shorter after every other (once in 33 steps in balance).  64 steps, us, without -> with it: 2 layers of 1024
+    // units, batch 5 / 8 / 16 147 / 154 / 175 -> 112 / 116 / 116, of 768, batch 8 / 16 125 / 140 -> 100 / 101, one of 1536, batch 1 / 16
+    // 147 / 167 -> 110 / 123, of 2048 183 / 204 -> 149 / 162.  Other choices (sixteenths more, sixteenths less, at first): 16, 1, 10 up to 3 %
+    // longer, 48, 1, 8 the same, 96, 1, 0 and the best constant of each shape 1 to 10 % longer.  Within one XCD the loop as it is is late enough
+    // (retries in 0 to 30 % of the steps, 600 clocks each); there such pauses made 12 narrow layers 2 to 13 % longer and little shorter.
+    constexpr int PAUSE_MORE = 32, PAUSE_LESS = 1, PAUSE_FIRST = 8 * 16, PAUSE_MOST = 64 * 16;   // sixteenths of a round of the loop, about 40 clocks
+    int pause = PAUSE_FIRST;
+    auto hold_back = [&]() {
+        for (int i = __builtin_amdgcn_readfirstlane(pause) >> 4; i > 0; --i) asm volatile("s_nop 7");
+    };
     // The chunks of slot s from `first` on in hv, waiting until all of them have been written; `meanwhile` runs while the first
-    // request travels.
-    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, int first, auto meanwhile) {
+    // request travels.  Returns how often they were asked for in vain.
+    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, int first, auto meanwhile) -> unsigned {
         unsigned spins = 0;
         for (;;) {
             ask(rs, s, first);
@@ -625,6 +642,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             asm volatile("" ::: "memory");
         }
         asm volatile("" ::: "memory");
+        return spins;
     };
     // partial products of this wave's K quarter (of the chunks from `first` on) added to acc
     auto multiply = [&](f32x4 (&acc)[RT], auto first) {
@@ -701,8 +719,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         if (w >= RT && s > 0)                        // (no use in asking before the workgroup's own tiles are out)
             while (lds_get(done + (w & (RT - 1))) < (unsigned)s) __builtin_amdgcn_s_sleep(1);
         constexpr std::integral_constant<int, 0> FRONT{};
-        if (s > 0) fetch(hrs, s - 1, FRONT, input_part);
-        else input_part();
+        if (s > 0) {
+            if (RNN_XR_WIDE) hold_back();
+            const unsigned in_vain = fetch(hrs, s - 1, FRONT, input_part);
+            if (RNN_XR_WIDE) pause = in_vain ? min(pause + PAUSE_MORE, PAUSE_MOST) : max(pause - PAUSE_LESS, 0);
+        } else input_part();
         multiply(acc, FRONT);
         if constexpr (HL < LN) {
             constexpr std::integral_constant<int, HL> REST{};
@@ -833,9 +854,6 @@ hipError_t launch_cell(const WavefrontXcdArgs& a, hipStream_t stream) {
 // units in groups of 160, 192 and 256 workgroups of 8 units on all XCDs (RNN_XR_WIDE = 2).
 #define RNN_XR_SHAPES_WIDE(X) X(4, 5) X(4, 6) X(4, 8)
 #define RNN_XR_SHAPES_CHIP(X) X(2, 10) X(2, 12) X(2, 16)
-#ifndef RNN_XR_WIDE
-#define RNN_XR_WIDE 0
-#endif
 
 #if RNN_XR_DT == 0
 typedef XRBf16 TRHere;
