@@ -256,16 +256,21 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
 
 // The same with every group on two XCDs, for `LP` layers in a launch: bf16 layers of 640 to 1024 units.  The state then goes
 // through memory (device-scope stores) as in the tag-in-data kernel, whose launches it takes over, but at half the bytes, without
-// tags to strip and without staging.  The line lies where that kernel needs more than four loads a wave for the state of a step,
-// B * H > 4096; below, its one to four probe-paced loads win.  64 steps, us, tag-in-data -> this:
-//     4 x 1024 units   batch 1 133 -> 170, 6 196 -> 191, 8 219 -> 192, 12 256 -> 200, 16 313 -> 204
-//     2 x 1024 units   batch 4 146 -> 149, 6 184 -> 174, 16 256 -> 186, 32 281 -> 188
-//     4 x 768 units    batch 4 134 -> 145, 6 170 -> 151, 8 177 -> 152, 16 270 -> 171
-//     2 x 640 units    batch 4 127 -> 133, 6 132 -> 131, 8 165 -> 130, 16 210 -> 146
+// tags to strip and without staging.  A launch costs some 5 us more than one of tagged words, a step a tenth to a half less, so that
+// calls of few steps stay there where it takes at most four loads a wave for the state of a step, B * H <= 4096: of a line through 117
+// shapes with 4 to 32 steps, what lies on this side is up to half as long, 2 % longer at most.  64 steps, us, tag-in-data -> this:
+//     1 x 640 units    batch 1 136 -> 91, 2 148 -> 91, 4 159 -> 91;    4 x 640 units    121 -> 118, 128 -> 118, 130 -> 119
+//     2 x 768 units    batch 1 123 -> 100, 4 129 -> 101;               both directions, 48 steps 189 -> 159, 203 -> 162
+//     1 x 1024 units   batch 1 126 -> 103, 2 133 -> 103, 4 138 -> 106; 4 x 1024 units   130 -> 124, 148 -> 124, 160 -> 123
+//     8 steps, 2 x 1024 batch 1 1.11 times as long, 2 1.00, 4 0.98; 4 x 1024 1.10, 0.89, 0.83; 1 x 640 1.00, 0.92, 0.89
+constexpr int XCD_WIDE_STEPS[] = {8, 12, 24};   // the fewest steps: several sequences; one, through one layer a launch; through several
+bool xcd_wide_pays(const rnn_model* m, int T, int B, int LP) {
+    return (size_t)B * m->H > 4096 || T >= XCD_WIDE_STEPS[B > 1 ? 0 : LP == 1 ? 1 : 2];
+}
 bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
     const int RT = 4, ncb = (B + 15) / 16, nrb = m->H / (RT * 4), stride = xcd_stride(m, B);
     if (!xcd_addressable(m, T, B)) return false;
-    if (m->compact < 0 || (size_t)B * m->H <= 4096) return false;
+    if (m->compact < 0 || !xcd_wide_pays(m, T, B, LP)) return false;
     const int gpx = (LP * m->D * ncb + XCDS / 2 - 1) / (XCDS / 2);
     if (!wavefront_xcd_wide_exists(m->dtype, RT, m->H, m->gru_reset_before) || gpx * nrb > 2 * (m->num_cus / XCDS)) return false;
     plan = Plan();
@@ -1441,8 +1446,16 @@ int rnn_model_reserve(rnn_model* m, int T, int B) {
     if (rc != RNN_OK) return rc;
     // Shorter calls of these sequences allocate nothing either.  The one choice that depends on the steps, passes or a launch of
     // larger tiles (call_us: both sides are linear in the steps), is made as for T steps or as for one.
-    if (m->H > PASSES_MAX_H || m->requested_plan == RNN_PLAN_CELLWISE) return RNN_OK;
+    if (m->requested_plan == RNN_PLAN_CELLWISE) return RNN_OK;
     Plan shorter;
+    if (m->H > PASSES_MAX_H) {   // few sequences through wide layers, also those of a last pass: below some steps on tagged words
+        for (int limit : XCD_WIDE_STEPS)
+            if (limit <= T && rc == RNN_OK) {
+                rc = resolve_plan(m, limit - 1, B, shorter);
+                if (rc == RNN_OK) rc = prepare_workspace(m, shorter, limit - 1, B);
+            }
+        return rc;
+    }
     rc = resolve_plan(m, 1, B, shorter);
     if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
     return prepare_workspace(m, shorter, T, B);

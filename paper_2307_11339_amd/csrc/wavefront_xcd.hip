@@ -186,11 +186,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                                                      // the compiler contracts and orders the gate phase otherwise, and 2 GRU
                                                      // layers of 256 units, reset gate first, take 110 us for 64 steps instead of 104)
     static_assert(RT <= 4, "one tile per wave");
-    // Layers of 1280 and 1536 units sum in the order of the tag-in-data kernel, which ran them before: the same results, to the bit, on
-    // inputs H or H / 2 wide and behind a projection (48 steps, us, in an order of their own, each workgroup from another K block on -> in
-    // that order: 2 layers of 1280, batch 8 214 -> 206, 1 on 1032 values, batch 16 117 -> 106; 2 of 1536, batch 16 255 -> 240).  At 2048
-    // units that order does not fit the registers.
-    constexpr bool TAGGED_ORDER = LN > 8 && LN <= 12;
+    // Layers of 640 to 1536 units sum in the order of the tag-in-data kernel, which ran them before (up to 1024 units it still does on few
+    // steps): the same results, to the bit, on inputs H or H / 2 wide and behind a projection.  At 1280 and 1536 units that order is also
+    // shorter than one of its own, each workgroup from another K block on (48 steps, us: 2 layers of 1280, batch 8 214 -> 206, 1 on 1032 values,
+    // batch 16 117 -> 106; 2 of 1536, batch 16 255 -> 240); up to 1024 units it costs up to 4 % (64 steps: 1, 2 and 4 layers of 768, batch 4,
+    // 92.0 -> 94.5, 97.1 -> 101, 114 -> 120, of 1024 105 -> 106, 111 -> 111, 119 -> 123; batch 16, 2 of 1024 118 -> 116).  At 2048 units
+    // it does not fit the registers.
+    constexpr bool TAGGED_ORDER = RNN_XR_WIDE && LN <= 12;
     // ... the i-th block of four chunks of wave w: of an input KX wide a quarter of the blocks, not every fourth; none from there on
     auto quarter_block = [](int i, int w, int KX) -> int {
         const int mine = XLN == LN ? LN : (KX + 16 * EPC - 1) / (16 * EPC);
@@ -664,8 +666,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         const int rt = min(w, RT - 1);
         f32x4 part[OTHERS];
 #pragma unroll
-        for (int k = 0; k < OTHERS; ++k) part[k] = red[buf * PART + (rt * OTHERS + k) * 64 + lane];
+        for (int k = 0; k < OTHERS; ++k) {
+            // (quarters 0 and 1, 2 and 3 belong together: entry k is that of wave w - 1 - k, so for an even w the quarter beside it is
+            // the last entry, for an odd one the first)
+            const int entry = TAGGED_ORDER && KEEP && (w & 1) == 0 ? OTHERS - 1 - k : k;
+            part[k] = red[buf * PART + (rt * OTHERS + entry) * 64 + lane];
+        }
         __builtin_amdgcn_sched_barrier(0);           // (one LDS round trip)
+        if constexpr (TAGGED_ORDER && KEEP) return (acc[0] + part[0]) + (part[1] + part[2]);
         if constexpr (TAGGED_ORDER) return (part[0] + part[1]) + (part[2] + part[OTHERS - 1]);
         return ((KEEP ? acc[0] : part[OTHERS - 1]) + part[0]) + (part[1] + part[2]);
     };
@@ -684,7 +692,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     for (int s = 0; s < T; ++s) {
         const int t = d ? T - 1 - s : s;
         // The recurrent product starts from the input part.  Not so in fp32, where one chain of sums as long as both products loses
-        // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7), nor in layers of more than 1024 units,
+        // precision (2 layers of 512 units, distance of hT from 64 bits 4.7e-7 against 3.6e-7), nor in layers of 640 units and more,
         // whose chains are the longest (cT after one step, 1536 units on 1536 values 1.92e-7 against 1.35e-7, 2048 on 2048 2.17e-7
         // against 1.45e-7; tagged words 1.37e-7 and 1.46e-7, and no time lost: 64 steps of 2 such layers 0 to 2 % shorter), nor in
         // passes that take a batch over from launches of larger tiles, which sum apart as well (p.apart; both directions of 512 units,
@@ -817,7 +825,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 // Forces one workgroup per compute unit: more than half of the 160 KiB.
 constexpr size_t MIN_LDS = 84 * 1024;
 
-constexpr bool apart(int MPL, int LN) { return MPL > 1 || LN > 8 || RNN_XR_APART; }
+constexpr bool apart(int MPL, int LN) { return MPL > 1 || RNN_XR_WIDE || RNN_XR_APART; }
 
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {

@@ -50,7 +50,12 @@ SHAPES = [
     (0, 2, 2, 512, 512, 6, 72, 1),      # passes of 64 and 8 sequences where a launch of larger tiles holds all 72
     (1, 3, 2, 40, 200, 5, 140, 1),      # the same padded, 128 and 12, a narrow input inside
     (0, 4, 1, 520, 256, 6, 300, 1),     # 256 and 44, the last pass with all layers in a launch
-    (0, 2, 1, 1024, 1024, 6, 4, 1),     # (the last batch that runs on tagged words)
+    (0, 2, 1, 1024, 1024, 6, 4, 1),     # (few steps of few sequences: tagged words)
+    (0, 2, 1, 1024, 1024, 8, 4, 1),     # (as many as this kernel takes)
+    (0, 4, 1, 768, 768, 24, 1, 1),      # one sequence, several layers in a launch
+    (1, 1, 1, 640, 640, 12, 1, 1),      # ... one layer
+    (0, 2, 2, 80, 640, 9, 3, 1),        # both directions, the second layer behind a projection
+    (0, 2, 1, 1024, 1024, 12, 258, 1),  # a last pass of two sequences
     (1, 1, 1, 1032, 1024, 6, 40, 1),    # projection in front, three blocks of sequences
     (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD
     (1, 2, 2, 768, 768, 7, 20, 1),      # both directions, the second launch behind a projection
@@ -328,13 +333,14 @@ def test_fp32_sums_of_the_two_products_are_kept_apart(gpu, oracle, shape, bound)
 
 
 @pytest.mark.parametrize("shape,bound", [((0, 1, 1, 1536, 1536, 4, 8, 1), 1.63e-7), ((0, 1, 1, 2048, 2048, 4, 5, 1), 1.8e-7),
-                                         ((0, 1, 2, 512, 512, 48, 72, 1), 1.24e-7), ((0, 1, 2, 256, 256, 48, 136, 1), 1.13e-7)],
-                         ids=["1536_units", "2048_units", "passes_of_512_units", "passes_of_256_units"])
+                                         ((0, 1, 2, 512, 512, 48, 72, 1), 1.24e-7), ((0, 1, 2, 256, 256, 48, 136, 1), 1.13e-7),
+                                         ((0, 1, 1, 1024, 1024, 4, 8, 1), 1.45e-7), ((0, 1, 1, 768, 768, 4, 16, 1), 1.35e-7)],
+                         ids=["1536_units", "2048_units", "passes_of_512_units", "passes_of_256_units", "1024_units", "768_units"])
 def test_bf16_sums_of_the_two_products_are_kept_apart(gpu, shape, bound):
     """Distance of cT after one step from 64 bits (2-norm over 2-norm; the cell state is not rounded to bf16, so it shows the sums).
     Products of the input and of the state in chains of their own: 1.35e-7, 1.45e-7, 1.13e-7 and 1.08e-7 (the kernels that ran these
-    shapes before 1.37e-7, 1.46e-7, 1.29e-7 and 1.14e-7); in one chain 1.92e-7, 2.17e-7, 1.35e-7 and 1.18e-7.  The bound is the
-    middle."""
+    shapes before 1.37e-7, 1.46e-7, 1.29e-7 and 1.14e-7); in one chain 1.92e-7, 2.17e-7, 1.35e-7 and 1.18e-7.  1024 and 768 units:
+    1.26e-7 and 1.20e-7, in one chain 1.65e-7 and 1.50e-7.  The bound is the middle."""
     import torch
     harness, rnn, W = gpu
     wl = _workload(W, shape, True)
@@ -403,11 +409,42 @@ def test_reserved_steps_cover_fewer(gpu, shape):
     model.close()
 
 
+@pytest.mark.parametrize("shape", [(0, 2, 1, 1024, 1024, 24, 2, 1), (1, 4, 1, 768, 768, 30, 1, 1), (0, 1, 1, 640, 640, 14, 1, 1), (0, 2, 1, 1024, 1024, 12, 258, 1)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d" % s[:7])
+def test_reserved_steps_of_wide_layers_cover_fewer(gpu, shape):
+    """Few sequences, or a last pass of few, through wide layers run on tagged words below a number of steps: rnn_model_reserve
+    covers every smaller number of steps, and the results are those of a model that reserved nothing."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, False)
+    c = wl.cfg
+    kept, io, other = harness.DeviceModel(wl), harness.DeviceIO(wl), harness.DeviceIO(wl)
+    assert rnn.rnn_model_reserve(kept.handle, c.T, c.B) == rnn.RNN_OK
+    held = rnn.rnn_model_device_bytes(kept.handle)
+    for T in sorted({1, 7, 8, 11, 12, 23, 24, c.T}):
+        if T > c.T:
+            continue
+        print("\n  case %r: %d steps" % (shape, T), flush=True)
+        fresh = harness.DeviceModel(wl)
+        for m, o in ((kept, io), (fresh, other)):
+            assert rnn.rnn_forward(m.handle, o.x, None, o.h0, o.c0, o.y, o.hT, o.cT, T, c.B, torch.cuda.current_stream()) == rnn.RNN_OK
+        torch.cuda.synchronize()
+        assert torch.equal(io.y[:T], other.y[:T]) and torch.equal(io.hT, other.hT)
+        assert rnn.rnn_model_device_bytes(kept.handle) == held
+        assert rnn.rnn_model_check(kept.handle) == rnn.RNN_OK
+        fresh.close()
+    kept.close()
+
+
 @pytest.mark.parametrize("shape,digest", [((0, 2, 1, 1536, 1536, 24, 8, 1), "4ab4e57c91be3f6a"), ((1, 1, 1, 640, 1280, 20, 16, 1), "7776007b4d984933"),
-                                          ((0, 1, 1, 1544, 1536, 12, 3, 1), "05ed68978cff64da")],
-                         ids=["lstm_1536", "gru_1280_on_640", "lstm_1536_projected"])
+                                          ((0, 1, 1, 1544, 1536, 12, 3, 1), "05ed68978cff64da"),
+                                          ((0, 2, 1, 1024, 1024, 24, 4, 1), "f3f474cdc2c0e4ce"), ((1, 4, 1, 768, 768, 30, 1, 1), "38bee8ffcfaf741c"),
+                                          ((0, 1, 1, 512, 1024, 12, 3, 1), "0f44c533d54e0b3d"), ((1, 2, 1, 1032, 640, 16, 4, 1), "3f3675137037fbc3"),
+                                          ((0, 2, 2, 768, 768, 24, 4, 1), "d67e88dcb0a544aa")],
+                         ids=["lstm_1536", "gru_1280_on_640", "lstm_1536_projected", "lstm_1024", "gru_768_one_sequence", "lstm_1024_on_512",
+                              "gru_640_projected", "lstm_768_both_directions"])
 def test_bits_of_the_tag_in_data_kernel(gpu, shape, digest):
-    """Layers of 1280 and 1536 units sum in the order of the tag-in-data kernel, which ran them first: its bits of y and hT."""
+    """Layers of 640 to 1536 units sum in the order of the tag-in-data kernel, which ran them first: its bits of y and hT."""
     import hashlib
     import torch
     harness, rnn, W = gpu
