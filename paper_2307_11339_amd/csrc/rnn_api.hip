@@ -298,6 +298,14 @@ bool choose_xcd_chip(const rnn_model* m, int T, int B, Plan& plan) {
     return true;
 }
 
+// ... with as many layers in a launch as fit.
+bool choose_xcd_wide_launches(const rnn_model* m, int T, int B, Plan& plan) {
+    const int lp_max = m->D == 1 ? std::min(m->L, (int)WF_MAX_LAYERS) : 1;
+    for (int launches = (m->L + lp_max - 1) / lp_max; launches <= m->L; ++launches)
+        if (choose_xcd_wide(m, T, B, (m->L + launches - 1) / launches, plan)) return true;
+    return false;
+}
+
 // Choose how the grid of cells is laid over the compute units for batch size B.
 bool choose_wavefront(const rnn_model* m, int T, int B, Plan& plan) {
     if (m->H % 4 != 0) return false;
@@ -460,6 +468,8 @@ int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = 
     return derive_launches(m, plan, T);
 }
 
+constexpr int PASSES_MAX_H = 512;   // the widest layers of choose_xcd
+
 // What one pass of `plan` over B sequences takes, in us: launches of T steps each.  Fitted to launches of 48 steps, 40 to 1100
 // sequences through 2 layers of 128 to 512 bf16 units, one and both directions (within a sixth where it decides), and checked where it
 // is used beyond that: of 150 shapes around the line, 1 to 8 layers, both cells, 1 to 400 steps, the 44 that it gives to passes (all in
@@ -468,10 +478,16 @@ int resolve_plan(const rnn_model* m, int T, int B, Plan& plan, bool may_chunk = 
 //     the tag-in-data kernel           2.7 (384 units, both directions, 72 sequences)
 //     large tiles, 64 columns          4.0 (256 units, 136 sequences) to 5.4 (512, 400); two layers in a launch 5.2 to 6.7
 //     large tiles, two chains          4.5 (512 units, 512 sequences) with the input product inside, else no faster than the former
+// On two XCDs (640 to 1024 units) a step of it takes 1.44 to 1.75, 6 % more with several layers in a launch; large tiles beside it 4.0 (128 sequences
+// through one layer of 640 units) to 5.8 (64 through four of 1024).  What a launch takes besides shows on few steps: 13 us
+// there, 16 with the second direction's projection, 18 of large tiles.
 double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
     const int launches = (m->L + plan.LP_asked - 1) / plan.LP_asked;
-    double step;
-    if (plan.xcd) {
+    double step, start = 6.0;
+    if (m->H > PASSES_MAX_H) start = plan.xcd || (plan.CT == 1 && plan.NCH == 1) ? 10.0 + 3.0 * m->D : 18.0;
+    if (plan.xcd && plan.span == 2) {
+        step = (0.95 + 0.00077 * m->H) * (plan.LP_asked > 1 ? 1.06 : 1.0);
+    } else if (plan.xcd) {
         const double fill = m->D == 1 ? std::min(1.0, plan.LP_asked * plan.ncb / (double)XCDS) : 1.0;
         step = (0.8 + m->H / 1000.0) * (0.6 + 0.4 * fill);
     } else if (plan.CT == 1 && plan.NCH == 1) {
@@ -480,12 +496,10 @@ double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
         const bool inside = m->D == 1 && m->I == m->H && plan.NCH == 2;
         step = (3.3 + 0.0013 * m->H + 7e-6 * m->H * m->D * plan.LP_asked * B) * (plan.LP_asked > 1 ? 1.2 : 1.0) * (inside ? 0.75 : 1.0);
     }
-    return launches * (6.0 + T * step);
+    return launches * (start + T * step);
 }
 
 int resolve_last_pass(const rnn_model* m, const Plan& plan, int T, int B, Plan& last);
-
-constexpr int PASSES_MAX_H = 512;   // layers whose passes are compared with launches of larger tiles (choose_xcd has no wider ones)
 
 // Every layer runs in the inside-product kernel, where one chain of sums holds the input product and the recurrent product.
 bool inside_everywhere(const rnn_model* m, Plan plan, int T) {
@@ -532,6 +546,17 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
             passes.apart = !inside_everywhere(m, plan, T);
             plan = passes;
         }
+        // The same for groups on two XCDs, which may also hold the batch at once with fewer layers in a launch.  48 steps, us, without ->
+        // with: 2 layers of 768 and of 1024 units, batch 64 250 -> 154 and 262 -> 178, both directions 559 -> 395 and 661 -> 506; 4 layers of 1024,
+        // batch 24 357 -> 188; 2 GRU layers of 1024 on 80 values, batch 44 469 -> 165.  Not where two chains of large tiles hold four layers or
+        // more side by side (4 layers of 1024, batch 64 283 -> 353, 6 of 640 1.57 times as long), nor in passes against chains with every input
+        // product inside (one layer of 1024, batch 128 232 -> 179, but at 192 236 -> 269, and 2 layers, batch 128 320 -> 355).
+        const bool side_by_side = plan.NCH == 2 && plan.LP >= 4;
+        if (!plan.xcd && !side_by_side &&
+            (choose_xcd_wide_launches(m, T, B, passes) ||
+             (may_chunk && !(plan.NCH == 2 && inside_everywhere(m, plan, T)) && choose_passes(m, T, B, passes, choose_xcd_wide_launches))) &&
+            1.05 * call_us(m, passes, T, B) < call_us(m, plan, T, B))
+            plan = passes;
         return RNN_OK;
     }
     if (m->requested_plan == RNN_PLAN_WAVEFRONT) return RNN_EUNSUPPORTED;
@@ -1438,27 +1463,31 @@ int rnn_model_set_validation(rnn_model* m, int on) {
     return RNN_OK;
 }
 
+// Calls of fewer than T steps on B sequences, whose plan for T steps is `plan`, find their workspace as well.  The choices that depend on the
+// steps, passes or a launch of larger tiles (call_us: both sides are linear in the steps) and tagged words for few sequences through wide
+// layers, are made as for T steps or as for one.
+static int cover_fewer_steps(rnn_model* m, const Plan& plan, int T, int B, bool may_chunk, Plan& shorter) {
+    const int rc = resolve_plan(m, 1, B, shorter, may_chunk);
+    if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
+    const bool few = m->H > PASSES_MAX_H && (size_t)B * m->H <= 4096;
+    return prepare_workspace(m, shorter, few ? std::min(T, XCD_WIDE_STEPS[2]) : T, B);
+}
+
 int rnn_model_reserve(rnn_model* m, int T, int B) {
     if (!m || T < 1 || B < 1) return RNN_EINVAL;
     Plan plan;
     int rc = resolve_plan(m, T, B, plan);
     if (rc == RNN_OK) rc = prepare_workspace(m, plan, T, B);
-    if (rc != RNN_OK) return rc;
-    // Shorter calls of these sequences allocate nothing either.  The one choice that depends on the steps, passes or a launch of
-    // larger tiles (call_us: both sides are linear in the steps), is made as for T steps or as for one.
-    if (m->requested_plan == RNN_PLAN_CELLWISE) return RNN_OK;
-    Plan shorter;
-    if (m->H > PASSES_MAX_H) {   // few sequences through wide layers, also those of a last pass: below some steps on tagged words
-        for (int limit : XCD_WIDE_STEPS)
-            if (limit <= T && rc == RNN_OK) {
-                rc = resolve_plan(m, limit - 1, B, shorter);
-                if (rc == RNN_OK) rc = prepare_workspace(m, shorter, limit - 1, B);
-            }
-        return rc;
+    if (rc != RNN_OK || m->requested_plan == RNN_PLAN_CELLWISE) return rc;
+    Plan shorter, last, unused;
+    rc = cover_fewer_steps(m, plan, T, B, true, shorter);
+    for (const Plan* p : {&plan, &shorter}) {      // ... nor does the last pass of a batch in passes allocate
+        const int rest = p->chunk > 0 ? B % p->chunk : 0;
+        if (rc != RNN_OK || rest == 0 || p->xcd) continue;   // (passes of the XCD-resident kernel keep the last one to it)
+        rc = resolve_plan(m, T, rest, last, false);
+        if (rc == RNN_OK) rc = cover_fewer_steps(m, last, T, rest, false, unused);
     }
-    rc = resolve_plan(m, 1, B, shorter);
-    if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
-    return prepare_workspace(m, shorter, T, B);
+    return rc;
 }
 
 // The workspace as a set of empty buffers that grow() fills with pieces of the static array.

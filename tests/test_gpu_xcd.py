@@ -56,6 +56,10 @@ SHAPES = [
     (1, 1, 1, 640, 640, 12, 1, 1),      # ... one layer
     (0, 2, 2, 80, 640, 9, 3, 1),        # both directions, the second layer behind a projection
     (0, 2, 1, 1024, 1024, 12, 258, 1),  # a last pass of two sequences
+    (0, 2, 1, 768, 768, 24, 64, 1),     # a launch for each layer where large tiles hold both in one
+    (1, 4, 1, 1024, 1024, 9, 20, 1),    # two launches of two layers
+    (0, 1, 1, 80, 640, 50, 100, 1),     # passes of 64 and 36 sequences
+    (0, 2, 2, 80, 1000, 20, 44, 1),     # padded, passes of 32 and 12, the second layer behind a projection
     (1, 1, 1, 1032, 1024, 6, 40, 1),    # projection in front, three blocks of sequences
     (0, 2, 1, 40, 600, 9, 17, 1),       # padded to 640 units: 20 workgroups on either XCD
     (1, 2, 2, 768, 768, 7, 20, 1),      # both directions, the second launch behind a projection
@@ -409,10 +413,12 @@ def test_reserved_steps_cover_fewer(gpu, shape):
     model.close()
 
 
-@pytest.mark.parametrize("shape", [(0, 2, 1, 1024, 1024, 24, 2, 1), (1, 4, 1, 768, 768, 30, 1, 1), (0, 1, 1, 640, 640, 14, 1, 1), (0, 2, 1, 1024, 1024, 12, 258, 1)],
+@pytest.mark.parametrize("shape", [(0, 2, 1, 1024, 1024, 24, 2, 1), (1, 4, 1, 768, 768, 30, 1, 1), (0, 1, 1, 640, 640, 14, 1, 1), (0, 2, 1, 1024, 1024, 12, 258, 1),
+                                   (0, 2, 1, 1024, 1024, 30, 300, 1), (0, 2, 1, 768, 768, 24, 64, 1), (0, 1, 2, 640, 640, 26, 40, 1)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d" % s[:7])
 def test_reserved_steps_of_wide_layers_cover_fewer(gpu, shape):
-    """Few sequences, or a last pass of few, through wide layers run on tagged words below a number of steps: rnn_model_reserve
+    """Few sequences, or a last pass of few, through wide layers run on tagged words below a number of steps, and more of them on large
+    tiles: rnn_model_reserve
     covers every smaller number of steps, and the results are those of a model that reserved nothing."""
     import torch
     harness, rnn, W = gpu
