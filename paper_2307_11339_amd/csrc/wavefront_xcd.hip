@@ -74,7 +74,7 @@ constexpr int AHEAD_UP = 8;                     // the same for the sequence han
                                                 // to three steps of loads in flight (two buffers and the lead), so that what it marked in a
                                                 // step is known to be done that much later: before the slot in front of it is published
 constexpr uint32_t UNWRITTEN = 0xFFFFFFFFu;
-enum { X_PLAIN, X_BELOW, X_PROJECTED };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
+enum { X_PLAIN, X_PROJECTED, X_BELOW };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
 constexpr int CELL_GRU_RB = 2;                  // GRU, reset gate before the candidate's recurrent product
 
 struct XRBf16 : TraitsBf16 {
@@ -155,6 +155,20 @@ __device__ inline __amdgpu_buffer_rsrc_t uniform_rsrc(const void* p, uint32_t by
                                              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
 }
 
+// K block b of those that a load brought, SEQS sequences of each, in lanes 0 .. SEQS - 1 of every 16.
+template <int SEQS>
+__device__ inline u32x4 rotate(const u32x4& v, int b) {
+    if (b == 0) return v;
+    u32x4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#define ROTATE_BY(k) case k: r[i] = __builtin_amdgcn_mov_dpp(v[i], 0x120 + 16 - k, 0xF, 0xF, true); break;   // row_ror
+        switch (b * SEQS) { ROTATE_BY(2) ROTATE_BY(4) ROTATE_BY(6) ROTATE_BY(8) ROTATE_BY(10) ROTATE_BY(12) ROTATE_BY(14) default: __builtin_unreachable(); }
+#undef ROTATE_BY
+    }
+    return r;
+}
+
 // cell_update with what the compiler makes of it in the tag-in-data kernel spelled out: which of the two products of the new state is
 // rounded by itself.  (With peepholes it makes the same of both kernels.)
 template <int CELL, bool EXT>
@@ -230,7 +244,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     if (g >= p.LP * p.D * p.ncb) return;
     const int ll = g % p.LP, d = (g / p.LP) % p.D, cb = g / (p.LP * p.D);
     const int l = p.l0 + ll, ld = ll * p.D + d;
-    const bool fused = ll > 0;
+    const bool fused = RNN_XR_WIDE < 2 && ll > 0;    // (launches of groups on all XCDs hold one layer)
     const bool project = ll == 0 && p.gx != nullptr;
     const bool last = ll == p.LP - 1;                // writes the layer output; the others hand their state to the layer above
     const int H = p.H, T = p.T, B = p.B;
@@ -313,6 +327,25 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         __syncthreads();
     };
 
+    // Groups on several XCDs, eight sequences or fewer: a load instruction's lanes for the sequences that are not there bring those of
+    // the next K blocks instead, two, four or eight of them, and the fragments are turned into place by rotating lanes (v_mov_dpp, no sums
+    // change).  A wave then asks for its share of the state in one to six loads instead of five to sixteen, so that a request takes less of the
+    // address unit and a vain one is back sooner (64 steps, us, without -> with it: one layer of 768 units, batch 1 / 4 / 8 92.8 / 94.3 /
+    // 96.0 -> 86.9 / 89.3 / 92.4, of 1536, batch 1 / 4 / 8 109 / 112 / 112 -> 99 / 112 / 112, of 2048, batch 1 137 -> 111; 4 of 1024, one sequence, 128
+    // steps 209 -> 191, 198 with the h waves alone).  At 2048 units only eight at a time (four: batch 4 140 -> 143; two do not fit the registers).  Groups
+    // on one XCD wait for the round trip and not for the loads: 512 units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers 78 -> 81 and 80 -> 84.
+    // f(K blocks that a load brings):
+    auto by_sequences = [&](auto f) {
+        constexpr bool PACK = RNN_XR_WIDE;
+        constexpr std::integral_constant<int, (PACK && LN <= 12 ? 2 : 1)> TWO{};
+        constexpr std::integral_constant<int, (PACK && LN <= 12 ? 4 : 1)> FOUR{};
+        constexpr std::integral_constant<int, (PACK ? 8 : 1)> EIGHT{};
+        if (EIGHT > 1 && ncol <= 16 / EIGHT) f(EIGHT);
+        else if (FOUR > 1 && ncol <= 16 / FOUR) f(FOUR);
+        else if (TWO > 1 && ncol <= 16 / TWO) f(TWO);
+        else f(std::integral_constant<int, 1>());
+    };
+
     if (wv >= 4) {
         __builtin_amdgcn_s_setprio(1);
         // ---- x waves: the input product, one step ahead of the h waves ------------------------------
@@ -365,10 +398,12 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // meet, the compiler copies what they loaded, and waits for it there and then (an x from HBM then stops the x wave for its
         // whole latency in every step: 657 us instead of 615 for 2 layers of 512 units, both directions, batch 64, 256 steps).
         constexpr int XBELOW = XLN < LN ? XLN : LN;  // (layers above the first: as many loads as their H takes)
-        auto request_below = [&](int s, u32x4 (&v)[XLN]) {
+        // (with room for PK K blocks in a load, as the h waves bring the state)
+        auto request_below = [&](auto pk, int s, u32x4 (&v)[XLN]) {
+            constexpr int PK = decltype(pk)::value;
             const uint32_t at = (uint32_t)min(s, T - 1) * slot_bytes;
 #pragma unroll
-            for (int i = 0; i < XBELOW; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
+            for (int i = 0; i < (XBELOW + PK - 1) / PK; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
         };
         auto request = [&](auto from, int s, u32x4 (&v)[XLN]) {
             const int sc = min(s, T - 1);
@@ -438,8 +473,9 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         const bool wait_gates = lead && w < RT && ((PRODUCT > 128 && XLN <= LN) || p.LP > 1);
         auto produce = [&](auto from, int sx, u32x4 (&cur)[XLN]) {
             constexpr int FROM = decltype(from)::value;
-            constexpr bool BELOW = FROM == X_BELOW, PROJECTED = FROM == X_PROJECTED;
-            constexpr int XL = PROJECTED ? 1 : BELOW ? XBELOW : XLN;
+            constexpr bool BELOW = FROM >= X_BELOW, PROJECTED = FROM == X_PROJECTED;
+            constexpr int PK = BELOW ? FROM - X_BELOW + 1 : 1;
+            constexpr int XL = PROJECTED ? 1 : BELOW ? (XBELOW + PK - 1) / PK : XLN;
             const int s = sx - lead;                 // between barriers s - 1 and s
             bool sent = s <= 0 || s >= T;
             if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
@@ -453,11 +489,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                         if (!__any(m == UNWRITTEN) || aborted) break;
                         if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
                         if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
-                        request_below(sx, cur);
+                        request_below(std::integral_constant<int, PK>(), sx, cur);
                         asm volatile("" ::: "memory");
                     }
                 }
-                if (!project && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+                if (!BELOW && !project && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
 #pragma unroll
                     for (int i = 0; i < XL; ++i) {
                         const int chunk = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4;
@@ -486,9 +522,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
                     for (int i = 0; i < XL; ++i)
 #pragma unroll
-                        for (int j = 0; j < MPL; ++j)
+                        for (int b = 0; b < PK; ++b) {
+                            if (PK > 1 && i * PK + b >= XBELOW) break;
+                            const u32x4 v = rotate<16 / PK>(cur[i], b);
 #pragma unroll
-                            for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][i * MPL + j], TR::part(cur[i], j), acc[rt]);
+                            for (int j = 0; j < MPL; ++j)
+#pragma unroll
+                                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][(i * PK + b) * MPL + j], TR::part(v, j), acc[rt]);
+                        }
                     // Results of a matrix instruction may be read a number of wait states after it was issued; the compiler
                     // counts them inside a block, but was seen not to where two branches join before the read (fp32, RT = 1).
 #pragma unroll
@@ -506,7 +547,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 if (RB) __syncthreads();
             }
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (BELOW) request_below(sx + 1, cur);
+            if constexpr (BELOW) request_below(std::integral_constant<int, PK>(), sx + 1, cur);
             else request(from, sx + NBUF, cur);
             __builtin_amdgcn_sched_barrier(0);
             if (LATE && !BELOW && s >= 0 && s < T) {
@@ -521,8 +562,20 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // Launches of one layer take one or two loads for it as it is.
         constexpr bool OWN_LOOP = MPL == 1 && LN <= 8 && XLN >= LN && (XLN == 3 || XLN > 4);
         if (fused) {
-            request_below(0, xb[0]);
-            for (int sx = 0; sx < T + lead; ++sx) produce(std::integral_constant<int, X_BELOW>(), sx, xb[0]);
+            auto layer_above = [&](auto pk) {
+                constexpr int PK = decltype(pk)::value;
+                if constexpr (PK > 1) {
+                    const int seqs = 16 / PK;
+#pragma unroll
+                    for (int i = 0; i < (XBELOW + PK - 1) / PK; ++i) {
+                        const int block = min(i * PK + n / seqs, XBELOW - 1);
+                        xoff[i] = ((uint32_t)((TAGGED_ORDER ? w * LN + block : block * 4 + w) * 4 + q) * Bs + min(n & (seqs - 1), ncol - 1)) * 16u;
+                    }
+                }
+                request_below(pk, 0, xb[0]);
+                for (int sx = 0; sx < T + lead; ++sx) produce(std::integral_constant<int, X_BELOW + PK - 1>(), sx, xb[0]);
+            };
+            by_sequences(layer_above);
         } else if (OWN_LOOP && project) {
             constexpr std::integral_constant<int, OWN_LOOP ? X_PROJECTED : X_PLAIN> FROM{};
 #pragma unroll
@@ -569,7 +622,6 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             }
         }
     }
-    const uint32_t hoff = ((uint32_t)(w * LN * 4 + q) * Bs + nc) * 16u;
 
     float c_reg[NOWN], h_reg[NOWN];
     f32x4 bias_reg[NOWN];
@@ -588,20 +640,37 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (p.c0) c_reg[o] = p.c0[state_row * Hu + unit];
         }
     }
-    constexpr int HL = LN > 12 ? LN / 2 : LN;        // B fragments of the state before the step, HL at a time (16 do not fit the
+    // The recurrence with PK K blocks in a load.
+    auto recurrence = [&](auto pk) {
+    constexpr int PK = decltype(pk)::value;
+    constexpr int SEQS = 16 / PK;                    // sequences of a K block that a load brings
+    constexpr int LOADS = (LN + PK - 1) / PK;
+    constexpr int HL = LOADS > 12 ? LOADS / 2 : LOADS;   // loads of the state before the step, HL at a time (16 do not fit the
     u32x4 hv[HL];                                    // registers beside 32 K blocks of weights)
-    u32x4* const h0_rest = turn + 4 * XLN * TURN + (w * 64 + lane) * (LN - HL);   // the other half of h0, read with the first: an
-                                                                                  // output may take its place
+    u32x4* const h0_rest = turn + 4 * XLN * TURN + (w * 64 + lane) * (LOADS - HL);   // the other half of h0, read with the first: an
+                                                                                     // output may take its place
+    // what this lane brings: sequence `mine` of the block, chunk q of K block i * PK + n / SEQS in the order of wh
+    const int mine = min(n & (SEQS - 1), ncol - 1);
+    auto block_of = [&](int i) -> int {
+        const int b = PK == 1 ? i : min(i * PK + n / SEQS, LN - 1);
+        return b + rot >= LN ? b + rot - LN : b + rot;
+    };
+    uint32_t hoff[PK == 1 ? 1 : LOADS];              // byte offset inside a slot (PK = 1: the K block is in the scalar offset)
+    if constexpr (PK == 1) hoff[0] = ((uint32_t)(w * LN * 4 + q) * Bs + mine) * 16u;
+    else {
 #pragma unroll
-    for (int i = 0; i < LN; ++i) {                   // step 0: the caller's h0
-        const int ir = i + rot >= LN ? i + rot - LN : i + rot;
-        const int k = ((w * LN + ir) * 4 + q) * EPC;
+        for (int i = 0; i < LOADS; ++i) hoff[i] = ((uint32_t)((w * LN + block_of(i)) * 4 + q) * Bs + mine) * 16u;
+    }
+    const size_t mine_row = (size_t)(l * p.D + d) * p.state_b + cb * 16 + mine;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {                // step 0: the caller's h0
+        const int k = ((w * LN + block_of(i)) * 4 + q) * EPC;
         float f[EPC];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) f[e] = 0.0f;
         if (p.h0 && k < Hu) {
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) f[e] = p.h0[state_row * Hu + k + e];
+            for (int e = 0; e < EPC; ++e) f[e] = p.h0[mine_row * Hu + k + e];
         }
         if (i < HL) hv[i < HL ? i : 0] = TR::pack(f);
         else h0_rest[i - HL] = TR::pack(f);
@@ -609,11 +678,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     start_wait();
     const bool local = __builtin_amdgcn_readfirstlane((int)lds_get(placed)) != 0;
 
-    auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s, int first) {   // request HL chunks of slot s
+    auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s, int first) {   // request HL loads of slot s
 #pragma unroll
         for (int i = 0; i < HL; ++i) {
-            const int ir = first + i + rot >= LN ? first + i + rot - LN : first + i + rot;
-            hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff, slot_of(s) + (uint32_t)(ir * 64) * Bs, 16);
+            if constexpr (PK == 1) hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[0], slot_of(s) + (uint32_t)(block_of(first + i) * 64) * Bs, 16);
+            else hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[i], slot_of(s), 16);
         }
     };
     // Groups on several XCDs: a wave waits before its first request of a step.  A request that finds a chunk unwritten costs a whole
@@ -646,14 +715,19 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         asm volatile("" ::: "memory");
         return spins;
     };
-    // partial products of this wave's K quarter (of the chunks from `first` on) added to acc
+    // partial products of this wave's K quarter (of the loads from `first` on) added to acc
     auto multiply = [&](f32x4 (&acc)[RT], auto first) {
 #pragma unroll
         for (int i = 0; i < HL; ++i)
 #pragma unroll
-            for (int j = 0; j < MPL; ++j)
+            for (int b = 0; b < PK; ++b) {
+                if ((first + i) * PK + b >= LN) break;
+                const u32x4 v = rotate<SEQS>(hv[i], b);
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][(first + i) * MPL + j], TR::part(hv[i], j), acc[rt]);
+                for (int j = 0; j < MPL; ++j)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][((first + i) * PK + b) * MPL + j], TR::part(v, j), acc[rt]);
+            }
     };
     // all tiles but the wave's own go to LDS
     auto hand_over = [&](const f32x4 (&acc)[RT], int buf) {
@@ -733,7 +807,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (RNN_XR_WIDE) pause = in_vain ? min(pause + PAUSE_MORE, PAUSE_MOST) : max(pause - PAUSE_LESS, 0);
         } else input_part();
         multiply(acc, FRONT);
-        if constexpr (HL < LN) {
+        if constexpr (HL < LOADS) {
             constexpr std::integral_constant<int, HL> REST{};
             if (s > 0) fetch(hrs, s - 1, REST, [] {});
             else {
@@ -766,7 +840,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     publish(rrs, sv, (rb * RT + w + 4 * o) * 4, s);
                 }
             }
-            static_assert(HL == LN, "the reset gate first: no variant of more than 512 units");
+            static_assert(HL == LOADS, "the reset gate first: no variant of more than 512 units");
             fetch(rrs, s, FRONT, [] {});
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -820,6 +894,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (p.cT && GATES == CELL_LSTM) p.cT[state_row * Hu + unit] = c_reg[o];
         }
     }
+    };
+    by_sequences(recurrence);
 }
 
 // Forces one workgroup per compute unit: more than half of the 160 KiB.
