@@ -198,11 +198,12 @@ constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 // turn.  us, a slot a step -> 64 / 16 / 8 slots: 3 layers of 320 units, both directions, 57 sequences, 301 steps 907 -> 804 / 788 / 786;
 // 2 of 512, both directions, batch 64, 256 steps 547 -> 528 / 517 / 518; 2 GRU layers of 256, reset gate first, 64 steps 99.9 -> 99.7 /
 // 92.6 / 99.2).  fp32 launches of one layer gain as well (2 of 256 units, both directions, batch 64, 128 steps 510 -> 472), those of
-// several lose a little (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48, 268 -> 270) and keep a slot a step.  Groups on several XCDs exchange through memory, where a line that other XCDs have
+// several lose a little (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48, 268 -> 270) and keep a slot a step, as do few steps of little
+// state (30 steps: one GRU layer of 128 and 256 units 22.9 -> 23.3 and 26.5 -> 26.8, but of 512 38.3 -> 36.8).  Groups on several XCDs exchange through memory, where a line that other XCDs have
 // read before costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.
 constexpr int XCD_RING = 16;
 int xcd_ring(const rnn_model* m, const Plan& plan, int T) {
-    const bool in_turn = plan.span == 1 && (m->dtype == DT_BF16 || plan.LP == 1);
+    const bool in_turn = plan.span == 1 && (T >= 64 ? m->dtype == DT_BF16 || plan.LP == 1 : m->dtype == DT_BF16 && m->H >= 384);
     const int few = m->compact > 0 ? 2 * XCD_AHEAD : in_turn ? XCD_RING : T + 1;
     return T >= few ? few : T + 1;
 }

@@ -74,7 +74,7 @@ constexpr int AHEAD_UP = 8;                     // the same for the sequence han
                                                 // to three steps of loads in flight (two buffers and the lead), so that what it marked in a
                                                 // step is known to be done that much later: before the slot in front of it is published
 constexpr uint32_t UNWRITTEN = 0xFFFFFFFFu;
-enum { X_PLAIN, X_PROJECTED, X_BELOW };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
+enum { X_PLAIN, X_BELOW, X_PROJECTED };          // where an x wave's input comes from: a finished tensor, the layer below, a projection
 constexpr int CELL_GRU_RB = 2;                  // GRU, reset gate before the candidate's recurrent product
 
 struct XRBf16 : TraitsBf16 {
@@ -187,7 +187,8 @@ __device__ inline float cell_update_tagged(const float a[SLOTS], float h_prev, f
 // LN / XLN: 16-byte chunks a lane loads per wave of the state / of the layer input (a wave's quarter of H is 4 * EPC * LN
 // units; K blocks of the input are dealt to the waves in turn, and those beyond its width get zero weights).  The first layer
 // of a launch may have its input product done by a projection launch (p.gx): its x waves then only bring that in.
-template <class TR, int CELL, int RT, int LN, int XLN, bool EXT, bool APART>
+// PK: K blocks that a load of the state brings (see packed_blocks).
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT, bool APART, int PK>
 __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) {
     constexpr bool RB = CELL == CELL_GRU_RB;
     constexpr int GATES = RB ? CELL_GRU : CELL;
@@ -327,25 +328,6 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         __syncthreads();
     };
 
-    // Groups on several XCDs, eight sequences or fewer: a load instruction's lanes for the sequences that are not there bring those of
-    // the next K blocks instead, two, four or eight of them, and the fragments are turned into place by rotating lanes (v_mov_dpp, no sums
-    // change).  A wave then asks for its share of the state in one to six loads instead of five to sixteen, so that a request takes less of the
-    // address unit and a vain one is back sooner (64 steps, us, without -> with it: one layer of 768 units, batch 1 / 4 / 8 92.8 / 94.3 /
-    // 96.0 -> 86.9 / 89.3 / 92.4, of 1536, batch 1 / 4 / 8 109 / 112 / 112 -> 99 / 112 / 112, of 2048, batch 1 137 -> 111; 4 of 1024, one sequence, 128
-    // steps 209 -> 191, 198 with the h waves alone).  At 2048 units only eight at a time (four: batch 4 140 -> 143; two do not fit the registers).  Groups
-    // on one XCD wait for the round trip and not for the loads: 512 units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers 78 -> 81 and 80 -> 84.
-    // f(K blocks that a load brings):
-    auto by_sequences = [&](auto f) {
-        constexpr bool PACK = RNN_XR_WIDE;
-        constexpr std::integral_constant<int, (PACK && LN <= 12 ? 2 : 1)> TWO{};
-        constexpr std::integral_constant<int, (PACK && LN <= 12 ? 4 : 1)> FOUR{};
-        constexpr std::integral_constant<int, (PACK ? 8 : 1)> EIGHT{};
-        if (EIGHT > 1 && ncol <= 16 / EIGHT) f(EIGHT);
-        else if (FOUR > 1 && ncol <= 16 / FOUR) f(FOUR);
-        else if (TWO > 1 && ncol <= 16 / TWO) f(TWO);
-        else f(std::integral_constant<int, 1>());
-    };
-
     if (wv >= 4) {
         __builtin_amdgcn_s_setprio(1);
         // ---- x waves: the input product, one step ahead of the h waves ------------------------------
@@ -398,12 +380,18 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // meet, the compiler copies what they loaded, and waits for it there and then (an x from HBM then stops the x wave for its
         // whole latency in every step: 657 us instead of 615 for 2 layers of 512 units, both directions, batch 64, 256 steps).
         constexpr int XBELOW = XLN < LN ? XLN : LN;  // (layers above the first: as many loads as their H takes)
-        // (with room for PK K blocks in a load, as the h waves bring the state)
-        auto request_below = [&](auto pk, int s, u32x4 (&v)[XLN]) {
-            constexpr int PK = decltype(pk)::value;
+        constexpr int XPACKED = (XBELOW + PK - 1) / PK;   // ... several K blocks each, as the h waves bring the state
+        if (PK > 1 && fused) {
+#pragma unroll
+            for (int i = 0; i < XPACKED; ++i) {
+                const int block = min(i * PK + n / (16 / PK), XBELOW - 1);
+                xoff[i] = ((uint32_t)((TAGGED_ORDER ? w * LN + block : block * 4 + w) * 4 + q) * Bs + min(n & (16 / PK - 1), ncol - 1)) * 16u;
+            }
+        }
+        auto request_below = [&](int s, u32x4 (&v)[XLN]) {
             const uint32_t at = (uint32_t)min(s, T - 1) * slot_bytes;
 #pragma unroll
-            for (int i = 0; i < (XBELOW + PK - 1) / PK; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
+            for (int i = 0; i < XPACKED; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(brs, xoff[i], at, 16);
         };
         auto request = [&](auto from, int s, u32x4 (&v)[XLN]) {
             const int sc = min(s, T - 1);
@@ -473,9 +461,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         const bool wait_gates = lead && w < RT && ((PRODUCT > 128 && XLN <= LN) || p.LP > 1);
         auto produce = [&](auto from, int sx, u32x4 (&cur)[XLN]) {
             constexpr int FROM = decltype(from)::value;
-            constexpr bool BELOW = FROM >= X_BELOW, PROJECTED = FROM == X_PROJECTED;
-            constexpr int PK = BELOW ? FROM - X_BELOW + 1 : 1;
-            constexpr int XL = PROJECTED ? 1 : BELOW ? (XBELOW + PK - 1) / PK : XLN;
+            constexpr bool BELOW = FROM == X_BELOW, PROJECTED = FROM == X_PROJECTED;
+            constexpr int XL = PROJECTED ? 1 : BELOW ? XPACKED : XLN;
             const int s = sx - lead;                 // between barriers s - 1 and s
             bool sent = s <= 0 || s >= T;
             if (!lead && OUT_FIRST && !sent) { forward(s - 1); sent = true; }
@@ -489,11 +476,11 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                         if (!__any(m == UNWRITTEN) || aborted) break;
                         if (!lead && !sent) { forward(s - 1); sent = true; }   // nothing to multiply yet
                         if ((++spins & 63u) == 0u || spins == 8u) give_up(spins);
-                        request_below(std::integral_constant<int, PK>(), sx, cur);
+                        request_below(sx, cur);
                         asm volatile("" ::: "memory");
                     }
                 }
-                if (!BELOW && !project && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+                if (!project && !(BELOW && PK > 1) && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
 #pragma unroll
                     for (int i = 0; i < XL; ++i) {
                         const int chunk = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4;
@@ -520,16 +507,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                     }
                 } else {
 #pragma unroll
-                    for (int i = 0; i < XL; ++i)
+                    for (int i = 0; i < (BELOW ? XBELOW : XL); ++i) {
+                        const u32x4 v = BELOW && PK > 1 ? rotate<16 / PK>(cur[i / PK], i % PK) : cur[i];
 #pragma unroll
-                        for (int b = 0; b < PK; ++b) {
-                            if (PK > 1 && i * PK + b >= XBELOW) break;
-                            const u32x4 v = rotate<16 / PK>(cur[i], b);
+                        for (int j = 0; j < MPL; ++j)
 #pragma unroll
-                            for (int j = 0; j < MPL; ++j)
-#pragma unroll
-                                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][(i * PK + b) * MPL + j], TR::part(v, j), acc[rt]);
-                        }
+                            for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wx[rt][i * MPL + j], TR::part(v, j), acc[rt]);
+                    }
                     // Results of a matrix instruction may be read a number of wait states after it was issued; the compiler
                     // counts them inside a block, but was seen not to where two branches join before the read (fp32, RT = 1).
 #pragma unroll
@@ -547,7 +531,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                 if (RB) __syncthreads();
             }
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (BELOW) request_below(std::integral_constant<int, PK>(), sx + 1, cur);
+            if constexpr (BELOW) request_below(sx + 1, cur);
             else request(from, sx + NBUF, cur);
             __builtin_amdgcn_sched_barrier(0);
             if (LATE && !BELOW && s >= 0 && s < T) {
@@ -562,20 +546,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // Launches of one layer take one or two loads for it as it is.
         constexpr bool OWN_LOOP = MPL == 1 && LN <= 8 && XLN >= LN && (XLN == 3 || XLN > 4);
         if (fused) {
-            auto layer_above = [&](auto pk) {
-                constexpr int PK = decltype(pk)::value;
-                if constexpr (PK > 1) {
-                    const int seqs = 16 / PK;
-#pragma unroll
-                    for (int i = 0; i < (XBELOW + PK - 1) / PK; ++i) {
-                        const int block = min(i * PK + n / seqs, XBELOW - 1);
-                        xoff[i] = ((uint32_t)((TAGGED_ORDER ? w * LN + block : block * 4 + w) * 4 + q) * Bs + min(n & (seqs - 1), ncol - 1)) * 16u;
-                    }
-                }
-                request_below(pk, 0, xb[0]);
-                for (int sx = 0; sx < T + lead; ++sx) produce(std::integral_constant<int, X_BELOW + PK - 1>(), sx, xb[0]);
-            };
-            by_sequences(layer_above);
+            request_below(0, xb[0]);
+            for (int sx = 0; sx < T + lead; ++sx) produce(std::integral_constant<int, X_BELOW>(), sx, xb[0]);
         } else if (OWN_LOOP && project) {
             constexpr std::integral_constant<int, OWN_LOOP ? X_PROJECTED : X_PLAIN> FROM{};
 #pragma unroll
@@ -622,6 +594,19 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             }
         }
     }
+    constexpr int LOADS = (LN + PK - 1) / PK;
+    constexpr int HL = LOADS > 12 ? LOADS / 2 : LOADS;   // loads of the state before the step, HL at a time (16 do not fit the
+                                                     // registers beside 32 K blocks of weights)
+    // With PK > 1 a lane brings sequence n % SEQS of K block i * PK + n / SEQS (in the order of wh) in load i.
+    constexpr int SEQS = 16 / PK;
+    const int own_seq = PK == 1 ? nc : min(n & (SEQS - 1), ncol - 1);
+    auto block_of = [&](int i) -> int {
+        const int b = PK == 1 ? i : min(i * PK + n / SEQS, LN - 1);
+        return b + rot >= LN ? b + rot - LN : b + rot;
+    };
+    uint32_t hoff[PK == 1 ? 1 : LOADS];              // byte offset inside a slot (PK = 1: without the K block)
+#pragma unroll
+    for (int i = 0; i < (PK == 1 ? 1 : LOADS); ++i) hoff[i] = ((uint32_t)((w * LN + (PK == 1 ? 0 : block_of(i))) * 4 + q) * Bs + own_seq) * 16u;
 
     float c_reg[NOWN], h_reg[NOWN];
     f32x4 bias_reg[NOWN];
@@ -640,28 +625,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (p.c0) c_reg[o] = p.c0[state_row * Hu + unit];
         }
     }
-    // The recurrence with PK K blocks in a load.
-    auto recurrence = [&](auto pk) {
-    constexpr int PK = decltype(pk)::value;
-    constexpr int SEQS = 16 / PK;                    // sequences of a K block that a load brings
-    constexpr int LOADS = (LN + PK - 1) / PK;
-    constexpr int HL = LOADS > 12 ? LOADS / 2 : LOADS;   // loads of the state before the step, HL at a time (16 do not fit the
-    u32x4 hv[HL];                                    // registers beside 32 K blocks of weights)
+    u32x4 hv[HL];                                    // B fragments of the state before the step, or PK of them each
     u32x4* const h0_rest = turn + 4 * XLN * TURN + (w * 64 + lane) * (LOADS - HL);   // the other half of h0, read with the first: an
                                                                                      // output may take its place
-    // what this lane brings: sequence `mine` of the block, chunk q of K block i * PK + n / SEQS in the order of wh
-    const int mine = min(n & (SEQS - 1), ncol - 1);
-    auto block_of = [&](int i) -> int {
-        const int b = PK == 1 ? i : min(i * PK + n / SEQS, LN - 1);
-        return b + rot >= LN ? b + rot - LN : b + rot;
-    };
-    uint32_t hoff[PK == 1 ? 1 : LOADS];              // byte offset inside a slot (PK = 1: the K block is in the scalar offset)
-    if constexpr (PK == 1) hoff[0] = ((uint32_t)(w * LN * 4 + q) * Bs + mine) * 16u;
-    else {
-#pragma unroll
-        for (int i = 0; i < LOADS; ++i) hoff[i] = ((uint32_t)((w * LN + block_of(i)) * 4 + q) * Bs + mine) * 16u;
-    }
-    const size_t mine_row = (size_t)(l * p.D + d) * p.state_b + cb * 16 + mine;
+    const size_t own_row = PK == 1 ? state_row : (size_t)(l * p.D + d) * p.state_b + cb * 16 + own_seq;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {                // step 0: the caller's h0
         const int k = ((w * LN + block_of(i)) * 4 + q) * EPC;
@@ -670,7 +637,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         for (int e = 0; e < EPC; ++e) f[e] = 0.0f;
         if (p.h0 && k < Hu) {
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) f[e] = p.h0[mine_row * Hu + k + e];
+            for (int e = 0; e < EPC; ++e) f[e] = p.h0[own_row * Hu + k + e];
         }
         if (i < HL) hv[i < HL ? i : 0] = TR::pack(f);
         else h0_rest[i - HL] = TR::pack(f);
@@ -682,7 +649,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 #pragma unroll
         for (int i = 0; i < HL; ++i) {
             if constexpr (PK == 1) hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[0], slot_of(s) + (uint32_t)(block_of(first + i) * 64) * Bs, 16);
-            else hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[i], slot_of(s), 16);
+            else hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[first + i], slot_of(s), 16);
         }
     };
     // Groups on several XCDs: a wave waits before its first request of a step.  A request that finds a chunk unwritten costs a whole
@@ -695,12 +662,13 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     // (retries in 0 to 30 % of the steps, 600 clocks each); there such pauses made 12 narrow layers 2 to 13 % longer and little shorter.
     constexpr int PAUSE_MORE = 32, PAUSE_LESS = 1, PAUSE_FIRST = 8 * 16, PAUSE_MOST = 64 * 16;   // sixteenths of a round of the loop, about 40 clocks
     int pause = PAUSE_FIRST;
+    unsigned in_vain = 0;                            // requests of the last fetch that found a chunk unwritten
     auto hold_back = [&]() {
         for (int i = __builtin_amdgcn_readfirstlane(pause) >> 4; i > 0; --i) asm volatile("s_nop 7");
     };
     // The chunks of slot s from `first` on in hv, waiting until all of them have been written; `meanwhile` runs while the first
-    // request travels.  Returns how often they were asked for in vain.
-    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, int first, auto meanwhile) -> unsigned {
+    // request travels.
+    auto fetch = [&](__amdgpu_buffer_rsrc_t rs, int s, int first, auto meanwhile) {
         unsigned spins = 0;
         for (;;) {
             ask(rs, s, first);
@@ -713,21 +681,19 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             asm volatile("" ::: "memory");
         }
         asm volatile("" ::: "memory");
-        return spins;
+        if (RNN_XR_WIDE) in_vain = spins;
     };
     // partial products of this wave's K quarter (of the loads from `first` on) added to acc
     auto multiply = [&](f32x4 (&acc)[RT], auto first) {
 #pragma unroll
-        for (int i = 0; i < HL; ++i)
+        for (int i = 0; i < HL * PK; ++i) {
+            if (PK > 1 && first * PK + i >= LN) break;
+            const u32x4 v = PK == 1 ? hv[i] : rotate<SEQS>(hv[i / PK], i % PK);
 #pragma unroll
-            for (int b = 0; b < PK; ++b) {
-                if ((first + i) * PK + b >= LN) break;
-                const u32x4 v = rotate<SEQS>(hv[i], b);
+            for (int j = 0; j < MPL; ++j)
 #pragma unroll
-                for (int j = 0; j < MPL; ++j)
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][((first + i) * PK + b) * MPL + j], TR::part(v, j), acc[rt]);
-            }
+                for (int rt = 0; rt < RT; ++rt) acc[rt] = TR::mfma(wh[rt][(first * PK + i) * MPL + j], TR::part(v, j), acc[rt]);
+        }
     };
     // all tiles but the wave's own go to LDS
     auto hand_over = [&](const f32x4 (&acc)[RT], int buf) {
@@ -803,7 +769,7 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         constexpr std::integral_constant<int, 0> FRONT{};
         if (s > 0) {
             if (RNN_XR_WIDE) hold_back();
-            const unsigned in_vain = fetch(hrs, s - 1, FRONT, input_part);
+            fetch(hrs, s - 1, FRONT, input_part);
             if (RNN_XR_WIDE) pause = in_vain ? min(pause + PAUSE_MORE, PAUSE_MOST) : max(pause - PAUSE_LESS, 0);
         } else input_part();
         multiply(acc, FRONT);
@@ -894,8 +860,6 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
             if (p.cT && GATES == CELL_LSTM) p.cT[state_row * Hu + unit] = c_reg[o];
         }
     }
-    };
-    by_sequences(recurrence);
 }
 
 // Forces one workgroup per compute unit: more than half of the 160 KiB.
@@ -903,12 +867,12 @@ constexpr size_t MIN_LDS = 84 * 1024;
 
 constexpr bool apart(int MPL, int LN) { return MPL > 1 || RNN_XR_WIDE || RNN_XR_APART; }
 
-template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT, int PK>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     const size_t need = (size_t)((RT == 4 ? 6 : 8) + 8) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
                         9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16 + (LN > 12 ? (size_t)4 * 64 * (LN / 2) * 16 : 0);
     const size_t smem = need < MIN_LDS ? MIN_LDS : need;
-    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT, apart(TR::MPL, LN)>;
+    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT, apart(TR::MPL, LN), PK>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -919,13 +883,35 @@ hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// K blocks that a load brings, in the groups on several XCDs that have variants for it.  With eight sequences or fewer a load instruction's
+// lanes for the sequences that are not there bring those of the next K blocks instead, two, four or eight of them, and the fragments are turned
+// into place by rotating lanes (v_mov_dpp; no sum changes).  A wave then asks for its share of the state in one to six loads instead of five to
+// sixteen, so that a request takes less of the address unit and a vain one is back sooner (64 steps, us, without -> with it: one layer of 768
+// units, batch 1 / 4 / 8 93.4 / 94.9 / 96.1 -> 87.5 / 89.8 / 92.4, of 1536 109 / 112 / 112 -> 98 / 109 / 109, of 2048, batch 1 129 -> 107; 4
+// layers of 1024, one sequence, 128 steps 209 -> 189, 198 with the h waves alone).  Groups on one XCD wait for the round trip and not for the loads: 512
+// units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers 78 -> 81 and 80 -> 84.
+int packed_blocks(int B) { return B <= 2 ? 8 : B <= 4 ? 4 : B <= 8 ? 2 : 1; }
+
+template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
+hipError_t launch_packed(const WavefrontXcdArgs& a, hipStream_t stream) {
+#if RNN_XR_WIDE
+    switch (packed_blocks(a.B)) {
+        case 8: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 8>(a, stream);
+        case 4: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 4>(a, stream);
+        case 2: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 2>(a, stream);
+        default: break;
+    }
+#endif
+    return launch_variant<TR, CELL, RT, LN, XLN, EXT, 1>(a, stream);
+}
+
 template <class TR, int RT, int LN, int XLN>
 hipError_t launch_cell(const WavefrontXcdArgs& a, hipStream_t stream) {
 #if RNN_XR_KIND == 2
-    return launch_variant<TR, CELL_GRU_RB, RT, LN, XLN, true>(a, stream);
+    return launch_packed<TR, CELL_GRU_RB, RT, LN, XLN, true>(a, stream);
 #else
-    if (a.cell == CELL_LSTM) return launch_variant<TR, CELL_LSTM, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
-    return launch_variant<TR, CELL_GRU, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
+    if (a.cell == CELL_LSTM) return launch_packed<TR, CELL_LSTM, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
+    return launch_packed<TR, CELL_GRU, RT, LN, XLN, RNN_XR_KIND == 1>(a, stream);
 #endif
 }
 

@@ -75,10 +75,18 @@ SHAPES = [
     (0, 2, 1, 1032, 768, 9, 8, 1),      # several layers behind a projection, six chunk loads a wave: a loop of one load
     (1, 3, 1, 40, 384, 7, 17, 1),       # ... three
     (0, 2, 1, 80, 1024, 6, 16, 1),      # ... eight
-    (0, 1, 2, 64, 256, 15, 18, 1),      # one step fewer than the slots of a sequence that are used in turn,
-    (1, 2, 1, 128, 128, 16, 9, 1),      # as many,
+    (0, 3, 1, 640, 640, 24, 1, 1),      # few sequences: eight K blocks a load, of five
+    (1, 4, 1, 640, 640, 10, 3, 1),      # ... four, a load of one behind it
+    (0, 2, 1, 768, 768, 9, 7, 1),       # ... two
+    (0, 1, 1, 1280, 1280, 6, 2, 1),     # ... eight, of ten
+    (1, 1, 1, 64, 1536, 9, 8, 1),       # ... two
+    (0, 1, 1, 2048, 2048, 6, 8, 1),
+    (0, 1, 1, 2048, 2048, 5, 4, 1),
+    (0, 1, 2, 64, 384, 15, 18, 1),      # one step fewer than the slots of a sequence that are used in turn,
+    (1, 2, 1, 400, 400, 16, 9, 1),      # as many,
     (0, 1, 1, 128, 512, 17, 20, 1),     # one more,
-    (1, 1, 2, 64, 128, 33, 17, 0),      # twice as many and one
+    (1, 1, 2, 64, 128, 65, 17, 0),      # four times as many and one, fp32
+    (1, 2, 1, 128, 256, 64, 5, 1),      # the fewest steps that narrower layers take in turn
 ]
 
 
