@@ -260,9 +260,12 @@ bool choose_xcd(const rnn_model* m, int T, int B, Plan& plan) {
 // tags to strip and without staging.  A launch costs some 5 us more than one of tagged words, a step a tenth to a half less, so that
 // calls of few steps stay there where it takes at most four loads a wave for the state of a step, B * H <= 4096: of a line through 117
 // shapes with 4 to 32 steps, what lies on this side is up to half as long, 2 % longer at most.  64 steps, us, tag-in-data -> this:
-//     1 x 640 units    batch 1 136 -> 91, 2 148 -> 91, 4 159 -> 91;    4 x 640 units    121 -> 118, 128 -> 118, 130 -> 119
-//     2 x 768 units    batch 1 123 -> 100, 4 129 -> 101;               both directions, 48 steps 189 -> 159, 203 -> 162
-//     1 x 1024 units   batch 1 126 -> 103, 2 133 -> 103, 4 138 -> 106; 4 x 1024 units   130 -> 124, 148 -> 124, 160 -> 123
+//     1 x 640 units    batch 1 136 -> 84, 2 147 -> 84, 4 158 -> 85;    4 x 640 units    122 -> 110, 128 -> 110, 131 -> 112
+//     2 x 768 units    batch 1 122 -> 93, 4 129 -> 96;                both directions, 48 steps 189 -> 151, 203 -> 154
+//     1 x 1024 units   batch 1 126 -> 94, 2 133 -> 95, 4 138 -> 99;   4 x 1024 units   129 -> 116, 147 -> 116, 160 -> 122
+//     4 x 1024 units   batch 6 196 -> 127, 8 219 -> 126, 12 256 -> 130, 16 313 -> 131;   2 x 1024, batch 16 and 32 256 -> 116, 281 -> 119
+//     4 x 768 units    batch 6 170 -> 113, 8 177 -> 114, 16 270 -> 120;   2 x 640, batch 8 and 16 165 -> 95, 210 -> 100
+// and, from before its loads brought several K blocks each,
 //     8 steps, 2 x 1024 batch 1 1.11 times as long, 2 1.00, 4 0.98; 4 x 1024 1.10, 0.89, 0.83; 1 x 640 1.00, 0.92, 0.89
 constexpr int XCD_WIDE_STEPS[] = {8, 12, 24};   // the fewest steps: several sequences; one, through one layer a launch; through several
 bool xcd_wide_pays(const rnn_model* m, int T, int B, int LP) {
@@ -284,9 +287,9 @@ bool choose_xcd_wide(const rnn_model* m, int T, int B, int LP, Plan& plan) {
 
 // The same with a group on all eight XCDs: bf16 layers of 1280, 1536 and 2048 units, 8 units a workgroup, one block of 16 sequences
 // and one layer in a launch.  A test of fit: faster than tagged words at every batch (2 layers, 48 steps, us, tagged words -> this):
-//     1280 units   batch 1 273 -> 221, 4 336 -> 223, 8 420 -> 220, 16 541 -> 224, 32 (two passes) 1091 -> 447
-//     1536 units   batch 1 283 -> 240, 4 452 -> 243, 8 523 -> 234, 16 656 -> 243
-//     2048 units   batch 1 346 -> 263, 4 1067 -> 269, 8 1187 -> 282, 16 1466 -> 302, 64 (four passes) 5890 -> 1172
+//     1280 units   batch 1 273 -> 145, 4 336 -> 152, 8 420 -> 149, 16 541 -> 173, 32 (two passes) 1091 -> 346
+//     1536 units   batch 1 283 -> 153, 4 452 -> 162, 8 523 -> 165, 16 656 -> 185
+//     2048 units   batch 1 346 -> 174, 4 1067 -> 195, 8 1187 -> 200, 16 1466 -> 229, 64 (four passes) 5890 -> 916
 bool choose_xcd_chip(const rnn_model* m, int T, int B, Plan& plan) {
     const int RT = 2, nrb = m->H / (RT * 4);
     if (m->compact < 0 || m->D != 1 || B > 16 || !xcd_addressable(m, T, B)) return false;

@@ -14,11 +14,12 @@
 // than one uses device-scope stores instead.
 // A bf16 layer of 640 to 1024 units needs more workgroups than an XCD has compute units: its group is laid over two, always with
 // device-scope stores.  What that still gains over tagged words (half the bytes, MFMA fragments straight from the load) stands at
-// the rule that chooses it; 16 sequences through one layer of 1024 units take 2.6 us a step instead of 4.
+// the rule that chooses it; 16 sequences through a layer of 1024 units take 1.7 us a step, one 1.4 (tagged words 4 and 1.9).
 // Layers of 1280 to 2048 units are laid over all eight, 8 units a workgroup (160 to 256 of them, one layer in a launch): every
 // workgroup brings in the whole state, 16 sequences x 3 KiB at 1536 units, 9.4 MiB a step over the chip, 93 % of the requests found in
-// the L2s, and a step takes 2.2 to 2.4 us at any batch up to 16 (tagged words 2.9 to 6.8).  At 2048 units the state comes in two
-// halves, one after the other: its fragments do not all fit the registers beside the weights (2.9 us).
+// the L2s, and a step takes 1.5 (one sequence) to 1.9 us (16; tagged words 2.9 to 6.8).  At 2048 units the state of more than eight
+// sequences comes in two halves, one after the other: its fragments do not all fit the registers beside the weights (2.3 us).
+// What such a group waits for most is a poll that came too early (see PAUSE_MORE).
 //
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
 // the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B
@@ -35,11 +36,14 @@
 // LDS, so that no store other than the state itself stands before the next poll of an h wave.
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
-// What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz, each with the stamp that took it): fetch of the state 820
-// (16 KiB into every compute unit, its 32 load instructions with those of the x waves behind an L2 round trip of 400; one of four
-// as much state takes 440), products 350, barrier 200, sum over the quarters 240, gates 370, publication 150: 0.89 of the 1.15 us that a
-// step takes (what lies between the stamps was not taken apart); the tag-in-data kernel took 2.5 us here.  Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
-// batch 64, 256 steps 1.29 -> 0.62 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64
+// What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz, each with its stamp of some 40; the slots of the state used in
+// turn): from the tile's sums to the request of the next state 590 (gather, store, mark, tile to the x waves, loop), the state 620 (880 with a
+// slot for every step; the same with one load instead of four and without the loads of the x waves, so that it is a round trip and no
+// queue), products 290, partial sums to LDS 120, barrier 190, sum 225, gates 330.  Asking sooner behind the publication makes
+// polls fail (20 to 90 %, 600 clocks each): 5 to 45 % longer.  Multiplying what has come while the rest travels: 0 to 33 % longer, since vain
+// products hold up the next poll.  Words in LDS instead of the barrier: 0 to 12 % longer; input asked for behind the state instead of behind the barrier: 3 to 15 %.
+// Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
+// batch 64, 256 steps 1.29 -> 0.55 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64
 // units 159 -> 103 us; 2 fp32 layers of 512 units at batch 64 1.15 -> 0.63 ms; GRU with the reset gate before the product (one
 // launch per cell part without it) 1719 -> 98 us.
 #include "wf_traits.h"
