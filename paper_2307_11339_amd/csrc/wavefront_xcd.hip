@@ -664,7 +664,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     // 147 / 167 -> 110 / 123, of 2048 183 / 204 -> 149 / 162.  Other choices (sixteenths more, sixteenths less, at first): 16, 1, 10 up to 3 %
     // longer, 48, 1, 8 the same, 96, 1, 0 and the best constant of each shape 1 to 10 % longer.  Within one XCD the loop as it is is late enough
     // (retries in 0 to 30 % of the steps, 600 clocks each); there such pauses made 12 narrow layers 2 to 13 % longer and little shorter.
-    constexpr int PAUSE_MORE = 32, PAUSE_LESS = 1, PAUSE_FIRST = 8 * 16, PAUSE_MOST = 64 * 16;   // sixteenths of a round of the loop, about 40 clocks
+    // Sixteenths of a round of the loop, about 40 clocks.  (640 and 768 units, their fewer workgroups sooner through: 32, 1, 8 -> 24, 1, 5, 64 steps, us,
+    // one layer, batch 1 and 8 85.1 and 90.1 -> 82.1 and 85.8, 87.1 and 91.3 -> 82.8 and 87.3; four, batch 2 and 12 111 and 117 -> 112 and 107, 106 and
+    // 118 -> 107 and 112.  Of 1024 units one layer gains 3 % by it, several lose 2 to 7, wider ones 0 to 3.)
+    constexpr int PAUSE_MORE = LN <= 6 ? 24 : 32, PAUSE_LESS = 1, PAUSE_FIRST = (LN <= 6 ? 5 : 8) * 16, PAUSE_MOST = 64 * 16;
     int pause = PAUSE_FIRST;
     unsigned in_vain = 0;                            // requests of the last fetch that found a chunk unwritten
     auto hold_back = [&]() {
