@@ -201,14 +201,20 @@ constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 // several lose a little (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48, 268 -> 270) and keep a slot a step, as do few steps of little
 // state (30 steps: one GRU layer of 128 and 256 units 22.9 -> 23.3 and 26.5 -> 26.8, but of 512 38.3 -> 36.8).  Groups on several XCDs exchange through memory, where a line that other XCDs have
 // read before costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.
-constexpr int XCD_RING = 16;
+constexpr int XCD_RING = 16, XCD_RING_STEPS = 64;
 int xcd_ring(const rnn_model* m, const Plan& plan, int T) {
-    const bool in_turn = plan.span == 1 && (T >= 64 ? m->dtype == DT_BF16 || plan.LP == 1 : m->dtype == DT_BF16 && m->H >= 384);
+    const bool in_turn = plan.span == 1 && (T >= XCD_RING_STEPS ? m->dtype == DT_BF16 || plan.LP == 1 : m->dtype == DT_BF16 && m->H >= 384);
     const int few = m->compact > 0 ? 2 * XCD_AHEAD : in_turn ? XCD_RING : T + 1;
     return T >= few ? few : T + 1;
 }
-// Slots that the workspace holds.  The static array holds one for every step unless compact: what fits it stays what it was.
-int xcd_slots(const rnn_model* m, const Plan& plan, int T) { return m->arena.on && m->compact <= 0 ? T : std::min(xcd_ring(m, plan, T), T); }
+// Slots that the workspace holds: as many as any call of up to T steps uses, so that a shorter call never outgrows what a longer one was
+// given (below XCD_RING_STEPS steps a slot each can be more than the few that more steps use in turn).  The static array is laid out for
+// every call by itself and holds a slot for every step unless compact: what fits it stays what it was.
+int xcd_slots(const rnn_model* m, const Plan& plan, int T) {
+    if (m->arena.on && m->compact <= 0) return T;
+    const int slots = std::min(xcd_ring(m, plan, T), T), below = XCD_RING_STEPS - 1;
+    return m->arena.on || T <= below ? slots : std::max(slots, std::min(xcd_ring(m, plan, below), below));
+}
 
 // Sequences side by side in a chunk row of its state sequences (WavefrontXcdArgs::stride): 4, 8 or 16, so that a workgroup's
 // chunks start a half or a whole cache line of their own.  With B side by side, workgroups that share a line hold up each other's

@@ -450,6 +450,78 @@ def test_reserved_steps_of_wide_layers_cover_fewer(gpu, shape):
     kept.close()
 
 
+def _call(rnn, model, io, T, B):
+    import torch
+    return rnn.rnn_forward(model.handle, io.x, None, io.h0, io.c0, io.y, io.hT, io.cT, T, B, torch.cuda.current_stream())
+
+
+def _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, steps):
+    """Calls of `steps` after one of more steps, recorded into a graph (which refuses to grow the workspace): the bits of a model of
+    their own, nothing allocated, and a graph of the longer call, recorded before them, still gives what it gave."""
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, False)
+    c = wl.cfg
+
+    def model_of():
+        m = harness.DeviceModel(wl)
+        assert rnn.rnn_model_set_gru_reset_before(m.handle, reset_before) == rnn.RNN_OK
+        return m
+
+    def recorded(m, io, T):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            rc = _call(rnn, m, io, T, c.B)
+        assert rc == rnn.RNN_OK, "%d steps: %s" % (T, rnn.rnn_status_string(rc))
+        return graph
+
+    side = torch.cuda.Stream()
+    kept, io, io_long, other = model_of(), harness.DeviceIO(wl), harness.DeviceIO(wl), harness.DeviceIO(wl)
+    want = {}
+    for T in steps:                              # (and the one-time set-up of the kernels)
+        fresh = model_of()
+        assert _call(rnn, fresh, other, T, c.B) == rnn.RNN_OK
+        torch.cuda.synchronize()
+        want[T] = (other.y[:T].clone(), other.hT.clone())
+        fresh.close()
+    if reserved:
+        assert rnn.rnn_model_reserve(kept.handle, c.T, c.B) == rnn.RNN_OK
+    assert _call(rnn, kept, io_long, c.T, c.B) == rnn.RNN_OK
+    torch.cuda.synchronize()
+    y, hT = io_long.y.clone(), io_long.hT.clone()
+    held = rnn.rnn_model_device_bytes(kept.handle)
+    long_graph = recorded(kept, io_long, c.T)
+    for T in steps:
+        print("\n  case %r: %d steps" % (shape, T), flush=True)
+        graph = recorded(kept, io, T)
+        for _ in range(2):
+            io.y.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(io.y[:T], want[T][0]) and torch.equal(io.hT, want[T][1])
+        assert _call(rnn, kept, io, T, c.B) == rnn.RNN_OK
+        torch.cuda.synchronize()
+        assert torch.equal(io.y[:T], want[T][0]) and torch.equal(io.hT, want[T][1])
+        assert rnn.rnn_model_device_bytes(kept.handle) == held
+        io_long.y.fill_(7.0)
+        long_graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(io_long.y, y) and torch.equal(io_long.hT, hT)
+        del graph
+    assert rnn.rnn_model_check(kept.handle) == rnn.RNN_OK
+    del long_graph
+    kept.close()
+
+
+@pytest.mark.parametrize("reserved", [True, False], ids=["reserved", "after_a_call"])
+@pytest.mark.parametrize("shape,reset_before", [((1, 2, 1, 256, 256, 64, 9, 1), 0), ((1, 2, 1, 256, 256, 301, 16, 1), 1), ((0, 2, 1, 128, 128, 301, 3, 1), 0),
+                                                ((0, 2, 2, 128, 128, 64, 18, 0), 0), ((0, 1, 1, 512, 512, 80, 20, 0), 0), ((0, 2, 1, 512, 512, 64, 5, 1), 0)],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)) if isinstance(s, tuple) else "rb%d" % s)
+def test_slots_in_turn_cover_fewer_steps(gpu, shape, reset_before, reserved):
+    """From 64 steps on a state sequence may use few slots in turn, below a slot for every step: the workspace holds the larger of both."""
+    _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, (1, 15, 16, 17, 40, 63))
+
+
 @pytest.mark.parametrize("shape,digest", [((0, 2, 1, 1536, 1536, 24, 8, 1), "4ab4e57c91be3f6a"), ((1, 1, 1, 640, 1280, 20, 16, 1), "7776007b4d984933"),
                                           ((0, 1, 1, 1544, 1536, 12, 3, 1), "05ed68978cff64da"),
                                           ((0, 2, 1, 1024, 1024, 24, 4, 1), "f3f474cdc2c0e4ce"), ((1, 4, 1, 768, 768, 30, 1, 1), "38bee8ffcfaf741c"),
