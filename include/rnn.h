@@ -200,8 +200,8 @@ int rnn_model_reserve(rnn_model* model, int T, int B);
  * A batch that no single persistent launch can hold (for example more than 256 sequences at 1024 units)
  * is run in passes over blocks of sequences, through copies in the workspace; results are the same.
  * Stream capture: the call may be recorded into a HIP graph (`stream` in capture mode) provided the
- * workspace already covers the shape (rnn_model_reserve, or an earlier call; RNN_EUNSUPPORTED
- * otherwise, with nothing recorded): it then records kernels only, the first of which clear the
+ * workspace already covers the shape (rnn_model_reserve, or an earlier call of as many sequences and of as
+ * many steps or more; RNN_EUNSUPPORTED otherwise, with nothing recorded): it then records kernels only, the first of which clear the
  * model's step flags, because every replay reuses the tags chosen at capture time.  A replay counts
  * as a forward in flight (one at a time per model), the pointers recorded are the ones passed here,
  * and kernel timing (rnn_model_set_profiling) is not recorded.

@@ -938,7 +938,8 @@ int prepare_workspace_pass(rnn_model* m, const Plan& plan, int T, int B, bool fi
 
 // The workspace of a whole call: that of one pass (of the last, shorter pass too, whose plan may differ),
 // the copies a batch run in passes goes through, and the time-major copies of a batch-first caller.
-int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B) {
+// tail_at: the number of steps whose plan the last pass is given (0: T).
+int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B, int tail_at = 0) {
     int rc;
     if (plan.chunk == 0) {
         rc = prepare_workspace_pass(m, plan, T, B);
@@ -951,7 +952,7 @@ int prepare_workspace(rnn_model* m, const Plan& plan, int T, int B) {
         const int tail = B % plan.chunk;
         if (rc == RNN_OK && tail != 0) {
             Plan last;
-            rc = resolve_last_pass(m, plan, T, tail, last);
+            rc = resolve_last_pass(m, plan, tail_at > 0 ? tail_at : T, tail, last);
             if (rc == RNN_OK) rc = prepare_workspace_pass(m, last, T, tail, at_once);
         }
         if (plan.xcd) {     // the kernels address the caller's tensors in place
@@ -1473,14 +1474,34 @@ int rnn_model_set_validation(rnn_model* m, int on) {
     return RNN_OK;
 }
 
-// Calls of fewer than T steps on B sequences, whose plan for T steps is `plan`, find their workspace as well.  The choices that depend on the
-// steps, passes or a launch of larger tiles (call_us: both sides are linear in the steps) and tagged words for few sequences through wide
-// layers, are made as for T steps or as for one.
-static int cover_fewer_steps(rnn_model* m, const Plan& plan, int T, int B, bool may_chunk, Plan& shorter) {
-    const int rc = resolve_plan(m, 1, B, shorter, may_chunk);
-    if (rc != RNN_OK || shorter.xcd == plan.xcd || !xcd_addressable(m, T, B)) return rc;
-    const bool few = m->H > PASSES_MAX_H && (size_t)B * m->H <= 4096;
-    return prepare_workspace(m, shorter, few ? std::min(T, XCD_WIDE_STEPS[2]) : T, B);
+// The launches of `plan` can address the state sequences of T steps.
+static bool plan_addresses(const rnn_model* m, const Plan& plan, int T, int B) {
+    if (plan.chunk > 0) B = plan.chunk;
+    if (plan.xcd) return xcd_addressable(m, T, B);
+    return plan.CT != 1 || plan.NCH != 1 || wavefront_ll_words(m->dtype, 2, T, B, m->H) * 8 < ((size_t)1 << 31);
+}
+
+// Workspace of every call of up to T steps on B sequences.  Fewer steps may be given another plan: passes or a launch of larger tiles, by
+// what each takes (call_us, linear in the steps), and tagged words for few sequences through wide layers, below the numbers of
+// XCD_WIDE_STEPS.  Between two of those numbers a choice changes once at most, so the plans of both ends are all there are; the last
+// pass of a batch in passes chooses by itself.
+static int prepare_up_to(rnn_model* m, int T, int B) {
+    const bool wide = m->dtype == DT_BF16 && m->H > PASSES_MAX_H;
+    int ends[4], n = 0, first = 1;
+    for (int steps : XCD_WIDE_STEPS)
+        if (wide && steps <= T) ends[n++] = steps - 1;
+    ends[n++] = T;
+    for (int i = 0; i < n; ++i) {
+        for (int at : {first, ends[i]}) {
+            Plan plan;
+            int rc = resolve_plan(m, at, B, plan);
+            for (int tail_at : {first, ends[i]})
+                if (rc == RNN_OK && plan_addresses(m, plan, ends[i], B)) rc = prepare_workspace(m, plan, ends[i], B, tail_at);
+            if (rc != RNN_OK) return rc;
+        }
+        first = ends[i] + 1;
+    }
+    return RNN_OK;
 }
 
 int rnn_model_reserve(rnn_model* m, int T, int B) {
@@ -1489,15 +1510,7 @@ int rnn_model_reserve(rnn_model* m, int T, int B) {
     int rc = resolve_plan(m, T, B, plan);
     if (rc == RNN_OK) rc = prepare_workspace(m, plan, T, B);
     if (rc != RNN_OK || m->requested_plan == RNN_PLAN_CELLWISE) return rc;
-    Plan shorter, last, unused;
-    rc = cover_fewer_steps(m, plan, T, B, true, shorter);
-    for (const Plan* p : {&plan, &shorter}) {      // ... nor does the last pass of a batch in passes allocate
-        const int rest = p->chunk > 0 ? B % p->chunk : 0;
-        if (rc != RNN_OK || rest == 0 || p->xcd) continue;   // (passes of the XCD-resident kernel keep the last one to it)
-        rc = resolve_plan(m, T, rest, last, false);
-        if (rc == RNN_OK) rc = cover_fewer_steps(m, last, T, rest, false, unused);
-    }
-    return rc;
+    return prepare_up_to(m, T, B);
 }
 
 // The workspace as a set of empty buffers that grow() fills with pieces of the static array.
@@ -1551,7 +1564,13 @@ static int forward_entry(rnn_model* m, const void* x, const int32_t* lengths, co
     Plan plan;
     int rc = resolve_plan(m, T, B, plan);
     if (rc != RNN_OK) return rc;
+    const size_t held = m->workspace_bytes;
     rc = m->arena.on ? fit_arena(m, T, B, plan) : prepare_workspace(m, plan, T, B);   // no-op when rnn_model_reserve has seen this shape and plan
+    if (rc == RNN_OK && m->workspace_bytes != held && m->requested_plan != RNN_PLAN_CELLWISE) {
+        // A call that grows the workspace grows it for fewer steps too: whatever plan these are given, they neither allocate nor free a
+        // buffer that a recorded graph of this call writes.  Where memory ends, the call itself still runs.
+        if (prepare_up_to(m, T, B) != RNN_OK) rc = prepare_workspace(m, plan, T, B);
+    }
     if (rc != RNN_OK) return rc;
     if (m->capturing || m->arena.on) {
         // (rnn_forward_static: the pieces of the static array hold whatever the last call left there.)

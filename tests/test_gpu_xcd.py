@@ -522,6 +522,16 @@ def test_slots_in_turn_cover_fewer_steps(gpu, shape, reset_before, reserved):
     _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, (1, 15, 16, 17, 40, 63))
 
 
+@pytest.mark.parametrize("reserved", [True, False], ids=["reserved", "after_a_call"])
+@pytest.mark.parametrize("shape,steps", [((0, 2, 1, 1024, 1024, 8, 64, 1), (1, 5, 6, 7)), ((0, 4, 1, 1024, 1024, 30, 1, 1), (1, 7, 12, 23, 24)),
+                                         ((0, 2, 2, 512, 512, 48, 72, 1), (1, 2, 4, 20)), ((0, 2, 1, 1024, 1024, 30, 300, 1), (1, 4, 8, 15)),
+                                         ((0, 2, 1, 1024, 1024, 12, 258, 1), (1, 7, 8, 11)), ((0, 2, 2, 640, 640, 12, 3, 1), (1, 7, 8))],
+                         ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_bf16" % s[:7] if len(s) == 8 else "to%d" % s[-1])
+def test_another_plan_of_fewer_steps_finds_its_workspace(gpu, shape, steps, reserved):
+    """Large tiles for a medium batch, tagged words for few sequences or a last pass of few."""
+    _fewer_steps_find_their_workspace(gpu, shape, 0, reserved, steps)
+
+
 @pytest.mark.parametrize("shape,digest", [((0, 2, 1, 1536, 1536, 24, 8, 1), "4ab4e57c91be3f6a"), ((1, 1, 1, 640, 1280, 20, 16, 1), "7776007b4d984933"),
                                           ((0, 1, 1, 1544, 1536, 12, 3, 1), "05ed68978cff64da"),
                                           ((0, 2, 1, 1024, 1024, 24, 4, 1), "f3f474cdc2c0e4ce"), ((1, 4, 1, 768, 768, 30, 1, 1), "38bee8ffcfaf741c"),

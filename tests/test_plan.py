@@ -192,6 +192,25 @@ def test_invariants_over_random_shapes():
     assert seen_kinds == {rnn.RNN_PLAN_CELLWISE, rnn.RNN_PLAN_WAVEFRONT}
 
 
+def test_fewer_steps_change_their_plan_once_in_a_range():
+    """What rnn_model_reserve goes by: between the numbers of steps where tagged words hand over (bf16 layers of more than 512 units) a
+    plan changes once at most, so the plans of both ends of such a range are all there are."""
+    rng = random.Random(7)
+    changes = 0
+    for _ in range(200):
+        cell, L, D = rng.randint(0, 1), rng.randint(1, 8), rng.choice((1, 1, 2))
+        H, dtype = rng.choice((128, 256, 384, 512, 640, 768, 1024, 640, 768, 1024)), rng.choice((0, 1, 1, 1, 1, 1))
+        I, B, T = rng.choice((H, 80, H // 2, 1032)), int(2 ** rng.uniform(0, 9.5)), rng.choice((7, 30, 90))
+        plan = lambda t: rnn.rnn_plan_query(cell, L, I, H, D, dtype, rnn.RNN_PLAN_AUTO, t, B, 256, 160 * 1024)
+        first = 1
+        for end in [e for e in (7, 11, 23) if dtype == 1 and H > 512 and e < T] + [T]:
+            known = (plan(first), plan(end))
+            changes += known[0] != known[1]
+            assert all(plan(t) in known for t in range(first, end)), (cell, L, D, I, H, dtype, B, first, end)
+            first = end + 1
+    assert changes > 5
+
+
 def test_errors():
     c = W.CONFIGS["C1"]
     q = lambda **kw: rnn.rnn_plan_query(kw.get("cell", c.cell), kw.get("L", c.L), c.I, kw.get("H", c.H), kw.get("D", c.D),
