@@ -890,19 +890,28 @@ hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// K blocks that a load brings, in the groups on several XCDs that have variants for it.  With eight sequences or fewer a load instruction's
-// lanes for the sequences that are not there bring those of the next K blocks instead, two, four or eight of them, and the fragments are turned
-// into place by rotating lanes (v_mov_dpp; no sum changes).  A wave then asks for its share of the state in one to six loads instead of five to
-// sixteen, so that a request takes less of the address unit and a vain one is back sooner (64 steps, us, without -> with it: one layer of 768
-// units, batch 1 / 4 / 8 93.4 / 94.9 / 96.1 -> 87.5 / 89.8 / 92.4, of 1536 109 / 112 / 112 -> 98 / 109 / 109, of 2048, batch 1 129 -> 107; 4
-// layers of 1024, one sequence, 128 steps 209 -> 189, 198 with the h waves alone).  Groups on one XCD wait for the round trip and not for the loads: 512
-// units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers 78 -> 81 and 80 -> 84.
-int packed_blocks(int B) { return B <= 2 ? 8 : B <= 4 ? 4 : B <= 8 ? 2 : 1; }
+// K blocks that a load brings, in the groups on several XCDs that have variants for it.  With eight sequences or fewer a load
+// instruction's lanes for the sequences that are not there bring those of the next K blocks instead, two, four or eight of them, and the
+// fragments are turned into place by rotating lanes (v_mov_dpp; no sum changes).  A wave then asks for its share of the state in one to
+// six loads instead of five to sixteen, so that a request takes less of the address unit and a vain one is back sooner.  64 steps, us, one
+// block a load -> this, one layer on an input as wide, batch 1 / 4 / 8:
+//     768 units   89.1 / 90.6 / 92.5 -> 83.9 / 85.0 / 87.6        1024   103 / 105 / 106 -> 92.5 / 96.8 / 101
+//     1280        101 / 103 / 103 -> 93.4 / 98.4 / 97.5           1536   109 / 111 / 111 -> 98.4 / 109 / 109
+//     2048        135 / 140 -> 110 / 137; on 80 values 118 / 117 / 120 -> 98.7 / 97.9 / 104, 3 layers, batch 8 402 -> 372
+// One launch is left out: a layer of 2048 units that reads rows as wide (not the chunks of a layer below), five to eight sequences, whose
+// state in one request of eight loads instead of two takes longer: batch 5 / 8 135 / 135 -> 140 / 141, GRU 135 -> 140.  (Other widths of
+// such rows gain: 1536 values 166 -> 164, 2000 163 -> 161.)
+// Groups on one XCD wait for the round trip and not for the loads: 512 units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers
+// 78 -> 81 and 80 -> 84.
+int packed_blocks(const WavefrontXcdArgs& a, int LN) {
+    if (LN > 12 && a.B > 4 && !a.gx && !a.x_blocked && a.I == a.H) return 1;
+    return a.B <= 2 ? 8 : a.B <= 4 ? 4 : a.B <= 8 ? 2 : 1;
+}
 
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT>
 hipError_t launch_packed(const WavefrontXcdArgs& a, hipStream_t stream) {
 #if RNN_XR_WIDE
-    switch (packed_blocks(a.B)) {
+    switch (packed_blocks(a, LN)) {
         case 8: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 8>(a, stream);
         case 4: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 4>(a, stream);
         case 2: return launch_variant<TR, CELL, RT, LN, XLN, EXT, 2>(a, stream);
