@@ -872,14 +872,14 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
 // Forces one workgroup per compute unit: more than half of the 160 KiB.
 constexpr size_t MIN_LDS = 84 * 1024;
 
-constexpr bool apart(int MPL, int LN) { return MPL > 1 || RNN_XR_WIDE || RNN_XR_APART; }
+constexpr bool apart(int MPL) { return MPL > 1 || RNN_XR_WIDE || RNN_XR_APART; }
 
 template <class TR, int CELL, int RT, int LN, int XLN, bool EXT, int PK>
 hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
     const size_t need = (size_t)((RT == 4 ? 6 : 8) + 8) * RT * 64 * sizeof(f32x4) + (size_t)RT * TR::PUB_LANES * sizeof(typename TR::pub_t) +
                         9 * sizeof(unsigned) + 16 + (size_t)4 * XLN * 4 * 18 * 16 + (LN > 12 ? (size_t)4 * 64 * (LN / 2) * 16 : 0);
     const size_t smem = need < MIN_LDS ? MIN_LDS : need;
-    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT, apart(TR::MPL, LN), PK>;
+    auto kern = wavefront_xcd_kernel<TR, CELL, RT, LN, XLN, EXT, apart(TR::MPL), PK>;
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -898,13 +898,14 @@ hipError_t launch_variant(const WavefrontXcdArgs& a, hipStream_t stream) {
 //     768 units   89.1 / 90.6 / 92.5 -> 83.9 / 85.0 / 87.6        1024   103 / 105 / 106 -> 92.5 / 96.8 / 101
 //     1280        101 / 103 / 103 -> 93.4 / 98.4 / 97.5           1536   109 / 111 / 111 -> 98.4 / 109 / 109
 //     2048        135 / 140 -> 110 / 137; on 80 values 118 / 117 / 120 -> 98.7 / 97.9 / 104, 3 layers, batch 8 402 -> 372
-// One launch is left out: a layer of 2048 units that reads rows as wide (not the chunks of a layer below), five to eight sequences, whose
-// state in one request of eight loads instead of two takes longer: batch 5 / 8 135 / 135 -> 140 / 141, GRU 135 -> 140.  (Other widths of
-// such rows gain: 1536 values 166 -> 164, 2000 163 -> 161.)
+// One launch is left out: from 8 steps on, a layer of 2048 units that reads rows as wide (not the chunks of a layer below), five to eight
+// sequences, whose state in one request of eight loads instead of two takes longer: 64 steps, batch 5 and 8 135 -> 140 and 141, GRU 135 ->
+// 140, 16 steps 46.9 -> 47.7 (6 steps 28.0 -> 28.1, 2 steps 19.6 -> 19.1; other widths of such rows gain, 1536 values 166 -> 164, 2000
+// 163 -> 161).
 // Groups on one XCD wait for the round trip and not for the loads: 512 units, batch 1 and 8 67.0 -> 68.4 and 68.2 -> 68.2, four layers
 // 78 -> 81 and 80 -> 84.
 int packed_blocks(const WavefrontXcdArgs& a, int LN) {
-    if (LN > 12 && a.B > 4 && !a.gx && !a.x_blocked && a.I == a.H) return 1;
+    if (LN > 12 && a.B > 4 && a.T >= 8 && !a.gx && !a.x_blocked && a.I == a.H) return 1;
     return a.B <= 2 ? 8 : a.B <= 4 ? 4 : a.B <= 8 ? 2 : 1;
 }
 

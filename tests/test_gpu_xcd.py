@@ -82,7 +82,7 @@ SHAPES = [
     (1, 1, 1, 64, 1536, 9, 8, 1),       # ... two
     (0, 1, 1, 2048, 2048, 6, 8, 1),
     (0, 1, 1, 2048, 2048, 5, 4, 1),
-    (0, 2, 1, 2048, 2048, 5, 7, 1),     # ... one, on rows as wide; two in the layer above
+    (0, 2, 1, 2048, 2048, 9, 7, 1),     # ... one, on rows as wide; two in the layer above
     (1, 1, 1, 80, 2048, 6, 5, 1),       # ... two
     (0, 1, 2, 64, 384, 15, 18, 1),      # one step fewer than the slots of a sequence that are used in turn,
     (1, 2, 1, 400, 400, 16, 9, 1),      # as many,
