@@ -625,6 +625,11 @@ OPT_SPECS = [
     (("lstm_opts_padded_h72", 0, 2, 2, 24, 72, 6, 5, 1, True, True), 0.6, True),      # 72 -> 128 units: padded peephole weights
     (("lstm_opts_4layer_sq_h1024_b1", 0, 4, 1, 1024, 1024, 7, 1, 1, False, True), 0.15, True),   # the batch-1 latency shape
     (("lstm_opts_two_xcds", 0, 2, 1, 768, 768, 7, 18, 1, True, True), 0.3, True),     # a layer's workgroups on two XCDs
+    (("lstm_opts_two_xcds_l4_b1", 0, 4, 1, 768, 768, 26, 1, 1, False, True), 0.15, True),   # ... eight, four, two K blocks a load of the state
+    (("lstm_opts_two_xcds_h1024_b3", 0, 2, 1, 1024, 1024, 10, 3, 1, True, True), 0.15, True),
+    (("lstm_opts_two_xcds_h640_b7", 0, 3, 1, 640, 640, 9, 7, 1, True, True), 0.3, True),
+    (("gru_clip_two_xcds_h640_b4", 1, 2, 1, 640, 640, 9, 4, 1, True, True), 0.15, False),
+    (("gru_clip_two_xcds_h768_b16", 1, 2, 1, 80, 768, 7, 16, 1, True, True), 0.15, False),
     (("lstm_opts_all_xcds_h1280", 0, 2, 1, 40, 1280, 6, 5, 1, True, True), 0.3, True),   # ... on all eight
     (("lstm_opts_all_xcds_padded_h1400", 0, 1, 1, 1032, 1400, 5, 16, 1, True, True), 0.3, True),
     (("lstm_opts_all_xcds_h2048", 0, 1, 1, 2048, 2048, 4, 3, 1, True, True), 0.15, True),

@@ -296,7 +296,9 @@ def test_an_infinite_feature_saturates_the_gates(gpu, oracle, shape):
 
 @pytest.mark.parametrize("shape", [(0, 2, 1, 128, 128, 9, 3, 1), (1, 3, 1, 256, 256, 12, 17, 1), (0, 2, 1, 512, 512, 14, 16, 1),
                                    (0, 2, 2, 384, 384, 10, 33, 1), (0, 12, 1, 64, 64, 20, 8, 0), (1, 1, 1, 256, 256, 9, 5, 0),
-                                   (0, 2, 1, 512, 512, 8, 20, 0)],
+                                   (0, 2, 1, 512, 512, 8, 20, 0),
+                                   # state slots in turn: written, read and marked again several times over
+                                   (0, 2, 1, 512, 512, 40, 9, 1), (1, 2, 1, 128, 128, 80, 5, 1), (1, 1, 1, 256, 256, 80, 18, 0)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)))
 @pytest.mark.parametrize("reset_before", [0, 1])
 def test_a_group_that_is_not_on_one_xcd(gpu, shape, reset_before):
@@ -550,6 +552,38 @@ def test_bits_of_the_tag_in_data_kernel(gpu, shape, digest):
     model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
     harness.forward(model, io)
     torch.cuda.synchronize()
+    got = hashlib.sha256(io.y.view(torch.int16).cpu().numpy().tobytes() + io.hT.cpu().numpy().tobytes()).hexdigest()[:16]
+    print("\n  case %r: %s" % (shape, got), flush=True)
+    assert got == digest
+    model.close()
+
+
+def _with_options(rnn, wl, handle, clip):
+    """Clipping, and for an LSTM peepholes from the workload's seed: what the model and an oracle are both given."""
+    c = wl.cfg
+    rng = np.random.default_rng(c.seed + 99)
+    ps = [rng.uniform(-1, 1, (3, c.H)).astype(np.float32) for _ in range(c.L * c.D)] if c.cell == 0 else None
+    assert rnn.rnn_model_set_clip(handle, clip) == rnn.RNN_OK
+    if ps:
+        assert rnn.rnn_model_set_peepholes(handle, ps, 0) == rnn.RNN_OK
+    return ps
+
+
+@pytest.mark.parametrize("shape,digest", [((0, 2, 1, 1024, 1024, 24, 3, 1), "0339149d51c5e864"), ((0, 4, 1, 768, 768, 30, 1, 1), "ad9396706a44a2cf"),
+                                          ((0, 1, 1, 512, 1024, 12, 3, 1), "422428672fbb0355"), ((1, 2, 1, 640, 640, 16, 4, 1), "509f0e6722b16bb3")],
+                         ids=["lstm_1024", "lstm_768_one_sequence", "lstm_1024_on_512", "gru_640"])
+def test_bits_of_the_tag_in_data_kernel_with_options(gpu, oracle, shape, digest):
+    """The same with peepholes (LSTM) and clipped gate arguments."""
+    import hashlib
+    import torch
+    harness, rnn, W = gpu
+    wl = _workload(W, shape, True)
+    model, io = harness.DeviceModel(wl), harness.DeviceIO(wl)
+    ps = _with_options(rnn, wl, model.handle, 0.3)
+    harness.forward(model, io)
+    torch.cuda.synchronize()
+    assert rnn.rnn_model_check(model.handle) == rnn.RNN_OK
+    _check(harness, wl, io, oracle.forward_workload(wl, nthreads=8, peepholes=ps, clip=0.3))
     got = hashlib.sha256(io.y.view(torch.int16).cpu().numpy().tobytes() + io.hT.cpu().numpy().tobytes()).hexdigest()[:16]
     print("\n  case %r: %s" % (shape, got), flush=True)
     assert got == digest
