@@ -194,13 +194,22 @@ constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 
 // Slots of a state sequence of the XCD-resident kernel (WavefrontXcdArgs::ring): few that are used in turn, or one for every step.
 // In turn where a group exchanges its state through one L2: the lines are there already, while with a slot for every step a fetch
-// waits for lines that are new to the L2 (880 clocks of the 2600 of a step at 512 units, whatever the number of loads; 620 in
-// turn.  us, a slot a step -> 64 / 16 / 8 slots: 3 layers of 320 units, both directions, 57 sequences, 301 steps 907 -> 804 / 788 / 786;
-// 2 of 512, both directions, batch 64, 256 steps 547 -> 528 / 517 / 518; 2 GRU layers of 256, reset gate first, 64 steps 99.9 -> 99.7 /
-// 92.6 / 99.2).  fp32 launches of one layer gain as well (2 of 256 units, both directions, batch 64, 128 steps 510 -> 472), those of
-// several lose a little (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48, 268 -> 270) and keep a slot a step, as do few steps of little
-// state (30 steps: one GRU layer of 128 and 256 units 22.9 -> 23.3 and 26.5 -> 26.8, but of 512 38.3 -> 36.8).  Groups on several XCDs exchange through memory, where a line that other XCDs have
-// read before costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.
+// waits for lines that are new to the L2 (880 clocks of the 2600 of a step at 512 units and 16 sequences, 620 in turn).  us, a slot a
+// step -> 64 / 16 / 8 slots: 3 layers of 320 units, both directions, 57 sequences, 301 steps 907 -> 804 / 788 / 786; 2 of 512, both
+// directions, batch 64, 256 steps 547 -> 528 / 517 / 518.  A slot a step -> 16 slots, at 24 / 64 / 256 steps:
+//     bf16, 512 units, 2 layers, batch 1          34.7 / 74.3 / 263 -> 34.3 / 70.6 / 244,  2 GRU layers, batch 8  35.2 / 73.1 / 255 ->
+//                                                 34.3 / 69.8 / 241
+//     384 units, 2 layers, batch 8 and 40         32.4 / 68.4 / 251 -> 32.4 / 68.3 / 236,  33.9 / 76.1 / 258 -> 34.0 / 72.7 / 243
+//     256 units, both directions, batch 16        46.7 / 105 / 440 -> 46.5 / 104 / 380,    a GRU layer  22.7 / 51.1 / 216 -> 22.7 / 51.0 / 186
+//     128 units, batch 16                         20.5 / 46.8 / 172 -> 20.4 / 46.7 / 172
+//     GRU of 256, reset gate first, batch 16      35.7 / 85.5 / 364 -> 35.7 / 85.0 / 321
+//     fp32, 256 units, both directions, batch 16  103 / 259 / 989 -> 103 / 240 / 910,      128 units  24.4 / 57.1 / 237 -> 24.4 / 57.0 / 212
+// Narrow layers gain once their sequences have grown to a MiB or two, and before nothing changes; with few steps of little state a slot
+// a step stays (30 steps of one GRU layer of 128 and 256 units 22.9 -> 23.3 and 26.5 -> 26.8).  So it does for fp32 launches of several
+// layers (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48 268 -> 270).  2 GRU layers of 512 units on 256 values, batch 8, 100 steps,
+// take 110 either way; why is not known.  Groups on several XCDs exchange through memory, where a line that other XCDs have read before
+// costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.  (A group that the
+// dispatcher lays over several XCDs although it fits one runs in turn all the same.)
 constexpr int XCD_RING = 16, XCD_RING_STEPS = 64;
 int xcd_ring(const rnn_model* m, const Plan& plan, int T) {
     const bool in_turn = plan.span == 1 && (T >= XCD_RING_STEPS ? m->dtype == DT_BF16 || plan.LP == 1 : m->dtype == DT_BF16 && m->H >= 384);
@@ -488,8 +497,8 @@ constexpr int PASSES_MAX_H = 512;   // the widest layers of choose_xcd
 //     the tag-in-data kernel           2.7 (384 units, both directions, 72 sequences)
 //     large tiles, 64 columns          4.0 (256 units, 136 sequences) to 5.4 (512, 400); two layers in a launch 5.2 to 6.7
 //     large tiles, two chains          4.5 (512 units, 512 sequences) with the input product inside, else no faster than the former
-// On two XCDs (640 to 1024 units) a step of it takes 1.44 to 1.75, 6 % more with several layers in a launch; large tiles beside it 4.0 (128 sequences
-// through one layer of 640 units) to 5.8 (64 through four of 1024).  What a launch takes besides shows on few steps: 13 us
+// On two XCDs (640 to 1024 units) a step of it takes 1.44 to 1.75, 6 % more with several layers in a launch; large tiles beside it 4.0
+// (128 sequences through one layer of 640 units) to 5.8 (64 through four of 1024).  What a launch takes besides shows on few steps: 13 us
 // there, 16 with the second direction's projection, 18 of large tiles.
 double pass_us(const rnn_model* m, const Plan& plan, int T, int B) {
     const int launches = (m->L + plan.LP_asked - 1) / plan.LP_asked;
@@ -557,10 +566,12 @@ int resolve_plan_shape(const rnn_model* m, int T, int B, Plan& plan, bool may_ch
             plan = passes;
         }
         // The same for groups on two XCDs, which may also hold the batch at once with fewer layers in a launch.  48 steps, us, without ->
-        // with: 2 layers of 768 and of 1024 units, batch 64 250 -> 154 and 262 -> 178, both directions 559 -> 395 and 661 -> 506; 4 layers of 1024,
-        // batch 24 357 -> 188; 2 GRU layers of 1024 on 80 values, batch 44 469 -> 165.  Not where two chains of large tiles hold four layers or
-        // more side by side (4 layers of 1024, batch 64 283 -> 353, 6 of 640 1.57 times as long), nor in passes against chains with every input
-        // product inside (one layer of 1024, batch 128 232 -> 179, but at 192 236 -> 269, and 2 layers, batch 128 320 -> 355).
+        // with: 2 layers of 768 and of 1024 units, batch 64 250 -> 154 and 262 -> 178, both directions 559 -> 395 and 661 -> 506; 4
+        // layers of 1024, batch 24 357 -> 188; 2 GRU layers of 1024 on 80 values, batch 44 469 -> 165.  Not where two chains of large
+        // tiles hold four layers or more side by side (4 layers of 1024, batch 64 283 -> 353, 6 of 640 1.57 times as long), nor in passes
+        // against chains with every input product inside (one layer of 1024, batch 128 232 -> 179, but at 192 236 -> 269, and 2 layers,
+        // batch 128 320 -> 355: such chains take nearly the same for 128 and for 192 sequences, and call_us, whose large tiles take
+        // longer with the batch, cannot tell the two apart; one layer at 65 to 128 sequences would gain).
         const bool side_by_side = plan.NCH == 2 && plan.LP >= 4;
         if (!plan.xcd && !side_by_side &&
             (choose_xcd_wide_launches(m, T, B, passes) ||
@@ -834,9 +845,10 @@ int launch_recurrent(rnn_model* m, const Plan& plan, int l0, int LP, int T, int 
 }
 
 // XCD-resident kernel: the x waves of a launch's first layer hold its W_ih slice for inputs of up to 8 chunk loads per wave (1024 bf16
-// or 512 fp32 values), in layers of more than 1024 units for inputs as wide as the layer (up to 16).  With several layers in the launch an input of an eighth of their width or less keeps its projection
-// launch; a launch of one layer takes it inside as well (48 steps, us, projected -> inside: 8 values into 128 units, 1 and 64
-// sequences 42 -> 38 and 54 -> 39; 64 into 512 units 61 -> 57 and 71 -> 62; fp32, 8 into 256 units 80 -> 68 and 93 -> 70).
+// or 512 fp32 values), in layers of more than 1024 units for inputs as wide as the layer (up to 16).  With several layers in the launch
+// an input of an eighth of their width or less keeps its projection launch; a launch of one layer takes it inside as well (48 steps, us,
+// projected -> inside: 8 values into 128 units, 1 and 64 sequences 42 -> 38 and 54 -> 39; 64 into 512 units 61 -> 57 and 71 -> 62; fp32,
+// 8 into 256 units 80 -> 68 and 93 -> 70).
 bool xcd_input_inside(const rnn_model* m, int width, bool several_layers) {
     return (!several_layers || 8 * width > m->H) && wavefront_xcd_input_chunks(m->dtype, m->H, width, several_layers) > 0;
 }

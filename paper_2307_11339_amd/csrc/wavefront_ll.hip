@@ -23,10 +23,11 @@
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
 // wavefront_xcd.hip takes the layers that fit one XCD, two, or all, where that is faster (choose_xcd, choose_xcd_wide,
-// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units up to B * H = 4096, fp32 layers of
-// 32 units, one sequence of 512 fp32 units, and calls of a few steps on batches of 384 units that passes of that kernel do not pay for;
-// its other variants serve devices with fewer compute units to an XCD.  Layers of more than 1024 units have none: where the 160 to 256
-// workgroups of such a layer fit the chip, wavefront_xcd.hip takes it, and both directions of one do not fit.
+// choose_xcd_chip).  On 256 compute units this kernel is left with bf16 layers of 640 to 1024 units, up to B * H = 4096 and fewer than 8 to
+// 24 steps (XCD_WIDE_STEPS), fp32 layers of 32 units, one sequence of 512 fp32 units, and calls of a few steps on batches of 384 units
+// that passes of that kernel do not pay for; its other variants serve devices with fewer compute units to an XCD.  Layers of more than
+// 1024 units have none: where the 160 to 256 workgroups of such a layer fit the chip, wavefront_xcd.hip takes it, and both directions of
+// one do not fit.
 #include "wf_traits.h"
 
 // The variants of this kernel are compiled in three translation units so that the build runs in

@@ -24,12 +24,12 @@
 // Layout of the exchanged state: 16-byte chunks (8 bf16 or 4 fp32 units of one sequence), chunk-major, the sequences of
 // the block side by side (room for 4, 8 or 16, so that a workgroup's chunks do not share a half line with another's).  A lane's MFMA B
 // fragment is one chunk, so a load instruction of a wave brings a whole K block of 16 sequences from 8 consecutive cache lines straight
-// into the registers the matrix instruction reads: no tags, no staging through LDS.  Whether a chunk has been written is told from the data: a slot is filled with the bit
-// pattern of all ones (two bf16 NaNs; one fp32 NaN) several steps before it is used, no published value has that
-// pattern (a NaN is published with another one), and what is stored at once (8 bytes in bf16, 4 in fp32) is checked
-// at once.  Order: a wave marks slot s + AHEAD in step s; before it publishes slot s it has waited for loads issued
-// after it had marked slot s + 1, and memory operations of a wave complete in order, so whoever has seen slot s finds
-// slot s + 1 marked or written.  The first AHEAD slots are marked before the group's start words are published.
+// into the registers the matrix instruction reads: no tags, no staging through LDS.  Whether a chunk has been written is told from the
+// data: a slot is filled with the bit pattern of all ones (two bf16 NaNs; one fp32 NaN) several steps before it is used, no published
+// value has that pattern (a NaN is published with another one), and what is stored at once (8 bytes in bf16, 4 in fp32) is checked at
+// once.  Order: a wave marks slot s + AHEAD in step s; before it publishes slot s it has waited for loads issued after it had marked slot
+// s + 1, and memory operations of a wave complete in order, so whoever has seen slot s finds slot s + 1 marked or written.  The first
+// AHEAD slots are marked before the group's start words are published.
 //
 // For layers in the same launch the layer below hands its state to the layer above through a second sequence with
 // device-scope stores (the two may run on different XCDs); the x waves do that, and write the layer output, from
@@ -37,15 +37,15 @@
 // Every wait is bounded (poll budget, shared status word), so the grid always drains.
 //
 // What a step costs, for 512 units and 16 sequences (clocks of 2.4 GHz, each with its stamp of some 40; the slots of the state used in
-// turn): from the tile's sums to the request of the next state 590 (gather, store, mark, tile to the x waves, loop), the state 620 (880 with a
-// slot for every step; the same with one load instead of four and without the loads of the x waves, so that it is a round trip and no
-// queue), products 290, partial sums to LDS 120, barrier 190, sum 225, gates 330.  Asking sooner behind the publication makes
-// polls fail (20 to 90 %, 600 clocks each): 5 to 45 % longer.  Multiplying what has come while the rest travels: 0 to 33 % longer, since vain
-// products hold up the next poll.  Words in LDS instead of the barrier: 0 to 12 % longer; input asked for behind the state instead of behind the barrier: 3 to 15 %.
-// Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions,
-// batch 64, 256 steps 1.29 -> 0.55 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64
-// units 159 -> 103 us; 2 fp32 layers of 512 units at batch 64 1.15 -> 0.63 ms; GRU with the reset gate before the product (one
-// launch per cell part without it) 1719 -> 98 us.
+// turn): from the tile's sums to the request of the next state 590 (gather, store, mark, tile to the x waves, loop), the state 620 (880
+// with a slot for every step; the same there with one load instead of four and without the loads of the x waves, so that it is a round
+// trip and no queue), products 290, partial sums to LDS 120, barrier 190, sum 225, gates 330.  Asking sooner behind the publication makes
+// polls fail (20 to 90 %, 600 clocks each): 5 to 45 % longer.  Multiplying what has come while the rest travels: 0 to 33 % longer, since
+// vain products hold up the next poll.  Words in LDS instead of the barrier: 0 to 12 % longer; input asked for behind the state instead
+// of behind the barrier: 3 to 15 %.  Whole forward passes, on tagged words -> here: 2-layer LSTM of 512 units, both directions, batch 64,
+// 256 steps 1.29 -> 0.55 ms; 2-layer GRU of 512 units at batch 8 183 -> 112 us for 100 steps; 12 fp32 layers of 64 units 159 -> 103 us; 2
+// fp32 layers of 512 units at batch 64 1.15 -> 0.63 ms; GRU with the reset gate before the product (one launch per cell part without it)
+// 1719 -> 98 us.
 #include "wf_traits.h"
 
 #include <type_traits>
@@ -167,7 +167,10 @@ __device__ inline u32x4 rotate(const u32x4& v, int b) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #define ROTATE_BY(k) case k: r[i] = __builtin_amdgcn_mov_dpp(v[i], 0x120 + 16 - k, 0xF, 0xF, true); break;   // row_ror
-        switch (b * SEQS) { ROTATE_BY(2) ROTATE_BY(4) ROTATE_BY(6) ROTATE_BY(8) ROTATE_BY(10) ROTATE_BY(12) ROTATE_BY(14) default: __builtin_unreachable(); }
+        switch (b * SEQS) {
+            ROTATE_BY(2) ROTATE_BY(4) ROTATE_BY(6) ROTATE_BY(8) ROTATE_BY(10) ROTATE_BY(12) ROTATE_BY(14)
+            default: __builtin_unreachable();
+        }
 #undef ROTATE_BY
     }
     return r;
@@ -207,10 +210,10 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     static_assert(RT <= 4, "one tile per wave");
     // Layers of 640 to 1536 units sum in the order of the tag-in-data kernel, which ran them before (up to 1024 units it still does on few
     // steps): the same results, to the bit, on inputs H or H / 2 wide and behind a projection.  At 1280 and 1536 units that order is also
-    // shorter than one of its own, each workgroup from another K block on (48 steps, us: 2 layers of 1280, batch 8 214 -> 206, 1 on 1032 values,
-    // batch 16 117 -> 106; 2 of 1536, batch 16 255 -> 240); up to 1024 units it costs up to 4 % (64 steps: 1, 2 and 4 layers of 768, batch 4,
-    // 92.0 -> 94.5, 97.1 -> 101, 114 -> 120, of 1024 105 -> 106, 111 -> 111, 119 -> 123; batch 16, 2 of 1024 118 -> 116).  At 2048 units
-    // it does not fit the registers.
+    // shorter than one of its own, each workgroup from another K block on (48 steps, us: 2 layers of 1280, batch 8 214 -> 206, 1 on 1032
+    // values, batch 16 117 -> 106; 2 of 1536, batch 16 255 -> 240); up to 1024 units it costs up to 4 % (64 steps: 1, 2 and 4 layers of
+    // 768, batch 4, 92.0 -> 94.5, 97.1 -> 101, 114 -> 120, of 1024 105 -> 106, 111 -> 111, 119 -> 123; batch 16, 2 of 1024 118 -> 116).
+    // At 2048 units it does not fit the registers.
     constexpr bool TAGGED_ORDER = RNN_XR_WIDE && LN <= 12;
     // ... the i-th block of four chunks of wave w: of an input KX wide a quarter of the blocks, not every fourth; none from there on
     auto quarter_block = [](int i, int w, int KX) -> int {
@@ -440,17 +443,16 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
         // With lead = 1 the part is there a step before h wave w picks it up, as the start of its accumulators, while its state
         // fragments travel; the product then waits until h wave w, on the same SIMD, is through its gates, whose vector
         // instructions otherwise queue behind matrix instructions one by one (2 layers of 512 units, both directions: a gate phase, sum
-        // and publication with it, of 1078 clocks instead of 860).  A product of a few instructions, or of an input wider than the state, which would come too late,
-        // does not wait in a launch of one layer (128 units, 48 steps, 16 groups or more: 51 us with the wait, 45 without; with layers
-        // above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so deep stacks on few
-        // steps take lead = 0 there (p.lead): then the layer output of step s - 1 leaves behind the product, or before it where that
-        // is long.
-        // With the reset gate first, r * h goes round the group behind the barrier: a first layer whose input is wider than its
-        // state, by more than four chunks a wave, asks before the barrier and multiplies in the step itself (1 layer of 512 units
-        // on 848 values, 33 sequences, 20 steps: 54.7 us, 58.4 the other way).  Up to four chunks the product is short and better
-        // done ahead (48 steps, late -> ahead: 2 layers of 64 to 256 units on 136 to 504 values, one sequence, 10 to 15 % shorter,
-        // 16 sequences 0 to 12 %; 1 layer 1 to 4 %, but 2 % longer at 256 units, 40 sequences; fp32, on 136 and 224 values, 2 layers,
-        // one sequence 8 to 15 % shorter, 16 sequences 3 to 5 % longer).
+        // and publication with it, of 1078 clocks instead of 860).  A product of a few instructions, or of an input wider than the state,
+        // which would come too late, does not wait in a launch of one layer (128 units, 48 steps, 16 groups or more: 51 us with the wait,
+        // 45 without; with layers above, 2 of 128 units, 47 with it and 52 without).  A layer above another is a step later for it, so
+        // deep stacks on few steps take lead = 0 there (p.lead): then the layer output of step s - 1 leaves behind the product, or before
+        // it where that is long.  With the reset gate first, r * h goes round the group behind the barrier: a first layer whose input is
+        // wider than its state, by more than four chunks a wave, asks before the barrier and multiplies in the step itself (1 layer of
+        // 512 units on 848 values, 33 sequences, 20 steps: 54.7 us, 58.4 the other way).  Up to four chunks the product is short and
+        // better done ahead (48 steps, late -> ahead: 2 layers of 64 to 256 units on 136 to 504 values, one sequence, 10 to 15 % shorter,
+        // 16 sequences 0 to 12 %; 1 layer 1 to 4 %, but 2 % longer at 256 units, 40 sequences; fp32, on 136 and 224 values, 2 layers, one
+        // sequence 8 to 15 % shorter, 16 sequences 3 to 5 % longer).
         constexpr bool LATE = RB && XLN > LN && XLN > 4;
         // In a launch of several fp32 layers of 256 units or more, on few steps, the first layer does without as well (p.lead_first): its
         // first barrier would wait for two long products, and every layer above with it (2 layers of 512 units, 16 sequences, us with
@@ -484,7 +486,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
                         asm volatile("" ::: "memory");
                     }
                 }
-                if (!project && !(BELOW && PK > 1) && XL * 16 * EPC > KX) {   // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+                // chunks beyond the input: zero like their weights (0 * infinity is no zero)
+                if (!project && !(BELOW && PK > 1) && XL * 16 * EPC > KX) {
 #pragma unroll
                     for (int i = 0; i < XL; ++i) {
                         const int chunk = (TAGGED_ORDER ? quarter_block(i, w, KX) : i * 4 + w) * 4;
@@ -610,7 +613,8 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     };
     uint32_t hoff[PK == 1 ? 1 : LOADS];              // byte offset inside a slot (PK = 1: without the K block)
 #pragma unroll
-    for (int i = 0; i < (PK == 1 ? 1 : LOADS); ++i) hoff[i] = ((uint32_t)((w * LN + (PK == 1 ? 0 : block_of(i))) * 4 + q) * Bs + own_seq) * 16u;
+    for (int i = 0; i < (PK == 1 ? 1 : LOADS); ++i)
+        hoff[i] = ((uint32_t)((w * LN + (PK == 1 ? 0 : block_of(i))) * 4 + q) * Bs + own_seq) * 16u;
 
     float c_reg[NOWN], h_reg[NOWN];
     f32x4 bias_reg[NOWN];
@@ -652,21 +656,24 @@ __global__ __launch_bounds__(512) void wavefront_xcd_kernel(WavefrontXcdArgs p) 
     auto ask = [&](__amdgpu_buffer_rsrc_t rs, int s, int first) {   // request HL loads of slot s
 #pragma unroll
         for (int i = 0; i < HL; ++i) {
-            if constexpr (PK == 1) hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[0], slot_of(s) + (uint32_t)(block_of(first + i) * 64) * Bs, 16);
+            if constexpr (PK == 1)
+                hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[0], slot_of(s) + (uint32_t)(block_of(first + i) * 64) * Bs, 16);
             else hv[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, hoff[first + i], slot_of(s), 16);
         }
     };
     // Groups on several XCDs: a wave waits before its first request of a step.  A request that finds a chunk unwritten costs a whole
-    // round trip through memory, and its answers delay the stores everybody waits for, so it is better sent late than too early; how late depends on
-    // the shape, the step and the wave (those without a tile of their own ask first and were sent back in four steps of five), so every wave finds out for
-    // itself: longer after a step that sent it back, a little shorter after every other (once in 33 steps in balance).  64 steps, us, without -> with it: 2 layers of 1024
-    // units, batch 5 / 8 / 16 147 / 154 / 175 -> 112 / 116 / 116, of 768, batch 8 / 16 125 / 140 -> 100 / 101, one of 1536, batch 1 / 16
-    // 147 / 167 -> 110 / 123, of 2048 183 / 204 -> 149 / 162.  Other choices (sixteenths more, sixteenths less, at first): 16, 1, 10 up to 3 %
-    // longer, 48, 1, 8 the same, 96, 1, 0 and the best constant of each shape 1 to 10 % longer.  Within one XCD the loop as it is is late enough
+    // round trip through memory, and its answers delay the stores everybody waits for, so it is better sent late than too early; how late
+    // depends on the shape, the step and the wave (those without a tile of their own ask first and were sent back in four steps of five),
+    // so every wave finds out for itself: longer after a step that sent it back, a little shorter after every other (in balance it is
+    // sent back once in 33 steps; in 25 at 640 and 768 units).  64 steps, us, without -> with it: 2 layers of 1024 units, batch 5 / 8 /
+    // 16 147 / 154 / 175 -> 112 / 116 / 116, of 768, batch 8 / 16 125 / 140 -> 100 / 101, one of 1536, batch 1 / 16 147 / 167 -> 110 /
+    // 123, of 2048 183 / 204 -> 149 / 162.  Other choices (sixteenths more, sixteenths less, at first): 16, 1, 10 up to 3 % longer, 48,
+    // 1, 8 the same, 96, 1, 0 and the best constant of each shape 1 to 10 % longer.  Within one XCD the loop as it is is late enough
     // (retries in 0 to 30 % of the steps, 600 clocks each); there such pauses made 12 narrow layers 2 to 13 % longer and little shorter.
-    // Sixteenths of a round of the loop, about 40 clocks.  (640 and 768 units, their fewer workgroups sooner through: 32, 1, 8 -> 24, 1, 5, 64 steps, us,
-    // one layer, batch 1 and 8 85.1 and 90.1 -> 82.1 and 85.8, 87.1 and 91.3 -> 82.8 and 87.3; four, batch 2 and 12 111 and 117 -> 112 and 107, 106 and
-    // 118 -> 107 and 112.  Of 1024 units one layer gains 3 % by it, several lose 2 to 7, wider ones 0 to 3.)
+    // Sixteenths of a round of the loop, about 40 clocks.  (640 and 768 units, their fewer workgroups sooner through: 32, 1, 8 -> 24, 1,
+    // 5, 64 steps, us, one layer, batch 1 and 8 85.1 and 90.1 -> 82.1 and 85.8, 87.1 and 91.3 -> 82.8 and 87.3; four, batch 2 and 12 111
+    // and 117 -> 112 and 107, 106 and 118 -> 107 and 112.  Of 1024 units one layer gains 3 % by it, several lose 2 to 7, wider ones 0 to
+    // 3.)
     constexpr int PAUSE_MORE = LN <= 6 ? 24 : 32, PAUSE_LESS = 1, PAUSE_FIRST = (LN <= 6 ? 5 : 8) * 16, PAUSE_MOST = 64 * 16;
     int pause = PAUSE_FIRST;
     unsigned in_vain = 0;                            // requests of the last fetch that found a chunk unwritten
