@@ -204,26 +204,22 @@ constexpr int XCDS = 8;   // workgroups are dealt to this many XCDs in turn
 //     128 units, batch 16                         20.5 / 46.8 / 172 -> 20.4 / 46.7 / 172
 //     GRU of 256, reset gate first, batch 16      35.7 / 85.5 / 364 -> 35.7 / 85.0 / 321
 //     fp32, 256 units, both directions, batch 16  103 / 259 / 989 -> 103 / 240 / 910,      128 units  24.4 / 57.1 / 237 -> 24.4 / 57.0 / 212
-// Narrow layers gain once their sequences have grown to a MiB or two, and before nothing changes; with few steps of little state a slot
-// a step stays (30 steps of one GRU layer of 128 and 256 units 22.9 -> 23.3 and 26.5 -> 26.8).  So it does for fp32 launches of several
-// layers (2 of 512, batch 32 597 -> 601, 3 of 200, batch 48 268 -> 270).  2 GRU layers of 512 units on 256 values, batch 8, 100 steps,
-// take 110 either way; why is not known.  Groups on several XCDs exchange through memory, where a line that other XCDs have read before
+// Narrow layers gain once their sequences have grown to a MiB or two, and before nothing changes: 225 shapes of 64 to 384 units and 17 to
+// 62 steps, four runs of each side, take 0.998 times as long in the mean (fp32, 256 units, both directions, batch 24, 48 and 62 steps 83.5 ->
+// 81.9 and 111 -> 104; one GRU layer of 256 bf16 units 17 steps 1.003, 24 and 32 steps 0.998).  So the number of steps has no part in the
+// rule, and a call of fewer steps never holds more slots than one of more.  fp32 launches of several layers lose a little (2 of 512, batch
+// 32 597 -> 601, 3 of 200, batch 48 268 -> 270) and keep a slot a step.  2 GRU layers of 512 units on 256 values, batch 8, 100 steps, take
+// 110 either way; why is not known.  Groups on several XCDs exchange through memory, where a line that other XCDs have read before
 // costs more to write again: two layers of 1024 units, batch 8, 1290 clocks a fetch with a slot a step, 1640 in turn.  (A group that the
 // dispatcher lays over several XCDs although it fits one runs in turn all the same.)
-constexpr int XCD_RING = 16, XCD_RING_STEPS = 64;
+constexpr int XCD_RING = 16;
 int xcd_ring(const rnn_model* m, const Plan& plan, int T) {
-    const bool in_turn = plan.span == 1 && (T >= XCD_RING_STEPS ? m->dtype == DT_BF16 || plan.LP == 1 : m->dtype == DT_BF16 && m->H >= 384);
+    const bool in_turn = plan.span == 1 && (m->dtype == DT_BF16 || plan.LP == 1);
     const int few = m->compact > 0 ? 2 * XCD_AHEAD : in_turn ? XCD_RING : T + 1;
     return T >= few ? few : T + 1;
 }
-// Slots that the workspace holds: as many as any call of up to T steps uses, so that a shorter call never outgrows what a longer one was
-// given (below XCD_RING_STEPS steps a slot each can be more than the few that more steps use in turn).  The static array is laid out for
-// every call by itself and holds a slot for every step unless compact: what fits it stays what it was.
-int xcd_slots(const rnn_model* m, const Plan& plan, int T) {
-    if (m->arena.on && m->compact <= 0) return T;
-    const int slots = std::min(xcd_ring(m, plan, T), T), below = XCD_RING_STEPS - 1;
-    return m->arena.on || T <= below ? slots : std::max(slots, std::min(xcd_ring(m, plan, below), below));
-}
+// Slots that the workspace holds.  The static array holds one for every step unless compact: what fits it stays what it was.
+int xcd_slots(const rnn_model* m, const Plan& plan, int T) { return m->arena.on && m->compact <= 0 ? T : std::min(xcd_ring(m, plan, T), T); }
 
 // Sequences side by side in a chunk row of its state sequences (WavefrontXcdArgs::stride): 4, 8 or 16, so that a workgroup's
 // chunks start a half or a whole cache line of their own.  With B side by side, workgroups that share a line hold up each other's

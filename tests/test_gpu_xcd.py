@@ -88,7 +88,10 @@ SHAPES = [
     (1, 2, 1, 400, 400, 16, 9, 1),      # as many,
     (0, 1, 1, 128, 512, 17, 20, 1),     # one more,
     (1, 1, 2, 64, 128, 65, 17, 0),      # four times as many and one, fp32
-    (1, 2, 1, 128, 256, 64, 5, 1),      # the fewest steps that narrower layers take in turn
+    (0, 1, 1, 64, 128, 17, 3, 0),
+    (1, 2, 1, 128, 256, 64, 5, 1),      # narrower layers: four times as many,
+    (0, 2, 1, 128, 128, 16, 9, 1),      # as many,
+    (1, 3, 1, 40, 256, 33, 2, 1),       # twice as many and one
 ]
 
 
@@ -522,7 +525,7 @@ def _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, steps)
                                                 ((0, 2, 2, 128, 128, 64, 18, 0), 0), ((0, 1, 1, 512, 512, 80, 20, 0), 0), ((0, 2, 1, 512, 512, 64, 5, 1), 0)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)) if isinstance(s, tuple) else "rb%d" % s)
 def test_slots_in_turn_cover_fewer_steps(gpu, shape, reset_before, reserved):
-    """From 64 steps on a state sequence may use few slots in turn, below a slot for every step: the workspace holds the larger of both."""
+    """A state sequence uses few slots in turn from 16 steps on, and a slot for every step below: no fewer steps hold more."""
     _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, (1, 15, 16, 17, 40, 63))
 
 
