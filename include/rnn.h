@@ -194,7 +194,8 @@ int rnn_model_reserve(rnn_model* model, int T, int B);
  *   stream                             hipStream_t passed as void* (NULL = the default stream)
  * The call enqueues work on `stream` and returns without waiting; outputs are valid once the
  * stream has reached the end of that work.  It allocates device memory only if this shape needs
- * more workspace than earlier calls or rnn_model_reserve provided (then it synchronises).
+ * more workspace than earlier calls or rnn_model_reserve provided (then it synchronises, and provides for fewer
+ * steps of as many sequences too, whatever plan these are given).
  * x and y must not overlap and must be 16-byte aligned (RNN_EINVAL otherwise: the kernels read and
  * write them in 16-byte pieces).  Inputs are not validated on the device beyond the clamping above.
  * A batch that no single persistent launch can hold (for example more than 256 sequences at 1024 units)
