@@ -522,7 +522,8 @@ def _fewer_steps_find_their_workspace(gpu, shape, reset_before, reserved, steps)
 
 @pytest.mark.parametrize("reserved", [True, False], ids=["reserved", "after_a_call"])
 @pytest.mark.parametrize("shape,reset_before", [((1, 2, 1, 256, 256, 64, 9, 1), 0), ((1, 2, 1, 256, 256, 301, 16, 1), 1), ((0, 2, 1, 128, 128, 301, 3, 1), 0),
-                                                ((0, 2, 2, 128, 128, 64, 18, 0), 0), ((0, 1, 1, 512, 512, 80, 20, 0), 0), ((0, 2, 1, 512, 512, 64, 5, 1), 0)],
+                                                ((0, 2, 2, 128, 128, 64, 18, 0), 0), ((0, 1, 1, 512, 512, 80, 20, 0), 0), ((0, 2, 1, 512, 512, 64, 5, 1), 0),
+                                                ((1, 1, 1, 64, 256, 80, 300, 1), 0)],
                          ids=lambda s: "c%d_L%d_D%d_I%d_H%d_T%d_B%d_%s" % (s[:7] + ("f32" if s[7] == 0 else "bf16",)) if isinstance(s, tuple) else "rb%d" % s)
 def test_slots_in_turn_cover_fewer_steps(gpu, shape, reset_before, reserved):
     """A state sequence uses few slots in turn from 16 steps on, and a slot for every step below: no fewer steps hold more."""
